@@ -19,6 +19,15 @@ struct AdW {
     double cm[3], cp[3];
 };
 
+// The 2D operator as the one-pass legs (k_wave2, k_lvl2_b) apply it: the residual in ad_ax's terms and order.
+struct Ad2 {
+    double c0, xl, xu, yl, yu, wd;
+    __device__ __forceinline__ double resid(double f, double xc, double xm, double xp, double ym, double yp) const {
+        const double s = c0 * xc + (xl * xm + xu * xp) + (yl * ym + yu * yp);
+        return f - s;
+    }
+};
+
 // (A x)_c at cell c = (i, j, k).
 template <int D>
 __device__ __forceinline__ double ad_ax(const double *__restrict__ x, int64_t c, int i, int j, int k, int lg, int bc,
@@ -440,11 +449,13 @@ __device__ __forceinline__ void ad_tail_sweep(const double *__restrict__ X, cons
 // sweeps, residual restriction, the exact solve Minv f on 4^d, then per
 // level up prolongation + nu2 sweeps.  f_t: right-hand side of level lg_t
 // (global); x_t: its correction (global).  nu1 >= 1; lg_t <= Tail<D>::LG.
+// ctl: first the cycle's convergence check, as k_tail runs it.
 template <int D>
 __global__ __launch_bounds__(Tail<D>::NT_AD) void k_ad_tail(const double *__restrict__ f_t, double *__restrict__ x_t,
                                                          const double *__restrict__ Minv, int lg_t, int bc,
                                                          AdLevels Wl, double omega, int nu1, int nu2,
-                                                         const int *stop) {
+                                                         const int *stop, const double *__restrict__ partial,
+                                                         int np, Ctl *ctl) {
     constexpr int NT = Tail<D>::NT_AD;
     static_assert(Tail<D>::cells(Tail<D>::LG) >> Tail<D>::LG <= NT, "ad_tail_sweep needs n^(D-1) <= NT");
     __shared__ double xs[Tail<D>::levels_sum()];
@@ -455,6 +466,13 @@ __global__ __launch_bounds__(Tail<D>::NT_AD) void k_ad_tail(const double *__rest
     constexpr int mq = D == 3 ? 64 : 16, mp = mq + 1;
     __shared__ double Ms[mq * mp];
     if (stop && *stop) return;
+    if (ctl) {
+        __shared__ int halt;
+        const int st = check_block<NT>(partial, np, ctl);
+        if (threadIdx.x == 0) halt = st;
+        __syncthreads();
+        if (halt) return;
+    }
     const int tid = threadIdx.x;
     auto off = [&](int l) -> int64_t {  // level l follows the finer levels lg_t .. l + 1
         return ((int64_t(1) << (D * (lg_t + 1))) - (int64_t(1) << (D * (l + 1)))) / ((int64_t(1) << D) - 1);

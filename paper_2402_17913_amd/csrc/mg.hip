@@ -12,6 +12,7 @@
 
 #include "mg_fused.h"
 #include "mg_block2.h"
+#include "mg_wave2.h"
 #include "mg_fused3.h"
 #include "mg_zfused.h"
 #include "mg_level.h"
@@ -134,6 +135,7 @@ struct Tuning {
     int fbnt = 1024;      // threads per workgroup of those block kernels (512: one per cell, or 1024)
     int z2wg = 1;         // one-pass kernels that fit fewer than four workgroups per CU aim at 512 workgroups
     int blk2 = 1;         // 2D levels of 128^2 .. 1024^2: one block kernel per leg (64 x 16 cells per workgroup)
+    int w2min = 10;       // smallest 2D level (log2 cells per axis) whose legs run on row-marching wavefronts (14: none)
 };
 static Tuning g_tune;
 int g_zc3 = 0;
@@ -403,6 +405,35 @@ struct CgcHook {
 // log2 size of the finest level of the cycle being enqueued (for profiling
 // the finest-level launches only).
 static thread_local int H_lg_top = -1;
+
+static bool aligned16(const void *a, const void *b) { return ((uintptr_t(a) | uintptr_t(b)) & 15) == 0; }
+
+// A leg of a 2D level; *np receives the number of workgroups.  From 2^w2min cells per axis on
+// row-marching wavefronts (k_wave2; `al`: the fields are 16-byte aligned, as its accesses need),
+// smaller ones on 64 x 16 blocks (k_lvl2_b), which fill the chip with fewer rows per wave: with
+// twelve FP64 cycles at 1024^2 the level took 933 us on wavefronts and 1008 on blocks, at 512^2 726
+// and 688.
+static bool w2_on(int lg, bool al) { return lg >= 7 && lg >= g_tune.w2min && al; }
+template <class S, class OP, int MODE, bool NORM>
+static np_status launch_leg2(bool al, const S *ec, const S *f, const S *xin, S *xout, S *fc, double *partial,
+                             unsigned *np, int lg, int bc, const OP &op, hipStream_t s, const int *stop) {
+    const int n = 1 << lg;
+    if (w2_on(lg, al)) {
+        // wavefronts aimed for: FP64 2048 (twelve cycles at 4096^2 4.06 ms, against 4.47 with 1024 and 4.12
+        // with 4096), else 4096 (four FP32 refinement steps at 2048^2 1.29 ms, against 1.33 and 1.32)
+        const int strips = W2<S, MODE>::strips(n), ry = wave2_rows(n, strips, sizeof(S) == 8 ? 2048 : 4096);
+        const int64_t waves = int64_t(strips) * ((n + ry - 1) / ry);
+        *np = unsigned((waves * 64 + kW2T - 1) / kW2T);
+        hipLaunchKernelGGL((k_wave2<S, OP, MODE, NORM>), dim3(*np), dim3(kW2T), 0, s, ec, f, xin, xout, fc, partial, lg,
+                           bc, ry, op, stop);
+    } else {
+        *np = unsigned((n / B2<S>::BX) * (n / B2<S>::BY));
+        hipLaunchKernelGGL((k_lvl2_b<S, OP, MODE, NORM>), dim3(*np), dim3(B2<S>::NT), 0, s, ec, f, xin, xout, fc, partial,
+                           lg, bc, op, stop);
+    }
+    NP_LAUNCH_CHECK();
+    return NP_OK;
+}
 
 template <int D, class S> struct Ops {
     typedef typename St<S>::C C;
@@ -714,24 +745,23 @@ template <int D, class S> struct Ops {
         }
     }
 
-    // 2D levels of 128^2 .. 1024^2 above the tail: one block kernel per leg (k_lvl2_b: MODE 0 the
-    // down-leg from zero, 1 the down-leg of an iterate, 2 the up-leg), 64 x 16 cells per workgroup.
-    static bool blk2_on(int lg) { return D == 2 && g_tune.blk2 && lg >= 7 && lg <= 10 && lg > Tail<2>::LG; }
+    // 2D levels above the tail run one kernel per leg (MODE 0 the down-leg from zero, 1 the down-leg of
+    // an iterate, 2 the up-leg; launch_leg2): on blocks up to 1024^2, on wavefronts from 2^w2min.
+    static bool leg2_on(int lg, bool al) {
+        return D == 2 && lg > Tail<2>::LG && (w2_on(lg, al) || (g_tune.blk2 && lg <= 10));
+    }
     template <int MODE, bool NORM>
-    static np_status lvl2b(const S *ec, const S *f, const S *xin, S *xout, S *fc, double *partial, int *np, int lg,
-                           int bc, double h, double omega, hipStream_t s, const int *stop) {
+    static np_status leg2(bool al, const S *ec, const S *f, const S *xin, S *xout, S *fc, double *partial, int *np,
+                          int lg, int bc, double h, double omega, hipStream_t s, const int *stop) {
         if constexpr (D == 2) {
-            const C inv_h2 = C(1.0 / (h * h)), wdiag = C(omega * h * h / (2.0 * D));
-            const int n = 1 << lg;
-            const unsigned nb = unsigned((n / B2<S>::BX) * (n / B2<S>::BY));
-            hipLaunchKernelGGL((k_lvl2_b<S, MODE, NORM>), dim3(nb), dim3(B2<S>::NT), 0, s, ec, f, xin, xout, fc,
-                               partial, lg, bc, inv_h2, wdiag, stop);
-            NP_LAUNCH_CHECK();
+            const Lap2<C> op{C(1.0 / (h * h)), C(omega * h * h / (2.0 * D))};
+            unsigned nb = 0;
+            NP_TRY((launch_leg2<S, Lap2<C>, MODE, NORM>(al, ec, f, xin, xout, fc, partial, &nb, lg, bc, op, s, stop)));
             if (np) *np = int(nb);
             return NP_OK;
         } else {
-            (void)ec; (void)f; (void)xin; (void)xout; (void)fc; (void)partial; (void)np; (void)lg; (void)bc; (void)h;
-            (void)omega; (void)s; (void)stop;
+            (void)al; (void)ec; (void)f; (void)xin; (void)xout; (void)fc; (void)partial; (void)np; (void)lg; (void)bc;
+            (void)h; (void)omega; (void)s; (void)stop;
             return NP_EINVAL;
         }
     }
@@ -868,6 +898,7 @@ template <int D, class S> struct Ops {
         const int L = H->L, bc = H->bc;
         const int *stop = &H->ctl->stop;
         H_lg_top = H->lg;
+        const bool al0 = aligned16(x0, f0);
         const bool fz = g_tune.fused && o.nu1 == 2 && o.nu2 == 2;
         const int fmin = D == 3 ? g_tune.fmin3 : g_tune.fmin2;
         const int fmax = D == 3 ? g_tune.fmax3 : g_tune.fmax2;
@@ -926,22 +957,22 @@ template <int D, class S> struct Ops {
                 std::swap(cur[l], oth[l]);  // the smoothed iterate is in the partner buffer
                 continue;
             }
-            if (o.nu1 == 2 && blk2_on(lg) && (!zero || g_tune.zero2)) {
-                // 2D: both pre-sweeps, the residual and the restriction in one block kernel; from zero
+            if (o.nu1 == 2 && leg2_on(lg, l > 0 || al0) && (!zero || g_tune.zero2)) {
+                // 2D: both pre-sweeps, the residual and the restriction in one kernel; from zero
                 // on level 0 into the partner buffer, so that the one-pass up-leg ends in the caller's x
                 if (zero) {
                     S *dst = l == 0 ? oth[0] : cur[l];
-                    NP_TRY((lvl2b<0, false>(nullptr, F[l], nullptr, dst, fc, nullptr, nullptr, lg, bc, hl, o.omega, s,
+                    NP_TRY((leg2<0, false>(l > 0 || al0, nullptr, F[l], nullptr, dst, fc, nullptr, nullptr, lg, bc, hl, o.omega, s,
                                             stop)));
                     if (l == 0) std::swap(cur[0], oth[0]);
                 } else if (check && l == 0) {
                     int nb = 0;
-                    NP_TRY((lvl2b<1, true>(nullptr, F[l], cur[l], oth[l], fc, H->red, &nb, lg, bc, hl, o.omega, s,
+                    NP_TRY((leg2<1, true>(l > 0 || al0, nullptr, F[l], cur[l], oth[l], fc, H->red, &nb, lg, bc, hl, o.omega, s,
                                            stop)));
                     NP_TRY(check_now(nb));
                     std::swap(cur[l], oth[l]);
                 } else {
-                    NP_TRY((lvl2b<1, false>(nullptr, F[l], cur[l], oth[l], fc, nullptr, nullptr, lg, bc, hl, o.omega,
+                    NP_TRY((leg2<1, false>(l > 0 || al0, nullptr, F[l], cur[l], oth[l], fc, nullptr, nullptr, lg, bc, hl, o.omega,
                                             s, stop)));
                     std::swap(cur[l], oth[l]);
                 }
@@ -1044,8 +1075,9 @@ template <int D, class S> struct Ops {
                 NP_TRY(up2b(res[l + 1], F[l], cur[l], oth[l], lg, bc, hl, o.omega, s, l == 0, stop));
                 std::swap(cur[l], oth[l]);
                 it = 2;
-            } else if (o.nu2 == 2 && blk2_on(lg) && psweep_on(lg, o.nu2) && (l > 0 || cur[0] != x0)) {
-                NP_TRY((lvl2b<2, false>(res[l + 1], F[l], cur[l], oth[l], nullptr, nullptr, nullptr, lg, bc, hl, o.omega,
+            } else if (o.nu2 == 2 && leg2_on(lg, l > 0 || al0) && psweep_on(lg, o.nu2) &&
+                       (l > 0 || cur[0] != x0)) {
+                NP_TRY((leg2<2, false>(l > 0 || al0, res[l + 1], F[l], cur[l], oth[l], nullptr, nullptr, nullptr, lg, bc, hl, o.omega,
                                         s, stop)));
                 std::swap(cur[l], oth[l]);
                 it = 2;
@@ -1587,7 +1619,7 @@ extern "C" np_status np_set_tuning(const char *key, int value) {
         {"batch", &g_tune.batch, 1, 64},        {"sweep3", &g_tune.sweep3, 0, 1},
         {"zero2", &g_tune.zero2, 0, 1},         {"psweep", &g_tune.psweep, 0, 1},
         {"ir_cpt", &g_tune.ir_cpt, 1, 2},      {"fuseb", &g_tune.fuseb, 0, 1}, {"fbnt", &g_tune.fbnt, 512, 1024},  {"sweep2z", &g_tune.sweep2z, 0, 1}, {"down2z", &g_tune.down2z, 0, 1}, {"blk2", &g_tune.blk2, 0, 1}, {"z2wg", &g_tune.z2wg, 0, 1}, {"greps", &g_tune.greps, 1, 8}, {"tailck", &g_tune.tailck, 0, 1}, {"zbar", &g_tune.zbar, 1, 2}, {"d2cpt", &g_tune.d2cpt, 1, 2}, {"d2wg", &g_tune.d2wg, 0, 1024},
-        {"fbmax", &g_tune.fbmax, 5, 10},
+        {"fbmax", &g_tune.fbmax, 5, 10},        {"w2min", &g_tune.w2min, 7, 14},
         {"batched_graphs", &g_batched_graphs, 0, 1}, {"batched_autotune", &g_batched_autotune, 0, 1},
         {"batched_rm", &g_batched_rm, 0, 1},    {"batched_wg", &g_batched_wg, 64, 1 << 20},
         {"zmarch_explicit", &g_zmarch_explicit, 0, 1}, {"mom_rows", &g_mom_rows, 4, 8}, {"mom_ring", &g_mom_ring, 2, 3}, {"zc3", &g_zc3, 0, 64}, {"conv3z", &g_conv3z, 0, 64},
@@ -1648,6 +1680,7 @@ extern "C" int np_get_tuning(const char *key) {
     if (!std::strcmp(key, "d2cpt")) return g_tune.d2cpt;
     if (!std::strcmp(key, "d2wg")) return g_tune.d2wg;
     if (!std::strcmp(key, "fbmax")) return g_tune.fbmax;
+    if (!std::strcmp(key, "w2min")) return g_tune.w2min;
     if (!std::strcmp(key, "batched_graphs")) return g_batched_graphs;
     if (!std::strcmp(key, "batched_autotune")) return g_batched_autotune;
     if (!std::strcmp(key, "batched_rm")) return g_batched_rm;
@@ -2306,6 +2339,8 @@ static np_status ad_l1_gauge(Hier *H, const double *x, const double *xold, hipSt
 // cell per thread.
 template <int D> static bool ad_zm3(int lg) { return D == 3 && lg >= 7 && g_tune.sweep3; }
 template <int D> static bool ad_rm2(int lg) { return D == 2 && lg >= 10 && g_tune.sweep3; }
+// whether a 2D level's V(2,2) legs run as one pass each (launch_leg2)
+template <int D> static bool ad_leg2(int lg, bool al) { return Ops<D, double>::leg2_on(lg, al); }
 
 // One relaxed-Jacobi sweep xo = xi + wd (f - A xi).  partial != null: also
 // the per-workgroup partials of ||f - A xi||^2, their count into *np.
@@ -2397,6 +2432,7 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
         hipLaunchKernelGGL((k_copy<double>), dim3(blocks_for(m0)), dim3(kBlock), 0, s, x, H->xold, m0, stop);
         NP_LAUNCH_CHECK();
     }
+    const bool al0 = aligned16(x, f);
     std::vector<double *> cur(L + 1), oth(L + 1);
     std::vector<const double *> F(L + 1);
     for (int l = 0; l <= L; ++l) {
@@ -2410,6 +2446,7 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
     if (g_tune.tail && co.nu1 >= 1)
         for (int l = 1; l <= L; ++l)
             if (lg0 - l <= Tail<D>::LG && lg0 - l > 2) { tl = l; break; }
+    int pend = 0;  // partials of the check that the tail runs
     double hl = h;
     for (int l = 0; l <= L; ++l, hl *= 2.0) {
         const int lg = lg0 - l;
@@ -2421,7 +2458,7 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
             AdLevels Wl{};
             for (int q = 0; q <= L - l; ++q) Wl.w[q] = ad_weights(op, D, hl * double(int64_t(1) << q));
             hipLaunchKernelGGL((k_ad_tail<D>), dim3(1), dim3(Tail<D>::NT_AD), 0, s, F[l], cur[l], H->ad_minv, lg, bc,
-                               Wl, co.omega, co.nu1, co.nu2, stop);
+                               Wl, co.omega, co.nu1, co.nu2, stop, H->red, pend, pend > 0 ? H->ctl : nullptr);
             NP_LAUNCH_CHECK();
             break;
         }
@@ -2442,6 +2479,29 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
         if (zero && co.nu1 == 0) {
             hipLaunchKernelGGL((k_zero<double>), dim3(blocks_for(m)), dim3(kBlock), 0, s, cur[l], m, stop);
             NP_LAUNCH_CHECK();
+        }
+        if (co.nu1 == 2 && ad_leg2<D>(lg, l > 0 || al0)) {
+            // both pre-sweeps, the residual and its restriction in one pass
+            if constexpr (D == 2) {
+                const Ad2 op2{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], wd};
+                double *fc = (double *)H->f[l + 1];
+                unsigned nb = 0;
+                if (zero) {
+                    NP_TRY((launch_leg2<double, Ad2, 0, false>(l > 0 || al0, nullptr, F[l], nullptr, cur[l], fc, nullptr, &nb, lg,
+                                                                bc, op2, s, stop)));
+                } else {
+                    NP_TRY((launch_leg2<double, Ad2, 1, true>(l > 0 || al0, nullptr, F[l], cur[l], oth[l], fc, H->red, &nb, lg, bc,
+                                                               op2, s, stop)));
+                    if (tl > 0 && g_tune.tailck) {  // x is not written before the tail
+                        pend = int(nb);
+                    } else {
+                        hipLaunchKernelGGL(k_check, dim3(1), dim3(kBlock), 0, s, H->red, int(nb), H->ctl);
+                        NP_LAUNCH_CHECK();
+                    }
+                    std::swap(cur[l], oth[l]);
+                }
+            }
+            continue;
         }
         for (int it = 0; it < co.nu1; ++it) {
             void *tok = nullptr;
@@ -2473,6 +2533,16 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
         const int64_t m = cells(D, lg);
         const AdW W = ad_weights(op, D, h * double(int64_t(1) << l));
         const double wd = co.omega / W.c0;
+        if (co.nu2 == 2 && ad_leg2<D>(lg, l > 0 || al0)) {  // prolongation + correction and both post-sweeps
+            if constexpr (D == 2) {
+                const Ad2 op2{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], wd};
+                unsigned nb = 0;
+                NP_TRY((launch_leg2<double, Ad2, 2, false>(l > 0 || al0, cur[l + 1], F[l], cur[l], oth[l], nullptr, nullptr, &nb, lg,
+                                                            bc, op2, s, stop)));
+            }
+            std::swap(cur[l], oth[l]);
+            continue;
+        }
         void *tok = nullptr;
         const bool prof = l == 0 && (prof_on() & kProfProlong);
         if (prof) NP_TRY(prof_begin(s, &tok));

@@ -23,6 +23,16 @@
 
 namespace np {
 
+// The operator a 2D leg applies: the residual at a cell from its neighbours, and the relaxed-Jacobi
+// weight.  Lap2: A = -Lap_h (the advection-diffusion operator: Ad2).
+template <class C> struct Lap2 {
+    C inv_h2, wd;
+    __device__ __forceinline__ C resid(C f, C xc, C xm, C xp, C ym, C yp) const {
+        const C s = ((xm + xp) + ym) + yp;
+        return f - (C(4) * xc - s) * inv_h2;
+    }
+};
+
 template <class S> struct B2 {
     static constexpr int BX = 64, BY = 16, NT = 1024;
     static constexpr int W(int k) { return BX + 2 * k; }
@@ -51,12 +61,11 @@ __device__ __forceinline__ int eval_pos2(int &a, int &b, int x0, int y0, int n, 
     return outs == 0 ? 1 : (outs == 1 ? -1 : 0);
 }
 
-template <class S, int MODE, bool NORM>
+template <class S, class OP, int MODE, bool NORM>
 __global__ __launch_bounds__(B2<S>::NT) void k_lvl2_b(const S *__restrict__ ec, const S *__restrict__ f,
                                                       const S *__restrict__ xin, S *__restrict__ xout,
                                                       S *__restrict__ fc, double *__restrict__ partial, int lg,
-                                                      int bc, typename St<S>::C inv_h2, typename St<S>::C wdiag,
-                                                      const int *stop) {
+                                                      int bc, OP op, const int *stop) {
     typedef typename St<S>::C C;
     typedef B2<S> G;
     constexpr int BX = G::BX, BY = G::BY, NT = G::NT;
@@ -159,10 +168,9 @@ __global__ __launch_bounds__(B2<S>::NT) void k_lvl2_b(const S *__restrict__ ec, 
                 const C fv = Fs[(b + RING_F) * WF + a + RING_F];
                 const int q = (b + RING_A) * WA + a + RING_A;
                 const C xc = A[q];
-                const C s = ((A[q - 1] + A[q + 1]) + A[q - WA]) + A[q + WA];
-                const C r = fv - (C(4) * xc - s) * inv_h2;
+                const C r = op.resid(fv, xc, A[q - 1], A[q + 1], A[q - WA], A[q + WA]);
                 if (NORM && own) acc += double(r) * double(r);
-                v = C(sgn) * st_round<S>(xc + wdiag * r);
+                v = C(sgn) * st_round<S>(xc + op.wd * r);
             }
             S1[e] = v;
         }
@@ -175,9 +183,8 @@ __global__ __launch_bounds__(B2<S>::NT) void k_lvl2_b(const S *__restrict__ ec, 
             const int a = e % BX, b = e / BX;
             const int q = (b + 1) * W1 + a + 1;
             const C xc = S1[q];
-            const C s = ((S1[q - 1] + S1[q + 1]) + S1[q - W1]) + S1[q + W1];
-            const C r = Fs[q] - (C(4) * xc - s) * inv_h2;
-            St<S>::st(xout + (int64_t(y0 + b) << lg) + x0 + a, xc + wdiag * r);
+            const C r = op.resid(Fs[q], xc, S1[q - 1], S1[q + 1], S1[q - W1], S1[q + W1]);
+            St<S>::st(xout + (int64_t(y0 + b) << lg) + x0 + a, xc + op.wd * r);
         }
     } else {
         // on ring 1 from S1 (ring 2); MODE 0 forms each neighbour's w f as its own product, as
@@ -191,20 +198,19 @@ __global__ __launch_bounds__(B2<S>::NT) void k_lvl2_b(const S *__restrict__ ec, 
             if (sgn != 0) {
                 const int q = (b + 2) * W2 + a + 2;
                 const C fv = Fs[q];
-                C xc, s;
+                C xc, r;
                 if constexpr (MODE == 0) {
-                    xc = wdiag * fv;
-                    const C xm = wdiag * Fs[q - 1];
-                    const C xp = wdiag * Fs[q + 1];
-                    const C ym = wdiag * Fs[q - W2];
-                    const C yp = wdiag * Fs[q + W2];
-                    s = ((xm + xp) + ym) + yp;
+                    xc = op.wd * fv;
+                    const C xm = op.wd * Fs[q - 1];
+                    const C xp = op.wd * Fs[q + 1];
+                    const C ym = op.wd * Fs[q - W2];
+                    const C yp = op.wd * Fs[q + W2];
+                    r = op.resid(fv, xc, xm, xp, ym, yp);
                 } else {
                     xc = S1[q];
-                    s = ((S1[q - 1] + S1[q + 1]) + S1[q - W2]) + S1[q + W2];
+                    r = op.resid(fv, xc, S1[q - 1], S1[q + 1], S1[q - W2], S1[q + W2]);
                 }
-                const C r = fv - (C(4) * xc - s) * inv_h2;
-                v = C(sgn) * st_round<S>(xc + wdiag * r);
+                v = C(sgn) * st_round<S>(xc + op.wd * r);
             }
             S2[e] = v;
             if (own && sgn != 0) St<S>::st(xout + (int64_t(y0 + b) << lg) + x0 + a, v);
@@ -217,8 +223,7 @@ __global__ __launch_bounds__(B2<S>::NT) void k_lvl2_b(const S *__restrict__ ec, 
             const int a = e % BX, b = e / BX;
             const int q = (b + 1) * W1 + a + 1;
             const C xc = S2[q];
-            const C s = ((S2[q - 1] + S2[q + 1]) + S2[q - W1]) + S2[q + W1];
-            Rr[e] = Fs[(b + 2) * W2 + a + 2] - (C(4) * xc - s) * inv_h2;
+            Rr[e] = op.resid(Fs[(b + 2) * W2 + a + 2], xc, S2[q - 1], S2[q + 1], S2[q - W1], S2[q + W1]);
         }
         __syncthreads();
         if (t < (BX / 2) * (BY / 2)) {

@@ -1,0 +1,97 @@
+"""One-pass legs of the 2D levels: row-marching wavefronts (k_wave2) against the block and
+per-cell kernels they replace, and both with the advection-diffusion operator."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+DIR, PER = 0, 1
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2402_17913_amd import binding
+    yield binding
+    binding.np_set_tuning("w2min", 10)
+    binding.np_release_all()
+
+
+def _rhs(n, seed, offset=0):
+    """A rough right-hand side; offset: that many values into its allocation."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    a = torch.randn(n * n + offset, dtype=torch.float64, device="cuda", generator=g)
+    return a[offset:].view(n, n)
+
+
+def _with(B, w2min, solve):
+    B.np_set_tuning("w2min", w2min)
+    try:
+        return solve()
+    finally:
+        B.np_set_tuning("w2min", 10)
+
+
+# 128: one strip with idle lanes; 256, 1024: strips of 120, 124 and 248 columns end inside a wave;
+# 2048: the per-cell kernels on the other side
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("bc", [DIR, PER])
+@pytest.mark.parametrize("n", [128, 256, 1024, 2048])
+def test_wavefront_legs_poisson(B, n, bc, prec):
+    """Fixed cycles (outer steps): the same sums in the same order, so bit for bit."""
+    import torch
+    f = _rhs(n, n + bc)
+    print("legs2 poisson", n, bc, prec, flush=True)
+
+    def solve():
+        x = torch.zeros_like(f)
+        _, st = B.mg_poisson_solve(f, x, 1.0 / n, bc, smooth_prec=prec, fixed_cycles=3)
+        return x, st["hist"]
+
+    a, b = _with(B, 14, solve), _with(B, 7, solve)
+    assert torch.isfinite(a[0]).all() and a[0].abs().max() > 0
+    assert torch.equal(a[0], b[0])
+    # the check sums its partials over other tiles: agreement to the rounding of n^2 terms
+    assert all(abs(u - v) <= 1e-12 * max(u, 1e-300) for u, v in zip(a[1], b[1]))
+
+
+@pytest.mark.parametrize("scheme,vel", [(0, [1.0, 1.0]), (0, [-1.0, 0.5]), (1, [0.2, -0.1])])
+@pytest.mark.parametrize("bc", [DIR, PER])
+@pytest.mark.parametrize("n", [128, 1024, 2048])
+def test_wavefront_legs_advection_diffusion(B, n, bc, scheme, vel):
+    """Against the block kernels bit for bit (up to 1024), against the separate sweep, restriction
+    and prolongation kernels to rounding (2048: 1e-13 per cycle of values of order one)."""
+    import torch
+    f = _rhs(n, n + bc)
+    op = B.ad_op(20.0, 2.0, vel, scheme)
+    print("legs2 ad", n, bc, scheme, vel, flush=True)
+
+    def solve():
+        x = torch.zeros_like(f)
+        B.np_ad_implicit_solve(f, x, 1.0, bc, op, fixed_cycles=3)
+        return x
+
+    a, b = _with(B, 14, solve), _with(B, 7, solve)
+    assert torch.isfinite(a).all() and a.abs().max() > 0
+    if n <= 1024:
+        assert torch.equal(a, b)
+    else:
+        assert (a - b).abs().max() <= 3e-13 * a.abs().max()
+
+
+@pytest.mark.parametrize("n", [1024, 2048])
+def test_legs_unaligned_fields(B, n):
+    """Fields that are not 16-byte aligned take the other kernels on the finest level."""
+    import torch
+    f = _rhs(n, n, offset=1)
+    assert f.data_ptr() % 16 == 8
+    g = f.clone()
+    x, y = torch.zeros(n * n + 1, dtype=torch.float64, device="cuda")[1:].view(n, n), torch.zeros_like(g)
+    B.mg_poisson_solve(f, x, 1.0 / n, DIR, fixed_cycles=2)
+    B.mg_poisson_solve(g, y, 1.0 / n, DIR, fixed_cycles=2)
+    assert torch.equal(x, y)
+    op = B.ad_op(20.0, 2.0, [1.0, 1.0], 0)
+    B.np_ad_implicit_solve(f, x, 1.0, DIR, op, fixed_cycles=2)
+    B.np_ad_implicit_solve(g, y, 1.0, DIR, op, fixed_cycles=2)
+    assert (x - y).abs().max() <= 2e-13 * y.abs().max()
