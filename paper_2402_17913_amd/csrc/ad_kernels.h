@@ -28,6 +28,16 @@ struct Ad2 {
     }
 };
 
+// The 3D operator as the one-pass legs apply it.
+struct Ad3 {
+    double c0, xl, xu, yl, yu, zl, zu, wd;
+    __device__ __forceinline__ double resid(double f, double xc, double xm, double xp, double ym, double yp, double zm,
+                                            double zp) const {
+        const double s = c0 * xc + (xl * xm + xu * xp) + (yl * ym + yu * yp) + (zl * zm + zu * zp);
+        return f - s;
+    }
+};
+
 // (A x)_c at cell c = (i, j, k).
 template <int D>
 __device__ __forceinline__ double ad_ax(const double *__restrict__ x, int64_t c, int i, int j, int k, int lg, int bc,

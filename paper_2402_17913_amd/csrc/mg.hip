@@ -569,24 +569,27 @@ template <int D, class S> struct Ops {
         return NP_OK;
     }
 
+    // The operator of the 3D one-pass legs.
+    static Lap3<C> lap3(double h, double omega) {
+        return Lap3<C>{C(1.0 / (h * h)), C(omega * h * h / (2.0 * D))};
+    }
+
     // Whether a 3D level runs the block kernels (k_down0_b, k_up2_b): levels from 32^3 up to 2^fbmax.
     static bool fuseb_on(int lg) { return D == 3 && g_tune.fuseb && lg >= 5 && lg <= g_tune.fbmax; }
 
     // The block forms of down0 and up2 (8^3 cells per workgroup).
-    static np_status down0b(const S *f, S *x, S *fc, int lg, int bc, double h, double omega, hipStream_t s,
+    template <class OP>
+    static np_status down0b(const S *f, S *x, S *fc, int lg, int bc, const OP &op, hipStream_t s,
                             bool finest, const int *stop) {
         if constexpr (D == 3) {
-            const C inv_h2 = C(1.0 / (h * h)), wdiag = C(omega * h * h / (2.0 * D));
             const unsigned nb = unsigned(int64_t(1) << (3 * (lg - 3)));
             void *tok = nullptr;
             const bool prof = finest && (prof_on() & kProfDownZero);
             if (prof) NP_TRY(prof_begin(s, &tok));
             if (g_tune.fbnt == 1024)
-                hipLaunchKernelGGL((k_down0_b<S, 8, 1024>), dim3(nb), dim3(1024), 0, s, f, x, fc, lg, bc, inv_h2, wdiag,
-                                   stop);
+                hipLaunchKernelGGL((k_down0_b<S, OP, 8, 1024>), dim3(nb), dim3(1024), 0, s, f, x, fc, lg, bc, op, stop);
             else
-                hipLaunchKernelGGL((k_down0_b<S, 8>), dim3(nb), dim3(BTile<8>::NT), 0, s, f, x, fc, lg, bc, inv_h2,
-                                   wdiag, stop);
+                hipLaunchKernelGGL((k_down0_b<S, OP, 8>), dim3(nb), dim3(BTile<8>::NT), 0, s, f, x, fc, lg, bc, op, stop);
             NP_LAUNCH_CHECK();
             if (prof) {
                 const double m = double(cells(D, lg));
@@ -594,24 +597,23 @@ template <int D, class S> struct Ops {
             }
             return NP_OK;
         } else {
-            (void)f; (void)x; (void)fc; (void)lg; (void)bc; (void)h; (void)omega; (void)s; (void)finest; (void)stop;
+            (void)f; (void)x; (void)fc; (void)lg; (void)bc; (void)op; (void)s; (void)finest; (void)stop;
             return NP_EINVAL;
         }
     }
-    static np_status up2b(const S *ec, const S *f, const S *x, S *xout, int lg, int bc, double h, double omega,
+    template <class OP>
+    static np_status up2b(const S *ec, const S *f, const S *x, S *xout, int lg, int bc, const OP &op,
                           hipStream_t s, bool finest, const int *stop) {
         if constexpr (D == 3) {
-            const C inv_h2 = C(1.0 / (h * h)), wdiag = C(omega * h * h / (2.0 * D));
             const unsigned nb = unsigned(int64_t(1) << (3 * (lg - 3)));
             void *tok = nullptr;
             const bool prof = finest && (prof_on() & kProfUp);
             if (prof) NP_TRY(prof_begin(s, &tok));
             if (g_tune.fbnt == 1024)
-                hipLaunchKernelGGL((k_up2_b<S, 8, 1024>), dim3(nb), dim3(1024), 0, s, ec, f, x, xout, lg, bc, inv_h2,
-                                   wdiag, stop);
+                hipLaunchKernelGGL((k_up2_b<S, OP, 8, 1024>), dim3(nb), dim3(1024), 0, s, ec, f, x, xout, lg, bc, op, stop);
             else
-                hipLaunchKernelGGL((k_up2_b<S, 8>), dim3(nb), dim3(BTile<8>::NT), 0, s, ec, f, x, xout, lg, bc,
-                                   inv_h2, wdiag, stop);
+                hipLaunchKernelGGL((k_up2_b<S, OP, 8>), dim3(nb), dim3(BTile<8>::NT), 0, s, ec, f, x, xout, lg, bc,
+                                   op, stop);
             NP_LAUNCH_CHECK();
             if (prof) {
                 const double m = double(cells(D, lg));
@@ -619,7 +621,7 @@ template <int D, class S> struct Ops {
             }
             return NP_OK;
         } else {
-            (void)ec; (void)f; (void)x; (void)xout; (void)lg; (void)bc; (void)h; (void)omega; (void)s; (void)finest;
+            (void)ec; (void)f; (void)x; (void)xout; (void)lg; (void)bc; (void)op; (void)s; (void)finest;
             (void)stop;
             return NP_EINVAL;
         }
@@ -631,10 +633,10 @@ template <int D, class S> struct Ops {
 
     // xout = sweep(sweep(x')) on a 3D level of 128 <= n <= 1024 (k_sweep2z), x' = x + P ec when ec is
     // given, else x; with `partial`, also the per-workgroup partials of |f - A x|^2 (their count in *np).
+    template <class OP>
     static np_status sweep2z(const S *ec, const S *f, const S *x, S *xout, double *partial, int *np, int lg,
-                             int bc, double h, double omega, hipStream_t s, bool finest, const int *stop) {
+                             int bc, const OP &op, hipStream_t s, bool finest, const int *stop) {
         if constexpr (D == 3) {
-            const C inv_h2 = C(1.0 / (h * h)), wdiag = C(omega * h * h / (2.0 * D));
             constexpr int CPT = ZCfg<S>::CPT;
             // up-leg: 512 workgroups (two per CU), 256 in FP64 (one per CU at 129 VGPRs)
             const int zc = sweep2z_planes<S>(lg, ec && g_tune.z2wg ? (sizeof(S) == 8 ? 256 : 512) : 1024);
@@ -643,14 +645,14 @@ template <int D, class S> struct Ops {
             const bool prof = finest && (prof_on() & (ec ? kProfUp : kProfJacobi));
             if (prof) NP_TRY(prof_begin(s, &tok));
             if (ec)
-                hipLaunchKernelGGL((k_sweep2z<S, true, false>), dim3(nb), dim3(kS3Threads), 0, s, ec, f, x, xout,
-                                   nullptr, lg, bc, zc, inv_h2, wdiag, stop);
+                hipLaunchKernelGGL((k_sweep2z<S, OP, true, false>), dim3(nb), dim3(kS3Threads), 0, s, ec, f, x, xout,
+                                   nullptr, lg, bc, zc, op, stop);
             else if (partial)
-                hipLaunchKernelGGL((k_sweep2z<S, false, true>), dim3(nb), dim3(kS3Threads), 0, s, nullptr, f, x,
-                                   xout, partial, lg, bc, zc, inv_h2, wdiag, stop);
+                hipLaunchKernelGGL((k_sweep2z<S, OP, false, true>), dim3(nb), dim3(kS3Threads), 0, s, nullptr, f, x,
+                                   xout, partial, lg, bc, zc, op, stop);
             else
-                hipLaunchKernelGGL((k_sweep2z<S, false, false>), dim3(nb), dim3(kS3Threads), 0, s, nullptr, f, x,
-                                   xout, nullptr, lg, bc, zc, inv_h2, wdiag, stop);
+                hipLaunchKernelGGL((k_sweep2z<S, OP, false, false>), dim3(nb), dim3(kS3Threads), 0, s, nullptr, f, x,
+                                   xout, nullptr, lg, bc, zc, op, stop);
             NP_LAUNCH_CHECK();
             if (prof) {
                 const double m = double(cells(D, lg));
@@ -659,29 +661,29 @@ template <int D, class S> struct Ops {
             if (np) *np = int(nb);
             return NP_OK;
         } else {
-            (void)ec; (void)f; (void)x; (void)xout; (void)partial; (void)np; (void)lg; (void)bc; (void)h;
-            (void)omega; (void)s; (void)finest; (void)stop;
+            (void)ec; (void)f; (void)x; (void)xout; (void)partial; (void)np; (void)lg; (void)bc; (void)op;
+            (void)s; (void)finest; (void)stop;
             return NP_EINVAL;
         }
     }
 
     // x = sweep(sweep(0)) and fc = R (f - A x) in one z-marching pass on a 3D level of
     // 128 <= n <= 1024 (k_down0z).
-    static np_status down0z(const S *f, S *x, S *fc, int lg, int bc, double h, double omega, hipStream_t s,
+    template <class OP>
+    static np_status down0z(const S *f, S *x, S *fc, int lg, int bc, const OP &op, hipStream_t s,
                             bool finest, const int *stop) {
         if constexpr (D == 3) {
-            const C inv_h2 = C(1.0 / (h * h)), wdiag = C(omega * h * h / (2.0 * D));
             constexpr int CPT = ZCfg<S>::CPT;
             const int zc = sweep2z_planes<S>(lg, sizeof(S) == 8 && g_tune.z2wg ? 512 : 1024);
             void *tok = nullptr;
             const bool prof = finest && (prof_on() & kProfDownZero);
             if (prof) NP_TRY(prof_begin(s, &tok));
-            if (g_tune.zbar == 1)
-                hipLaunchKernelGGL((k_down0z1<S>), dim3(zblocks(lg, CPT, zc)), dim3(kS3Threads), 0, s, f, x, fc, lg,
-                                   bc, zc, inv_h2, wdiag, stop);
-            else
+            if (g_tune.zbar == 1 || !std::is_same<OP, Lap3<C>>::value)
+                hipLaunchKernelGGL((k_down0z1<S, OP>), dim3(zblocks(lg, CPT, zc)), dim3(kS3Threads), 0, s, f, x, fc, lg,
+                                   bc, zc, op, stop);
+            else if constexpr (std::is_same<OP, Lap3<C>>::value)
                 hipLaunchKernelGGL((k_down0z<S>), dim3(zblocks(lg, CPT, zc)), dim3(kS3Threads), 0, s, f, x, fc, lg,
-                                   bc, zc, inv_h2, wdiag, stop);
+                                   bc, zc, op.inv_h2, op.wd, stop);
             NP_LAUNCH_CHECK();
             if (prof) {
                 const double m = double(cells(D, lg));
@@ -689,7 +691,7 @@ template <int D, class S> struct Ops {
             }
             return NP_OK;
         } else {
-            (void)f; (void)x; (void)fc; (void)lg; (void)bc; (void)h; (void)omega; (void)s; (void)finest; (void)stop;
+            (void)f; (void)x; (void)fc; (void)lg; (void)bc; (void)op; (void)s; (void)finest; (void)stop;
             return NP_EINVAL;
         }
     }
@@ -706,11 +708,11 @@ template <int D, class S> struct Ops {
         return z2_on(lg) && lg >= 8 && (sizeof(S) == 8 || (sizeof(S) == 4 && g_tune.d2cpt == 2)) &&
                g_tune.down2z;
     }
+    template <class OP>
     static np_status down2z(const S *f, const S *xin, S *x, S *fc, double *partial, int *np, int lg, int bc,
-                            double h, double omega, hipStream_t s, bool finest, const int *stop) {
+                            const OP &op, hipStream_t s, bool finest, const int *stop) {
         if constexpr (D == 3) {
-            const C inv_h2 = C(1.0 / (h * h)), wdiag = C(omega * h * h / (2.0 * D));
-            const bool two = g_tune.d2cpt == 2;  // two cells per thread (k_down2z2)
+            const bool two = g_tune.d2cpt == 2 || !std::is_same<OP, Lap3<C>>::value;  // two cells per thread (k_down2z2)
             // two cells per thread: one workgroup per CU in FP64 (148 VGPRs: the FP64 solve measured
             // 6.18 ms at 512 workgroups, 5.95 at 256), two in FP32 (85: 3.97 ms at 512, 4.13 at 256)
             const int wg2 = g_tune.d2wg ? g_tune.d2wg : (sizeof(S) == 8 ? 256 : 512);
@@ -720,17 +722,19 @@ template <int D, class S> struct Ops {
             const bool prof = finest && (prof_on() & kProfDown);
             if (prof) NP_TRY(prof_begin(s, &tok));
             if (two && partial)
-                hipLaunchKernelGGL((k_down2z2<S, true>), dim3(nb), dim3(kS3Threads), 0, s, f, xin, x, fc, partial, lg,
-                                   bc, zc, inv_h2, wdiag, stop);
+                hipLaunchKernelGGL((k_down2z2<S, OP, true>), dim3(nb), dim3(kS3Threads), 0, s, f, xin, x, fc, partial, lg,
+                                   bc, zc, op, stop);
             else if (two)
-                hipLaunchKernelGGL((k_down2z2<S, false>), dim3(nb), dim3(kS3Threads), 0, s, f, xin, x, fc, nullptr,
-                                   lg, bc, zc, inv_h2, wdiag, stop);
-            else if (partial)
-                hipLaunchKernelGGL((k_down2z<S, true>), dim3(nb), dim3(kS3Threads), 0, s, f, xin, x, fc, partial, lg,
-                                   bc, zc, inv_h2, wdiag, stop);
-            else
-                hipLaunchKernelGGL((k_down2z<S, false>), dim3(nb), dim3(kS3Threads), 0, s, f, xin, x, fc, nullptr,
-                                   lg, bc, zc, inv_h2, wdiag, stop);
+                hipLaunchKernelGGL((k_down2z2<S, OP, false>), dim3(nb), dim3(kS3Threads), 0, s, f, xin, x, fc, nullptr,
+                                   lg, bc, zc, op, stop);
+            else if constexpr (std::is_same<OP, Lap3<C>>::value) {
+                if (partial)
+                    hipLaunchKernelGGL((k_down2z<S, true>), dim3(nb), dim3(kS3Threads), 0, s, f, xin, x, fc, partial, lg,
+                                       bc, zc, op.inv_h2, op.wd, stop);
+                else
+                    hipLaunchKernelGGL((k_down2z<S, false>), dim3(nb), dim3(kS3Threads), 0, s, f, xin, x, fc, nullptr,
+                                       lg, bc, zc, op.inv_h2, op.wd, stop);
+            }
             NP_LAUNCH_CHECK();
             if (prof) {
                 const double m = double(cells(D, lg));
@@ -739,7 +743,7 @@ template <int D, class S> struct Ops {
             if (np) *np = int(nb);
             return NP_OK;
         } else {
-            (void)f; (void)xin; (void)x; (void)fc; (void)partial; (void)np; (void)lg; (void)bc; (void)h; (void)omega;
+            (void)f; (void)xin; (void)x; (void)fc; (void)partial; (void)np; (void)lg; (void)bc; (void)op;
             (void)s; (void)finest; (void)stop;
             return NP_EINVAL;
         }
@@ -983,8 +987,8 @@ template <int D, class S> struct Ops {
                 // both pre-sweeps from zero, the residual and the restriction in one pass; on level 0
                 // into the partner buffer, so that the one-pass up-leg ends in the caller's x
                 S *dst = l == 0 ? oth[0] : cur[l];
-                if (fuseb_on(lg)) NP_TRY(down0b(F[l], dst, fc, lg, bc, hl, o.omega, s, l == 0, stop));
-                else NP_TRY(down0z(F[l], dst, fc, lg, bc, hl, o.omega, s, l == 0, stop));
+                if (fuseb_on(lg)) NP_TRY(down0b(F[l], dst, fc, lg, bc, lap3(hl, o.omega), s, l == 0, stop));
+                else NP_TRY(down0z(F[l], dst, fc, lg, bc, lap3(hl, o.omega), s, l == 0, stop));
                 if (l == 0) std::swap(cur[0], oth[0]);
                 if (l + 1 == tl) { hl *= 2.0; break; }
                 continue;
@@ -1007,10 +1011,10 @@ template <int D, class S> struct Ops {
                 const bool ck = check && l == 0 && !zero;
                 int nb = 0;
                 if (down2_on(lg)) {
-                    NP_TRY(down2z(F[l], cur[l], oth[l], fc, ck ? H->red : nullptr, &nb, lg, bc, hl, o.omega, s, l == 0,
+                    NP_TRY(down2z(F[l], cur[l], oth[l], fc, ck ? H->red : nullptr, &nb, lg, bc, lap3(hl, o.omega), s, l == 0,
                                   stop));
                 } else {
-                    NP_TRY(sweep2z(nullptr, F[l], cur[l], oth[l], ck ? H->red : nullptr, &nb, lg, bc, hl, o.omega, s,
+                    NP_TRY(sweep2z(nullptr, F[l], cur[l], oth[l], ck ? H->red : nullptr, &nb, lg, bc, lap3(hl, o.omega), s,
                                    l == 0, stop));
                 }
                 if (ck) NP_TRY(check_now(nb));
@@ -1072,7 +1076,7 @@ template <int D, class S> struct Ops {
             // prolongation + correction and both post-sweeps in one pass (on level 0 only when the
             // result lands in the caller's x)
             if (o.nu2 == 2 && fuseb_on(lg) && psweep_on(lg, o.nu2) && (l > 0 || cur[0] != x0)) {
-                NP_TRY(up2b(res[l + 1], F[l], cur[l], oth[l], lg, bc, hl, o.omega, s, l == 0, stop));
+                NP_TRY(up2b(res[l + 1], F[l], cur[l], oth[l], lg, bc, lap3(hl, o.omega), s, l == 0, stop));
                 std::swap(cur[l], oth[l]);
                 it = 2;
             } else if (o.nu2 == 2 && leg2_on(lg, l > 0 || al0) && psweep_on(lg, o.nu2) &&
@@ -1082,7 +1086,7 @@ template <int D, class S> struct Ops {
                 std::swap(cur[l], oth[l]);
                 it = 2;
             } else if (o.nu2 == 2 && z2_on(lg) && psweep_on(lg, o.nu2) && (l > 0 || cur[0] != x0)) {
-                NP_TRY(sweep2z(res[l + 1], F[l], cur[l], oth[l], nullptr, nullptr, lg, bc, hl, o.omega, s, l == 0,
+                NP_TRY(sweep2z(res[l + 1], F[l], cur[l], oth[l], nullptr, nullptr, lg, bc, lap3(hl, o.omega), s, l == 0,
                                stop));
                 std::swap(cur[l], oth[l]);
                 it = 2;
@@ -2160,23 +2164,23 @@ static np_status op_level(int kind, const void *f, void *x, void *xout, void *c,
     switch (kind) {
     case 0: return O::sweep((const S *)f, nullptr, (S *)x, lg, bc, h, w, 2, nullptr, nullptr, s, false, nullptr);
     case 1: return O::restrict_((const S *)f, (const S *)x, (S *)c, lg, bc, h, s, nullptr);
-    case 2: return O::down0b((const S *)f, (S *)x, (S *)c, lg, bc, h, w, s, false, nullptr);
+    case 2: return O::down0b((const S *)f, (S *)x, (S *)c, lg, bc, O::lap3(h, w), s, false, nullptr);
     case 3:
         NP_TRY(O::psweep((const S *)c, (const S *)f, (const S *)x, (S *)xout, lg, bc, h, w, s, false, nullptr));
         return O::sweep((const S *)f, (const S *)xout, (S *)x, lg, bc, h, w, 0, nullptr, nullptr, s, false, nullptr);
-    case 4: return O::up2b((const S *)c, (const S *)f, (const S *)x, (S *)xout, lg, bc, h, w, s, false, nullptr);
+    case 4: return O::up2b((const S *)c, (const S *)f, (const S *)x, (S *)xout, lg, bc, O::lap3(h, w), s, false, nullptr);
     case 5:
     case 6:
     case 7:
     case 8:
         if (lg < 7 || lg > 10) { set_error("kinds 5 to 8 need 128 <= n <= 1024"); return NP_EINVAL; }
-        if (kind == 7) return O::down0z((const S *)f, (S *)x, (S *)c, lg, bc, h, w, s, false, nullptr);
+        if (kind == 7) return O::down0z((const S *)f, (S *)x, (S *)c, lg, bc, O::lap3(h, w), s, false, nullptr);
         if (kind == 8) {
-            return O::down2z((const S *)f, (const S *)x, (S *)xout, (S *)c, nullptr, nullptr, lg, bc, h, w, s, false,
+            return O::down2z((const S *)f, (const S *)x, (S *)xout, (S *)c, nullptr, nullptr, lg, bc, O::lap3(h, w), s, false,
                              nullptr);
         }
         return O::sweep2z(kind == 5 ? (const S *)c : nullptr, (const S *)f, (const S *)x, (S *)xout, nullptr,
-                          nullptr, lg, bc, h, w, s, false, nullptr);
+                          nullptr, lg, bc, O::lap3(h, w), s, false, nullptr);
     }
     return NP_EINVAL;
 }
@@ -2339,8 +2343,52 @@ static np_status ad_l1_gauge(Hier *H, const double *x, const double *xold, hipSt
 // cell per thread.
 template <int D> static bool ad_zm3(int lg) { return D == 3 && lg >= 7 && g_tune.sweep3; }
 template <int D> static bool ad_rm2(int lg) { return D == 2 && lg >= 10 && g_tune.sweep3; }
-// whether a 2D level's V(2,2) legs run as one pass each (launch_leg2)
-template <int D> static bool ad_leg2(int lg, bool al) { return Ops<D, double>::leg2_on(lg, al); }
+// Whether a level's V(2,2) legs run as one pass each, on the Poisson cycle's kernels with this
+// operator: 2D launch_leg2; 3D the z-marching tiles (aligned fields) and, below 128^3, the blocks,
+// which have no down-leg of a nonzero iterate (`zero`).  Measured against the separate sweep,
+// restriction and prolongation kernels (three to six passes over each level): the 256^3 solve
+// 18.2 -> 9.4 ms, a fused leg moving 25 bytes per cell where the separate kernels moved 64 and 65.
+template <int D> static bool ad_leg(int lg, bool al, bool zero) {
+    typedef Ops<D, double> O;
+    if (D == 2) return O::leg2_on(lg, al);
+    return (O::z2_on(lg) && al) || (O::fuseb_on(lg) && zero);
+}
+template <int D>
+static np_status ad_down(bool zero, bool al, const double *f, const double *xin, double *xout, double *fc,
+                         double *partial, int *np, int lg, int bc, const AdW &W, double wd, hipStream_t s,
+                         const int *stop) {
+    typedef Ops<D, double> O;
+    if constexpr (D == 2) {
+        const Ad2 op{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], wd};
+        unsigned nb = 0;
+        if (zero)
+            return launch_leg2<double, Ad2, 0, false>(al, nullptr, f, nullptr, xout, fc, nullptr, &nb, lg, bc, op, s,
+                                                      stop);
+        NP_TRY((launch_leg2<double, Ad2, 1, true>(al, nullptr, f, xin, xout, fc, partial, &nb, lg, bc, op, s, stop)));
+        *np = int(nb);
+        return NP_OK;
+    } else {
+        const Ad3 op{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], W.cm[2], W.cp[2], wd};
+        if (!zero) return O::down2z(f, xin, xout, fc, partial, np, lg, bc, op, s, false, stop);
+        if (O::fuseb_on(lg)) return O::down0b(f, xout, fc, lg, bc, op, s, false, stop);
+        return O::down0z(f, xout, fc, lg, bc, op, s, false, stop);
+    }
+}
+template <int D>
+static np_status ad_up(bool al, const double *ec, const double *f, const double *xin, double *xout, int lg, int bc,
+                       const AdW &W, double wd, hipStream_t s, const int *stop) {
+    typedef Ops<D, double> O;
+    if constexpr (D == 2) {
+        const Ad2 op{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], wd};
+        unsigned nb = 0;
+        return launch_leg2<double, Ad2, 2, false>(al, ec, f, xin, xout, nullptr, nullptr, &nb, lg, bc, op, s, stop);
+    } else {
+        (void)al;
+        const Ad3 op{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], W.cm[2], W.cp[2], wd};
+        if (O::fuseb_on(lg)) return O::up2b(ec, f, xin, xout, lg, bc, op, s, false, stop);
+        return O::sweep2z(ec, f, xin, xout, nullptr, nullptr, lg, bc, op, s, false, stop);
+    }
+}
 
 // One relaxed-Jacobi sweep xo = xi + wd (f - A xi).  partial != null: also
 // the per-workgroup partials of ||f - A xi||^2, their count into *np.
@@ -2480,26 +2528,19 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
             hipLaunchKernelGGL((k_zero<double>), dim3(blocks_for(m)), dim3(kBlock), 0, s, cur[l], m, stop);
             NP_LAUNCH_CHECK();
         }
-        if (co.nu1 == 2 && ad_leg2<D>(lg, l > 0 || al0)) {
+        if (co.nu1 == 2 && ad_leg<D>(lg, l > 0 || al0, zero)) {
             // both pre-sweeps, the residual and its restriction in one pass
-            if constexpr (D == 2) {
-                const Ad2 op2{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], wd};
-                double *fc = (double *)H->f[l + 1];
-                unsigned nb = 0;
-                if (zero) {
-                    NP_TRY((launch_leg2<double, Ad2, 0, false>(l > 0 || al0, nullptr, F[l], nullptr, cur[l], fc, nullptr, &nb, lg,
-                                                                bc, op2, s, stop)));
+            int nb = 0;
+            NP_TRY((ad_down<D>(zero, l > 0 || al0, F[l], cur[l], zero ? cur[l] : oth[l], (double *)H->f[l + 1], H->red,
+                               &nb, lg, bc, W, wd, s, stop)));
+            if (!zero) {
+                if (tl > 0 && g_tune.tailck) {  // x is not written before the tail
+                    pend = nb;
                 } else {
-                    NP_TRY((launch_leg2<double, Ad2, 1, true>(l > 0 || al0, nullptr, F[l], cur[l], oth[l], fc, H->red, &nb, lg, bc,
-                                                               op2, s, stop)));
-                    if (tl > 0 && g_tune.tailck) {  // x is not written before the tail
-                        pend = int(nb);
-                    } else {
-                        hipLaunchKernelGGL(k_check, dim3(1), dim3(kBlock), 0, s, H->red, int(nb), H->ctl);
-                        NP_LAUNCH_CHECK();
-                    }
-                    std::swap(cur[l], oth[l]);
+                    hipLaunchKernelGGL(k_check, dim3(1), dim3(kBlock), 0, s, H->red, nb, H->ctl);
+                    NP_LAUNCH_CHECK();
                 }
+                std::swap(cur[l], oth[l]);
             }
             continue;
         }
@@ -2533,13 +2574,8 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
         const int64_t m = cells(D, lg);
         const AdW W = ad_weights(op, D, h * double(int64_t(1) << l));
         const double wd = co.omega / W.c0;
-        if (co.nu2 == 2 && ad_leg2<D>(lg, l > 0 || al0)) {  // prolongation + correction and both post-sweeps
-            if constexpr (D == 2) {
-                const Ad2 op2{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], wd};
-                unsigned nb = 0;
-                NP_TRY((launch_leg2<double, Ad2, 2, false>(l > 0 || al0, cur[l + 1], F[l], cur[l], oth[l], nullptr, nullptr, &nb, lg,
-                                                            bc, op2, s, stop)));
-            }
+        if (co.nu2 == 2 && ad_leg<D>(lg, l > 0 || al0, true)) {  // prolongation + correction and both post-sweeps
+            NP_TRY((ad_up<D>(l > 0 || al0, cur[l + 1], F[l], cur[l], oth[l], lg, bc, W, wd, s, stop)));
             std::swap(cur[l], oth[l]);
             continue;
         }

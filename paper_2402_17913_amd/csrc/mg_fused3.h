@@ -19,6 +19,17 @@
 
 namespace np {
 
+// The operator a 3D leg applies: the residual at a cell from its neighbours, and the relaxed-Jacobi
+// weight.  Lap3: A = -Lap_h (the advection-diffusion operator: Ad3).
+template <class C> struct Lap3 {
+    C inv_h2, wd;
+    __device__ __forceinline__ C resid(C f, C xc, C xm, C xp, C ym, C yp, C zm, C zp) const {
+        const C t = ((xm + xp) + ym) + yp;
+        const C s = (t + zm) + zp;
+        return f - (C(6) * xc - s) * inv_h2;
+    }
+};
+
 // Boundary rule along one axis for a position g at most two cells outside
 // [0, n): the cell whose value it holds (periodic: wrapped; Dirichlet: the
 // mirror about the face, with the sign flipped).
@@ -80,10 +91,9 @@ __device__ __forceinline__ int eval_pos(int &a, int &b, int &c, int x0, int y0, 
 // one-cell ring from f on a two-cell ring, x2 stored; the residuals of the
 // block's cells; their restriction, summed per coarse cell in the order of
 // k_restrict (z, then y, then x children, from zero).
-template <class S, int B, int NTH = B * B * B>
+template <class S, class OP, int B, int NTH = B * B * B>
 __global__ __launch_bounds__(NTH) void k_down0_b(const S *__restrict__ f, S *__restrict__ xout,
-                                                          S *__restrict__ fc, int lg, int bc,
-                                                          typename St<S>::C inv_h2, typename St<S>::C wdiag,
+                                                          S *__restrict__ fc, int lg, int bc, OP op,
                                                           const int *stop) {
     typedef typename St<S>::C C;
     typedef BTile<B, NTH> T;
@@ -116,17 +126,15 @@ __global__ __launch_bounds__(NTH) void k_down0_b(const S *__restrict__ f, S *__r
             const int q = ((c + 2) * W2 + b + 2) * W2 + a + 2;
             // x1 = w f formed per value, each product a statement of its own (k_sweep's zero-start pair)
             const C fcv = F[q];
-            const C xc = wdiag * fcv;
-            const C xm = wdiag * F[q - 1];
-            const C xp = wdiag * F[q + 1];
-            const C ym = wdiag * F[q - W2];
-            const C yp = wdiag * F[q + W2];
-            const C zm = wdiag * F[q - Q2];
-            const C zp = wdiag * F[q + Q2];
-            C s = ((xm + xp) + ym) + yp;
-            s = (s + zm) + zp;
-            const C r = fcv - (C(6) * xc - s) * inv_h2;
-            v = C(sgn) * st_round<S>(xc + wdiag * r);
+            const C xc = op.wd * fcv;
+            const C xm = op.wd * F[q - 1];
+            const C xp = op.wd * F[q + 1];
+            const C ym = op.wd * F[q - W2];
+            const C yp = op.wd * F[q + W2];
+            const C zm = op.wd * F[q - Q2];
+            const C zp = op.wd * F[q + Q2];
+            const C r = op.resid(fcv, xc, xm, xp, ym, yp, zm, zp);
+            v = C(sgn) * st_round<S>(xc + op.wd * r);
         }
         X[e] = v;
         if (own) St<S>::st(xout + ((int64_t(z0 + c) << lg) + y0 + b) * n + x0 + a, v);
@@ -136,9 +144,8 @@ __global__ __launch_bounds__(NTH) void k_down0_b(const S *__restrict__ f, S *__r
         const int a = t % B, b = (t / B) % B, c = t / (B * B);
         const int q = ((c + 1) * W1 + b + 1) * W1 + a + 1;
         const C xc = X[q];
-        C s = ((X[q - 1] + X[q + 1]) + X[q - W1]) + X[q + W1];
-        s = (s + X[q - Q1]) + X[q + Q1];
-        Rr[t] = F[((c + 2) * W2 + b + 2) * W2 + a + 2] - (C(6) * xc - s) * inv_h2;
+        Rr[t] = op.resid(F[((c + 2) * W2 + b + 2) * W2 + a + 2], xc, X[q - 1], X[q + 1], X[q - W1], X[q + W1],
+                         X[q - Q1], X[q + Q1]);
     }
     __syncthreads();
     constexpr int BC = B / 2;
@@ -157,11 +164,10 @@ __global__ __launch_bounds__(NTH) void k_down0_b(const S *__restrict__ f, S *__r
 // each position, ghosts from the coarse ghosts, as k_psweep3 does), the first
 // sweep on the block and a one-cell ring (Dirichlet ghosts minus the mirror),
 // the second sweep on the block, stored.
-template <class S, int B, int NTH = B * B * B>
+template <class S, class OP, int B, int NTH = B * B * B>
 __global__ __launch_bounds__(NTH) void k_up2_b(const S *__restrict__ ec, const S *__restrict__ f,
                                                         const S *__restrict__ xin, S *__restrict__ xout, int lg,
-                                                        int bc, typename St<S>::C inv_h2, typename St<S>::C wdiag,
-                                                        const int *stop) {
+                                                        int bc, OP op, const int *stop) {
     typedef typename St<S>::C C;
     typedef BTile<B, NTH> T;
     constexpr int NT = T::NT, W1 = T::W1, W2 = T::W2, Q2 = W2 * W2, Q1 = W1 * W1;
@@ -219,10 +225,8 @@ __global__ __launch_bounds__(NTH) void k_up2_b(const S *__restrict__ ec, const S
             const C fcv = St<S>::ld(f + ((int64_t(gk) << lg) + gj) * n + gi);
             const int q = ((c + 2) * W2 + b + 2) * W2 + a + 2;
             const C xc = Xp[q];
-            C sm = ((Xp[q - 1] + Xp[q + 1]) + Xp[q - W2]) + Xp[q + W2];
-            sm = (sm + Xp[q - Q2]) + Xp[q + Q2];
-            const C r = fcv - (C(6) * xc - sm) * inv_h2;
-            v = C(sgn) * st_round<S>(xc + wdiag * r);
+            const C r = op.resid(fcv, xc, Xp[q - 1], Xp[q + 1], Xp[q - W2], Xp[q + W2], Xp[q - Q2], Xp[q + Q2]);
+            v = C(sgn) * st_round<S>(xc + op.wd * r);
         }
         Y[e] = v;
     }
@@ -232,10 +236,8 @@ __global__ __launch_bounds__(NTH) void k_up2_b(const S *__restrict__ ec, const S
         const int64_t g = ((int64_t(z0 + c) << lg) + y0 + b) * n + x0 + a;
         const int q = ((c + 1) * W1 + b + 1) * W1 + a + 1;
         const C xc = Y[q];
-        C s = ((Y[q - 1] + Y[q + 1]) + Y[q - W1]) + Y[q + W1];
-        s = (s + Y[q - Q1]) + Y[q + Q1];
-        const C r = St<S>::ld(f + g) - (C(6) * xc - s) * inv_h2;
-        St<S>::st(xout + g, xc + wdiag * r);
+        const C r = op.resid(St<S>::ld(f + g), xc, Y[q - 1], Y[q + 1], Y[q - W1], Y[q + W1], Y[q - Q1], Y[q + Q1]);
+        St<S>::st(xout + g, xc + op.wd * r);
     }
 }
 

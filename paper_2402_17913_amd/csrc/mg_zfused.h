@@ -111,12 +111,11 @@ template <class S> inline int sweep2z_planes(int lg, int wg = 1024) {
     return z2_planes(lg, Z2Cfg<S>::TX, Z2Cfg<S>::TY, wg);
 }
 
-template <class S, bool CORR, bool NORM>
+template <class S, class OP, bool CORR, bool NORM>
 __global__ __launch_bounds__(kS3Threads) void k_sweep2z(const S *__restrict__ ec, const S *__restrict__ f,
                                                         const S *__restrict__ xin, S *__restrict__ xout,
                                                         double *__restrict__ partial, int lg, int bc, int zc,
-                                                        typename St<S>::C inv_h2, typename St<S>::C wdiag,
-                                                        const int *stop) {
+                                                        OP op, const int *stop) {
     typedef typename St<S>::C C;
     typedef Z2Cfg<S> G;
     constexpr int TX = G::TX, TY = G::TY, CPT = G::CPT, TP = G::TP, W1 = G::W1, W2 = G::W2, CW = G::CW;
@@ -203,10 +202,8 @@ __global__ __launch_bounds__(kS3Threads) void k_sweep2z(const S *__restrict__ ec
     };
     // a sweep at an LDS position of plane z (in-plane neighbours from Ax), z-neighbours given
     auto sweep1 = [&](const C *A, int q, C xc, C xm, C xp, C fv, C &r) -> C {
-        const C t0 = ((A[q - 1] + A[q + 1]) + A[q - W2]) + A[q + W2];
-        const C s = (t0 + xm) + xp;
-        r = fv - (C(6) * xc - s) * inv_h2;
-        return xc + wdiag * r;
+        r = op.resid(fv, xc, A[q - 1], A[q + 1], A[q - W2], A[q + W2], xm, xp);
+        return xc + op.wd * r;
     };
 
     // registers: own x' at z - 1, z, z + 1; first sweep at z - 2 .. z; f at z, z - 1; ring values
@@ -336,10 +333,8 @@ __global__ __launch_bounds__(kS3Threads) void k_sweep2z(const S *__restrict__ ec
                 const C yn = dn ? -xc : ln;
                 const C zl = dzl ? -xc : so[0][c];
                 const C zu = dzu ? -xc : sn[c];
-                const C t0 = ((xw + xe) + ys) + yn;
-                const C s = (t0 + zl) + zu;
-                const C r = fo[1][c] - (C(6) * xc - s) * inv_h2;
-                out[c] = xc + wdiag * r;
+                const C r = op.resid(fo[1][c], xc, xw, xe, ys, yn, zl, zu);
+                out[c] = xc + op.wd * r;
             }
             store_cells<S, CPT>(xout + (uint32_t(p) << pl) + osrc, out);
         }
@@ -589,11 +584,10 @@ __global__ __launch_bounds__(kS3Threads) void k_down0z(const S *__restrict__ f, 
 // the slot the previous step filled), so every LDS read of a step comes from a
 // slot written before the previous step's barrier.  Same tiles, arithmetic and
 // term order: the outputs equal k_down0z's bit for bit.
-template <class S>
+template <class S, class OP>
 __global__ __launch_bounds__(kS3Threads) void k_down0z1(const S *__restrict__ f, S *__restrict__ xout,
                                                         S *__restrict__ fc, int lg, int bc, int zc,
-                                                        typename St<S>::C inv_h2, typename St<S>::C wdiag,
-                                                        const int *stop) {
+                                                        OP op, const int *stop) {
     typedef typename St<S>::C C;
     typedef Z2Cfg<S> G;
     constexpr int TX = G::TX, TY = G::TY, CPT = G::CPT, TP = G::TP, W1 = G::W1, W2 = G::W2;
@@ -639,10 +633,8 @@ __global__ __launch_bounds__(kS3Threads) void k_down0z1(const S *__restrict__ f,
         else v[0] = St<S>::ld(base + osrc);
     };
     auto sweep1 = [&](const C *A, int q, C xc, C xm, C xp, C fv) -> C {
-        const C t0 = ((A[q - 1] + A[q + 1]) + A[q - W2]) + A[q + W2];
-        const C s = (t0 + xm) + xp;
-        const C r = fv - (C(6) * xc - s) * inv_h2;
-        return xc + wdiag * r;
+        const C r = op.resid(fv, xc, A[q - 1], A[q + 1], A[q - W2], A[q + W2], xm, xp);
+        return xc + op.wd * r;
     };
     // registers at the start of step z: own f and x1 = (signed) w f at z - 2 .. z, x2 at
     // z - 3, z - 2; ring cells (both rings) the same f and x1 at their cell
@@ -664,8 +656,8 @@ __global__ __launch_bounds__(kS3Threads) void k_down0z1(const S *__restrict__ f,
         ld_own(f + poff(q), fo[z]);
         rf[z] = St<S>::ld(f + poff(q) + rsrc);
         const C sg = psign(q);
-        for (int c = 0; c < CPT; ++c) xo[z][c] = sg * (wdiag * fo[z][c]);
-        rx[z] = (sg * rsg) * (wdiag * rf[z]);
+        for (int c = 0; c < CPT; ++c) xo[z][c] = sg * (op.wd * fo[z][c]);
+        rx[z] = (sg * rsg) * (op.wd * rf[z]);
     }
     pload(k0, std::integral_constant<int, 0>{});
     C pair = C(0);  // residual sum of the plane pair
@@ -708,9 +700,7 @@ __global__ __launch_bounds__(kS3Threads) void k_down0z1(const S *__restrict__ f,
                 const C yn = dn ? -xc : ln;
                 const C zl = dzl ? -xc : so[0][c];
                 const C zu = dzu ? -xc : sn[c];
-                const C t0 = ((xw + xe) + ys) + yn;
-                const C s = (t0 + zl) + zu;
-                const C rc = fo[0][c] - (C(6) * xc - s) * inv_h2;
+                const C rc = op.resid(fo[0][c], xc, xw, xe, ys, yn, zl, zu);
                 if (c == 0) r = rc;
                 else r += rc;
             }
@@ -741,7 +731,7 @@ __global__ __launch_bounds__(kS3Threads) void k_down0z1(const S *__restrict__ f,
             fo[2][c] = pf[1 - U][c];
             xo[0][c] = xo[1][c];
             xo[1][c] = xo[2][c];
-            xo[2][c] = sg1 * (wdiag * pf[1 - U][c]);
+            xo[2][c] = sg1 * (op.wd * pf[1 - U][c]);
         }
         if (r1 || r2) {
             rf[0] = rf[1];
@@ -749,7 +739,7 @@ __global__ __launch_bounds__(kS3Threads) void k_down0z1(const S *__restrict__ f,
             rf[2] = pr[1 - U];
             rx[0] = rx[1];
             rx[1] = rx[2];
-            rx[2] = (sg1 * rsg) * (wdiag * pr[1 - U]);
+            rx[2] = (sg1 * rsg) * (op.wd * pr[1 - U]);
         }
     };
     step(k0 - 1, std::true_type{});  // k0 even: x1 of plane k0 - 1 only
@@ -1020,12 +1010,11 @@ template <class S> struct Z4Cfg {
     static_assert(NR3 <= 64 * NW1, "the three-cell ring fits the ring-1 waves");
 };
 
-template <class S, bool NORM>
+template <class S, class OP, bool NORM>
 __global__ __launch_bounds__(kS3Threads) void k_down2z2(const S *__restrict__ f, const S *__restrict__ xin,
                                                         S *__restrict__ xout, S *__restrict__ fc,
                                                         double *__restrict__ partial, int lg, int bc, int zc,
-                                                        typename St<S>::C inv_h2, typename St<S>::C wdiag,
-                                                        const int *stop) {
+                                                        OP op, const int *stop) {
     typedef typename St<S>::C C;
     typedef Z4Cfg<S> G;
     constexpr int TX = G::TX, TY = G::TY, TP = G::TP, W1 = G::W1, W2 = G::W2, W3 = G::W3;
@@ -1082,10 +1071,8 @@ __global__ __launch_bounds__(kS3Threads) void k_down2z2(const S *__restrict__ f,
     // a sweep at an LDS position with in-plane neighbours from frame L (row width W), z-neighbours
     // given; the residual r of the input
     auto sweepL = [&](const C *L, int W, int q, C xc, C xm, C xp, C fv, C &r) -> C {
-        const C t0 = ((L[q - 1] + L[q + 1]) + L[q - W]) + L[q + W];
-        const C s = (t0 + xm) + xp;
-        r = fv - (C(6) * xc - s) * inv_h2;
-        return xc + wdiag * r;
+        r = op.resid(fv, xc, L[q - 1], L[q + 1], L[q - W], L[q + W], xm, xp);
+        return xc + op.wd * r;
     };
     // the same with Dirichlet ghosts selected as minus the centre value
     auto sweepD = [&](const C *L, int W, int q, C xc, C xm, C xp, C fv, bool w, bool e, bool so, bool no,
@@ -1093,10 +1080,8 @@ __global__ __launch_bounds__(kS3Threads) void k_down2z2(const S *__restrict__ f,
         const C lw = L[q - 1], le = L[q + 1], ls = L[q - W], ln = L[q + W];
         const C xw = w ? -xc : lw, xe = e ? -xc : le, ys = so ? -xc : ls, yn = no ? -xc : ln;
         const C zm = zl ? -xc : xm, zp = zu ? -xc : xp;
-        const C t0 = ((xw + xe) + ys) + yn;
-        const C s = (t0 + zm) + zp;
-        r = fv - (C(6) * xc - s) * inv_h2;
-        return xc + wdiag * r;
+        r = op.resid(fv, xc, xw, xe, ys, yn, zm, zp);
+        return xc + op.wd * r;
     };
     // registers: own x at z - 1 .. z + 1, x1 at z - 2 .. z, x2 at z - 3, z - 2, f at z, z - 1, z - 2;
     // ring cell (rings 1 and 2): x at z - 1 .. z + 1, x1 at z - 2 .. z (ring 1), f at z, z - 1;

@@ -1,5 +1,6 @@
-"""One-pass legs of the 2D levels: row-marching wavefronts (k_wave2) against the block and
-per-cell kernels they replace, and both with the advection-diffusion operator."""
+"""One-pass legs: the 2D row-marching wavefronts (k_wave2) against the block and per-cell kernels
+they replace, and the 2D and 3D legs with the advection-diffusion operator against its separate
+kernels."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -95,3 +96,30 @@ def test_legs_unaligned_fields(B, n):
     B.np_ad_implicit_solve(f, x, 1.0, DIR, op, fixed_cycles=2)
     B.np_ad_implicit_solve(g, y, 1.0, DIR, op, fixed_cycles=2)
     assert (x - y).abs().max() <= 2e-13 * y.abs().max()
+
+
+@pytest.mark.parametrize("scheme,vel", [(0, [1.0, 1.0, 1.0]), (0, [-1.0, 0.5, -0.3]), (1, [0.2, -0.1, 0.15])])
+@pytest.mark.parametrize("bc", [DIR, PER])
+@pytest.mark.parametrize("n", [32, 64, 128, 256])
+def test_legs3_advection_diffusion(B, n, bc, scheme, vel):
+    """The 3D legs (z-marching tiles from 128^3, blocks below) against the separate sweep,
+    restriction and prolongation kernels: 1e-13 per cycle of values of order one."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n + bc)
+    f = torch.randn(n, n, n, dtype=torch.float64, device="cuda", generator=g)
+    op = B.ad_op(20.0, 2.0, vel, scheme)
+    print("legs3 ad", n, bc, scheme, vel, flush=True)
+    out = []
+    try:
+        for on in (0, 1):
+            B.np_set_tuning("sweep2z", on)
+            B.np_set_tuning("fuseb", on)
+            x = torch.zeros_like(f)
+            _, st = B.np_ad_implicit_solve(f, x, 1.0, bc, op, fixed_cycles=3)
+            out.append((x, st["hist"]))
+    finally:
+        B.np_set_tuning("sweep2z", 1)
+        B.np_set_tuning("fuseb", 1)
+    assert torch.isfinite(out[0][0]).all() and out[0][0].abs().max() > 0
+    assert (out[0][0] - out[1][0]).abs().max() <= 3e-13 * out[0][0].abs().max()
+    assert all(abs(u - v) <= 1e-12 * max(u, 1e-300) for u, v in zip(out[0][1], out[1][1]))
