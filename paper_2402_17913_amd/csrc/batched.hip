@@ -23,6 +23,7 @@
 
 #include "mg_kernels.h"
 #include "mg_level.h"
+#include "mg_wave2.h"
 #include "np_internal.h"
 
 namespace np {
@@ -606,6 +607,41 @@ __global__ __launch_bounds__(kRmT) void kb_prolong_rm(const S *__restrict__ Ec, 
     }
 }
 
+// ------------------------------------------------------- one-pass legs
+// The V(2,2) legs of a depth above the tail on row-marching wavefronts
+// (wave2_leg): both pre-sweeps, the residual and its restriction (X or zero -> T,
+// the restricted residual into depth k - 1's right-hand side), or prolongation +
+// correction and both post-sweeps (T -> X), over every problem present there.
+// Bound by memory: 12 bytes per FP32 cell and leg, where the separate kernels
+// moved 33; the batch of 64 problems of 64^2 .. 1024^2 with four FP32 inner cycles took
+// 7.43 -> 3.91 ms.  Wavefront w takes strip w mod strips, then the chunk, then the slot.
+template <class S, bool UP>
+__global__ __launch_bounds__(kW2T) void kb_leg(const S *__restrict__ F, const S *__restrict__ Xin,
+                                               S *__restrict__ Xout, const S *__restrict__ Ec, S *__restrict__ Fc,
+                                               const int *__restrict__ slot_prob, const BProb *__restrict__ P,
+                                               const BState *__restrict__ st, const BGlobal *__restrict__ g, int k,
+                                               int nsl, int cyc, double omega, int ry) {
+    typedef typename St<S>::C C;
+    const int lg = k + 2, n = 1 << lg;
+    const W2Strips t = w2_strips<S, 1>(n, 0);  // the zero-start leg needs no more ghosts than MODE 1
+    const int w = __builtin_amdgcn_readfirstlane(int(blockIdx.x) * (kW2T / 64) + (int(threadIdx.x) >> 6));
+    const int per = t.count * ((n + ry - 1) / ry), slot = w / per, q = w % per;
+    if (slot >= nsl) return;
+    const int p = slot_prob[slot];
+    if (g->stop || st[p].stop) return;
+    const int c0 = (q % t.count) * t.cols, j0 = (q / t.count) * ry, j1 = min(j0 + ry, n);
+    const double h = depth_h(P[p], k);
+    const Lap2<C> op{C(1.0 / (h * h)), C(omega * h * h / 4.0)};
+    const int64_t so = int64_t(slot) << (2 * lg), sc = int64_t(P[p].slot[k - 1]) << (2 * (lg - 1));
+    if constexpr (UP) {
+        (void)wave2_leg<S, Lap2<C>, 2, false>(Ec + sc, F + so, Xin + so, Xout + so, nullptr, lg, 0, c0, t.gl, j0, j1, op);
+    } else if (k < P[p].L || cyc == 0) {
+        (void)wave2_leg<S, Lap2<C>, 0, false>(nullptr, F + so, nullptr, Xout + so, Fc + sc, lg, 0, c0, t.gl, j0, j1, op);
+    } else {
+        (void)wave2_leg<S, Lap2<C>, 1, false>(nullptr, F + so, Xin + so, Xout + so, Fc + sc, lg, 0, c0, t.gl, j0, j1, op);
+    }
+}
+
 // Refinement blocks of kb_ir_rm: on a problem with n >= 128 a row-marching
 // tile (strip a, row block b: G groups of kIrRows rows), else kIrCells
 // consecutive cells from a (b = -1).
@@ -930,8 +966,26 @@ np_status enqueue_step(Plan *B, int kind, int inner, const BOpts &o, hipStream_t
     NP_LAUNCH_CHECK();
     hipLaunchKernelGGL(kb_check_any, dim3(1), dim3(1024), 0, s, B->d_st, B->d_g, B->nprob);
     NP_LAUNCH_CHECK();
+    // V(2,2): one pass per leg, `wg` wavefronts aimed for; other sweep counts run a kernel per stage
+    const bool legs = o.rm && o.nu1 == 2 && o.nu2 == 2;
+    auto leg = [&](auto up, int k, int c) -> np_status {
+        constexpr bool UP = decltype(up)::value;
+        const int nsl = int(B->slots[k].size()), n = 1 << (k + 2), strips = w2_strips<S, 1>(n, 0).count;
+        const int ry = wave2_rows(n, int64_t(strips) * nsl, o.wg);
+        const int64_t waves = int64_t(strips) * ((n + ry - 1) / ry) * nsl;
+        S *X = (S *)B->X[k], *T = (S *)B->T[k];
+        hipLaunchKernelGGL((kb_leg<S, UP>), dim3(unsigned((waves * 64 + kW2T - 1) / kW2T)), dim3(kW2T), 0, s,
+                           (const S *)B->F[k], UP ? T : X, UP ? X : T, (const S *)B->X[k - 1], (S *)B->F[k - 1],
+                           B->d_slot_prob[k], B->d_P, B->d_st, B->d_g, k, nsl, c, o.omega, ry);
+        NP_LAUNCH_CHECK();
+        return NP_OK;
+    };
     for (int c = 0; c < inner; ++c) {
         for (int k = B->K; k > kTailDepth; --k) {
+            if (legs) {
+                NP_TRY(leg(std::false_type{}, k, c));
+                continue;
+            }
             const unsigned nsl = unsigned(B->slots[k].size());
             const int64_t m = int64_t(1) << (2 * (k + 2));
             S *cur = (S *)B->X[k], *oth = (S *)B->T[k];
@@ -961,6 +1015,10 @@ np_status enqueue_step(Plan *B, int kind, int inner, const BOpts &o, hipStream_t
                            B->d_st, B->d_g, c, o.omega, o.nu1, o.nu2);
         NP_LAUNCH_CHECK();
         for (int k = kTailDepth + 1; k <= B->K; ++k) {
+            if (legs) {
+                NP_TRY(leg(std::true_type{}, k, c));
+                continue;
+            }
             const unsigned nsl = unsigned(B->slots[k].size());
             const int64_t m = int64_t(1) << (2 * (k + 2));
             // after an odd number of pre-sweeps the iterate sits in T

@@ -83,25 +83,35 @@ template <class S, int N> struct Run {
 template <class S, int MODE> struct W2 {
     static constexpr int CPL = sizeof(S) == 8 ? 2 : 4;
     static constexpr int GL = MODE != 0 && CPL == 2 ? 2 : 1;
-    static constexpr int COLS = (64 - 2 * GL) * CPL;  // columns a wave stores
-    static int strips(int n) { return (n + COLS - 1) / COLS; }
-    static __device__ __forceinline__ int strips_d(int n) { return (n + COLS - 1) / COLS; }
 };
 constexpr int kW2T = 256;  // threads per workgroup: four wavefronts on adjacent strips
 
-// One wavefront's chunk of a leg: strip `strip`, rows [j0, j1), both even, of an
-// n x n level (n = 2^lg); returns its share of |f - A x|^2 (NORM).
+// Strips of an n x n level: `gl` ghost lanes per side, none where one wavefront
+// spans the level from wall to wall.
+struct W2Strips {
+    int gl, cols, count;  // ghost lanes per side, columns a strip stores, strips
+};
+template <class S, int MODE> __host__ __device__ __forceinline__ W2Strips w2_strips(int n, int bc) {
+    typedef W2<S, MODE> G;
+    const int gl = !bc && n <= 64 * G::CPL ? 0 : G::GL, cols = (64 - 2 * gl) * G::CPL;
+    return W2Strips{gl, cols, (n + cols - 1) / cols};
+}
+
+// One wavefront's chunk of a leg: the columns from c0 on (gl ghost lanes per side),
+// rows [j0, j1), both even, of an n x n level (n = 2^lg); returns its share of
+// |f - A x|^2 (NORM).
 template <class S, class OP, int MODE, bool NORM>
 __device__ __forceinline__ double wave2_leg(const S *__restrict__ ec, const S *__restrict__ f,
                                             const S *__restrict__ xin, S *__restrict__ xout, S *__restrict__ fc,
-                                            int lg, int bc, int strip, int j0, int j1, const OP &op) {
+                                            int lg, int bc, int c0, int gl, int j0, int j1,
+                                            const OP &op) {
     typedef typename St<S>::C C;
     typedef W2<S, MODE> G;
     constexpr int N = G::CPL, NC = N / 2;
     typedef Run<S, N> V;
     const int n = 1 << lg, last = n - 1, lane = int(threadIdx.x) & 63;
-    const int col = strip * G::COLS + (lane - G::GL) * N;  // first column of this lane
-    const bool own = lane >= G::GL && lane < 64 - G::GL && col < n;
+    const int col = c0 + (lane - gl) * N;  // first column of this lane
+    const bool own = lane >= gl && lane < 64 - gl && col < n;
     // periodic: ghost columns wrap; Dirichlet: columns outside are loaded from the nearest cells, unused
     const int lc = bc ? (col & last) : min(max(col, 0), n - N);
     const bool west = !bc && col == 0, east = !bc && col + N == n;
@@ -304,7 +314,7 @@ __device__ __forceinline__ double wave2_leg(const S *__restrict__ ec, const S *_
 
 // Rows per chunk: even, for about `waves` wavefronts over the level, at least 8
 // (a chunk computes two to four rows beyond its own).
-inline int wave2_rows(int n, int strips, int waves) {
+inline int wave2_rows(int n, int64_t strips, int waves) {
     int64_t ry = (int64_t(n) * strips + waves - 1) / waves;
     ry = (ry + 1) & ~int64_t(1);
     return int(ry < 8 ? (n < 8 ? n : 8) : (ry > n ? n : ry));
@@ -319,12 +329,13 @@ __global__ __launch_bounds__(kW2T) void k_wave2(const S *__restrict__ ec, const 
                                                 double *__restrict__ partial, int lg, int bc, int ry, OP op,
                                                 const int *stop) {
     if (stop && *stop) return;
-    const int n = 1 << lg, strips = W2<S, MODE>::strips_d(n);
+    const int n = 1 << lg;
+    const W2Strips t = w2_strips<S, MODE>(n, bc);
     const int w = __builtin_amdgcn_readfirstlane(int(xcd_block(blockIdx.x, gridDim.x)) * (kW2T / 64) +
                                                  (int(threadIdx.x) >> 6));
-    const int strip = w % strips, j0 = (w / strips) * ry;
+    const int c0 = (w % t.count) * t.cols, j0 = (w / t.count) * ry;
     double acc = 0.0;
-    if (j0 < n) acc = wave2_leg<S, OP, MODE, NORM>(ec, f, xin, xout, fc, lg, bc, strip, j0, min(j0 + ry, n), op);
+    if (j0 < n) acc = wave2_leg<S, OP, MODE, NORM>(ec, f, xin, xout, fc, lg, bc, c0, t.gl, j0, min(j0 + ry, n), op);
     if constexpr (NORM) {
         acc = block_sum_n<kW2T>(acc);
         if (threadIdx.x == 0) partial[blockIdx.x] = acc;

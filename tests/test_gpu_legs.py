@@ -123,3 +123,25 @@ def test_legs3_advection_diffusion(B, n, bc, scheme, vel):
     assert torch.isfinite(out[0][0]).all() and out[0][0].abs().max() > 0
     assert (out[0][0] - out[1][0]).abs().max() <= 3e-13 * out[0][0].abs().max()
     assert all(abs(u - v) <= 1e-12 * max(u, 1e-300) for u, v in zip(out[0][1], out[1][1]))
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_batched_legs(B, prec):
+    """The batched V(2,2) legs against the per-stage tiles (one cell pair per thread), problems of
+    one and of several strips and of every start (zero and not), bit for bit."""
+    import torch
+    sizes = [128, 1024, 64, 256, 512, 128, 16]
+    fs = [torch.randn(n, n, dtype=torch.float64, device="cuda", generator=torch.Generator(device="cuda").manual_seed(n + i))
+          for i, n in enumerate(sizes)]
+    out = []
+    try:
+        for rm in (0, 1):
+            B.np_set_tuning("batched_rm", rm)
+            xs = [torch.zeros_like(f) for f in fs]
+            B.mg_poisson_solve_batched(fs, xs, [1.0 / n for n in sizes], smooth_prec=prec, inner_cycles=3, fixed_cycles=2)
+            out.append(xs)
+    finally:
+        B.np_set_tuning("batched_rm", 1)
+    for n, a, b in zip(sizes, *out):
+        assert a.abs().max() > 0
+        assert torch.equal(a, b), n
