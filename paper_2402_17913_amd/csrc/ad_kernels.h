@@ -399,175 +399,22 @@ __global__ __launch_bounds__(kR2) void k_ad_restrict2(const double *__restrict__
     }
 }
 
-// ------------------------------------- small levels in one workgroup (LDS)
-// Weights of the levels handled by k_ad_tail, finest first.
+// Weights of the levels handled by the one-workgroup tail, finest first.
 struct AdLevels {
     AdW w[12];
 };
-
-// One relaxed-Jacobi sweep T = X + wd (F - A X) (RESID: the residual T = F - A X)
-// of a level of k_ad_tail, all three in LDS.  Each thread marches along the
-// last axis over a run of one column's cells (neighbours along that axis from
-// registers, in-plane offsets fixed per column); same terms and grouping as
-// ad_ax.  Needs n^(D-1) <= NT.
-template <int D, int NT, bool RESID, bool ZERO2 = false>
-__device__ __forceinline__ void ad_tail_sweep(const double *__restrict__ X, const double *__restrict__ F,
-                                              double *__restrict__ T, int lg, int bc, const AdW &W, double wd) {
-    // ZERO2: the sweep after a first one from zero; its input iterate wd f is formed from F (X unused)
-    auto xv = [&](int q) -> double { return ZERO2 ? wd * F[q] : X[q]; };
-    const int n = 1 << lg, last = n - 1, sm = D == 3 ? n * n : n;
-    const int chunks = NT / sm < n ? NT / sm : n, len = n / chunks;
-    const int t = threadIdx.x;
-    if (t < sm * chunks) {
-        const bool per = bc != 0;
-        const int i = t & last, j = D == 3 ? (t >> lg) & last : 0, z0 = (t / sm) * len;
-        const int oxm = i > 0 ? -1 : (per ? last : 0), oxp = i < last ? 1 : (per ? -last : 0);
-        const bool fxm = i > 0 || per, fxp = i < last || per;
-        const int oym = j > 0 ? -n : (per ? last * n : 0), oyp = j < last ? n : (per ? -last * n : 0);
-        const bool fym = j > 0 || per, fyp = j < last || per;
-        int c = z0 * sm + (t & (sm - 1));
-        double xc = xv(c);
-        double zm = xv(z0 > 0 ? c - sm : (per ? c + last * sm : c));
-        bool fzm = z0 > 0 || per;
-        for (int z = z0; z < z0 + len; ++z, c += sm) {
-            const double zp = xv(z < last ? c + sm : (per ? c - last * sm : c));
-            const bool fzp = z < last || per;
-            const double rxm = xv(c + oxm), rxp = xv(c + oxp);  // unconditional: no branch around a load
-            const double xm = fxm ? rxm : -xc, xp = fxp ? rxp : -xc;
-            const double am = fzm ? zm : -xc, ap = fzp ? zp : -xc;  // along the marching axis
-            double s;
-            if (D == 3) {
-                const double rym = xv(c + oym), ryp = xv(c + oyp);
-                const double ym = fym ? rym : -xc, yp = fyp ? ryp : -xc;
-                s = W.c0 * xc + (W.cm[0] * xm + W.cp[0] * xp) + (W.cm[1] * ym + W.cp[1] * yp);
-                s += W.cm[2] * am + W.cp[2] * ap;
-            } else {
-                s = W.c0 * xc + (W.cm[0] * xm + W.cp[0] * xp) + (W.cm[1] * am + W.cp[1] * ap);
-            }
-            if (RESID) T[c] = F[c] - s;
-            else T[c] = xc + wd * (F[c] - s);
-            zm = xc;
-            fzm = true;
-            xc = zp;
-        }
-    }
-}
-
-// V(nu1, nu2) cycle on levels lg_t .. 2 (coarsest 4^d) in one workgroup,
-// every level in LDS, from a zero iterate on every level (the levels below
-// the finest ones of a cycle): first sweep x = wdiag f, nu1 - 1 further
-// sweeps, residual restriction, the exact solve Minv f on 4^d, then per
-// level up prolongation + nu2 sweeps.  f_t: right-hand side of level lg_t
-// (global); x_t: its correction (global).  nu1 >= 1; lg_t <= Tail<D>::LG.
-// ctl: first the cycle's convergence check, as k_tail runs it.
-template <int D>
-__global__ __launch_bounds__(Tail<D>::NT_AD) void k_ad_tail(const double *__restrict__ f_t, double *__restrict__ x_t,
-                                                         const double *__restrict__ Minv, int lg_t, int bc,
-                                                         AdLevels Wl, double omega, int nu1, int nu2,
-                                                         const int *stop, const double *__restrict__ partial,
-                                                         int np, Ctl *ctl) {
-    constexpr int NT = Tail<D>::NT_AD;
-    static_assert(Tail<D>::cells(Tail<D>::LG) >> Tail<D>::LG <= NT, "ad_tail_sweep needs n^(D-1) <= NT");
-    __shared__ double xs[Tail<D>::levels_sum()];
-    __shared__ double fs[Tail<D>::levels_sum()];
-    __shared__ double ts[Tail<D>::cells(Tail<D>::LG)];
-    // the coarsest inverse, transposed with padded rows (thread i reading entry
-    // (i, q) hits consecutive banks); its loads go out with the right-hand side's
-    constexpr int mq = D == 3 ? 64 : 16, mp = mq + 1;
-    __shared__ double Ms[mq * mp];
-    if (stop && *stop) return;
-    if (ctl) {
-        __shared__ int halt;
-        const int st = check_block<NT>(partial, np, ctl);
-        if (threadIdx.x == 0) halt = st;
-        __syncthreads();
-        if (halt) return;
-    }
-    const int tid = threadIdx.x;
-    auto off = [&](int l) -> int64_t {  // level l follows the finer levels lg_t .. l + 1
-        return ((int64_t(1) << (D * (lg_t + 1))) - (int64_t(1) << (D * (l + 1)))) / ((int64_t(1) << D) - 1);
-    };
-    const int mt = 1 << (D * lg_t);
-    {
-        constexpr int per = int(Tail<D>::cells(Tail<D>::LG) / NT);
-        double fv[per];
-#pragma unroll
-        for (int u = 0; u < per; ++u)
-            if (tid + u * NT < mt) fv[u] = f_t[tid + u * NT];
-        for (int g = tid; g < mq * mq; g += NT) Ms[(g % mq) * mp + g / mq] = Minv[g];
-#pragma unroll
-        for (int u = 0; u < per; ++u)
-            if (tid + u * NT < mt) fs[tid + u * NT] = fv[u];
-    }
-    __syncthreads();
-    // cnt sweeps alternating between X and ts; the result ends in X
-    auto sweeps = [&](double *X, const double *F, int lg, const AdW &W, double wd, int cnt) {
-        double *cur = X, *nxt = ts;
-        for (int it = 0; it < cnt; ++it) {
-            ad_tail_sweep<D, NT, false>(cur, F, nxt, lg, bc, W, wd);
-            __syncthreads();
-            double *t = cur;
-            cur = nxt;
-            nxt = t;
-        }
-        if (cur != X) {
-            for (int c = tid; c < (1 << (D * lg)); c += NT) X[c] = cur[c];
-            __syncthreads();
-        }
-    };
-    for (int lg = lg_t; lg > 2; --lg) {
-        const int m = 1 << (D * lg);
-        double *X = xs + off(lg), *F = fs + off(lg);
-        const AdW W = Wl.w[lg_t - lg];
+// The operators of the tail's levels (as LapTail).
+template <int D> struct AdTail {
+    AdLevels lv;
+    double omega;
+    int lg_t;
+    template <int LG> __device__ __forceinline__ auto at() const {
+        const AdW &W = lv.w[lg_t - LG];
         const double wd = omega / W.c0;
-        if (nu1 >= 2) {
-            // the first two sweeps from zero in one pass, straight into X
-            ad_tail_sweep<D, NT, false, true>(F, F, X, lg, bc, W, wd);
-            __syncthreads();
-            sweeps(X, F, lg, W, wd, nu1 - 2);
-        } else {
-            for (int c = tid; c < m; c += NT) X[c] = wd * F[c];
-            __syncthreads();
-            sweeps(X, F, lg, W, wd, nu1 - 1);
-        }
-        // residual into ts, then its 2^d-cell average into the next level's rhs
-        ad_tail_sweep<D, NT, true>(X, F, ts, lg, bc, W, wd);
-        __syncthreads();
-        const int lgc = lg - 1, mc = 1 << (D * lgc);
-        double *Fc = fs + off(lgc);
-        for (int cc = tid; cc < mc; cc += NT) {
-            int I, J, K;
-            decode<D>(cc, lgc, I, J, K);
-            double acc = 0.0;
-            for (int kk = 0; kk < (D == 3 ? 2 : 1); ++kk)
-                for (int jj = 0; jj < 2; ++jj)
-                    for (int ii = 0; ii < 2; ++ii) {
-                        const int i = 2 * I + ii, j = 2 * J + jj, k = D == 3 ? 2 * K + kk : 0;
-                        acc += ts[(k << (2 * lg)) | (j << lg) | i];
-                    }
-            Fc[cc] = acc * (D == 3 ? 0.125 : 0.25);
-        }
-        __syncthreads();
+        if constexpr (D == 2) return Ad2{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], wd};
+        else return Ad3{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], W.cm[2], W.cp[2], wd};
     }
-    {
-        double *X = xs + off(2), *F = fs + off(2);
-        if (tid < mq) {
-            double acc = 0.0;
-            for (int q = 0; q < mq; ++q) acc += Ms[tid + q * mp] * F[q];
-            X[tid] = acc;
-        }
-        __syncthreads();
-    }
-    for (int lg = 3; lg <= lg_t; ++lg) {
-        const int lgc = lg - 1;
-        double *X = xs + off(lg), *F = fs + off(lg), *E = xs + off(lgc);
-        const AdW W = Wl.w[lg_t - lg];
-        tail_prolong<D, double, NT>(E, X, lg, bc);
-        __syncthreads();
-        sweeps(X, F, lg, W, omega / W.c0, nu2);
-    }
-    for (int c = tid; c < mt; c += NT) x_t[c] = xs[c];
-}
+};
 
 // Partials of ||a - b||_1 (||a||_1 when b is null) over a strided grid (fixed
 // order), gated by the controller: the change of the iterate over the cycle

@@ -23,6 +23,7 @@
 
 #include "mg_kernels.h"
 #include "mg_level.h"
+#include "mg_tail.h"
 #include "mg_wave2.h"
 #include "np_internal.h"
 
@@ -741,21 +742,23 @@ __global__ __launch_bounds__(kBlock) void kb_ir_rm(BPtrs<SL> ptr, SL *const *epo
     if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
 
-// Depths min(L_p, kTailDepth) .. 0 of every problem, one workgroup each.
+// Depths min(L_p, kTailDepth) .. 0 of every problem, one workgroup each.  A problem whose finest
+// depth is one of them starts from its iterate after the first inner cycle.
 template <class S>
-__global__ __launch_bounds__(Tail<2>::NT_B) void kb_tail(S *const *Xpool, S *const *Fpool, const double *__restrict__ Minv1,
-                                                       const BProb *__restrict__ P, const BState *__restrict__ st,
-                                                       const BGlobal *__restrict__ g, int cyc, double omega, int nu1,
-                                                       int nu2) {
+__global__ __launch_bounds__(Tail<2>::NT) void kb_tail(S *const *Xpool, S *const *Fpool, const double *__restrict__ Minv1,
+                                                     const BProb *__restrict__ P, const BState *__restrict__ st,
+                                                     const BGlobal *__restrict__ g, int cyc, double omega, int nu1,
+                                                     int nu2) {
     typedef typename St<S>::C C;
+    constexpr int NT = Tail<2>::NT, M = int(Tail<2>::cells(Tail<2>::LG));
     __shared__ C xs[Tail<2>::levels_sum()];
     __shared__ C fs[Tail<2>::levels_sum()];
-    __shared__ C ts[Tail<2>::cells(Tail<2>::LG)];
+    __shared__ C ts[M];
+    __shared__ double Ms[16 * 17];
     const int p = blockIdx.x;
     if (g->stop || st[p].stop) return;
     const BProb &pp = P[p];
-    const int t = min(pp.L, kTailDepth);
-    const int64_t m = int64_t(1) << (2 * (t + 2));
+    const int t = min(pp.L, kTailDepth), lg = t + 2, m = 1 << (2 * lg), o = tail_off<2>(lg);
     S *x = Xpool[t] + int64_t(pp.slot[t]) * m;
     const S *f = Fpool[t] + int64_t(pp.slot[t]) * m;
     const bool warm = t == pp.L && cyc > 0;
@@ -763,10 +766,23 @@ __global__ __launch_bounds__(Tail<2>::NT_B) void kb_tail(S *const *Xpool, S *con
     // Minv1 is the inverse for unit coarsest spacing; the coarsest spacing here
     // is h * 2^t, and the Dirichlet operator scales as 1/h^2.
     const double hc = h * double(1 << t);
-    __shared__ double Ms[16 * 16];
-    for (int q = threadIdx.x; q < 256; q += blockDim.x) Ms[q] = Minv1[q] * (hc * hc);
+    const LapTail<2, C> ops{1.0 / (h * h), omega * h * h / 4.0, lg};
+    tail_minv<2, NT>(Ms, Minv1, hc * hc);
+    tail_fetch<S, NT, M>(fs + o, f, m);
+    if (warm) tail_fetch<S, NT, M>(xs + o, x, m);
     __syncthreads();
-    tail_cycle<2, S, Tail<2>::NT_B>(xs, fs, ts, f, x, warm ? x : nullptr, Ms, t + 2, 0, h, omega, nu1, nu2);
+    tail_by_level<2>(lg, [&](auto l) {
+        constexpr int LG = decltype(l)::value;
+        if constexpr (LG > 2) {
+            if (warm) {
+                tail_sweeps<2, C, NT, LG>(xs + tail_off<2>(LG), fs + tail_off<2>(LG), ts, 0, ops.template at<LG>(), nu1);
+                tail_down_up<2, C, NT, LG>(xs, fs, ts, Ms, 0, ops, nu1, nu2);
+                return;
+            }
+        }
+        tail_zero<2, C, NT, LG>(xs, fs, ts, Ms, 0, ops, nu1, nu2);  // 4^2: exact whatever the start
+    });
+    for (int c = int(threadIdx.x); c < m; c += NT) St<S>::st(x + c, xs[o + c]);
 }
 
 // ----------------------------------------------------------------- plan
@@ -1011,7 +1027,7 @@ np_status enqueue_step(Plan *B, int kind, int inner, const BOpts &o, hipStream_t
                                    s, F, cur, (S *)B->F[k - 1], B->d_slot_prob[k], B->d_P, B->d_st, B->d_g, k);
             NP_LAUNCH_CHECK();
         }
-        hipLaunchKernelGGL((kb_tail<S>), dim3(B->nprob), dim3(Tail<2>::NT_B), 0, s, Xp, Fp, B->d_Minv1, B->d_P,
+        hipLaunchKernelGGL((kb_tail<S>), dim3(B->nprob), dim3(Tail<2>::NT), 0, s, Xp, Fp, B->d_Minv1, B->d_P,
                            B->d_st, B->d_g, c, o.omega, o.nu1, o.nu2);
         NP_LAUNCH_CHECK();
         for (int k = kTailDepth + 1; k <= B->K; ++k) {

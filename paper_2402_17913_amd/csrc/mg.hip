@@ -18,6 +18,7 @@
 #include "mg_level.h"
 #include "mg_kernels.h"
 #include "ad_kernels.h"
+#include "mg_tail.h"
 #include "np_internal.h"
 
 namespace np {
@@ -532,8 +533,9 @@ template <int D, class S> struct Ops {
     static np_status tail(const S *f, S *x, const double *Minv, int lg, int bc, double h, const CycleOpts &o,
                           hipStream_t s, const int *stop, const double *partial = nullptr, int np = 0,
                           Ctl *ctl = nullptr) {
-        hipLaunchKernelGGL((k_tail<D, S>), dim3(1), dim3(Tail<D>::NT), 0, s, f, x, Minv, lg, bc, h, o.omega, o.nu1,
-                           o.nu2, stop, partial, np, ctl);
+        const LapTail<D, C> ops{1.0 / (h * h), o.omega * h * h / (2.0 * D), lg};
+        hipLaunchKernelGGL((k_tail<D, S, LapTail<D, C>>), dim3(1), dim3(Tail<D>::NT), 0, s, f, x, Minv, lg, bc, ops,
+                           o.nu1, o.nu2, stop, partial, np, ctl);
         NP_LAUNCH_CHECK();
         return NP_OK;
     }
@@ -2503,10 +2505,10 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
         const double wd = co.omega / W.c0;
         const bool zero = l > 0;
         if (l > 0 && l == tl) {  // levels tl .. L in one workgroup
-            AdLevels Wl{};
-            for (int q = 0; q <= L - l; ++q) Wl.w[q] = ad_weights(op, D, hl * double(int64_t(1) << q));
-            hipLaunchKernelGGL((k_ad_tail<D>), dim3(1), dim3(Tail<D>::NT_AD), 0, s, F[l], cur[l], H->ad_minv, lg, bc,
-                               Wl, co.omega, co.nu1, co.nu2, stop, H->red, pend, pend > 0 ? H->ctl : nullptr);
+            AdTail<D> ops{{}, co.omega, lg};
+            for (int q = 0; q <= L - l; ++q) ops.lv.w[q] = ad_weights(op, D, hl * double(int64_t(1) << q));
+            hipLaunchKernelGGL((k_tail<D, double, AdTail<D>>), dim3(1), dim3(Tail<D>::NT), 0, s, F[l], cur[l], H->ad_minv,
+                               lg, bc, ops, co.nu1, co.nu2, stop, H->red, pend, pend > 0 ? H->ctl : nullptr);
             NP_LAUNCH_CHECK();
             break;
         }

@@ -10,8 +10,6 @@
 //  - k_restrict:  residual and 2^d-cell average with coalesced fine-grid reads:
 //                 a workgroup owns a 64 x 2 x 2 (3D) / 128 x 2 (2D) block of fine
 //                 cells, each thread one residual, children summed through LDS;
-//  - k_tail:      the whole V-cycle below a level of 16^3 (3D) / 64^2 (2D) cells
-//                 in one workgroup, every level resident in LDS.
 // Arithmetic per cell is that of mg_kernels.h (same expressions and orders).
 #pragma once
 
@@ -767,292 +765,7 @@ template <int D> struct Tail {
         for (int l = LG; l >= 2; --l) s += cells(l);
         return s;
     }
-    // threads (2D 512: the 128^2 solve measured 0.571 -> 0.552 ms against 1024; 3D 512 no
-    // faster, 256 slower); NT_B: the batched solver's 2D tail, one workgroup per problem
-    static constexpr int NT = D == 3 ? 1024 : 512;
-    static constexpr int NT_B = 1024;
-    // threads of the advection-diffusion tail (3D measured slower with 1024: 19.3 against 17.3 us)
-    static constexpr int NT_AD = D == 3 ? 512 : 1024;
+    static constexpr int NT = D == 3 ? 1024 : 512;  // threads
 };
-
-// nb_sum for a level held in LDS, without branches: every neighbour is read
-// unconditionally (a Dirichlet ghost reads the cell itself and flips its sign,
-// a periodic one reads the wrapped cell), so the six reads are in flight
-// together.  Same values and summation order as nb_sum.
-template <int D, class C>
-__device__ __forceinline__ C nb_sum_lds(const C *X, int c, int i, int j, int k, int lg, int bc) {
-    const int last = (1 << lg) - 1, sy = 1 << lg, sz = 1 << (2 * lg);
-    const bool per = bc != 0;
-    const C xm = X[i > 0 ? c - 1 : (per ? c + last : c)];
-    const C xp = X[i < last ? c + 1 : (per ? c - last : c)];
-    const C ym = X[j > 0 ? c - sy : (per ? c + last * sy : c)];
-    const C yp = X[j < last ? c + sy : (per ? c - last * sy : c)];
-    C s = (((i > 0 || per) ? xm : -xm) + ((i < last || per) ? xp : -xp) + ((j > 0 || per) ? ym : -ym)) +
-          ((j < last || per) ? yp : -yp);
-    if (D == 3) {
-        const C zm = X[k > 0 ? c - sz : (per ? c + last * sz : c)];
-        const C zp = X[k < last ? c + sz : (per ? c - last * sz : c)];
-        s = (s + ((k > 0 || per) ? zm : -zm)) + ((k < last || per) ? zp : -zp);
-    }
-    return s;
-}
-
-// One weighted-Jacobi sweep T = X + wdiag (F - A X) (RESID: the residual
-// T = F - A X) of a level of the one-workgroup tail (all three in LDS).  Each thread marches along the last
-// axis over a run of one column's cells: the neighbours along that axis come
-// from registers, the in-plane ones from offsets fixed per column.  Same
-// values and summation order as nb_sum.  Needs n^(D-1) <= NT.
-template <int D, class C, int NT, bool RESID = false, bool ZERO2 = false>
-__device__ __forceinline__ void tail_sweep(const C *__restrict__ X, const C *__restrict__ F, C *__restrict__ T,
-                                           int lg, int bc, C inv_h2, C wdiag) {
-    // ZERO2: the sweep after a first one from zero; its input iterate w f is formed from F (X unused)
-    auto xv = [&](int q) -> C { return ZERO2 ? wdiag * F[q] : X[q]; };
-    const int n = 1 << lg, last = n - 1, sm = D == 3 ? n * n : n;  // sm: cells per plane = marching stride
-    const int chunks = NT / sm < n ? NT / sm : n, len = n / chunks;
-    const int t = threadIdx.x;
-    if (t < sm * chunks) {
-        const bool per = bc != 0;
-        const int i = t & last, j = D == 3 ? (t >> lg) & last : 0, z0 = (t / sm) * len;
-        const int oxm = i > 0 ? -1 : (per ? last : 0), oxp = i < last ? 1 : (per ? -last : 0);
-        const bool fxm = i > 0 || per, fxp = i < last || per;
-        const int oym = j > 0 ? -n : (per ? last * n : 0), oyp = j < last ? n : (per ? -last * n : 0);
-        const bool fym = j > 0 || per, fyp = j < last || per;
-        int c = z0 * sm + (t & (sm - 1));
-        C xc = xv(c);
-        C zm = xv(z0 > 0 ? c - sm : (per ? c + last * sm : c));
-        bool fzm = z0 > 0 || per;
-        for (int z = z0; z < z0 + len; ++z, c += sm) {
-            const C zp = xv(z < last ? c + sm : (per ? c - last * sm : c));
-            const bool fzp = z < last || per;
-            const C xm = xv(c + oxm), xp = xv(c + oxp);
-            C s = (fxm ? xm : -xc) + (fxp ? xp : -xc);
-            if (D == 3) {
-                const C ym = xv(c + oym), yp = xv(c + oyp);
-                s = (s + (fym ? ym : -xc)) + (fyp ? yp : -xc);
-            }
-            s = (s + (fzm ? zm : -xc)) + (fzp ? zp : -xc);
-            if (RESID) T[c] = F[c] - (C(2 * D) * xc - s) * inv_h2;  // the residual only
-            else T[c] = xc + wdiag * (F[c] - (C(2 * D) * xc - s) * inv_h2);
-            zm = xc;
-            fzm = true;
-            xc = zp;
-        }
-    }
-}
-
-// X += P E on a level of the one-workgroup tail (E: the next coarser level),
-// marching like tail_sweep: the in-plane interpolation indices and signs are
-// fixed per column.  Same terms and summation order as k_prolong_add.
-template <int D, class C, int NT>
-__device__ __forceinline__ void tail_prolong(const C *__restrict__ E, C *__restrict__ X, int lg, int bc) {
-    const int n = 1 << lg, last = n - 1, lgc = lg - 1, nc = n >> 1, sm = D == 3 ? n * n : n;
-    const int chunks = NT / sm < n ? NT / sm : n, len = n / chunks;
-    const int t = threadIdx.x;
-    if (t < sm * chunks) {
-        const int z0 = (t / sm) * len;
-        int oi, ni, oj = 0, nj = 0;
-        float si, sj = 1.0f;
-        pro_axis(t & last, nc, bc, oi, ni, si);
-        if (D == 3) pro_axis((t >> lg) & last, nc, bc, oj, nj, sj);
-        int c = z0 * sm + (t & (sm - 1));
-        for (int z = z0; z < z0 + len; ++z, c += sm) {
-            int oz, nz;
-            float sz;
-            pro_axis(z, nc, bc, oz, nz, sz);
-            C s = C(0);
-            if (D == 3) {
-                for (int cz = 0; cz < 2; ++cz)
-                    for (int b = 0; b < 2; ++b)
-                        for (int a = 0; a < 2; ++a) {
-                            const C w = C(a ? 0.25 : 0.75) * C(b ? 0.25 : 0.75) * C(cz ? 0.25 : 0.75);
-                            const C sg = C((a ? si : 1.0f) * (b ? sj : 1.0f) * (cz ? sz : 1.0f));
-                            const int q = ((cz ? nz : oz) << (2 * lgc)) | ((b ? nj : oj) << lgc) | (a ? ni : oi);
-                            s = np_fma(w, sg * E[q], s);
-                        }
-            } else {
-                // the marching axis is y
-                for (int b = 0; b < 2; ++b)
-                    for (int a = 0; a < 2; ++a) {
-                        const C w = C(a ? 0.25 : 0.75) * C(b ? 0.25 : 0.75) * C(1.0);
-                        const C sg = C((a ? si : 1.0f) * (b ? sz : 1.0f) * 1.0f);
-                        const int q = ((b ? nz : oz) << lgc) | (a ? ni : oi);
-                        s = np_fma(w, sg * E[q], s);
-                    }
-            }
-            X[c] = X[c] + s;
-        }
-    }
-}
-
-// V(nu1, nu2) cycle on levels lg_t .. 2 in one workgroup, every level in LDS
-// (xs, fs: all levels, finest first; ts: scratch of the finest level).
-// f_t: right-hand side of level lg_t (global); x_t: result (global); x_in:
-// starting iterate of level lg_t (global), or null for a zero iterate (then
-// the first sweep is w f).  Coarser levels always start from zero.
-// h_t: spacing of level lg_t.  nu1 >= 1 when x_in is null.  Entry (i, q) of
-// the coarsest inverse sits at Minv[i * m_rs + q * m_cs].
-template <int D, class S, int NT>
-__device__ __forceinline__ void tail_cycle(typename St<S>::C *xs, typename St<S>::C *fs, typename St<S>::C *ts,
-                                           const S *__restrict__ f_t, S *__restrict__ x_t,
-                                           const S *__restrict__ x_in, const double *__restrict__ Minv, int lg_t,
-                                           int bc, double h_t, double omega, int nu1, int nu2,
-                                           int m_rs = D == 3 ? 64 : 16, int m_cs = 1) {
-    typedef typename St<S>::C C;
-    const int tid = threadIdx.x;
-    // level l starts after the finer levels lg_t .. l+1 (geometric sum)
-    auto off = [&](int l) -> int64_t {
-        return ((int64_t(1) << (D * (lg_t + 1))) - (int64_t(1) << (D * (l + 1)))) / ((int64_t(1) << D) - 1);
-    };
-    // cnt sweeps on level lg, alternating between X and ts; the result ends in X
-    auto sweeps = [&](C *X, const C *F, int lg, C inv_h2, C wdiag, int cnt) {
-        C *cur = X, *nxt = ts;
-        for (int it = 0; it < cnt; ++it) {
-            tail_sweep<D, C, NT>(cur, F, nxt, lg, bc, inv_h2, wdiag);
-            __syncthreads();
-            C *t = cur;
-            cur = nxt;
-            nxt = t;
-        }
-        if (cur != X) {
-            const int m = 1 << (D * lg);
-            for (int c = tid; c < m; c += NT) X[c] = cur[c];
-            __syncthreads();
-        }
-    };
-    static_assert(Tail<D>::cells(Tail<D>::LG) >> Tail<D>::LG <= NT, "tail_sweep needs n^(D-1) <= NT");
-    const int64_t mt = int64_t(1) << (D * lg_t);
-    {
-        // all of this thread's loads first, then the LDS stores: one round trip to memory
-        constexpr int per = int((Tail<D>::cells(Tail<D>::LG) + NT - 1) / NT);
-        C fv[per], xv[per];
-#pragma unroll
-        for (int u = 0; u < per; ++u) {
-            const int c = tid + u * NT;
-            if (c < mt) {
-                fv[u] = St<S>::ld(f_t + c);
-                if (x_in) xv[u] = St<S>::ld(x_in + c);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < per; ++u) {
-            const int c = tid + u * NT;
-            if (c < mt) {
-                fs[off(lg_t) + c] = fv[u];
-                if (x_in) xs[off(lg_t) + c] = xv[u];
-            }
-        }
-    }
-    __syncthreads();
-    double h = h_t;
-    // ------------------------------------------------------------- down
-    for (int lg = lg_t; lg > 2; --lg, h *= 2.0) {
-        const int64_t m = int64_t(1) << (D * lg);
-        C *X = xs + off(lg), *F = fs + off(lg);
-        const C inv_h2 = C(1.0 / (h * h)), wdiag = C(omega * h * h / (2.0 * D));
-        int it0 = 0;
-        if (!(x_in && lg == lg_t)) {
-            if (nu1 >= 2) {
-                // the first two sweeps from zero in one pass, straight into X
-                tail_sweep<D, C, NT, false, true>(F, F, X, lg, bc, inv_h2, wdiag);
-                __syncthreads();
-                it0 = 2;
-            } else {
-                // first sweep from zero
-                for (int64_t c = tid; c < m; c += NT) X[c] = wdiag * F[c];
-                __syncthreads();
-                it0 = 1;
-            }
-        }
-        sweeps(X, F, lg, inv_h2, wdiag, nu1 - it0);
-        // residual into ts, then its 2^d-cell average into the next level's rhs
-        tail_sweep<D, C, NT, true>(X, F, ts, lg, bc, inv_h2, wdiag);
-        __syncthreads();
-        const int lgc = lg - 1;
-        const int mc = 1 << (D * lgc);
-        C *Fc = fs + off(lgc);
-        for (int cc = tid; cc < mc; cc += NT) {
-            int I, J, K;
-            decode<D>(cc, lgc, I, J, K);
-            C acc = C(0);
-            for (int kk = 0; kk < (D == 3 ? 2 : 1); ++kk)
-                for (int jj = 0; jj < 2; ++jj)
-                    for (int ii = 0; ii < 2; ++ii) {
-                        const int i = 2 * I + ii, j = 2 * J + jj, k = D == 3 ? 2 * K + kk : 0;
-                        acc += ts[(k << (2 * lg)) | (j << lg) | i];
-                    }
-            Fc[cc] = acc * C(D == 3 ? 0.125 : 0.25);
-        }
-        __syncthreads();
-    }
-    // ------------------------------------------------- coarsest (zero guess)
-    {
-        constexpr int m = D == 3 ? 64 : 16;
-        C *X = xs + off(2), *F = fs + off(2);
-        if (lg_t == 2) {
-            // the whole grid is the coarsest: x <- x + Minv (f - A x)
-            __shared__ double rr[m];
-            if (tid < m) {
-                int i, j, k;
-                decode<D>(tid, 2, i, j, k);
-                const double xc = x_in ? double(X[tid]) : 0.0;
-                double s = 0.0;
-                if (x_in) s = double(nb_sum_lds<D, C>(X, tid, i, j, k, 2, bc));
-                rr[tid] = double(F[tid]) - (double(2 * D) * xc - s) / (h * h);
-            }
-            __syncthreads();
-            if (tid < m) {
-                double acc = 0.0;
-                for (int q = 0; q < m; ++q) acc += Minv[tid * m_rs + q * m_cs] * rr[q];
-                X[tid] = C((x_in ? double(X[tid]) : 0.0) + acc);
-            }
-        } else if (tid < m) {
-            double acc = 0.0;
-            for (int q = 0; q < m; ++q) acc += Minv[tid * m_rs + q * m_cs] * double(F[q]);
-            X[tid] = C(0.0 + acc);
-        }
-        __syncthreads();
-    }
-    // --------------------------------------------------------------- up
-    for (int lg = 3; lg <= lg_t; ++lg) {
-        h *= 0.5;
-        const int lgc = lg - 1;
-        C *X = xs + off(lg), *F = fs + off(lg), *E = xs + off(lgc);
-        const C inv_h2 = C(1.0 / (h * h)), wdiag = C(omega * h * h / (2.0 * D));
-        tail_prolong<D, C, NT>(E, X, lg, bc);
-        __syncthreads();
-        sweeps(X, F, lg, inv_h2, wdiag, nu2);
-    }
-    for (int64_t c = tid; c < mt; c += NT) St<S>::st(x_t + c, xs[off(lg_t) + c]);
-}
-
-// One-workgroup V-cycle from a zero iterate on levels lg_t .. 2.  ctl: first the
-// cycle's convergence check on the np partials of the finest level's residual
-// norm (the check of k_check), and nothing more if it stops the solve.
-template <int D, class S>
-__global__ __launch_bounds__(Tail<D>::NT) void k_tail(const S *__restrict__ f_t, S *__restrict__ x_t,
-                                                      const double *__restrict__ Minv, int lg_t, int bc,
-                                                      double h_t, double omega, int nu1, int nu2,
-                                                      const int *stop, const double *__restrict__ partial,
-                                                      int np, Ctl *ctl) {
-    typedef typename St<S>::C C;
-    __shared__ C xs[Tail<D>::levels_sum()];
-    __shared__ C fs[Tail<D>::levels_sum()];
-    __shared__ C ts[Tail<D>::cells(Tail<D>::LG)];
-    // The coarsest inverse, staged in LDS transposed with padded rows: the loads
-    // are issued with the right-hand side's (one round trip to memory, not one per
-    // term of the product), and thread i reading entry (i, q) hits consecutive banks.
-    constexpr int m = D == 3 ? 64 : 16, mp = m + 1;
-    __shared__ double Ms[m * mp];
-    if (stop && *stop) return;
-    if (ctl) {
-        __shared__ int halt;
-        const int st = check_block<Tail<D>::NT>(partial, np, ctl);
-        if (threadIdx.x == 0) halt = st;
-        __syncthreads();
-        if (halt) return;
-    }
-    for (int g = threadIdx.x; g < m * m; g += Tail<D>::NT) Ms[(g % m) * mp + g / m] = Minv[g];
-    tail_cycle<D, S, Tail<D>::NT>(xs, fs, ts, f_t, x_t, nullptr, Ms, lg_t, bc, h_t, omega, nu1, nu2, 1, mp);
-}
 
 }  // namespace np
