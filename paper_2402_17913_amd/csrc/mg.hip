@@ -122,6 +122,7 @@ struct Tuning {
     int batch = 4;        // first batch of cycles enqueued before reading the controller
     int greps = 8;        // most cycles (outer steps) one graph holds: 1, 2, 4 or 8
     int tailck = 1;       // the cycle's convergence check run by the one-workgroup tail kernel
+    int one = 1;          // grids of at most 64^2 / 16^3: the whole solve in one launch of one workgroup
     int zbar = 1;         // barriers per plane step of the 3D zero-start down-leg pass (1 or 2)
     int d2cpt = 2;        // cells per thread of the 3D nonzero down-leg pass (1: k_down2z, 2: k_down2z2)
     int d2wg = 0;         // workgroups k_down2z2 aims for (256, 512 or 1024; 0: 256 in FP64, 512 otherwise)
@@ -1361,6 +1362,54 @@ static np_status solve_fp64(Hier *H, const double *f, double *x, double h, doubl
     return status_of(c, tol);
 }
 
+// ------------------------------------------- solves in one workgroup
+// Whether a solve runs as one launch (k_solve1, k_solve1m): V(nu1, nu2) cycles with nu1 >= 1 in FP64, or
+// refinement with FP32 inner cycles, on 8^2 .. 64^2 or 8^3 .. 16^3 cells, from a zero or the caller's
+// iterate.  BF16 storage rounds every stage of the finest level and stays on the level kernels.
+static bool one_on(int d, int lg, double tol, const np_mg_opts &o) {
+    if (!g_tune.one || !g_tune.tail || prof_on() || o.cycle != 0 || o.smooth_prec == NP_BF16 || o.warm_start == 1 ||
+        o.nu1 < 1 || lg < 3 || lg > (d == 2 ? Tail<2>::LG : Tail<3>::LG))
+        return false;
+    // stopped before the first cycle: the level path's own rule
+    return o.fixed_cycles > 0 || (tol < 1.0 && o.max_cycles > 0);
+}
+static Solve1 solve1_of(const np_mg_opts &o, double tol, int bc, bool mean, bool known0) {
+    return Solve1{tol, o.nu1, o.nu2, o.fixed_cycles, o.max_cycles, 1, bc, mean ? 1 : 0, o.warm_start == 2 ? 1 : 0,
+                  known0 ? 1 : 0};
+}
+// The controller's record goes straight to pinned host memory (a workspace without one: to the
+// device record, read back).
+static Ctl *one_out(Hier *H) { return H->direct ? H->ctl : H->hctl; }
+static np_status one_done(Hier *H, double tol, int inner, hipStream_t s, np_mg_stats *stats) {
+    NP_LAUNCH_CHECK();
+    if (H->direct) NP_TRY(read_ctl(H, s));
+    else NP_HIP_TRY(hipStreamSynchronize(s));
+    const Ctl &c = *H->hctl;
+    if (c.k < 0) {
+        set_error("non-finite right-hand side");
+        return NP_ENAN;
+    }
+    if (c.nhist == 0) return NP_OK;  // a zero right-hand side
+    fill_stats(stats, c, c.k * inner, c.k);
+    return status_of(c, tol);
+}
+// A Poisson solve; H: the workspace with the coarsest inverse.
+template <int D>
+static np_status solve_one(Hier *H, int lg, int bc, const double *f, double *x, double h, double tol,
+                           const np_mg_opts &o, hipStream_t s, np_mg_stats *stats) {
+    const double ih = 1.0 / (h * h), wd = o.omega * h * h / (2.0 * D);
+    Solve1 p = solve1_of(o, tol, bc, bc == NP_BC_PERIODIC, o.smooth_prec == NP_FP64);
+    if (o.smooth_prec == NP_FP64) {
+        hipLaunchKernelGGL((k_solve1<D, LapTail<D, double>>), dim3(1), dim3(kSolve1T), 0, s, f, x, H->Minv, lg,
+                           (LapTail<D, double>{ih, wd, lg}), p, one_out(H));
+    } else {
+        p.inner = o.inner_cycles > 0 ? o.inner_cycles : g_tune.inner_fp32;
+        hipLaunchKernelGGL((k_solve1m<D>), dim3(1), dim3(kSolve1T), 0, s, f, x, H->Minv, lg,
+                           (LapTail<D, double>{ih, wd, lg}), (LapTail<D, float>{ih, wd, lg}), p, one_out(H));
+    }
+    return one_done(H, tol, p.inner, s, stats);
+}
+
 // One sawtooth cycle (Section 2.2; Appendix B), FP64, every launch gated by the
 // controller: the finest residual (its norm is the convergence check), the
 // residual restricted level by level to the coarsest grid, then on each level
@@ -1624,7 +1673,7 @@ extern "C" np_status np_set_tuning(const char *key, int value) {
         {"inner_fp32", &g_tune.inner_fp32, 1, 64}, {"inner_bf16", &g_tune.inner_bf16, 1, 64},
         {"batch", &g_tune.batch, 1, 64},        {"sweep3", &g_tune.sweep3, 0, 1},
         {"zero2", &g_tune.zero2, 0, 1},         {"psweep", &g_tune.psweep, 0, 1},
-        {"ir_cpt", &g_tune.ir_cpt, 1, 2},      {"fuseb", &g_tune.fuseb, 0, 1}, {"fbnt", &g_tune.fbnt, 512, 1024},  {"sweep2z", &g_tune.sweep2z, 0, 1}, {"down2z", &g_tune.down2z, 0, 1}, {"blk2", &g_tune.blk2, 0, 1}, {"z2wg", &g_tune.z2wg, 0, 1}, {"greps", &g_tune.greps, 1, 8}, {"tailck", &g_tune.tailck, 0, 1}, {"zbar", &g_tune.zbar, 1, 2}, {"d2cpt", &g_tune.d2cpt, 1, 2}, {"d2wg", &g_tune.d2wg, 0, 1024},
+        {"ir_cpt", &g_tune.ir_cpt, 1, 2},      {"fuseb", &g_tune.fuseb, 0, 1}, {"fbnt", &g_tune.fbnt, 512, 1024},  {"sweep2z", &g_tune.sweep2z, 0, 1}, {"down2z", &g_tune.down2z, 0, 1}, {"blk2", &g_tune.blk2, 0, 1}, {"z2wg", &g_tune.z2wg, 0, 1}, {"greps", &g_tune.greps, 1, 8}, {"tailck", &g_tune.tailck, 0, 1}, {"one", &g_tune.one, 0, 1}, {"zbar", &g_tune.zbar, 1, 2}, {"d2cpt", &g_tune.d2cpt, 1, 2}, {"d2wg", &g_tune.d2wg, 0, 1024},
         {"fbmax", &g_tune.fbmax, 5, 10},        {"w2min", &g_tune.w2min, 7, 14},
         {"batched_graphs", &g_batched_graphs, 0, 1}, {"batched_autotune", &g_batched_autotune, 0, 1},
         {"batched_rm", &g_batched_rm, 0, 1},    {"batched_wg", &g_batched_wg, 64, 1 << 20},
@@ -1682,6 +1731,7 @@ extern "C" int np_get_tuning(const char *key) {
     if (!std::strcmp(key, "z2wg")) return g_tune.z2wg;
     if (!std::strcmp(key, "greps")) return g_tune.greps;
     if (!std::strcmp(key, "tailck")) return g_tune.tailck;
+    if (!std::strcmp(key, "one")) return g_tune.one;
     if (!std::strcmp(key, "zbar")) return g_tune.zbar;
     if (!std::strcmp(key, "d2cpt")) return g_tune.d2cpt;
     if (!std::strcmp(key, "d2wg")) return g_tune.d2wg;
@@ -1769,6 +1819,9 @@ np_status poisson_solve(np_dims dims, double h, np_bc bc, const double *rhs, dou
     const int64_t m = cells(d, lg);
     if (!HL) NP_TRY(ensure_coarse(H, h, s));
     else NP_TRY(ensure_coarse(HL, h, s));
+    if (one_on(d, lg, tol, o))
+        return d == 2 ? solve_one<2>(HL ? HL : H, lg, bc, rhs, x, h, tol, o, s, stats)
+                      : solve_one<3>(HL ? HL : H, lg, bc, rhs, x, h, tol, o, s, stats);
     const double *f = rhs;
     if (bc == NP_BC_PERIODIC) {
         if (!H->f64) NP_TRY(dmalloc((void **)&H->f64, sizeof(double) * m));
@@ -1975,6 +2028,9 @@ extern "C" np_status mg_poisson_solve_noalloc(np_dims dims, double h, np_bc bc, 
     hipStream_t s = (hipStream_t)o.stream;
     const int64_t m = cells(d, lg);
     NP_TRY(ensure_coarse(&H, h, s));
+    if (one_on(d, lg, tol, o))
+        return d == 2 ? solve_one<2>(&H, lg, bc, rhs, x, h, tol, o, s, stats)
+                      : solve_one<3>(&H, lg, bc, rhs, x, h, tol, o, s, stats);
     const double *f = rhs;
     if (bc == NP_BC_PERIODIC) {
         NP_HIP_TRY(hipMemcpyAsync(H.f64, rhs, sizeof(double) * m, hipMemcpyDeviceToDevice, s));
@@ -2691,6 +2747,18 @@ static np_status solve_ad(Hier *H, const np_ad_op &op, const double *f, double *
     return status_of(c, tol);
 }
 
+// The solve in one workgroup (solve_one).
+template <int D>
+static np_status ad_solve_one(Hier *H, const np_ad_op &op, const double *f, double *x, double h, double tol,
+                              const np_mg_opts &o, hipStream_t s, np_mg_stats *stats) {
+    NP_TRY(ad_coarse(H, op, h * double(int64_t(1) << H->L), s));
+    AdTail<D> ops{{}, o.omega, H->lg};
+    for (int q = 0; q <= H->L; ++q) ops.lv.w[q] = ad_weights(op, D, h * double(int64_t(1) << q));
+    hipLaunchKernelGGL((k_solve1<D, AdTail<D>>), dim3(1), dim3(kSolve1T), 0, s, f, x, H->ad_minv, H->lg, ops,
+                       solve1_of(o, tol, H->bc, false, false), one_out(H));
+    return one_done(H, tol, 1, s, stats);
+}
+
 static np_status check_ad_op(const np_ad_op *op, int d) {
     if (!op) { set_error("null operator"); return NP_EINVAL; }
     if (!(op->dt > 0.0) || !std::isfinite(op->dt)) { set_error("dt must be positive"); return NP_EINVAL; }
@@ -2725,6 +2793,9 @@ extern "C" np_status np_ad_implicit_solve(np_dims dims, double h, np_bc bc, cons
     NP_TRY(get_hier(d, lg, bc, NP_FP64, &H));
     std::lock_guard<std::mutex> lk(H->mu);
     const int64_t m = cells(d, lg);
+    if (!l1_change && one_on(d, lg, tol, o))
+        return d == 2 ? ad_solve_one<2>(H, op2, rhs, x, h, tol, o, s, stats)
+                      : ad_solve_one<3>(H, op2, rhs, x, h, tol, o, s, stats);
     NP_TRY(dsum(H, rhs, m, 1, 0, s));
     NP_TRY(read_scalars(H, 1, s));
     const double nf = H->hred[0];

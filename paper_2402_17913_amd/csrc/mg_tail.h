@@ -1,6 +1,6 @@
 // Levels of at most 64^2 (2D) or 16^3 (3D) cells in one workgroup, every level in
 // LDS: the end of a larger grid's V-cycle (k_tail, and kb_tail of the batched
-// solver).
+// solver), and whole FP64 solves of grids that small (k_solve1).
 // What bounds it: one CU does all the work, so each stage costs its LDS and
 // FP64 issue (64^2 in FP64: 4096 cells, about 1300 cycles of LDS reads a sweep)
 // and, on the smaller levels, one LDS round trip, one chain of dependent
@@ -328,6 +328,193 @@ __global__ __launch_bounds__(Tail<D>::NT) void k_tail(const S *__restrict__ f_t,
         tail_zero<D, C, NT, decltype(lg)::value>(xs, fs, ts, Ms, bc, ops, nu1, nu2);
     });
     for (int c = int(threadIdx.x); c < mt; c += NT) St<S>::st(x_t + c, xs[o + c]);
+}
+
+// ------------------------------------------------------------ whole solves
+// A solve of a grid that fits one workgroup, from the right-hand side's norm to
+// the last cycle, in one launch with every field in LDS.  The multi-launch solve
+// spent five to seven launches a cycle on such a grid.  Measured, twelve FP64 cycles: 8^2
+// 276 -> 40 us, 64^2 431 -> 112 us, 16^3 479 -> 120 us; a 64^2 solve to 1e-10 529 -> 134 us.
+constexpr int kSolve1T = 512;  // threads (1024 in 3D: 128 registers, spilled)
+struct Solve1 {
+    double tol;
+    int nu1, nu2, fixed, maxc;  // as the controller's
+    int inner;                  // mixed: V-cycles per refinement step
+    int bc, mean;               // mean: remove the right-hand side's and the solution's mean
+    int warm, known0;           // x is the starting iterate; the zero iterate's check is known (rr = 1)
+};
+
+// v -= its mean.
+template <int NT> __device__ __forceinline__ void tail_demean(double *v, int m) {
+    __shared__ double mean;
+    double a = 0.0;
+    for (int c = int(threadIdx.x); c < m; c += NT) a += v[c];
+    a = block_sum_n<NT>(a);
+    if (threadIdx.x == 0) mean = a * (1.0 / double(m));
+    __syncthreads();
+    for (int c = int(threadIdx.x); c < m; c += NT) v[c] -= mean;
+    __syncthreads();
+}
+
+// The controller's rule (check_block) on the sum of squares `acc` shared by the workgroup: the stop
+// state, 0 while running.
+template <int NT>
+__device__ __forceinline__ int solve1_check(double acc, double nf, const Solve1 &p, int k, double *hist) {
+    __shared__ int halt;
+    acc = block_sum_n<NT>(acc);
+    if (threadIdx.x == 0) {
+        const double rr = sqrt(acc) / nf;
+        if (k < 256) hist[k] = rr;
+        int st = kRunning;
+        if (!(rr <= 1.0e300)) st = kNonFinite;
+        else if (p.fixed > 0) { if (k >= p.fixed) st = kFixedDone; }
+        else if (rr <= p.tol) st = kConverged;
+        else if (k >= p.maxc) st = kMaxCycles;
+        else if (k >= 3 && k < 256 && hist[k - 3] < hist[k - 2] && hist[k - 2] < hist[k - 1] && hist[k - 1] < rr)
+            st = kDiverged;
+        halt = st;
+    }
+    __syncthreads();
+    return halt;
+}
+
+// Loads f (and x), takes |f| (of the mean-free f): false when there is nothing to solve -- x is then
+// zero (f = 0) or untouched (a non-finite f, out->k = -1) and *out says so.
+template <int NT, int MAX>
+__device__ __forceinline__ bool solve1_start(const double *f, double *x, double *F, double *X, int m, const Solve1 &p,
+                                             double &nf, Ctl *out) {
+    __shared__ double norm;
+    tail_fetch<double, NT, MAX>(F, f, m);
+    if (p.warm) tail_fetch<double, NT, MAX>(X, x, m);
+    __syncthreads();
+    if (p.mean) tail_demean<NT>(F, m);
+    double a = 0.0;
+    for (int c = int(threadIdx.x); c < m; c += NT) a += F[c] * F[c];
+    a = block_sum_n<NT>(a);
+    if (threadIdx.x == 0) norm = sqrt(a);
+    __syncthreads();
+    nf = norm;
+    if (nf > 0.0 && nf <= 1.7976931348623157e308) return true;
+    if (nf == 0.0)
+        for (int c = int(threadIdx.x); c < m; c += NT) x[c] = 0.0;
+    if (threadIdx.x == 0) {
+        out->stop = nf == 0.0 ? kConverged : kNonFinite;
+        out->k = nf == 0.0 ? 0 : -1;
+        out->nhist = 0;
+    }
+    return false;
+}
+
+// The result and the controller's record.
+template <int NT>
+__device__ __forceinline__ void solve1_end(double *X, double *x, int m, const Solve1 &p, int stop, int k,
+                                           const double *hist, Ctl *out) {
+    if (p.mean) tail_demean<NT>(X, m);
+    for (int c = int(threadIdx.x); c < m; c += NT) x[c] = X[c];
+    const int nh = k + 1 < 256 ? k + 1 : 256;
+    for (int c = int(threadIdx.x); c < nh; c += NT) out->hist[c] = hist[c];
+    if (threadIdx.x == 0) {
+        out->stop = stop;
+        out->k = k;
+        out->nhist = nh;
+    }
+}
+
+// nu1 pre-sweeps of the finest level from the iterate X and the rest of the cycle.
+template <int D, class C, int NT, int LG, class OPS>
+__device__ __forceinline__ void solve1_cycle(C *xs, C *fs, C *ts, const double *Ms, int bc, const OPS &ops, int nu1,
+                                             int nu2) {
+    tail_sweeps<D, C, NT, LG>(xs + tail_off<D>(LG), fs + tail_off<D>(LG), ts, bc, ops.template at<LG>(), nu1);
+    tail_down_up<D, C, NT, LG>(xs, fs, ts, Ms, bc, ops, nu1, nu2);
+}
+
+// FP64 V(nu1, nu2) cycles, nu1 >= 1, on a grid of 2^lg cells per axis, 3 <= lg <= Tail<D>::LG.
+template <int D, class OPS>
+__global__ __launch_bounds__(kSolve1T) void k_solve1(const double *__restrict__ f, double *__restrict__ x,
+                                                        const double *__restrict__ Minv, int lg, OPS ops, Solve1 p,
+                                                        Ctl *__restrict__ out) {
+    constexpr int NT = kSolve1T, M = int(Tail<D>::cells(Tail<D>::LG)), mc = D == 3 ? 64 : 16;
+    __shared__ double xs[Tail<D>::levels_sum()];
+    __shared__ double fs[Tail<D>::levels_sum()];
+    __shared__ double ts[M];
+    __shared__ double Ms[mc * (mc + 1)];
+    __shared__ double hist[256];
+    const int o = tail_off<D>(lg), m = 1 << (D * lg);
+    double nf;
+    tail_minv<D, NT>(Ms, Minv);
+    if (!solve1_start<NT, M>(f, x, fs + o, xs + o, m, p, nf, out)) return;
+    int stop = kRunning, k = 0;
+    tail_by_level<D>(lg, [&](auto l) {
+        constexpr int LG = decltype(l)::value;
+        if constexpr (LG > 2) {
+            double *X = xs + tail_off<D>(LG), *F = fs + tail_off<D>(LG);
+            const auto op = ops.template at<LG>();
+            if (!p.warm && p.known0) {
+                tail_zero<D, double, NT, LG>(xs, fs, ts, Ms, p.bc, ops, p.nu1, p.nu2);
+                if (threadIdx.x == 0) hist[0] = 1.0;
+                k = 1;
+            } else if (!p.warm) {
+                for (int c = int(threadIdx.x); c < m; c += NT) X[c] = 0.0;
+                __syncthreads();
+            }
+            for (;; ++k) {
+                // the first pre-sweep forms the residual of the iterate, which it leaves in place
+                const double acc = tail_stage<D, double, NT, LG, kTailSweep>(X, F, ts, p.bc, op);
+                stop = solve1_check<NT>(acc, nf, p, k, hist);
+                if (stop) break;
+                if (p.nu1 >= 2) {
+                    tail_stage<D, double, NT, LG, kTailSweep>(ts, F, X, p.bc, op);
+                    __syncthreads();
+                    if (p.nu1 > 2) tail_sweeps<D, double, NT, LG>(X, F, ts, p.bc, op, p.nu1 - 2);
+                } else {
+                    for (int c = int(threadIdx.x); c < m; c += NT) X[c] = ts[c];
+                    __syncthreads();
+                }
+                tail_down_up<D, double, NT, LG>(xs, fs, ts, Ms, p.bc, ops, p.nu1, p.nu2);
+            }
+        }
+    });
+    solve1_end<NT>(xs + o, x, m, p, stop, k, hist, out);
+}
+
+// Refinement steps with FP32 inner cycles (solve_mixed): r = f - A x in FP64, rounded; `inner` cycles
+// from a zero correction in FP32; x += e in FP64.
+template <int D>
+__global__ __launch_bounds__(kSolve1T) void k_solve1m(const double *__restrict__ f, double *__restrict__ x,
+                                                         const double *__restrict__ Minv, int lg, LapTail<D, double> op64,
+                                                         LapTail<D, float> ops, Solve1 p, Ctl *__restrict__ out) {
+    constexpr int NT = kSolve1T, M = int(Tail<D>::cells(Tail<D>::LG)), mc = D == 3 ? 64 : 16;
+    __shared__ double X[M], F[M];
+    __shared__ float xs[Tail<D>::levels_sum()];
+    __shared__ float fs[Tail<D>::levels_sum()];
+    __shared__ float ts[M];
+    __shared__ double Ms[mc * (mc + 1)];
+    __shared__ double hist[256];
+    const int m = 1 << (D * lg);
+    double nf;
+    tail_minv<D, NT>(Ms, Minv);
+    if (!solve1_start<NT, M>(f, x, F, X, m, p, nf, out)) return;
+    if (!p.warm)
+        for (int c = int(threadIdx.x); c < m; c += NT) X[c] = 0.0;
+    __syncthreads();
+    int stop = kRunning, k = 0;
+    tail_by_level<D>(lg, [&](auto l) {
+        constexpr int LG = decltype(l)::value;
+        if constexpr (LG > 2) {
+            const auto op = op64.template at<LG>();
+            for (;; ++k) {
+                const double acc = tail_stage<D, double, NT, LG, kTailResid>(X, F, fs + tail_off<D>(LG), p.bc, op);
+                stop = solve1_check<NT>(acc, nf, p, k, hist);
+                if (stop) break;
+                tail_zero<D, float, NT, LG>(xs, fs, ts, Ms, p.bc, ops, p.nu1, p.nu2);
+                for (int c = 1; c < p.inner; ++c)
+                    solve1_cycle<D, float, NT, LG>(xs, fs, ts, Ms, p.bc, ops, p.nu1, p.nu2);
+                for (int c = int(threadIdx.x); c < m; c += NT) X[c] += double(xs[tail_off<D>(LG) + c]);
+                __syncthreads();
+            }
+        }
+    });
+    solve1_end<NT>(X, x, m, p, stop, k, hist, out);
 }
 
 }  // namespace np

@@ -145,3 +145,56 @@ def test_batched_legs(B, prec):
     for n, a, b in zip(sizes, *out):
         assert a.abs().max() > 0
         assert torch.equal(a, b), n
+
+
+# every grid the one-workgroup solve takes, and the options it accepts
+ONE = [dict(), dict(fixed_cycles=3), dict(nu1=1, nu2=2), dict(nu1=3, nu2=1, fixed_cycles=4), dict(warm_start=2),
+       dict(smooth_prec=1), dict(smooth_prec=1, fixed_cycles=2), dict(smooth_prec=1, warm_start=2, inner_cycles=2),
+       dict(max_cycles=2)]
+
+
+@pytest.mark.parametrize("bc", [DIR, PER])
+@pytest.mark.parametrize("d,n", [(2, 8), (2, 16), (2, 32), (2, 64), (3, 8), (3, 16)])
+def test_one_workgroup_solves(B, d, n, bc):
+    """A whole solve in one launch against the level kernels: the same cycles, status and history, the
+    iterate to the rounding of the mean and of the coarsest product (1e-12 of its largest value)."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n + bc)
+    f = torch.randn((n,) * d, dtype=torch.float64, device="cuda", generator=g)
+    op = B.ad_op(20.0, 2.0, [1.0, -0.5, 0.3][:d], 0)
+    print("one workgroup", d, n, bc, flush=True)
+
+    def pair(solve):
+        out = []
+        try:
+            for one in (0, 1):
+                B.np_set_tuning("one", one)
+                x = 0.3 * f
+                out.append((x,) + solve(x))
+        finally:
+            B.np_set_tuning("one", 1)
+        (x, st, s), (y, tt, t) = out
+        assert st == tt and s["cycles"] == t["cycles"] and s["outer_iters"] == t["outer_iters"]
+        assert x.abs().max() > 0 and (x - y).abs().max() <= 1e-12 * x.abs().max()
+        assert len(s["hist"]) == len(t["hist"])
+        assert all(abs(u - v) <= 1e-10 * max(1.0, u) for u, v in zip(s["hist"], t["hist"]))
+
+    for kw in ONE:
+        pair(lambda x: B.mg_poisson_solve(f, x, 1.0 / n, bc, check=False, **kw))
+    for kw in (dict(), dict(warm_start=2), dict(fixed_cycles=2)):
+        pair(lambda x: B.np_ad_implicit_solve(f, x, 1.0, bc, op, check=False, **kw))
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_one_workgroup_right_hand_sides(B, prec):
+    """A zero right-hand side gives zero in no cycles; a non-finite one leaves x alone."""
+    import torch
+    f = torch.zeros((32, 32), dtype=torch.float64, device="cuda")
+    x = torch.full_like(f, 3.0)
+    _, st = B.mg_poisson_solve(f, x, 1.0 / 32, DIR, smooth_prec=prec)
+    assert st["cycles"] == 0 and bool((x == 0).all())
+    for bad in (float("nan"), float("inf")):
+        f[3, 4] = bad
+        x.fill_(3.0)
+        st, _ = B.mg_poisson_solve(f, x, 1.0 / 32, DIR, smooth_prec=prec, check=False)
+        assert st == B.NP_ENAN and bool((x == 3.0).all())
