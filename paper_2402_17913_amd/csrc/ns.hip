@@ -9,6 +9,7 @@
 #include <tuple>
 #include <vector>
 
+#include "adx.h"
 #include "np_internal.h"
 
 namespace np {
@@ -164,11 +165,6 @@ __device__ __forceinline__ double ad_rate(const IN &T, const double *const *a, c
     return adv - nu_inv_h2 * lap;
 }
 
-struct APtrs {
-    const double *a[3];
-    int has;
-};
-
 template <int D, int STAGE>
 __global__ __launch_bounds__(kBlock) void k_ad_stage(const double *__restrict__ T, const double *__restrict__ Tt,
                                                      double *__restrict__ out, APtrs ap, Gen g, double dt,
@@ -182,241 +178,6 @@ __global__ __launch_bounds__(kBlock) void k_ad_stage(const double *__restrict__ 
     if (STAGE == 0) R = ad_rate<D>(LdArr{T}, a, g, i, j, k, inv_2h, nu_inv_h2);
     else R = ad_rate<D>(LdHalf{Tt, T}, a, g, i, j, k, inv_2h, nu_inv_h2);
     out[c] = T[c] - dt * R;
-}
-
-// ------------------------------------- explicit step, filter families
-// The filters of Section 2.1 and Appendix A on any n >= 3 (all axes equal):
-// scheme 0 central (3-point first differences, 5-/7-point diffusion), 1
-// first-order upwind advection (the upstream value: backward difference for a
-// positive velocity component) with the same diffusion, 2 the finite-element
-// (bilinear / trilinear) filters: first derivatives averaged across the other
-// axes with weights (1, 4, 1)/6, diffusion 16 delta - (1,2,1)x(1,2,1) over
-// 4 h^2 (2D) or 88 / -6 / -3 / -2 on the centre, faces, edges and corners over
-// 26 h^2 (3D).  Boundary rule bc: 0 Dirichlet-0 (ghost = -value), 1 periodic,
-// 2 zero normal derivative (ghost = value, the copy padding of Section 2.4).
-
-// Index along one axis of the cell q (at most one cell outside [0, n)) and the
-// sign its value takes.
-__device__ __forceinline__ int adx_res(int q, int n, int bc, double &sg) {
-    sg = 1.0;
-    if (q < 0) {
-        if (bc == 1) return n - 1;
-        if (bc == 0) sg = -1.0;
-        return 0;
-    }
-    if (q >= n) {
-        if (bc == 1) return 0;
-        if (bc == 0) sg = -1.0;
-        return n - 1;
-    }
-    return q;
-}
-
-constexpr int kAdxX = 64, kAdxY = 4;  // workgroup: 64 cells along x, 4 rows
-
-// The 3^d neighbourhood v[dz + 1][dy + 1][dx + 1] of cell (i, j, k) of F
-// (HALF: of (F + G)/2) with the boundary rule; the 5/7-point families load
-// the face neighbours only (the other entries stay zero).
-template <int D, int SCHEME, bool HALF>
-__device__ __forceinline__ void adx_gather(const double *__restrict__ F, const double *__restrict__ G, int i, int j,
-                                           int k, int n, int bc, double (&v)[3][3][3]) {
-    const int64_t nn = n;
-    int ix[3];
-    double sx[3];
-    for (int o = 0; o < 3; ++o) ix[o] = adx_res(i + o - 1, n, bc, sx[o]);
-#pragma unroll
-    for (int dz = -1; dz <= 1; ++dz) {
-        if (D == 2 && dz != 0) continue;
-        double sz = 1.0;
-        const int kk = D == 3 ? adx_res(k + dz, n, bc, sz) : 0;
-#pragma unroll
-        for (int dy = -1; dy <= 1; ++dy) {
-            double sy;
-            const int jj = adx_res(j + dy, n, bc, sy);
-            const int64_t row = (int64_t(kk) * nn + jj) * nn;
-#pragma unroll
-            for (int dx = -1; dx <= 1; ++dx) {
-                if (SCHEME != 2 && (dx != 0) + (dy != 0) + (dz != 0) > 1) continue;  // 5/7-point only
-                const int64_t q = row + ix[dx + 1];
-                const double t = HALF ? 0.5 * (G[q] + F[q]) : F[q];
-                v[dz + 1][dy + 1][dx + 1] = sx[dx + 1] * sy * sz * t;
-            }
-        }
-    }
-}
-
-// First derivative along axis e of the gathered field: the finite-element
-// filter (scheme 2) or the central difference.
-template <int D, int SCHEME>
-__device__ __forceinline__ double adx_deriv(const double (&v)[3][3][3], int e, double h) {
-    if (SCHEME == 2) {
-        const double w[3] = {1.0, 4.0, 1.0};
-        double g = 0.0;
-        if (D == 2) {
-#pragma unroll
-            for (int p = 0; p < 3; ++p) g += w[p] * (e == 0 ? v[1][p][2] - v[1][p][0] : v[1][2][p] - v[1][0][p]);
-            return g / (12.0 * h);
-        }
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-#pragma unroll
-            for (int q = 0; q < 3; ++q)
-                g += w[p] * w[q] *
-                     (e == 0 ? v[p][q][2] - v[p][q][0] : (e == 1 ? v[p][2][q] - v[p][0][q] : v[2][p][q] - v[0][p][q]));
-        return g / (72.0 * h);
-    }
-    const double xm = e == 0 ? v[1][1][0] : (e == 1 ? v[1][0][1] : v[0][1][1]);
-    const double xp = e == 0 ? v[1][1][2] : (e == 1 ? v[1][2][1] : v[2][1][1]);
-    return (xp - xm) / (2.0 * h);
-}
-
-// Advection + diffusion rate of the gathered field, a the velocity at the
-// cell (used when has_a).
-template <int D, int SCHEME>
-__device__ __forceinline__ double adx_rate_at(const double (&v)[3][3][3], const double (&a)[3], bool has_a, double nu,
-                                              double h) {
-    const double v0 = v[1][1][1];
-    double adv = 0.0, dif;
-    if (SCHEME == 2) {
-        if (D == 2) {
-            const double b[3] = {1.0, 2.0, 1.0};
-            double sm = 0.0;
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-#pragma unroll
-                for (int q = 0; q < 3; ++q) sm += b[p] * b[q] * v[1][p][q];
-            dif = (16.0 * v0 - sm) / (4.0 * h * h);
-        } else {
-            const double cw[4] = {88.0, -6.0, -3.0, -2.0};  // by the number of nonzero offsets
-            double sm = 0.0;
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-#pragma unroll
-                for (int q = 0; q < 3; ++q)
-#pragma unroll
-                    for (int r = 0; r < 3; ++r) sm += cw[(p != 1) + (q != 1) + (r != 1)] * v[p][q][r];
-            dif = sm / (26.0 * h * h);
-        }
-        if (has_a)
-#pragma unroll
-            for (int e = 0; e < D; ++e) adv += a[e] * adx_deriv<D, 2>(v, e, h);
-    } else {
-        const double xm[3] = {v[1][1][0], v[1][0][1], v[0][1][1]}, xp[3] = {v[1][1][2], v[1][2][1], v[2][1][1]};
-        double lap = 0.0;
-#pragma unroll
-        for (int e = 0; e < D; ++e) {
-            lap += (v0 - xm[e]) + (v0 - xp[e]);
-            if (!has_a) continue;
-            if (SCHEME == 0) adv += a[e] * (xp[e] - xm[e]) / (2.0 * h);
-            else adv += a[e] >= 0.0 ? a[e] * (v0 - xm[e]) / h : a[e] * (xp[e] - v0) / h;
-        }
-        dif = lap / (h * h);
-    }
-    return adv + nu * dif;
-}
-
-// STAGE 0: out = T - dt R(T), and tcopy = T (so that the corrector can write
-// the caller's array); STAGE 1: out = T - dt R((Tt + T)/2).  One thread per
-// cell; the 3^d neighbourhood is gathered with the boundary rule, then every
-// filter of the family reads it.
-template <int D, int SCHEME, int STAGE>
-__global__ __launch_bounds__(kAdxX * kAdxY) void k_adx_stage(const double *__restrict__ T,
-                                                             const double *__restrict__ Tt,
-                                                             double *__restrict__ out, double *__restrict__ tcopy,
-                                                             APtrs ap, int n, int bc, double dt, double nu,
-                                                             double h) {
-    const int i = int(blockIdx.x) * kAdxX + int(threadIdx.x), j = int(blockIdx.y) * kAdxY + int(threadIdx.y);
-    const int k = D == 3 ? int(blockIdx.z) : 0;
-    if (i >= n || j >= n) return;
-    double v[3][3][3] = {};
-    adx_gather<D, SCHEME, STAGE == 1>(T, Tt, i, j, k, n, bc, v);
-    const int64_t c = (int64_t(k) * n + j) * n + i;
-    double a[3] = {0.0, 0.0, 0.0};
-    if (ap.has)
-#pragma unroll
-        for (int e = 0; e < D; ++e) a[e] = ap.a[e][c];
-    out[c] = T[c] - dt * adx_rate_at<D, SCHEME>(v, a, ap.has != 0, nu, h);
-    if (STAGE == 0) tcopy[c] = T[c];
-}
-
-// 2D grids with n >= 1024, n a multiple of kAx2: row-marching tiles.  A
-// workgroup of kAx2 threads owns kAx2 consecutive columns and ry rows; each
-// step publishes the next row of the stage input (ghost rule and signs
-// applied, the strip's edge threads adding the cells beyond it) into a ring
-// of four LDS rows, so one barrier per row suffices, and every thread reads
-// its 3 x 3 (or 5-point) neighbourhood from rows j - 1, j, j + 1.  The values
-// and the rate are those of k_adx_stage, so the results are bit-identical.
-constexpr int kAx2 = 256;
-
-inline int adx_rows2(int n) {
-    int ry = 32;
-    while (int64_t(n / kAx2) * (n / ry) < 2048 && ry > 4) ry /= 2;
-    return ry;
-}
-
-template <int SCHEME, int STAGE>
-__global__ __launch_bounds__(kAx2) void k_adx_stage2r(const double *__restrict__ T, const double *__restrict__ Tt,
-                                                      double *__restrict__ out, double *__restrict__ tcopy,
-                                                      APtrs ap, int n, int bc, int ry, double dt, double nu,
-                                                      double h) {
-    __shared__ double rows[4][kAx2 + 2];
-    const int strips = n / kAx2, tid = int(threadIdx.x);
-    const int x0 = (int(blockIdx.x) % strips) * kAx2, j0 = (int(blockIdx.x) / strips) * ry;
-    const int i = x0 + tid;
-    // the edge threads also publish the column beyond the strip (ghost rule)
-    const bool hl = tid == 0, hr = tid == kAx2 - 1;
-    double hsx = 1.0;
-    const int hi = (hl || hr) ? adx_res(hl ? x0 - 1 : x0 + kAx2, n, bc, hsx) : 0;
-    const int64_t nn = n;
-    auto tv = [&](int64_t q) { return STAGE == 1 ? 0.5 * (Tt[q] + T[q]) : T[q]; };
-    // row jr of the stage input (jr may be -1 or n): own column and edge value;
-    // raw: T at the own column of that row (the corrector's T^n, kept for later)
-    auto fetch = [&](int jr, double &own, double &edge, double &raw) {
-        double sy;
-        const int jj = adx_res(jr < n ? jr : n, n, bc, sy);
-        const int64_t q = int64_t(jj) * nn + i;
-        raw = T[q];
-        own = (1.0 * sy * 1.0) * (STAGE == 1 ? 0.5 * (Tt[q] + raw) : raw);
-        edge = (hl || hr) ? (hsx * sy * 1.0) * tv(int64_t(jj) * nn + hi) : 0.0;
-    };
-    auto publish = [&](int jr, double own, double edge) {
-        double *r = rows[jr & 3];
-        r[tid + 1] = own;
-        if (hl) r[0] = edge;
-        if (hr) r[kAx2 + 1] = edge;
-    };
-    double o, e, r;
-    fetch(j0 - 1, o, e, r);
-    publish(j0 - 1, o, e);
-    fetch(j0, o, e, r);
-    publish(j0, o, e);
-    double rc = r;  // T at the own column of row j
-    double no, ne, nr;
-    fetch(j0 + 1, no, ne, nr);
-    for (int j = j0; j < j0 + ry; ++j) {
-        publish(j + 1, no, ne);
-        const int64_t c = int64_t(j) * nn + i;
-        double a[3] = {0.0, 0.0, 0.0};
-        if (ap.has)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) a[q] = ap.a[q][c];
-        const double tc = rc;
-        rc = nr;
-        __syncthreads();
-        if (j + 1 < j0 + ry) fetch(j + 2, no, ne, nr);
-        double v[3][3][3] = {};
-#pragma unroll
-        for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-            for (int dx = -1; dx <= 1; ++dx) {
-                if (SCHEME != 2 && (dx != 0) + (dy != 0) > 1) continue;  // 5-point families
-                v[1][dy + 1][dx + 1] = rows[(j + dy) & 3][tid + 1 + dx];
-            }
-        // the stage input of the predictor is T itself: its own value is in the ring
-        const double t0 = STAGE == 1 ? tc : v[1][1][1];
-        out[c] = t0 - dt * adx_rate_at<2, SCHEME>(v, a, ap.has != 0, nu, h);
-        if (STAGE == 0) tcopy[c] = t0;
-    }
 }
 
 // 3D levels on z-marching tiles: a workgroup of kZx x TY threads owns a
@@ -538,40 +299,13 @@ struct ZRing {
     }
 };
 
-template <int SCHEME, int STAGE>
-__global__ __launch_bounds__(kZx * zrows(SCHEME)) void k_adx_stage3z(const double *__restrict__ T,
-                                                                     const double *__restrict__ Tt,
-                                                                     double *__restrict__ out,
-                                                                     double *__restrict__ tcopy, APtrs ap, int n,
-                                                                     int bc, int zc, double dt, double nu, double h) {
-    typedef ZRing<1, zrows(SCHEME)> Ring;
-    __shared__ typename Ring::Plane pl[1];
-    Ring R(n, bc, zc);
-    auto ld = [&](int, int64_t q) { return STAGE == 0 ? T[q] : 0.5 * (Tt[q] + T[q]); };
-    const int i = R.x0 + R.tx, j = R.y0 + R.ty;
-    R.march(ld, pl, [&](int z) {
-        if (i < n && j < n) {
-            double v[3][3][3] = {};
-            R.template gather<SCHEME>(pl[0], z, v);
-            const int64_t c = int64_t(z) * R.P + int64_t(j) * n + i;
-            double a[3] = {0.0, 0.0, 0.0};
-            if (ap.has)
-#pragma unroll
-                for (int e = 0; e < 3; ++e) a[e] = ap.a[e][c];
-            const double tc = T[c];
-            out[c] = tc - dt * adx_rate_at<3, SCHEME>(v, a, ap.has != 0, nu, h);
-            if (STAGE == 0) tcopy[c] = tc;
-        }
-    });
-}
-
 // Collocated momentum stage (as k_nsc_stage) on z-marching tiles: the three
 // components' stage input and the pressure in LDS rings.
 template <int SCHEME, int STAGE>
 __global__ __launch_bounds__(kZx * zrows(SCHEME)) void k_nsc_stage3z(Vel qn, Vel qt, double *__restrict__ o0,
                                                                      double *__restrict__ o1, double *__restrict__ o2,
                                                                      const double *__restrict__ p, int n, int zc,
-                                                                     double dt, double nu, double h) {
+                                                                     double dt, AdxK K) {
     typedef ZRing<4, zrows(SCHEME)> Ring;
     __shared__ typename Ring::Plane pl[4];
     Ring R(n, 1, zc);
@@ -594,13 +328,13 @@ __global__ __launch_bounds__(kZx * zrows(SCHEME)) void k_nsc_stage3z(Vel qn, Vel
                 double vp[3][3][3] = {};
                 R.template gather<SCHEME>(pl[3], z, vp);
 #pragma unroll
-                for (int comp = 0; comp < 3; ++comp) gp[comp] = adx_deriv<3, SCHEME>(vp, comp, h);
+                for (int comp = 0; comp < 3; ++comp) gp[comp] = adx_deriv<3, SCHEME>(vp, comp, K);
             }
 #pragma unroll
             for (int comp = 0; comp < 3; ++comp) {
                 double v[3][3][3] = {};
                 R.template gather<SCHEME>(pl[comp], z, v);
-                const double Rr = adx_rate_at<3, SCHEME>(v, a, true, nu, h) + gp[comp];
+                const double Rr = adx_rate_at<3, SCHEME>(v, a, true, K) + gp[comp];
                 out[comp][c] = a[comp] - dt * Rr;
             }
         }
@@ -609,8 +343,7 @@ __global__ __launch_bounds__(kZx * zrows(SCHEME)) void k_nsc_stage3z(Vel qn, Vel
 
 // rhs = scale * sum_e D_e q_e on z-marching tiles.
 template <int SCHEME>
-__global__ __launch_bounds__(kZx * 8) void k_nsc_div3z(Vel q, double *__restrict__ rhs, int n, int zc, double h,
-                                                       double scale) {
+__global__ __launch_bounds__(kZx * 8) void k_nsc_div3z(Vel q, double *__restrict__ rhs, int n, int zc, AdxK K, double scale) {
     __shared__ ZRing<3, 8>::Plane pl[3];
     ZRing<3, 8> R(n, 1, zc);
     auto ld = [&](int f, int64_t x) { return q.q[f][x]; };
@@ -622,7 +355,7 @@ __global__ __launch_bounds__(kZx * 8) void k_nsc_div3z(Vel q, double *__restrict
             for (int e = 0; e < 3; ++e) {
                 double v[3][3][3] = {};
                 R.template gather<SCHEME>(pl[e], z, v);
-                s += adx_deriv<3, SCHEME>(v, e, h);
+                s += adx_deriv<3, SCHEME>(v, e, K);
             }
             rhs[int64_t(z) * R.P + int64_t(j) * n + i] = s * scale;
         }
@@ -633,8 +366,7 @@ __global__ __launch_bounds__(kZx * 8) void k_nsc_div3z(Vel q, double *__restrict
 template <int SCHEME>
 __global__ __launch_bounds__(kZx * 8) void k_nsc_correct3z(Vel qs, double *__restrict__ o0, double *__restrict__ o1,
                                                            double *__restrict__ o2, double *__restrict__ p,
-                                                           const double *__restrict__ dp, int n, int zc, double dt,
-                                                           double h) {
+                                                           const double *__restrict__ dp, int n, int zc, double dt, AdxK K) {
     __shared__ ZRing<1, 8>::Plane pl[1];
     ZRing<1, 8> R(n, 1, zc);
     auto ld = [&](int, int64_t x) { return dp[x]; };
@@ -646,7 +378,7 @@ __global__ __launch_bounds__(kZx * 8) void k_nsc_correct3z(Vel qs, double *__res
             double v[3][3][3] = {};
             R.template gather<SCHEME>(pl[0], z, v);
 #pragma unroll
-            for (int e = 0; e < 3; ++e) out[e][c] = qs.q[e][c] - dt * adx_deriv<3, SCHEME>(v, e, h);
+            for (int e = 0; e < 3; ++e) out[e][c] = qs.q[e][c] - dt * adx_deriv<3, SCHEME>(v, e, K);
             p[c] += v[1][1][1];
         }
     });
@@ -921,8 +653,7 @@ inline unsigned zgrid(int n, int ty, int zc) {
 template <int D, int SCHEME, int STAGE>
 __global__ __launch_bounds__(kAdxX * kAdxY) void k_nsc_stage(Vel qn, Vel qt, double *__restrict__ o0,
                                                              double *__restrict__ o1, double *__restrict__ o2,
-                                                             const double *__restrict__ p, int n, double dt,
-                                                             double nu, double h) {
+                                                             const double *__restrict__ p, int n, double dt, AdxK K) {
     const int i = int(blockIdx.x) * kAdxX + int(threadIdx.x), j = int(blockIdx.y) * kAdxY + int(threadIdx.y);
     const int k = D == 3 ? int(blockIdx.z) : 0;
     if (i >= n || j >= n) return;
@@ -937,15 +668,14 @@ __global__ __launch_bounds__(kAdxX * kAdxY) void k_nsc_stage(Vel qn, Vel qt, dou
     for (int comp = 0; comp < D; ++comp) {
         double v[3][3][3] = {};
         adx_gather<D, SCHEME, STAGE == 1>(qn.q[comp], qt.q[comp], i, j, k, n, 1, v);
-        const double R = adx_rate_at<D, SCHEME>(v, a, true, nu, h) + adx_deriv<D, SCHEME>(vp, comp, h);
+        const double R = adx_rate_at<D, SCHEME>(v, a, true, K) + adx_deriv<D, SCHEME>(vp, comp, K);
         out[comp][c] = a[comp] - dt * R;
     }
 }
 
 // rhs = scale * sum_e D_e q_e (scale = -1/dt).
 template <int D, int SCHEME>
-__global__ __launch_bounds__(kAdxX * kAdxY) void k_nsc_div(Vel q, double *__restrict__ rhs, int n, double h,
-                                                           double scale) {
+__global__ __launch_bounds__(kAdxX * kAdxY) void k_nsc_div(Vel q, double *__restrict__ rhs, int n, AdxK K, double scale) {
     const int i = int(blockIdx.x) * kAdxX + int(threadIdx.x), j = int(blockIdx.y) * kAdxY + int(threadIdx.y);
     const int k = D == 3 ? int(blockIdx.z) : 0;
     if (i >= n || j >= n) return;
@@ -954,7 +684,7 @@ __global__ __launch_bounds__(kAdxX * kAdxY) void k_nsc_div(Vel q, double *__rest
     for (int e = 0; e < D; ++e) {
         double v[3][3][3] = {};
         adx_gather<D, SCHEME, false>(q.q[e], nullptr, i, j, k, n, 1, v);
-        s += adx_deriv<D, SCHEME>(v, e, h);
+        s += adx_deriv<D, SCHEME>(v, e, K);
     }
     rhs[(int64_t(k) * n + j) * n + i] = s * scale;
 }
@@ -964,7 +694,7 @@ template <int D, int SCHEME>
 __global__ __launch_bounds__(kAdxX * kAdxY) void k_nsc_correct(Vel qs, double *__restrict__ o0,
                                                                double *__restrict__ o1, double *__restrict__ o2,
                                                                double *__restrict__ p, const double *__restrict__ dp,
-                                                               int n, double dt, double h) {
+                                                               int n, double dt, AdxK K) {
     const int i = int(blockIdx.x) * kAdxX + int(threadIdx.x), j = int(blockIdx.y) * kAdxY + int(threadIdx.y);
     const int k = D == 3 ? int(blockIdx.z) : 0;
     if (i >= n || j >= n) return;
@@ -973,7 +703,7 @@ __global__ __launch_bounds__(kAdxX * kAdxY) void k_nsc_correct(Vel qs, double *_
     adx_gather<D, SCHEME, false>(dp, nullptr, i, j, k, n, 1, v);
     double *out[3] = {o0, o1, o2};
 #pragma unroll
-    for (int e = 0; e < D; ++e) out[e][c] = qs.q[e][c] - dt * adx_deriv<D, SCHEME>(v, e, h);
+    for (int e = 0; e < D; ++e) out[e][c] = qs.q[e][c] - dt * adx_deriv<D, SCHEME>(v, e, K);
     p[c] += v[1][1][1];
 }
 
@@ -1115,6 +845,7 @@ static np_status nsc_step_impl(int lg, double h, double *u, double *v, double *w
     std::lock_guard<std::mutex> lk(W->mu);
     hipStream_t s = opts ? (hipStream_t)opts->stream : nullptr;
     const int n = 1 << lg;
+    const AdxK K = adx_consts(nu, h);
     const int64_t m = int64_t(1) << (D * lg);
     double *qt[3] = {W->buf, W->buf + m, D == 3 ? W->buf + 2 * m : nullptr};
     double *qs[3] = {W->buf + D * m, W->buf + (D + 1) * m, D == 3 ? W->buf + (D + 2) * m : nullptr};
@@ -1129,20 +860,18 @@ static np_status nsc_step_impl(int lg, double h, double *u, double *v, double *w
     const unsigned nzs = zgrid(n, tys, zcs), nz3 = zgrid(n, 8, zc);
     if (zm) {
         hipLaunchKernelGGL((k_nsc_stage3z<SCHEME, 0>), dim3(nzs), dim3(kZx * tys), 0, s, qn, vt, qt[0], qt[1], qt[2],
-                           p, n, zcs, dt, nu, h);
+                           p, n, zcs, dt, K);
         NP_LAUNCH_CHECK();
         hipLaunchKernelGGL((k_nsc_stage3z<SCHEME, 1>), dim3(nzs), dim3(kZx * tys), 0, s, qn, vt, qs[0], qs[1], qs[2],
-                           p, n, zcs, dt, nu, h);
+                           p, n, zcs, dt, K);
         NP_LAUNCH_CHECK();
-        hipLaunchKernelGGL((k_nsc_div3z<SCHEME>), dim3(nz3), dim3(kZx * 8), 0, s, vs, rhs, n, zc, h, -1.0 / dt);
+        hipLaunchKernelGGL((k_nsc_div3z<SCHEME>), dim3(nz3), dim3(kZx * 8), 0, s, vs, rhs, n, zc, K, -1.0 / dt);
     } else {
-        hipLaunchKernelGGL((k_nsc_stage<D, SCHEME, 0>), grd, blk, 0, s, qn, vt, qt[0], qt[1], qt[2], p, n, dt, nu,
-                           h);
+        hipLaunchKernelGGL((k_nsc_stage<D, SCHEME, 0>), grd, blk, 0, s, qn, vt, qt[0], qt[1], qt[2], p, n, dt, K);
         NP_LAUNCH_CHECK();
-        hipLaunchKernelGGL((k_nsc_stage<D, SCHEME, 1>), grd, blk, 0, s, qn, vt, qs[0], qs[1], qs[2], p, n, dt, nu,
-                           h);
+        hipLaunchKernelGGL((k_nsc_stage<D, SCHEME, 1>), grd, blk, 0, s, qn, vt, qs[0], qs[1], qs[2], p, n, dt, K);
         NP_LAUNCH_CHECK();
-        hipLaunchKernelGGL((k_nsc_div<D, SCHEME>), grd, blk, 0, s, vs, rhs, n, h, -1.0 / dt);
+        hipLaunchKernelGGL((k_nsc_div<D, SCHEME>), grd, blk, 0, s, vs, rhs, n, K, -1.0 / dt);
     }
     NP_LAUNCH_CHECK();
     np_mg_opts o;
@@ -1156,10 +885,9 @@ static np_status nsc_step_impl(int lg, double h, double *u, double *v, double *w
     np_status st = poisson_solve(dims, h, NP_BC_PERIODIC, rhs, dp, tol, &o, stats);
     if (st == NP_EINVAL || st == NP_EHIP || st == NP_ENOMEM) return st;
     if (zm)
-        hipLaunchKernelGGL((k_nsc_correct3z<SCHEME>), dim3(nz3), dim3(kZx * 8), 0, s, vs, u, v, w, p, dp, n, zc, dt,
-                           h);
+        hipLaunchKernelGGL((k_nsc_correct3z<SCHEME>), dim3(nz3), dim3(kZx * 8), 0, s, vs, u, v, w, p, dp, n, zc, dt, K);
     else
-        hipLaunchKernelGGL((k_nsc_correct<D, SCHEME>), grd, blk, 0, s, vs, u, v, w, p, dp, n, dt, h);
+        hipLaunchKernelGGL((k_nsc_correct<D, SCHEME>), grd, blk, 0, s, vs, u, v, w, p, dp, n, dt, K);
     NP_LAUNCH_CHECK();
     NP_HIP_TRY(hipStreamSynchronize(s));
     return st;
@@ -1204,11 +932,11 @@ extern "C" np_status np_nsc_divergence(np_dims dims, double h, const double *u, 
     const dim3 blk(kAdxX, kAdxY), grd(unsigned((n + kAdxX - 1) / kAdxX), unsigned((n + kAdxY - 1) / kAdxY),
                                       dims.ndim == 3 ? unsigned(n) : 1u);
     if (dims.ndim == 2) {
-        if (scheme == 2) hipLaunchKernelGGL((k_nsc_div<2, 2>), grd, blk, 0, s, q, div, n, h, 1.0);
-        else hipLaunchKernelGGL((k_nsc_div<2, 0>), grd, blk, 0, s, q, div, n, h, 1.0);
+        if (scheme == 2) hipLaunchKernelGGL((k_nsc_div<2, 2>), grd, blk, 0, s, q, div, n, adx_consts(0.0, h), 1.0);
+        else hipLaunchKernelGGL((k_nsc_div<2, 0>), grd, blk, 0, s, q, div, n, adx_consts(0.0, h), 1.0);
     } else {
-        if (scheme == 2) hipLaunchKernelGGL((k_nsc_div<3, 2>), grd, blk, 0, s, q, div, n, h, 1.0);
-        else hipLaunchKernelGGL((k_nsc_div<3, 0>), grd, blk, 0, s, q, div, n, h, 1.0);
+        if (scheme == 2) hipLaunchKernelGGL((k_nsc_div<3, 2>), grd, blk, 0, s, q, div, n, adx_consts(0.0, h), 1.0);
+        else hipLaunchKernelGGL((k_nsc_div<3, 0>), grd, blk, 0, s, q, div, n, adx_consts(0.0, h), 1.0);
     }
     NP_LAUNCH_CHECK();
     NP_HIP_TRY(hipStreamSynchronize(s));
@@ -1241,7 +969,7 @@ extern "C" np_status ns_projection_step(np_dims dims, double h, double *u, doubl
     return ns_projection_step_io(dims, h, u, v, w, p, dt, nu, bc, tol, opts, stats, nullptr, nullptr);
 }
 
-// Two scratch fields of m cells for the explicit steps (cached per device and size).
+// Two scratch fields of m cells for the explicit steps (np_ad_explicit_step uses the first) (cached per device and size).
 static np_status ad_scratch(int64_t m, double **out) {
     int dev = 0;
     NP_HIP_TRY(hipGetDevice(&dev));
@@ -1333,55 +1061,54 @@ extern "C" np_status np_ad_explicit_step(np_dims dims, double h, double *T, cons
     const dim3 blk(kAdxX, kAdxY), grd(unsigned((n + kAdxX - 1) / kAdxX), unsigned((n + kAdxY - 1) / kAdxY),
                                       dims.ndim == 3 ? unsigned(n) : 1u);
     const int ni = int(n);
-    // predictor: scr = T~, scr + m = T^n; corrector: T = T^n - dt R((T~ + T^n)/2)
+    const AdxK K = adx_consts(nu, h);
+    // two launches of one cell per thread: scr = (T~ + T)/2, then T
 #define NP_ADX(D, S)                                                                                              \
     do {                                                                                                          \
-        hipLaunchKernelGGL((k_adx_stage<D, S, 0>), grd, blk, 0, s, T, T, scr, scr + m, ap, ni, int(bc), dt, nu,   \
-                           h);                                                                                    \
-        hipLaunchKernelGGL((k_adx_stage<D, S, 1>), grd, blk, 0, s, scr + m, scr, T, nullptr, ap, ni, int(bc), dt, \
-                           nu, h);                                                                                \
+        hipLaunchKernelGGL((k_adx_stage<D, S, 0>), grd, blk, 0, s, T, nullptr, scr, ap, ni, int(bc), dt, K);      \
+        hipLaunchKernelGGL((k_adx_stage<D, S, 1>), grd, blk, 0, s, T, scr, T, ap, ni, int(bc), dt, K);            \
     } while (0)
-    // 3D: z-marching tiles (three LDS planes) from 32^3 up
-#define NP_ADX3(S)                                                                                                \
+    const bool vec = ni % 2 == 0 && ((uintptr_t(T) | uintptr_t(ap.a[0]) | uintptr_t(ap.a[1])) & 15) == 0;
+    const int ry = step2_rows(ni), strips = (ni + kStep2Cols - 1) / kStep2Cols, chunks = (ni + ry - 1) / ry;
+    const unsigned nw2 = unsigned((int64_t(strips) * chunks * 64 + kBlock - 1) / kBlock);
+#define NP_STEP2(S)                                                                                               \
     do {                                                                                                          \
-        constexpr int ty = zrows(S);                                                                              \
-        const int zc = adx_planes(ni, ty);                                                                        \
-        const unsigned nz3 = zgrid(ni, ty, zc);                                                                   \
-        hipLaunchKernelGGL((k_adx_stage3z<S, 0>), dim3(nz3), dim3(kZx * ty), 0, s, T, T, scr, scr + m, ap, ni,    \
-                           int(bc), zc, dt, nu, h);                                                               \
-        hipLaunchKernelGGL((k_adx_stage3z<S, 1>), dim3(nz3), dim3(kZx * ty), 0, s, scr + m, scr, T, nullptr, ap,  \
-                           ni, int(bc), zc, dt, nu, h);                                                           \
+        hipLaunchKernelGGL(k_adx_shell2, dim3(blocks_for(int64_t(chunks) * 4 * n + n * strips * 4)), dim3(kBlock), \
+                           0, s, T, scr, ni, ry, strips, chunks);                                                 \
+        if (vec)                                                                                                  \
+            hipLaunchKernelGGL((k_adx_step2<S, true>), dim3(nw2), dim3(kBlock), 0, s, T, scr, ap, ni, int(bc), ry, \
+                               strips, dt, K);                                                                    \
+        else                                                                                                      \
+            hipLaunchKernelGGL((k_adx_step2<S, false>), dim3(nw2), dim3(kBlock), 0, s, T, scr, ap, ni, int(bc), ry, \
+                               strips, dt, K);                                                                    \
     } while (0)
-    // 2D: row-marching tiles from 1024^2 up (n a multiple of the strip width)
-    const int ry2 = adx_rows2(ni);
-    const unsigned nr2 = unsigned((ni / kAx2) * (ni / ry2));
-#define NP_ADX2(S)                                                                                                \
+    const int zc = step3_planes(ni);
+    const unsigned nt3 = unsigned(int64_t((ni + kSx - 1) / kSx) * ((ni + kSy - 1) / kSy) * ((ni + zc - 1) / zc));
+#define NP_STEP3(S)                                                                                               \
     do {                                                                                                          \
-        hipLaunchKernelGGL((k_adx_stage2r<S, 0>), dim3(nr2), dim3(kAx2), 0, s, T, T, scr, scr + m, ap, ni,        \
-                           int(bc), ry2, dt, nu, h);                                                              \
-        hipLaunchKernelGGL((k_adx_stage2r<S, 1>), dim3(nr2), dim3(kAx2), 0, s, scr + m, scr, T, nullptr, ap, ni,  \
-                           int(bc), ry2, dt, nu, h);                                                              \
+        hipLaunchKernelGGL(k_adx_copy, dim3(blocks_for((m + 3) / 4)), dim3(kBlock), 0, s, T, scr, m);             \
+        hipLaunchKernelGGL((k_adx_step3<S>), dim3(nt3), dim3(kSt), 0, s, scr, T, ap, ni, int(bc), zc, dt, K);     \
     } while (0)
-    if (dims.ndim == 2 && ni >= 1024 && ni % kAx2 == 0 && g_zmarch_explicit) {
-        if (scheme == 0) NP_ADX2(0);
-        else if (scheme == 1) NP_ADX2(1);
-        else NP_ADX2(2);
+    if (dims.ndim == 2 && ni >= kStep2Min && g_zmarch_explicit) {
+        if (scheme == 0) NP_STEP2(0);
+        else if (scheme == 1) NP_STEP2(1);
+        else NP_STEP2(2);
     } else if (dims.ndim == 2) {
         if (scheme == 0) NP_ADX(2, 0);
         else if (scheme == 1) NP_ADX(2, 1);
         else NP_ADX(2, 2);
-    } else if (ni >= 32 && g_zmarch_explicit) {
-        if (scheme == 0) NP_ADX3(0);
-        else if (scheme == 1) NP_ADX3(1);
-        else NP_ADX3(2);
+    } else if (ni >= step3_min(scheme) && g_zmarch_explicit) {
+        if (scheme == 0) NP_STEP3(0);
+        else if (scheme == 1) NP_STEP3(1);
+        else NP_STEP3(2);
     } else {
         if (scheme == 0) NP_ADX(3, 0);
         else if (scheme == 1) NP_ADX(3, 1);
         else NP_ADX(3, 2);
     }
 #undef NP_ADX
-#undef NP_ADX2
-#undef NP_ADX3
+#undef NP_STEP2
+#undef NP_STEP3
     NP_LAUNCH_CHECK();
     NP_HIP_TRY(hipStreamSynchronize(s));
     return NP_OK;
