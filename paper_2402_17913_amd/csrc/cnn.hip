@@ -43,11 +43,47 @@ __device__ __forceinline__ uint16_t f2b(float f) { return float_to_bf16(f); }
 __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
 // ------------------------------------------------------------------ conv
+// What a convolution writes: BF16 after ReLU (forward); FP32; BF16 where the activation `act` is
+// positive and zero elsewhere (a data gradient already masked for the layer below it, so that the
+// FP32 gradient is never stored); FP32 of channel 0 alone (the prediction).
+enum ConvOut { kOutRelu, kOutF32, kOutMask, kOutOne };
+
+// Stores output channels 4 grp .. 4 grp + 3 of voxel v.
+template <ConvOut OUT>
+__device__ __forceinline__ void conv_store(const f32x4 &acc, const float *__restrict__ bias,
+                                           const uint16_t *__restrict__ act, void *__restrict__ Y, int64_t v, int grp) {
+    float o[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float t = acc[r] + (bias ? bias[4 * grp + r] : 0.f);
+        if (OUT == kOutRelu) t = t > 0.f ? t : 0.f;
+        o[r] = t;
+    }
+    if constexpr (OUT == kOutF32) {
+        *reinterpret_cast<float4 *>(reinterpret_cast<float *>(Y) + v * kC + 4 * grp) = make_float4(o[0], o[1], o[2], o[3]);
+    } else if constexpr (OUT == kOutOne) {
+        if (grp == 0) reinterpret_cast<float *>(Y)[v] = o[0];
+    } else {
+        if constexpr (OUT == kOutMask) {
+            const uint2 a = *reinterpret_cast<const uint2 *>(act + v * kC + 4 * grp);
+            const uint32_t aw[2] = {a.x, a.y};
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (!(b2f(uint16_t(aw[r >> 1] >> (16 * (r & 1)))) > 0.f)) o[r] = 0.f;
+        }
+        uint2 pk;
+        pk.x = float2_to_bf16x2(o[0], o[1]);
+        pk.y = float2_to_bf16x2(o[2], o[3]);
+        *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(Y) + v * kC + 4 * grp) = pk;
+    }
+}
+
 // Y = conv(X, W) (+ bias, ReLU) on an n^3 periodic grid, n = 2^lg >= 16.
 // Workgroup: TXV = min(64, n) voxels along x, 4 rows along y, one plane.
-template <bool RELU, bool OUT32>
+template <ConvOut OUT>
 __global__ __launch_bounds__(256) void k_conv(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W,
-                                              const float *__restrict__ bias, void *__restrict__ Y, int lg) {
+                                              const float *__restrict__ bias, const uint16_t *__restrict__ act,
+                                              void *__restrict__ Y, int lg) {
     __shared__ uint4 xs[(64 + 2) * 6 * 3 * 2];  // halo voxels x 32 B
     __shared__ uint4 ws[kTaps * kC * 2];         // 27 x 16 rows x 32 B
     const int n = 1 << lg, txv = n < 64 ? n : 64, hx = txv + 2;
@@ -92,21 +128,7 @@ __global__ __launch_bounds__(256) void k_conv(const uint16_t *__restrict__ X, co
         // lane holds output channels 4*grp .. +3 of voxel `col`
         const int gx = x0 + tt * 16 + col, gy = y0 + w;
         const int64_t v = (((int64_t(z) << lg) + gy) << lg) + gx;
-        float o[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float t = acc[r] + (bias ? bias[4 * grp + r] : 0.f);
-            if (RELU) t = t > 0.f ? t : 0.f;
-            o[r] = t;
-        }
-        if (OUT32) {
-            *reinterpret_cast<float4 *>(reinterpret_cast<float *>(Y) + v * kC + 4 * grp) = make_float4(o[0], o[1], o[2], o[3]);
-        } else {
-            uint2 pk;
-            pk.x = float2_to_bf16x2(o[0], o[1]);
-            pk.y = float2_to_bf16x2(o[2], o[3]);
-            *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(Y) + v * kC + 4 * grp) = pk;
-        }
+        conv_store<OUT>(acc, bias, act, Y, v, grp);
     }
 }
 
@@ -131,9 +153,10 @@ __device__ __forceinline__ void cz_fill(uint4 *__restrict__ dst, const uint4 *__
     }
 }
 
-template <bool RELU, bool OUT32>
+template <ConvOut OUT>
 __global__ __launch_bounds__(kCzT) void k_conv3z(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W,
-                                                 const float *__restrict__ bias, void *__restrict__ Y, int lg, int zc) {
+                                                 const float *__restrict__ bias, const uint16_t *__restrict__ act,
+                                                 void *__restrict__ Y, int lg, int zc) {
     __shared__ uint4 xs[3][kCzSlots];
     const int n = 1 << lg, txv = n < 64 ? n : 64, hx = txv + 2;
     const int tiles_x = n / txv, tiles_y = n / kCzY;
@@ -178,22 +201,7 @@ __global__ __launch_bounds__(kCzT) void k_conv3z(const uint16_t *__restrict__ X,
             // lane holds output channels 4*grp .. +3 of voxel `col`
             const int gx = x0 + tt * 16 + col, gy = y0 + w;
             const int64_t v = (((int64_t(z) << lg) + gy) << lg) + gx;
-            float o[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float t = acc[r] + (bias ? bias[4 * grp + r] : 0.f);
-                if (RELU) t = t > 0.f ? t : 0.f;
-                o[r] = t;
-            }
-            if (OUT32) {
-                *reinterpret_cast<float4 *>(reinterpret_cast<float *>(Y) + v * kC + 4 * grp) =
-                    make_float4(o[0], o[1], o[2], o[3]);
-            } else {
-                uint2 pk;
-                pk.x = float2_to_bf16x2(o[0], o[1]);
-                pk.y = float2_to_bf16x2(o[2], o[3]);
-                *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(Y) + v * kC + 4 * grp) = pk;
-            }
+            conv_store<OUT>(acc, bias, act, Y, v, grp);
         }
         __syncthreads();  // every read of the oldest buffer is done before it takes plane z + 2
         if (z + 2 <= z0 + zc) cz_fill(xs[(z + 2) % 3], X4, plane(z + 2), tid, hx, x0, y0, lg);
@@ -356,32 +364,25 @@ __global__ __launch_bounds__(kWmT) void k_wgrad_mfma(const uint16_t *__restrict_
 }
 
 // G[i] += sum over workgroups of P[blk][i] (fixed order): a workgroup owns 32
-// consecutive entries; its 8 slices of 32 threads sum every eighth partial,
-// then the slices are added in order through LDS.
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float *__restrict__ P, int nblk, float *__restrict__ G) {
-    __shared__ float part[8][32];
+// consecutive entries; its kRedSl slices of 32 threads sum every kRedSl-th partial,
+// then the slices are added in order through LDS.  Bound by the chain of dependent
+// loads of a slice: with 8 slices (96 loads) it took 21 us, with 32 (24 loads) 8 us.
+constexpr int kRedSl = 32;
+__global__ __launch_bounds__(32 * kRedSl) void k_wgrad_reduce(const float *__restrict__ P, int nblk,
+                                                              float *__restrict__ G) {
+    __shared__ float part[kRedSl][32];
     const int li = threadIdx.x & 31, sl = threadIdx.x >> 5, i = blockIdx.x * 32 + li;
     float s = 0.f;
     if (i < kPsz)
-        for (int b = sl; b < nblk; b += 8) s += P[int64_t(b) * kPsz + i];
+        for (int b = sl; b < nblk; b += kRedSl) s += P[int64_t(b) * kPsz + i];
     part[sl][li] = s;
     __syncthreads();
     if (sl == 0 && i < kPsz) {
         float t = part[0][li];
 #pragma unroll
-        for (int q = 1; q < 8; ++q) t += part[q][li];
+        for (int q = 1; q < kRedSl; ++q) t += part[q][li];
         G[i] += t;
     }
-}
-
-// dZ = round_bf16(dY * (act > 0)) (act null: no mask).
-__global__ __launch_bounds__(256) void k_mask(const float *__restrict__ dY, const uint16_t *__restrict__ act,
-                                              uint16_t *__restrict__ dZ, int64_t m) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= m) return;
-    float g = dY[i];
-    if (act && !(b2f(act[i]) > 0.f)) g = 0.f;
-    dZ[i] = f2b(g);
 }
 
 // Flipped, transposed filter for the data gradient: Wt[26 - t][c][o] = W[t][o][c].
@@ -392,113 +393,157 @@ __global__ __launch_bounds__(256) void k_wflip(const uint16_t *__restrict__ W, u
     Wt[(26 - t) * 256 + c * 16 + o] = W[i];
 }
 
-// 2x2x2 average (n fine -> n/2), bf16.
-__global__ __launch_bounds__(256) void k_pool(const uint16_t *__restrict__ X, uint16_t *__restrict__ Y, int lgc) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    const int nc = 1 << lgc;
-    if (i >= (int64_t(kC) << (3 * lgc))) return;
-    const int ch = int(i & 15);
-    const int64_t v = i >> 4;
-    const int x = int(v & (nc - 1)), y = int((v >> lgc) & (nc - 1)), z = int(v >> (2 * lgc));
-    const int lg = lgc + 1;
-    float s = 0.f;
-    for (int dz = 0; dz < 2; ++dz)
-        for (int dy = 0; dy < 2; ++dy)
-            for (int dx = 0; dx < 2; ++dx)
-                s += b2f(X[(((((int64_t(2 * z + dz) << lg) + 2 * y + dy) << lg) + 2 * x + dx) << 4) + ch]);
-    Y[i] = f2b(s * 0.125f);
+// The elementwise kernels below are bound by memory: a thread takes eight channels of a voxel (one
+// 16-byte BF16 access), and the backward ones write BF16 gradients masked for the next layer.
+struct Ch8 {
+    float v[8];
+};
+__device__ __forceinline__ Ch8 ld8(const uint16_t *__restrict__ p) {
+    const uint4 d = *reinterpret_cast<const uint4 *>(p);
+    const uint32_t w[4] = {d.x, d.y, d.z, d.w};
+    Ch8 r;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r.v[e] = b2f(uint16_t(w[e >> 1] >> (16 * (e & 1))));
+    return r;
+}
+__device__ __forceinline__ Ch8 ld8(const float *__restrict__ p) {
+    const float4 a = reinterpret_cast<const float4 *>(p)[0], b = reinterpret_cast<const float4 *>(p)[1];
+    return Ch8{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
+}
+__device__ __forceinline__ void st8(uint16_t *__restrict__ p, const Ch8 &r) {
+    uint4 d;
+    d.x = float2_to_bf16x2(r.v[0], r.v[1]);
+    d.y = float2_to_bf16x2(r.v[2], r.v[3]);
+    d.z = float2_to_bf16x2(r.v[4], r.v[5]);
+    d.w = float2_to_bf16x2(r.v[6], r.v[7]);
+    *reinterpret_cast<uint4 *>(p) = d;
+}
+// g where the activation is positive, else zero
+__device__ __forceinline__ void mask8(Ch8 &g, const uint16_t *__restrict__ act) {
+    const Ch8 a = ld8(act);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (!(a.v[e] > 0.f)) g.v[e] = 0.f;
 }
 
-// dX(fine) += dY(coarse) / 8, FP32.
-__global__ __launch_bounds__(256) void k_pool_back(const float *__restrict__ dY, float *__restrict__ dX, int lg) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= (int64_t(kC) << (3 * lg))) return;
-    const int ch = int(i & 15);
-    const int64_t v = i >> 4;
-    const int n = 1 << lg, lgc = lg - 1;
+// 2x2x2 average (n fine -> n/2), bf16.
+__global__ __launch_bounds__(256) void k_pool(const uint16_t *__restrict__ X, uint16_t *__restrict__ Y, int lgc) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x, v = i >> 1;
+    const int nc = 1 << lgc, lg = lgc + 1, c8 = int(i & 1) * 8;
+    if (v >= (int64_t(1) << (3 * lgc))) return;
+    const int x = int(v & (nc - 1)), y = int((v >> lgc) & (nc - 1)), z = int(v >> (2 * lgc));
+    Ch8 s{};
+    for (int dz = 0; dz < 2; ++dz)
+        for (int dy = 0; dy < 2; ++dy)
+            for (int dx = 0; dx < 2; ++dx) {
+                const Ch8 t = ld8(X + (((((int64_t(2 * z + dz) << lg) + 2 * y + dy) << lg) + 2 * x + dx) << 4) + c8);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s.v[e] += t.v[e];
+            }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s.v[e] *= 0.125f;
+    st8(Y + (v << 4) + c8, s);
+}
+
+// Gradient of an encoder level's output, masked by it: dY(coarse) / 8 through the pooling plus the
+// skip's gradient K (both FP32).
+__global__ __launch_bounds__(256) void k_join_back(const float *__restrict__ dY, const float *__restrict__ K,
+                                                   const uint16_t *__restrict__ act, uint16_t *__restrict__ Z, int lg) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x, v = i >> 1;
+    const int n = 1 << lg, lgc = lg - 1, c8 = int(i & 1) * 8;
+    if (v >= (int64_t(1) << (3 * lg))) return;
     const int x = int(v & (n - 1)), y = int((v >> lg) & (n - 1)), z = int(v >> (2 * lg));
-    dX[i] += dY[(((((int64_t(z >> 1) << lgc) + (y >> 1)) << lgc) + (x >> 1)) << 4) + ch] * 0.125f;
+    const Ch8 t = ld8(dY + (((((int64_t(z >> 1) << lgc) + (y >> 1)) << lgc) + (x >> 1)) << 4) + c8);
+    Ch8 g = ld8(K + (v << 4) + c8);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) g.v[e] = t.v[e] * 0.125f + g.v[e];
+    mask8(g, act + (v << 4) + c8);
+    st8(Z + (v << 4) + c8, g);
 }
 
 // Y(fine) = up(Xc) + S, periodic cell-centred trilinear, bf16.
 __global__ __launch_bounds__(256) void k_up_add(const uint16_t *__restrict__ Xc, const uint16_t *__restrict__ S,
                                                 uint16_t *__restrict__ Y, int lg) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= (int64_t(kC) << (3 * lg))) return;
-    const int ch = int(i & 15);
-    const int64_t v = i >> 4;
-    const int n = 1 << lg, lgc = lg - 1, nc = n >> 1;
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x, v = i >> 1;
+    const int n = 1 << lg, lgc = lg - 1, nc = n >> 1, c8 = int(i & 1) * 8;
+    if (v >= (int64_t(1) << (3 * lg))) return;
     const int x = int(v & (n - 1)), y = int((v >> lg) & (n - 1)), z = int(v >> (2 * lg));
     const int ox = x >> 1, oy = y >> 1, oz = z >> 1;
     const int nx = wrapi((x & 1) ? ox + 1 : ox - 1, nc), ny = wrapi((y & 1) ? oy + 1 : oy - 1, nc),
               nz = wrapi((z & 1) ? oz + 1 : oz - 1, nc);
-    float s = 0.f;
+    Ch8 s{};
     for (int cz = 0; cz < 2; ++cz)
         for (int cy = 0; cy < 2; ++cy)
             for (int cx = 0; cx < 2; ++cx) {
                 const float wgt = (cx ? 0.25f : 0.75f) * (cy ? 0.25f : 0.75f) * (cz ? 0.25f : 0.75f);
                 const int64_t q = ((((int64_t(cz ? nz : oz) << lgc) + (cy ? ny : oy)) << lgc) + (cx ? nx : ox));
-                s += wgt * b2f(Xc[(q << 4) + ch]);
+                const Ch8 t = ld8(Xc + (q << 4) + c8);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s.v[e] += wgt * t.v[e];
             }
-    Y[i] = f2b(s + b2f(S[i]));
+    const Ch8 t = ld8(S + (v << 4) + c8);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s.v[e] = s.v[e] + t.v[e];
+    st8(Y + (v << 4) + c8, s);
 }
 
-// dXc(coarse) = up^T dY(fine): each coarse cell gathers the 4 fine cells per
+// Z(coarse) = up^T dY(fine), masked by act: each coarse cell gathers the 4 fine cells per
 // axis that reference it (weights 1/4, 3/4, 3/4, 1/4 at 2I-1 .. 2I+2).
-__global__ __launch_bounds__(256) void k_up_back(const float *__restrict__ dY, float *__restrict__ dXc, int lgc) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= (int64_t(kC) << (3 * lgc))) return;
-    const int ch = int(i & 15);
-    const int64_t v = i >> 4;
-    const int nc = 1 << lgc, lg = lgc + 1, n = nc << 1;
+__global__ __launch_bounds__(256) void k_up_back(const float *__restrict__ dY, const uint16_t *__restrict__ act,
+                                                 uint16_t *__restrict__ Zc, int lgc) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x, v = i >> 1;
+    const int nc = 1 << lgc, lg = lgc + 1, n = nc << 1, c8 = int(i & 1) * 8;
+    if (v >= (int64_t(1) << (3 * lgc))) return;
     const int X = int(v & (nc - 1)), Yc = int((v >> lgc) & (nc - 1)), Z = int(v >> (2 * lgc));
     const float w1[4] = {0.25f, 0.75f, 0.75f, 0.25f};
-    float s = 0.f;
+    Ch8 s{};
     for (int a = 0; a < 4; ++a) {
         const int fz = wrapi(2 * Z - 1 + a, n);
         for (int bb = 0; bb < 4; ++bb) {
             const int fy = wrapi(2 * Yc - 1 + bb, n);
+#pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const int fx = wrapi(2 * X - 1 + c, n);
-                s += w1[a] * w1[bb] * w1[c] * dY[(((((int64_t(fz) << lg) + fy) << lg) + fx) << 4) + ch];
+                const Ch8 t = ld8(dY + (((((int64_t(fz) << lg) + fy) << lg) + fx) << 4) + c8);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s.v[e] += w1[a] * w1[bb] * w1[c] * t.v[e];
             }
         }
     }
-    dXc[i] = s;
-}
-
-// dst += src (FP32).
-__global__ __launch_bounds__(256) void k_add(const float *__restrict__ src, float *__restrict__ dst, int64_t m) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i < m) dst[i] += src[i];
+    mask8(s, act + (v << 4) + c8);
+    st8(Zc + (v << 4) + c8, s);
 }
 
 // Input packing: channel 0 = f (FP32), others 0, bf16.
 __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ f, uint16_t *__restrict__ X, int64_t m) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= m * kC) return;
-    X[i] = (i & 15) ? uint16_t(0) : f2b(f[i >> 4]);
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x, v = i >> 1;
+    if (v >= m) return;
+    const uint32_t c0 = (i & 1) ? 0u : uint32_t(f2b(f[v]));
+    *reinterpret_cast<uint4 *>(X + i * 8) = make_uint4(c0, 0, 0, 0);
 }
 
-// Prediction = channel 0 of the FP32 output.
-__global__ __launch_bounds__(256) void k_take0(const float *__restrict__ Y, float *__restrict__ y, int64_t m) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i < m) y[i] = Y[i * kC];
-}
-
-// MSE: partials of (y - t)^2 / m per workgroup; dY[v][0] = 2 (y - t) / m, other channels 0.
-__global__ __launch_bounds__(256) void k_mse(const float *__restrict__ Y, const float *__restrict__ t,
-                                             float *__restrict__ dY, double *__restrict__ part, int64_t m) {
+// MSE of the prediction y: partials of (y - t)^2 / m per workgroup; Z[v][0] = bf16(2 (y - t) / m), the
+// other channels 0.
+__global__ __launch_bounds__(256) void k_mse(const float *__restrict__ y, const float *__restrict__ t,
+                                             uint16_t *__restrict__ Z, double *__restrict__ part, int64_t m) {
     const int64_t v = int64_t(blockIdx.x) * 256 + threadIdx.x;
     double acc = 0.0;
     if (v < m) {
-        const float d = Y[v * kC] - t[v];
+        const float d = y[v] - t[v];
         acc = double(d) * double(d) / double(m);
-        dY[v * kC] = 2.f * d / float(m);
-        for (int c = 1; c < kC; ++c) dY[v * kC + c] = 0.f;
+        uint4 *z = reinterpret_cast<uint4 *>(Z + v * kC);
+        z[0] = make_uint4(uint32_t(f2b(2.f * d / float(m))), 0, 0, 0);
+        z[1] = make_uint4(0, 0, 0, 0);
     }
     acc = block_sum(acc);
     if (threadIdx.x == 0) part[blockIdx.x] = acc;
+}
+
+// Gradient sums and loss to zero.
+__global__ __launch_bounds__(256) void k_clear(float *__restrict__ g, int64_t np, double *__restrict__ loss) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i < np) g[i] = 0.f;
+    if (i == 0) loss[0] = 0.0;
 }
 
 __global__ __launch_bounds__(256) void k_dsum(const double *__restrict__ part, int np, double *__restrict__ out) {
@@ -567,10 +612,11 @@ struct Net {
     float *w = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;  // FP32 master, Adam moments, gradient sums
     uint16_t *wb = nullptr, *wt = nullptr;                            // bf16 weights, flipped for the data gradient
     int64_t step = 0;
-    // per level: h (input), a, e (encoder); u, c, d (decoder); Z (bf16 scratch); S0, S1, K (FP32 grads)
-    std::vector<uint16_t *> h, a, e, u, c, d, Z;
-    std::vector<float *> S0, S1, K;
-    float *out = nullptr, *gout = nullptr;  // FP32 [n^3][16]
+    // per level: h (input), a, e (encoder); u, c, d (decoder); Z, Z2 (masked BF16 gradients); FP32
+    // gradients: S (of an encoder level's input, levels >= 1), K (of a decoder level's input)
+    std::vector<uint16_t *> h, a, e, u, c, d, Z, Z2;
+    std::vector<float *> S, K;
+    float *out = nullptr, *scr = nullptr;  // FP32: prediction [n^3]; scratch of two such fields
     float *wpart = nullptr;                 // weight-gradient partials
     double *lpart = nullptr, *lsum = nullptr, *hsum = nullptr;
     std::vector<void *> owned;
@@ -589,115 +635,100 @@ np_status nalloc(Net *N, void **p, size_t bytes) {
 
 int64_t vox(int lg) { return int64_t(1) << (3 * lg); }
 
-np_status conv(Net *N, int k, const uint16_t *X, void *Y, int lg, bool relu, bool out32, bool flip, hipStream_t s) {
+template <ConvOut OUT>
+np_status conv(Net *N, int k, const uint16_t *X, const uint16_t *act, void *Y, int lg, bool flip, hipStream_t s) {
     const int n = 1 << lg, txv = n < 64 ? n : 64;
-    const unsigned grid = unsigned((n / txv) * (n / 4) * n);
     const uint16_t *W = (flip ? N->wt : N->wb) + int64_t(k) * kWsz;
     const float *bias = flip ? nullptr : N->w + int64_t(k) * kPsz + kWsz;
     // z-marching tiles: n / 32 planes per workgroup at n = 64, n / 16 from n = 128 (measured best; below
     // n = 64 the one-plane form keeps more workgroups in flight and wins)
-    int zc = g_conv3z == 1 ? (n >= 128 ? n / 16 : n / 32) : (g_conv3z < n ? g_conv3z : n);
-    if (g_conv3z && zc >= 2) {
-        const int tiles = (n / txv) * (n / kCzY);
-        const unsigned g3 = unsigned(tiles * (n / zc));
-        if (relu && !out32)
-            hipLaunchKernelGGL((k_conv3z<true, false>), dim3(g3), dim3(kCzT), 0, s, X, W, bias, Y, lg, zc);
-        else if (!relu && out32)
-            hipLaunchKernelGGL((k_conv3z<false, true>), dim3(g3), dim3(kCzT), 0, s, X, W, bias, Y, lg, zc);
-        else if (!relu && !out32)
-            hipLaunchKernelGGL((k_conv3z<false, false>), dim3(g3), dim3(kCzT), 0, s, X, W, bias, Y, lg, zc);
-        else
-            hipLaunchKernelGGL((k_conv3z<true, true>), dim3(g3), dim3(kCzT), 0, s, X, W, bias, Y, lg, zc);
-        NP_LAUNCH_CHECK();
-        return NP_OK;
-    }
-    if (relu && !out32) hipLaunchKernelGGL((k_conv<true, false>), dim3(grid), dim3(256), 0, s, X, W, bias, Y, lg);
-    else if (!relu && out32) hipLaunchKernelGGL((k_conv<false, true>), dim3(grid), dim3(256), 0, s, X, W, bias, Y, lg);
-    else if (!relu && !out32) hipLaunchKernelGGL((k_conv<false, false>), dim3(grid), dim3(256), 0, s, X, W, bias, Y, lg);
-    else hipLaunchKernelGGL((k_conv<true, true>), dim3(grid), dim3(256), 0, s, X, W, bias, Y, lg);
+    const int zc = g_conv3z == 1 ? (n >= 128 ? n / 16 : n / 32) : (g_conv3z < n ? g_conv3z : n);
+    if (g_conv3z && zc >= 2)
+        hipLaunchKernelGGL((k_conv3z<OUT>), dim3(unsigned((n / txv) * (n / kCzY) * (n / zc))), dim3(kCzT), 0, s, X, W,
+                           bias, act, Y, lg, zc);
+    else
+        hipLaunchKernelGGL((k_conv<OUT>), dim3(unsigned((n / txv) * (n / 4) * n)), dim3(256), 0, s, X, W, bias, act, Y,
+                           lg);
     NP_LAUNCH_CHECK();
     return NP_OK;
 }
 
-// Backward through conv k with input `in`, post-activation `act` (null: no
-// ReLU), upstream gradient `gy` (FP32); accumulates dW, db and writes the
-// input gradient to gx (if not null).
-np_status back(Net *N, int k, const uint16_t *in, const uint16_t *act, const float *gy, float *gx, int l,
-               hipStream_t s) {
+// Weight and bias gradients of conv k with input `in` from its masked output gradient z (level l).
+np_status wgrad(Net *N, int k, const uint16_t *in, const uint16_t *z, int l, hipStream_t s) {
     const int lg = N->lg0 - l;
-    const int64_t m = vox(lg) * kC;
-    hipLaunchKernelGGL(k_mask, dim3(nb(m)), dim3(256), 0, s, gy, act, N->Z[l], m);
-    NP_LAUNCH_CHECK();
     const int n = 1 << lg, txv = n < 64 ? n : 64, ntile = (n / txv) * (n / 4) * n;
     const int nblk = ntile < kWgBlocks ? ntile : kWgBlocks;
-    if (g_wgrad_mfma) hipLaunchKernelGGL(k_wgrad_mfma, dim3(nblk), dim3(kWmT), 0, s, in, N->Z[l], N->wpart, lg);
-    else hipLaunchKernelGGL(k_wgrad, dim3(nblk), dim3(256), 0, s, in, N->Z[l], N->wpart, lg);
+    if (g_wgrad_mfma) hipLaunchKernelGGL(k_wgrad_mfma, dim3(nblk), dim3(kWmT), 0, s, in, z, N->wpart, lg);
+    else hipLaunchKernelGGL(k_wgrad, dim3(nblk), dim3(256), 0, s, in, z, N->wpart, lg);
     NP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(unsigned((kPsz + 31) / 32)), dim3(256), 0, s, N->wpart, nblk,
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(unsigned((kPsz + 31) / 32)), dim3(32 * kRedSl), 0, s, N->wpart, nblk,
                        N->g + int64_t(k) * kPsz);
     NP_LAUNCH_CHECK();
-    if (gx) NP_TRY(conv(N, k, N->Z[l], gx, lg, false, true, true, s));
     return NP_OK;
 }
 
-// Forward: f (FP32, n^3) -> out [n^3][16] FP32 (channel 0 = prediction).
-np_status forward(Net *N, const float *f, hipStream_t s) {
+// Forward: f (FP32, n^3) -> prediction (FP32, n^3).
+np_status forward(Net *N, const float *f, float *pred, hipStream_t s) {
     const int L = N->levels;
     const int64_t m0 = vox(N->lg0);
-    hipLaunchKernelGGL(k_pack, dim3(nb(m0 * kC)), dim3(256), 0, s, f, N->h[0], m0);
+    hipLaunchKernelGGL(k_pack, dim3(nb(m0 * 2)), dim3(256), 0, s, f, N->h[0], m0);
     NP_LAUNCH_CHECK();
     int k = 0;
     for (int l = 0; l < L; ++l) {
         const int lg = N->lg0 - l;
         if (l > 0) {
-            hipLaunchKernelGGL(k_pool, dim3(nb(vox(lg) * kC)), dim3(256), 0, s, N->e[l - 1], N->h[l], lg);
+            hipLaunchKernelGGL(k_pool, dim3(nb(vox(lg) * 2)), dim3(256), 0, s, N->e[l - 1], N->h[l], lg);
             NP_LAUNCH_CHECK();
         }
-        NP_TRY(conv(N, k++, N->h[l], N->a[l], lg, true, false, false, s));
-        NP_TRY(conv(N, k++, N->a[l], N->e[l], lg, true, false, false, s));
+        NP_TRY(conv<kOutRelu>(N, k++, N->h[l], nullptr, N->a[l], lg, false, s));
+        NP_TRY(conv<kOutRelu>(N, k++, N->a[l], nullptr, N->e[l], lg, false, s));
     }
     const uint16_t *dn = N->e[L - 1];
     for (int l = L - 2; l >= 0; --l) {
         const int lg = N->lg0 - l;
-        hipLaunchKernelGGL(k_up_add, dim3(nb(vox(lg) * kC)), dim3(256), 0, s, dn, N->e[l], N->u[l], lg);
+        hipLaunchKernelGGL(k_up_add, dim3(nb(vox(lg) * 2)), dim3(256), 0, s, dn, N->e[l], N->u[l], lg);
         NP_LAUNCH_CHECK();
-        NP_TRY(conv(N, k++, N->u[l], N->c[l], lg, true, false, false, s));
-        NP_TRY(conv(N, k++, N->c[l], N->d[l], lg, true, false, false, s));
+        NP_TRY(conv<kOutRelu>(N, k++, N->u[l], nullptr, N->c[l], lg, false, s));
+        NP_TRY(conv<kOutRelu>(N, k++, N->c[l], nullptr, N->d[l], lg, false, s));
         dn = N->d[l];
     }
-    NP_TRY(conv(N, k, dn, N->out, N->lg0, false, true, false, s));
+    NP_TRY(conv<kOutOne>(N, k, dn, nullptr, pred, N->lg0, false, s));
     return NP_OK;
 }
 
-// Backward from N->gout (gradient wrt out); gradient sums accumulate in N->g.
+// Backward from Z[0] (the prediction's gradient, BF16, channel 0); gradient sums accumulate in N->g.
+// Every layer's output gradient is masked by its activation where it is formed, alternating between Z
+// and Z2 of a level; FP32 gradients are stored only where two are added (K) or crossed by a transfer.
+// Two samples of 128^3 with four levels: 5.22 ms with FP32 gradients everywhere, separate mask, add and
+// clearing passes and 16-channel FP32 predictions, 3.51 ms so.
 np_status backward(Net *N, hipStream_t s) {
     const int L = N->levels;
-    const int kout = N->nconv - 1;
     const uint16_t *dtop = L >= 2 ? N->d[0] : N->e[0];
-    NP_TRY(back(N, kout, dtop, nullptr, N->gout, N->S0[0], 0, s));
-    // decoder levels 0 .. L-2 (conv indices 2L + 2 (L-2-l) .. +1)
+    NP_TRY(wgrad(N, N->nconv - 1, dtop, N->Z[0], 0, s));
+    NP_TRY(conv<kOutMask>(N, N->nconv - 1, N->Z[0], dtop, N->Z2[0], N->lg0, true, s));
+    // decoder levels 0 .. L-2 (conv indices 2L + 2 (L-2-l) .. +1), entered with the gradient in Z2
     for (int l = 0; l <= L - 2; ++l) {
-        const int k1 = 2 * L + 2 * (L - 2 - l), k2 = k1 + 1;
-        NP_TRY(back(N, k2, N->c[l], N->d[l], N->S0[l], N->S1[l], l, s));
-        NP_TRY(back(N, k1, N->u[l], N->c[l], N->S1[l], N->K[l], l, s));
-        const int lgc = N->lg0 - l - 1;
-        hipLaunchKernelGGL(k_up_back, dim3(nb(vox(lgc) * kC)), dim3(256), 0, s, N->K[l], N->S0[l + 1], lgc);
+        const int k1 = 2 * L + 2 * (L - 2 - l), k2 = k1 + 1, lg = N->lg0 - l;
+        NP_TRY(wgrad(N, k2, N->c[l], N->Z2[l], l, s));
+        NP_TRY(conv<kOutMask>(N, k2, N->Z2[l], N->c[l], N->Z[l], lg, true, s));
+        NP_TRY(wgrad(N, k1, N->u[l], N->Z[l], l, s));
+        NP_TRY(conv<kOutF32>(N, k1, N->Z[l], nullptr, N->K[l], lg, true, s));
+        hipLaunchKernelGGL(k_up_back, dim3(nb(vox(lg - 1) * 2)), dim3(256), 0, s, N->K[l],
+                           l + 1 <= L - 2 ? N->d[l + 1] : N->e[L - 1], N->Z2[l + 1], lg - 1);
         NP_LAUNCH_CHECK();
     }
+    // encoder levels L-1 .. 0, likewise
     for (int l = L - 1; l >= 0; --l) {
         const int lg = N->lg0 - l;
-        const int64_t m = vox(lg) * kC;
         if (l < L - 1) {
-            hipLaunchKernelGGL(k_add, dim3(nb(m)), dim3(256), 0, s, N->K[l], N->S0[l], m);
+            hipLaunchKernelGGL(k_join_back, dim3(nb(vox(lg) * 2)), dim3(256), 0, s, N->S[l + 1], N->K[l], N->e[l],
+                               N->Z2[l], lg);
             NP_LAUNCH_CHECK();
         }
-        NP_TRY(back(N, 2 * l + 1, N->a[l], N->e[l], N->S0[l], N->S1[l], l, s));
-        NP_TRY(back(N, 2 * l, N->h[l], N->a[l], N->S1[l], l > 0 ? N->S0[l] : nullptr, l, s));
-        if (l > 0) {
-            NP_HIP_TRY(hipMemsetAsync(N->S0[l - 1], 0, sizeof(float) * vox(lg + 1) * kC, s));
-            hipLaunchKernelGGL(k_pool_back, dim3(nb(vox(lg + 1) * kC)), dim3(256), 0, s, N->S0[l], N->S0[l - 1], lg + 1);
-            NP_LAUNCH_CHECK();
-        }
+        NP_TRY(wgrad(N, 2 * l + 1, N->a[l], N->Z2[l], l, s));
+        NP_TRY(conv<kOutMask>(N, 2 * l + 1, N->Z2[l], N->a[l], N->Z[l], lg, true, s));
+        NP_TRY(wgrad(N, 2 * l, N->h[l], N->Z[l], l, s));
+        if (l > 0) NP_TRY(conv<kOutF32>(N, 2 * l, N->Z[l], nullptr, N->S[l], lg, true, s));
     }
     return NP_OK;
 }
@@ -715,7 +746,7 @@ np_status refresh(Net *N, hipStream_t s) {
 
 np_status loss_grad(Net *N, const float *target, hipStream_t s) {
     const int64_t m = vox(N->lg0);
-    hipLaunchKernelGGL(k_mse, dim3(nb(m)), dim3(256), 0, s, N->out, target, N->gout, N->lpart, m);
+    hipLaunchKernelGGL(k_mse, dim3(nb(m)), dim3(256), 0, s, N->out, target, N->Z[0], N->lpart, m);
     NP_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_dsum, dim3(1), dim3(256), 0, s, N->lpart, int(nb(m)), N->lsum);
     NP_LAUNCH_CHECK();
@@ -767,12 +798,10 @@ np_status cnn_warm_start(int d, int lg, int bc, const double *f, double *x0, con
     NP_HIP_TRY(hipStreamSynchronize(s));
     const double rms = std::sqrt(N->hsum[0] / double(mc));
     if (!(rms > 0.0) || !std::isfinite(rms)) return NP_OK;
-    float *in = N->S1[0], *pred = N->S1[0] + mc;  // FP32 scratch (the gradient buffers are idle)
+    float *in = N->scr, *pred = N->scr + mc;
     hipLaunchKernelGGL(k_to32, dim3(nb(mc)), dim3(256), 0, s, src, in, 1.0 / rms, mc);
     NP_LAUNCH_CHECK();
-    NP_TRY(forward(N, in, s));
-    hipLaunchKernelGGL(k_take0, dim3(nb(mc)), dim3(256), 0, s, N->out, pred, mc);
-    NP_LAUNCH_CHECK();
+    NP_TRY(forward(N, in, pred, s));
     double *xc = ell > 0 ? (double *)xl[ell] : x0;
     hipLaunchKernelGGL(k_to64, dim3(nb(mc)), dim3(256), 0, s, pred, xc, rms, mc);
     NP_LAUNCH_CHECK();
@@ -819,12 +848,10 @@ np_status cnn_coarse_guess(int lg, const double *fc, double *xc, hipStream_t s, 
     NP_HIP_TRY(hipStreamSynchronize(s));
     const double rms = std::sqrt(N->hsum[0] / double(mc));
     if (!(rms > 0.0) || !std::isfinite(rms)) return NP_OK;
-    float *in = N->S1[0], *pred = N->S1[0] + mc;  // FP32 scratch (the gradient buffers are idle)
+    float *in = N->scr, *pred = N->scr + mc;
     hipLaunchKernelGGL(k_to32, dim3(nb(mc)), dim3(256), 0, s, fc, in, 1.0 / rms, mc);
     NP_LAUNCH_CHECK();
-    NP_TRY(forward(N, in, s));
-    hipLaunchKernelGGL(k_take0, dim3(nb(mc)), dim3(256), 0, s, N->out, pred, mc);
-    NP_LAUNCH_CHECK();
+    NP_TRY(forward(N, in, pred, s));
     hipLaunchKernelGGL(k_to64, dim3(nb(mc)), dim3(256), 0, s, pred, xc, rms, mc);
     NP_LAUNCH_CHECK();
     *used = true;
@@ -861,16 +888,16 @@ extern "C" np_status np_cnn_create(int n_in, int levels, np_cnn **out) {
     A((void **)&N->g, sizeof(float) * N->npar);
     A((void **)&N->wb, sizeof(uint16_t) * N->nconv * kWsz);
     A((void **)&N->wt, sizeof(uint16_t) * N->nconv * kWsz);
-    N->h.assign(levels, nullptr); N->a = N->h; N->e = N->h; N->u = N->h; N->c = N->h; N->d = N->h; N->Z = N->h;
-    N->S0.assign(levels, nullptr); N->S1 = N->S0; N->K = N->S0;
+    N->h.assign(levels, nullptr); N->a = N->h; N->e = N->h; N->u = N->h; N->c = N->h; N->d = N->h; N->Z = N->h; N->Z2 = N->h;
+    N->S.assign(levels, nullptr); N->K = N->S;
     for (int l = 0; l < levels; ++l) {
         const size_t mb = size_t(vox(N->lg0 - l)) * kC;
         A((void **)&N->h[l], 2 * mb);
         A((void **)&N->a[l], 2 * mb);
         A((void **)&N->e[l], 2 * mb);
         A((void **)&N->Z[l], 2 * mb);
-        A((void **)&N->S0[l], 4 * mb);
-        A((void **)&N->S1[l], 4 * mb);
+        A((void **)&N->Z2[l], 2 * mb);
+        if (l > 0) A((void **)&N->S[l], 4 * mb);
         if (l < levels - 1) {
             A((void **)&N->u[l], 2 * mb);
             A((void **)&N->c[l], 2 * mb);
@@ -879,8 +906,8 @@ extern "C" np_status np_cnn_create(int n_in, int levels, np_cnn **out) {
         }
     }
     const size_t m0 = size_t(vox(N->lg0));
-    A((void **)&N->out, 4 * m0 * kC);
-    A((void **)&N->gout, 4 * m0 * kC);
+    A((void **)&N->out, 4 * m0);
+    A((void **)&N->scr, 4 * 2 * m0);
     A((void **)&N->wpart, sizeof(float) * kWgBlocks * kPsz);
     A((void **)&N->lpart, sizeof(double) * std::max<size_t>(kRedBlocks, (m0 + 255) / 256));
     A((void **)&N->lsum, sizeof(double));
@@ -944,9 +971,7 @@ extern "C" np_status np_cnn_forward(np_cnn *net, const float *in, float *out, vo
     Net *N = net->net;
     std::lock_guard<std::mutex> lk(N->mu);
     hipStream_t s = (hipStream_t)stream;
-    NP_TRY(forward(N, in, s));
-    hipLaunchKernelGGL(k_take0, dim3(nb(vox(N->lg0))), dim3(256), 0, s, N->out, out, vox(N->lg0));
-    NP_LAUNCH_CHECK();
+    NP_TRY(forward(N, in, out, s));
     NP_HIP_TRY(hipStreamSynchronize(s));
     return NP_OK;
 }
@@ -956,10 +981,10 @@ extern "C" np_status np_cnn_forward(np_cnn *net, const float *in, float *out, vo
 // pairs' MSE.
 static np_status grads_for(Net *N, int batch, const float *const *in, const float *const *target, double *loss,
                            hipStream_t s) {
-    NP_HIP_TRY(hipMemsetAsync(N->g, 0, sizeof(float) * N->npar, s));
-    NP_HIP_TRY(hipMemsetAsync(N->lsum, 0, sizeof(double), s));
+    hipLaunchKernelGGL(k_clear, dim3(nb(N->npar)), dim3(256), 0, s, N->g, N->npar, N->lsum);
+    NP_LAUNCH_CHECK();
     for (int b = 0; b < batch; ++b) {
-        NP_TRY(forward(N, in[b], s));
+        NP_TRY(forward(N, in[b], N->out, s));
         NP_TRY(loss_grad(N, target[b], s));
         NP_TRY(backward(N, s));
     }
