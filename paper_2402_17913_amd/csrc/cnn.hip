@@ -260,106 +260,162 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t *__restrict__ X, c
     if (c == 0) Pb[kWsz + o] = bacc;
 }
 
-// The same partials on the matrix cores: per tap t, dW_t[o][c] = sum over
-// voxels v of dZ[v][o] X[v + t][c] is a 16 x 16 product with the voxels as the
-// contraction (v_mfma_f32_16x16x32_bf16, 32 voxels per step).  Both tiles are
-// staged channel-major in LDS, so a lane's operand (8 consecutive voxels of one
-// channel) is one 16-byte read for dZ and, for X shifted by the tap's dx, two
-// aligned 16-byte reads funnel-shifted by 0, 2 or 4 bytes (rows padded to a
-// multiple of 8 voxels).  The three taps of a (dz, dy) group read one X row and
-// differ by the shift; wave w owns groups w, w + 4 (and 8 for wave 0), so no
-// partial crosses waves; the bias gradient is one more product with X = 1.
-constexpr int kWmT = 256;
+// The same partials on the matrix cores: per tap t, dW_t[o][c] = sum over voxels v of dZ[v][o] X[v + t][c]
+// is a 16 x 16 product with the voxels as the contraction (v_mfma_f32_16x16x32_bf16, 32 voxels per step);
+// the bias gradient is one more product with X = 1.  A workgroup marches through a chunk of planes of a
+// column of TXV x 4 voxels: a ring of four X planes with their halo and two dZ planes lie in LDS, three and
+// one of them in use while the next of each arrives through registers, so that a plane costs one barrier.  Both are staged channel-major, two voxels of a
+// channel per dword, so that a lane's operand (8 consecutive voxels of one channel) is one 16-byte read for
+// dZ and, for X, one 16-byte and one 4-byte read that serve the three taps of a (dz, dy) row, funnel-shifted
+// by 0, 2 or 4 bytes.  The channel pitches put the 16 channels of a read on different banks.  A wave owns
+// every fourth step of 32 voxels and all 28 products, and the waves' sums are added in order at the end.
+// At 128^3 it takes 54 us, against 125 us when every plane of a tile staged
+// a three-plane halo of its own with 2-byte LDS writes and each wave read all of dZ for its share of the taps.
+// The two operands read once would take 28 us; what is left is one barrier and a full load latency per plane
+// at two workgroups per CU, which the 28 accumulators of a lane allow.
+constexpr int kWmT = 256, kWmAim = 512;
+constexpr int kWmRow = 72;                    // halo row of up to 66 voxels, a multiple of 8
+constexpr int kWmCh = 4 * 6 * kWmRow + 8;     // channel pitch of X (868 dwords: 36 modulo the 64 banks)
+constexpr int kWmZCh = 64 * 4 + 8;            // channel pitch of dZ (132 dwords: 4 modulo 64)
 
 __device__ __forceinline__ uint32_t wm_shift(uint32_t lo, uint32_t hi, int bytes) {
     return bytes == 0 ? lo : __builtin_amdgcn_alignbyte(hi, lo, bytes);
 }
 
+// Eight channels of two neighbouring voxels a, b to the channel-major rows dst, dst + pitch, ... (dwords)
+__device__ __forceinline__ void wm_put(uint32_t *dst, int pitch, const uint4 &a, const uint4 &b) {
+    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        dst[e * pitch] = __builtin_amdgcn_perm(bw[e >> 1], aw[e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+}
+
 __global__ __launch_bounds__(kWmT) void k_wgrad_mfma(const uint16_t *__restrict__ X, const uint16_t *__restrict__ dZ,
-                                                     float *__restrict__ P, int lg) {
-    constexpr int HXP = 72;  // padded halo row (txv + 2 <= 66 voxels), a multiple of 8
-    __shared__ __align__(16) uint16_t xt[kC * 3 * 6 * HXP];   // [c][plane][row][x]
-    __shared__ __align__(16) uint16_t zt[kC * 64 * 4];        // [o][voxel of the tile]
-    const int n = 1 << lg, txv = n < 64 ? n : 64, hx = txv + 2;
-    const int tiles_x = n / txv, ntile = tiles_x * (n / 4) * n;
+                                                     float *__restrict__ P, int lg, int nch) {
+    __shared__ __align__(16) uint16_t xt[kC * kWmCh];   // [c][ring slot][row][x]
+    __shared__ __align__(16) uint16_t zt[2][kC * kWmZCh];  // [plane & 1][o][voxel]
+    static_assert(sizeof(xt) >= 4 * 7 * 256 * sizeof(float), "the sum over waves takes the place of X");
+    const int n = 1 << lg, lt = lg < 6 ? lg : 6, txv = 1 << lt, hp = (txv + 2) / 2;
+    const int tiles_x = n / txv, ncol = tiles_x * (n / 4);
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int ch = l & 15, g = l >> 4;  // operand channel (o for dZ, c for X); voxel run within 32
-    f32x4 acc[9];
-#pragma unroll
-    for (int u = 0; u < 9; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint16_t one = 0x3f80;  // bf16 1.0
-    const uint4 ones = make_uint4(one | (uint32_t(one) << 16), one | (uint32_t(one) << 16),
-                                  one | (uint32_t(one) << 16), one | (uint32_t(one) << 16));
     const uint4 *X4 = reinterpret_cast<const uint4 *>(X), *Z4 = reinterpret_cast<const uint4 *>(dZ);
-    for (int b = blockIdx.x; b < ntile; b += gridDim.x) {
-        const int tx = b % tiles_x, y4 = (b / tiles_x) % (n / 4), z = b / (tiles_x * (n / 4));
-        const int x0 = tx * txv, y0 = 4 * y4;
-        __syncthreads();  // the previous tile's operands are read
-        // X halo tile (3 planes x 6 rows x hx voxels), transposed to channel-major
-        for (int q = tid; q < hx * 6 * 3 * 2; q += kWmT) {
-            const int v = q >> 1, half = q & 1;
-            const int lx = v % hx, ly = (v / hx) % 6, lz = v / (hx * 6);
-            const uint4 d = X4[((((int64_t(wrapi(z + lz - 1, n)) << lg) + wrapi(y0 + ly - 1, n)) << lg) +
-                                wrapi(x0 + lx - 1, n)) * 2 + half];
-            const uint32_t dw[4] = {d.x, d.y, d.z, d.w};
+    uint32_t *xd = reinterpret_cast<uint32_t *>(xt);
+    f32x4 acc[kTaps + 1];
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                xt[(((8 * half + e) * 3 + lz) * 6 + ly) * HXP + lx] = uint16_t(dw[e >> 1] >> (16 * (e & 1)));
+    for (int u = 0; u <= kTaps; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint32_t one2 = 0x3f803f80u;  // two BF16 ones
+    const uint4 ones = make_uint4(one2, one2, one2, one2);
+    // this thread's staging slots: pairs of voxels x half a voxel's channels
+    const int nxs = hp * 6 * 2, nzs = txv * 4;
+    int xs[2], xl[2], zl = 0;  // offset of a slot's pair in a row and its place in LDS
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int q = tid + u * kWmT, v = q >> 1;
+        xs[u] = v % hp;
+        xl[u] = 8 * (q & 1) * (kWmCh / 2) + (v / hp) * (kWmRow / 2) + v % hp;
+    }
+    const int zp = (tid >> 1) & (txv / 2 - 1), zy = (tid >> 1) >> (lt - 1);
+    zl = 8 * (tid & 1) * (kWmZCh / 2) + zy * (txv / 2) + zp;
+    for (int b = blockIdx.x; b < ncol * nch; b += gridDim.x) {
+        const int col = b % ncol, x0 = (col % tiles_x) * txv, y0 = (col / tiles_x) * 4;
+        const int z0 = int(int64_t(n) * (b / ncol) / nch), z1 = int(int64_t(n) * (b / ncol + 1) / nch);
+        int64_t xa[2], xb[2], za = 0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int q = tid + u * kWmT, row = wrapi(y0 + (q >> 1) / hp - 1, n), gx = x0 + 2 * xs[u];
+            xa[u] = ((int64_t(row) << lg) + wrapi(gx - 1, n)) * 2 + (q & 1);
+            xb[u] = ((int64_t(row) << lg) + wrapi(gx, n)) * 2 + (q & 1);
         }
-        // dZ tile (4 rows x txv voxels), transposed
-        for (int q = tid; q < txv * 4 * 2; q += kWmT) {
-            const int v = q >> 1, half = q & 1;
-            const int lx = v % txv, ly = v / txv;
-            const uint4 d = Z4[((((int64_t(z) << lg) + y0 + ly) << lg) + x0 + lx) * 2 + half];
-            const uint32_t dw[4] = {d.x, d.y, d.z, d.w};
+        za = ((int64_t(y0 + zy) << lg) + x0 + 2 * zp) * 2 + (tid & 1);
+        uint4 xv[2][2], zv[2];
+        auto fetch_x = [&](int z) {
+            const uint4 *p = X4 + (int64_t(wrapi(z, n)) << (2 * lg + 1));
 #pragma unroll
-            for (int e = 0; e < 8; ++e) zt[(8 * half + e) * 256 + v] = uint16_t(dw[e >> 1] >> (16 * (e & 1)));
-        }
-        __syncthreads();
-        for (int kb = 0; kb < txv * 4 / 32; ++kb) {
-            const int v0 = kb * 32 + 8 * g, ly = v0 / txv, lx0 = v0 % txv;  // 8 voxels of one row
-            const uint4 a4 = *reinterpret_cast<const uint4 *>(&zt[ch * 256 + v0]);
-            const bf16x8 av = __builtin_bit_cast(bf16x8, a4);
-#pragma unroll
-            for (int jg = 0; jg < 3; ++jg) {
-                const int G = w + 4 * jg;  // tap group (dz, dy): its three taps share one X row
-                if (G < 9) {
-                    const int dz = G / 3 - 1, dy = G % 3 - 1;
-                    const uint16_t *row = &xt[((ch * 3 + 1 + dz) * 6 + (ly + 1 + dy)) * HXP + lx0];
-                    const uint4 lo = *reinterpret_cast<const uint4 *>(row);
-                    const uint4 hi = *reinterpret_cast<const uint4 *>(row + 8);
-                    const uint32_t d[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-                    for (int s0 = 0; s0 < 3; ++s0) {  // dx = s0 - 1: the run starts s0 voxels in
-                        const int wsh = s0 >> 1, bsh = 2 * (s0 & 1);
-                        uint4 b4;
-                        b4.x = wm_shift(d[wsh + 0], d[wsh + 1], bsh);
-                        b4.y = wm_shift(d[wsh + 1], d[wsh + 2], bsh);
-                        b4.z = wm_shift(d[wsh + 2], d[wsh + 3], bsh);
-                        b4.w = wm_shift(d[wsh + 3], d[wsh + 4], bsh);
-                        acc[3 * jg + s0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            av, __builtin_bit_cast(bf16x8, b4), acc[3 * jg + s0], 0, 0, 0);
-                    }
-                } else if (jg == 2 && w == 3) {
-                    // wave 3's spare slot: the bias gradient, sum over voxels of dZ[v][o]
-                    acc[6] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, ones), acc[6],
-                                                                     0, 0, 0);
+            for (int u = 0; u < 2; ++u)
+                if (tid + u * kWmT < nxs) {
+                    xv[u][0] = p[xa[u]];
+                    xv[u][1] = p[xb[u]];
                 }
+        };
+        auto store_x = [&](int slot) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (tid + u * kWmT < nxs) wm_put(xd + xl[u] + slot * (6 * kWmRow / 2), kWmCh / 2, xv[u][0], xv[u][1]);
+        };
+        auto fetch_z = [&](int z) {
+            if (tid < nzs) {
+                const uint4 *p = Z4 + (int64_t(z) << (2 * lg + 1)) + za;
+                zv[0] = p[0];
+                zv[1] = p[2];
+            }
+        };
+        auto store_z = [&](int z) {
+            if (tid < nzs) wm_put(reinterpret_cast<uint32_t *>(zt[z & 1]) + zl, kWmZCh / 2, zv[0], zv[1]);
+        };
+        __syncthreads();  // the previous column's operands are read
+        fetch_z(z0);
+        fetch_x(z0 - 1);
+        store_x((z0 - 1) & 3);
+        fetch_x(z0);
+        store_x(z0 & 3);
+        fetch_x(z0 + 1);
+        store_x((z0 + 1) & 3);
+        store_z(z0);
+        for (int z = z0; z < z1; ++z) {
+            __syncthreads();  // planes z - 1 .. z + 1 and dZ's z are in LDS; z - 2 and dZ's z - 1 are read
+            if (z + 1 < z1) {
+                fetch_x(z + 2);
+                fetch_z(z + 1);
+            }
+            for (int kb = w; kb < txv * 4 / 32; kb += 4) {
+                const int v0 = kb * 32 + 8 * g, ly = v0 >> lt, lx0 = v0 & (txv - 1);  // 8 voxels of one row
+                const bf16x8 av =
+                    __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(&zt[z & 1][ch * kWmZCh + v0]));
+#pragma unroll
+                for (int G = 0; G < 9; ++G) {  // (dz, dy): its three taps share one X row
+                    const uint16_t *row = &xt[ch * kWmCh + (((z + G / 3 - 1) & 3) * 6 + ly + G % 3) * kWmRow + lx0];
+                    const uint4 lo = *reinterpret_cast<const uint4 *>(row);
+                    const uint32_t d[5] = {lo.x, lo.y, lo.z, lo.w, *reinterpret_cast<const uint32_t *>(row + 8)};
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) {  // dx = t - 1: the run starts t voxels in
+                        const int wsh = t >> 1, bsh = 2 * (t & 1);
+                        uint4 b4;
+                        b4.x = wm_shift(d[wsh + 0], d[bsh ? 1 : wsh], bsh);
+                        b4.y = wm_shift(d[wsh + 1], d[bsh ? 2 : wsh + 1], bsh);
+                        b4.z = wm_shift(d[wsh + 2], d[bsh ? 3 : wsh + 2], bsh);
+                        b4.w = wm_shift(d[wsh + 3], d[bsh ? 4 : wsh + 3], bsh);
+                        acc[3 * G + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, b4),
+                                                                                 acc[3 * G + t], 0, 0, 0);
+                    }
+                }
+                acc[kTaps] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, ones), acc[kTaps], 0,
+                                                                     0, 0);
+            }
+            if (z + 1 < z1) {
+                store_x((z + 2) & 3);
+                store_z(z + 1);
             }
         }
     }
-    // lane holds C[o = 4 g + r][c = ch] of each of its products
-    float *Pb = P + int64_t(blockIdx.x) * kPsz;
+    // lane holds C[o = 4 g + r][c = ch] of each product; the waves' sums are added in order, seven products
+    // at a time
+    float *sum = reinterpret_cast<float *>(xt), *Pb = P + int64_t(blockIdx.x) * kPsz;
 #pragma unroll
-    for (int jg = 0; jg < 3; ++jg) {
-        const int G = w + 4 * jg;
+    for (int t0 = 0; t0 <= kTaps; t0 += 7) {
+        __syncthreads();
 #pragma unroll
-        for (int s0 = 0; s0 < 3; ++s0)
+        for (int t = 0; t < 7; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (G < 9) Pb[(3 * G + s0) * 256 + (4 * g + r) * 16 + ch] = acc[3 * jg + s0][r];
-                else if (jg == 2 && w == 3 && s0 == 0 && ch == 0) Pb[kWsz + 4 * g + r] = acc[6][r];
-            }
+            for (int r = 0; r < 4; ++r) sum[(w * 7 + t) * 256 + (4 * g + r) * 16 + ch] = acc[t0 + t][r];
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 7; ++t) {
+            const float v = ((sum[t * 256 + tid] + sum[(7 + t) * 256 + tid]) + sum[(14 + t) * 256 + tid]) +
+                            sum[(21 + t) * 256 + tid];
+            if (t0 + t < kTaps) Pb[(t0 + t) * 256 + tid] = v;
+            else if ((tid & 15) == 0) Pb[kWsz + (tid >> 4)] = v;
+        }
     }
 }
 
@@ -657,9 +713,15 @@ np_status conv(Net *N, int k, const uint16_t *X, const uint16_t *act, void *Y, i
 np_status wgrad(Net *N, int k, const uint16_t *in, const uint16_t *z, int l, hipStream_t s) {
     const int lg = N->lg0 - l;
     const int n = 1 << lg, txv = n < 64 ? n : 64, ntile = (n / txv) * (n / 4) * n;
-    const int nblk = ntile < kWgBlocks ? ntile : kWgBlocks;
-    if (g_wgrad_mfma) hipLaunchKernelGGL(k_wgrad_mfma, dim3(nblk), dim3(kWmT), 0, s, in, z, N->wpart, lg);
-    else hipLaunchKernelGGL(k_wgrad, dim3(nblk), dim3(256), 0, s, in, z, N->wpart, lg);
+    int nblk = ntile < kWgBlocks ? ntile : kWgBlocks;
+    if (g_wgrad_mfma) {
+        // chunks of planes per column, so that kWmAim workgroups (two per CU) run where there are as many tiles
+        const int ncol = ntile / n, nch = std::min(n, std::max(1, kWmAim / ncol));
+        nblk = std::min(ncol * nch, kWgBlocks);
+        hipLaunchKernelGGL(k_wgrad_mfma, dim3(nblk), dim3(kWmT), 0, s, in, z, N->wpart, lg, nch);
+    } else {
+        hipLaunchKernelGGL(k_wgrad, dim3(nblk), dim3(256), 0, s, in, z, N->wpart, lg);
+    }
     NP_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_wgrad_reduce, dim3(unsigned((kPsz + 31) / 32)), dim3(32 * kRedSl), 0, s, N->wpart, nblk,
                        N->g + int64_t(k) * kPsz);
