@@ -23,6 +23,7 @@
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // kept in registers over a barrier, where uint4 arrays go to scratch
 
 namespace np {
 namespace {
@@ -48,14 +49,23 @@ __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >
 // FP32 gradient is never stored); FP32 of channel 0 alone (the prediction).
 enum ConvOut { kOutRelu, kOutF32, kOutMask, kOutOne };
 
-// Stores output channels 4 grp .. 4 grp + 3 of voxel v.
+// Output channels 4 grp .. 4 grp + 3: the lane's bias (zero for data gradients)
+__device__ __forceinline__ f32x4 conv_bias(const float *__restrict__ bias, int grp) {
+    return bias ? f32x4{bias[4 * grp], bias[4 * grp + 1], bias[4 * grp + 2], bias[4 * grp + 3]} : f32x4{0.f, 0.f, 0.f, 0.f};
+}
+// The activations of these channels of voxel v that mask them
+template <ConvOut OUT> __device__ __forceinline__ uint2 conv_act(const uint16_t *__restrict__ act, int64_t v, int grp) {
+    if constexpr (OUT == kOutMask) return *reinterpret_cast<const uint2 *>(act + v * kC + 4 * grp);
+    else return make_uint2(0, 0);
+}
+// Stores these channels of voxel v.
 template <ConvOut OUT>
-__device__ __forceinline__ void conv_store(const f32x4 &acc, const float *__restrict__ bias,
-                                           const uint16_t *__restrict__ act, void *__restrict__ Y, int64_t v, int grp) {
+__device__ __forceinline__ void conv_store(const f32x4 &acc, const f32x4 &bias, const uint2 &act, void *__restrict__ Y,
+                                           int64_t v, int grp) {
     float o[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        float t = acc[r] + (bias ? bias[4 * grp + r] : 0.f);
+        float t = acc[r] + bias[r];
         if (OUT == kOutRelu) t = t > 0.f ? t : 0.f;
         o[r] = t;
     }
@@ -65,8 +75,7 @@ __device__ __forceinline__ void conv_store(const f32x4 &acc, const float *__rest
         if (grp == 0) reinterpret_cast<float *>(Y)[v] = o[0];
     } else {
         if constexpr (OUT == kOutMask) {
-            const uint2 a = *reinterpret_cast<const uint2 *>(act + v * kC + 4 * grp);
-            const uint32_t aw[2] = {a.x, a.y};
+            const uint32_t aw[2] = {act.x, act.y};
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (!(b2f(uint16_t(aw[r >> 1] >> (16 * (r & 1)))) > 0.f)) o[r] = 0.f;
@@ -105,6 +114,7 @@ __global__ __launch_bounds__(256) void k_conv(const uint16_t *__restrict__ X, co
     const int w = tid >> 6, l = tid & 63;
     const int col = l & 15, grp = l >> 4;
     const int tsel = grp >> 1, cb = grp & 1;
+    const f32x4 bv4 = conv_bias(bias, grp);
     for (int tt = 0; tt < txv / 16; ++tt) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -128,47 +138,57 @@ __global__ __launch_bounds__(256) void k_conv(const uint16_t *__restrict__ X, co
         // lane holds output channels 4*grp .. +3 of voxel `col`
         const int gx = x0 + tt * 16 + col, gy = y0 + w;
         const int64_t v = (((int64_t(z) << lg) + gy) << lg) + gx;
-        conv_store<OUT>(acc, bias, act, Y, v, grp);
+        conv_store<OUT>(acc, bv4, conv_act<OUT>(act, v, grp), Y, v, grp);
     }
 }
 
-// Z-marching form of the same convolution (same MFMA sequence per output, so
-// the same bits): a workgroup of 256 threads (4 waves, one row each) owns a
-// TXV x 4 tile of the plane (TXV = min(64, n)) and zc consecutive planes.
-// Input planes z - 1, z, z + 1 with their one-voxel halo sit in a ring of
-// three LDS buffers, the weights are staged once per workgroup, and plane
-// z + 2 replaces plane z - 1 after plane z is computed, so each input plane is
-// read about once per workgroup instead of three times.
-constexpr int kCzT = 256, kCzY = 4;
-constexpr int kCzSlots = (64 + 2) * (kCzY + 2) * 2;  // uint4 per plane buffer (halo tile, two per voxel)
-
-// This thread's share of an input plane of k_conv3z, loaded straight into
-// its ring buffer: slot q holds half (q & 1) of voxel (q >> 1) of the halo tile.
-__device__ __forceinline__ void cz_fill(uint4 *__restrict__ dst, const uint4 *__restrict__ X4, int64_t base, int tid,
-                                        int hx, int x0, int y0, int lg) {
-    const int n = 1 << lg, nslot = hx * (kCzY + 2) * 2;
-    for (int q = tid; q < nslot; q += kCzT) {
-        const int v = q >> 1, half = q & 1, lx = v % hx, ly = v / hx;
-        dst[q] = X4[base + ((int64_t(wrapi(y0 + ly - 1, n)) << lg) + wrapi(x0 + lx - 1, n)) * 2 + half];
-    }
-}
+// Z-marching form of the same convolution (same MFMA sequence per output, so the same bits).  A workgroup
+// owns a column of 256 voxels (TXV = min(64, n) along x by 256 / TXV rows) and zc planes of it; a wave owns
+// 16 voxels along x by four rows.  Input planes arrive one by one in a ring of three LDS buffers, through
+// registers a plane ahead, and each is used for all three output planes it reaches, whose sums a lane holds:
+// of an output's 14 steps (pairs of taps, in order) 0 .. 3 read the plane below it, 4 the plane below and its
+// own, 5 .. 8 its own, 9 .. 13 the plane above.  Neighbouring outputs share most operands of a plane: with
+// row operands A (dx -1, 0), B (dx 0, 1), C (dx 1, then -1 of the next row), D (dx 1 of the row above in the
+// plane below, then -1 of the row below) and E (dx 1, then nothing), four rows and three planes take 26 LDS
+// reads where one output row at a time takes 56.  At 128^3 a forward convolution takes 33 us against 67 us
+// of a kernel that read all operands per output row (its floor, 64 MB read and 64 MB written: 28 us).
+constexpr int kCzT = 256, kCzRows = 4;
+constexpr int kCzSlots = (64 + 2) * (kCzRows + 2) * 2;  // uint4 per plane buffer (halo tile, two per voxel)
 
 template <ConvOut OUT>
 __global__ __launch_bounds__(kCzT) void k_conv3z(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W,
                                                  const float *__restrict__ bias, const uint16_t *__restrict__ act,
                                                  void *__restrict__ Y, int lg, int zc) {
     __shared__ uint4 xs[3][kCzSlots];
-    const int n = 1 << lg, txv = n < 64 ? n : 64, hx = txv + 2;
-    const int tiles_x = n / txv, tiles_y = n / kCzY;
-    const int b = blockIdx.x;
-    const int x0 = (b % tiles_x) * txv, y0 = ((b / tiles_x) % tiles_y) * kCzY, z0 = (b / (tiles_x * tiles_y)) * zc;
+    const int n = 1 << lg, lt = lg < 6 ? lg : 6, txv = 1 << lt, rows = kCzT >> lt, hx = txv + 2;
+    const int tiles_x = n / txv, ncol = tiles_x * (n / rows);
+    const int b = int(xcd_block(blockIdx.x, gridDim.x));
+    const int x0 = (b % tiles_x) * txv, y0 = ((b % ncol) / tiles_x) * rows, z0 = (b / ncol) * zc, z1 = z0 + zc;
     const int tid = threadIdx.x;
     const uint4 *W4 = reinterpret_cast<const uint4 *>(W);
-    const uint4 *X4 = reinterpret_cast<const uint4 *>(X);
-    auto plane = [&](int z) { return int64_t(wrapi(z, n)) << (2 * lg + 1); };
-    cz_fill(xs[(z0 + 2) % 3], X4, plane(z0 - 1), tid, hx, x0, y0, lg);
-    cz_fill(xs[z0 % 3], X4, plane(z0), tid, hx, x0, y0, lg);
-    cz_fill(xs[(z0 + 1) % 3], X4, plane(z0 + 1), tid, hx, x0, y0, lg);
+    const u32x4 *X4 = reinterpret_cast<const u32x4 *>(X);
+    // this thread's share of a plane: slot q holds half (q & 1) of voxel (q >> 1) of the halo tile (slots
+    // beyond the tile repeat the last one)
+    constexpr int NF = (kCzSlots + kCzT - 1) / kCzT;
+    const int nslot = hx * (rows + 2) * 2;
+    int off[NF], at_q[NF];
+    u32x4 pf[NF];
+#pragma unroll
+    for (int u = 0; u < NF; ++u) {
+        const int q = tid + u * kCzT < nslot ? tid + u * kCzT : nslot - 1, v = q >> 1;
+        off[u] = ((wrapi(y0 + v / hx - 1, n) << lg) + wrapi(x0 + v % hx - 1, n)) * 2 + (q & 1);
+        at_q[u] = q;
+    }
+    auto fetch = [&](int z) {
+        const u32x4 *p = X4 + (int64_t(wrapi(z, n)) << (2 * lg + 1));
+#pragma unroll
+        for (int u = 0; u < NF; ++u) pf[u] = p[off[u]];
+    };
+    auto place = [&](int slot) {
+#pragma unroll
+        for (int u = 0; u < NF; ++u) reinterpret_cast<u32x4 *>(xs[slot])[at_q[u]] = pf[u];
+    };
+    fetch(z0 - 1);
     const int w = tid >> 6, l = tid & 63;
     const int col = l & 15, grp = l >> 4;
     const int tsel = grp >> 1, cb = grp & 1;
@@ -181,30 +201,84 @@ __global__ __launch_bounds__(kCzT) void k_conv3z(const uint16_t *__restrict__ X,
         const uint4 a4 = W4[((live ? 2 * s + tsel : kTaps - 1) * kC + col) * 2 + cb];
         wa[s] = __builtin_bit_cast(bf16x8, live ? a4 : make_uint4(0, 0, 0, 0));
     }
-    for (int z = z0; z < z0 + zc; ++z) {
-        __syncthreads();  // planes z - 1, z, z + 1 are in LDS
-        for (int tt = 0; tt < txv / 16; ++tt) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    place(0);
+    fetch(z0);
+    const int wx = (w << 4) & (txv - 1), wy = ((w << 4) >> lt) * kCzRows;  // the wave's voxels in the tile
+    // LDS index of this lane's part of an operand at the wave's row 0
+    const int at = ((wy + 1) * hx + wx + col + 1) * 2 + cb;
+    const int ia = at + (tsel ? 0 : -2), ib = at + (tsel ? 2 : 0), ic = at + (tsel ? 2 * hx - 2 : 2),
+              id = at + (tsel ? -2 * hx - 2 : 2 * hx + 2), ie = at + 2;
+    const int hr = 2 * hx;
+    const int64_t v0 = (int64_t(y0 + wy) << lg) + x0 + wx + col;
+    const f32x4 bv4 = conv_bias(bias, grp);
+    f32x4 top[kCzRows], mid[kCzRows], low[kCzRows];  // sums of the output planes z + 1, z, z - 1 at input plane z
 #pragma unroll
-            for (int s = 0; s < 14; ++s) {
-                // the 28th tap does not exist: read tap 26's operand and zero it by value
-                const bool live = 2 * s + tsel < kTaps;
-                const int tap = live ? 2 * s + tsel : kTaps - 1;
-                const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-                const int hv = (w + 1 + dy) * hx + (tt * 16 + col + 1 + dx);
-                const uint4 b4 = xs[(z + dz + 3) % 3][hv * 2 + cb];
-                const uint4 zz = make_uint4(0, 0, 0, 0);
-                const bf16x8 av = wa[s];
-                const bf16x8 bv = __builtin_bit_cast(bf16x8, live ? b4 : zz);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc, 0, 0, 0);
+    for (int y = 0; y < kCzRows; ++y) mid[y] = low[y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto mac = [&](int s, const uint4 &x, const f32x4 &c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[s], __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
+    };
+    // one input plane; T, M, L: it reaches the output planes z + 1, z, z - 1 of this chunk
+    auto plane = [&](auto T, auto M, auto L, const uint4 *cur, const uint4 *prev) {
+#pragma unroll
+        for (int y = 0; y < kCzRows; ++y) {
+            f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
+            const uint4 am = cur[ia + (y - 1) * hr], ap = cur[ia + (y + 1) * hr], cm = cur[ic + (y - 1) * hr],
+                        b0 = cur[ib + y * hr];
+            if constexpr (T.value) {
+                t = mac(0, am, t);
+                t = mac(1, cm, t);
+                t = mac(2, b0, t);
+                t = mac(3, ap, t);
             }
-            // lane holds output channels 4*grp .. +3 of voxel `col`
-            const int gx = x0 + tt * 16 + col, gy = y0 + w;
-            const int64_t v = (((int64_t(z) << lg) + gy) << lg) + gx;
-            conv_store<OUT>(acc, bias, act, Y, v, grp);
+            if constexpr (M.value) {
+                f32x4 m = mac(4, (tsel ? cur : prev)[id + y * hr], mid[y]);
+                m = mac(5, cur[ib + (y - 1) * hr], m);
+                m = mac(6, cur[ia + y * hr], m);
+                m = mac(7, cur[ic + y * hr], m);
+                mid[y] = mac(8, cur[ib + (y + 1) * hr], m);
+            }
+            if constexpr (L.value) {
+                f32x4 o = mac(9, am, low[y]);
+                o = mac(10, cm, o);
+                o = mac(11, b0, o);
+                o = mac(12, ap, o);
+                const uint4 e = cur[ie + (y + 1) * hr];
+                low[y] = mac(13, tsel ? make_uint4(0, 0, 0, 0) : e, o);
+            }
+            top[y] = t;
         }
-        __syncthreads();  // every read of the oldest buffer is done before it takes plane z + 2
-        if (z + 2 <= z0 + zc) cz_fill(xs[(z + 2) % 3], X4, plane(z + 2), tid, hx, x0, y0, lg);
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    int cs = 0;  // ring slot of plane z
+    for (int z = z0 - 1; z <= z1; ++z) {
+        const int ns = cs == 2 ? 0 : cs + 1, ps = cs == 0 ? 2 : cs - 1;
+        __syncthreads();  // plane z is in LDS, and plane z - 2, whose buffer takes z + 1, is read
+        if (z < z1) place(ns);
+        uint2 ya[kCzRows] = {};  // asked for before the next plane, so that waiting for them does not wait for it
+        if (z > z0)
+#pragma unroll
+            for (int y = 0; y < kCzRows; ++y)
+                ya[y] = conv_act<OUT>(act, (int64_t(z - 1) << (2 * lg)) + v0 + (int64_t(y) << lg), grp);
+        if (z + 1 < z1) fetch(z + 2);
+        const uint4 *cur = xs[cs], *prev = xs[ps];
+        if (z == z0 - 1) plane(yes, no, no, cur, prev);
+        else if (z == z1) plane(no, no, yes, cur, prev);
+        else if (zc == 1) plane(no, yes, no, cur, prev);
+        else if (z == z0) plane(yes, yes, no, cur, prev);
+        else if (z == z1 - 1) plane(no, yes, yes, cur, prev);
+        else plane(yes, yes, yes, cur, prev);
+        if (z > z0) {
+            const int64_t v = (int64_t(z - 1) << (2 * lg)) + v0;
+#pragma unroll
+            for (int y = 0; y < kCzRows; ++y) conv_store<OUT>(low[y], bv4, ya[y], Y, v + (int64_t(y) << lg), grp);
+        }
+#pragma unroll
+        for (int y = 0; y < kCzRows; ++y) {
+            low[y] = mid[y];
+            mid[y] = top[y];
+        }
+        cs = ns;
     }
 }
 
@@ -696,11 +770,12 @@ np_status conv(Net *N, int k, const uint16_t *X, const uint16_t *act, void *Y, i
     const int n = 1 << lg, txv = n < 64 ? n : 64;
     const uint16_t *W = (flip ? N->wt : N->wb) + int64_t(k) * kWsz;
     const float *bias = flip ? nullptr : N->w + int64_t(k) * kPsz + kWsz;
-    // z-marching tiles: n / 32 planes per workgroup at n = 64, n / 16 from n = 128 (measured best; below
-    // n = 64 the one-plane form keeps more workgroups in flight and wins)
-    const int zc = g_conv3z == 1 ? (n >= 128 ? n / 16 : n / 32) : (g_conv3z < n ? g_conv3z : n);
-    if (g_conv3z && zc >= 2)
-        hipLaunchKernelGGL((k_conv3z<OUT>), dim3(unsigned((n / txv) * (n / kCzY) * (n / zc))), dim3(kCzT), 0, s, X, W,
+    // planes per workgroup: n / 8 from n = 128 (three convolutions at 128^3: 160 us with 2 planes, 127 with 8,
+    // 122 with 16, 147 with 32; at 256^3 943 with 8, 898 with 32), below it as few as fill the chip (64^3: 49 us
+    // with 1 or 2, 63 with 8; 32^3: 34 with 1, 43 with 4, and 36 with the one-plane form)
+    const int zc = g_conv3z == 1 ? (n >= 128 ? n / 8 : std::max(1, n / 32)) : std::min(g_conv3z, n);
+    if (g_conv3z)
+        hipLaunchKernelGGL((k_conv3z<OUT>), dim3(unsigned((n / txv) * (n * txv / kCzT) * (n / zc))), dim3(kCzT), 0, s, X, W,
                            bias, act, Y, lg, zc);
     else
         hipLaunchKernelGGL((k_conv<OUT>), dim3(unsigned((n / txv) * (n / 4) * n)), dim3(256), 0, s, X, W, bias, act, Y,

@@ -71,3 +71,37 @@ def test_zero_activations_stop_gradients():
     assert g[-16] != 0.0
     g[-16] = 0.0
     assert not g.any()
+
+
+def test_two_tiles_along_x():
+    """128^3 has two tiles along x: the plane-marching convolution gives the bits of
+    the one-plane form for every plane count, and the weight gradients agree with the
+    FP32 vector path to FP32 rounding (sums in another order; 1e-5 relative)."""
+    import torch
+    from paper_2402_17913_amd import binding as B
+    n, per = 128, 27 * 16 * 16 + 16
+    rng = np.random.default_rng(4)
+    net = B.Cnn(n, 1)
+    net.set_params((rng.standard_normal(3 * per) * 0.05).astype(np.float32))
+    f, t = (torch.from_numpy(a.astype(np.float32)).cuda() for a in rng.standard_normal((2, n, n, n)))
+    got = {}
+    try:
+        for z, w in ((0, 1), (1, 1), (4, 1), (32, 1), (1, 0)):
+            B.np_set_tuning("conv3z", z)
+            B.np_set_tuning("wgrad_mfma", w)
+            y = torch.empty_like(f)
+            net.forward(f, y)
+            loss = net.gradients([f], [t])
+            got[z, w] = y.cpu().numpy(), loss, net.get_grads().astype(np.float64)
+    finally:
+        B.np_set_tuning("conv3z", 1)
+        B.np_set_tuning("wgrad_mfma", 1)
+        net.close()
+    y0, l0, g0 = got[0, 1]
+    for k in ((1, 1), (4, 1), (32, 1)):
+        y, l, g = got[k]
+        assert np.array_equal(y, y0) and l == l0 and np.array_equal(g, g0), k
+    gv = got[1, 0][2]
+    for k in range(3):
+        a, b = g0[k * per:(k + 1) * per], gv[k * per:(k + 1) * per]
+        assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b), k
