@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t *__restrict__ X, c
 // dZ and, for X, one 16-byte and one 4-byte read that serve the three taps of a (dz, dy) row, funnel-shifted
 // by 0, 2 or 4 bytes.  The channel pitches put the 16 channels of a read on different banks.  A wave owns
 // every fourth step of 32 voxels and all 28 products, and the waves' sums are added in order at the end.
-// At 128^3 it takes 54 us, against 125 us when every plane of a tile staged
+// At 128^3 it takes 47 us, against 125 us when every plane of a tile staged
 // a three-plane halo of its own with 2-byte LDS writes and each wave read all of dZ for its share of the taps.
 // The two operands read once would take 28 us; what is left is one barrier and a full load latency per plane
 // at two workgroups per CU, which the 28 accumulators of a lane allow.
@@ -357,11 +357,10 @@ __device__ __forceinline__ uint32_t wm_shift(uint32_t lo, uint32_t hi, int bytes
 }
 
 // Eight channels of two neighbouring voxels a, b to the channel-major rows dst, dst + pitch, ... (dwords)
-__device__ __forceinline__ void wm_put(uint32_t *dst, int pitch, const uint4 &a, const uint4 &b) {
-    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
+__device__ __forceinline__ void wm_put(uint32_t *dst, int pitch, const u32x4 &a, const u32x4 &b) {
 #pragma unroll
     for (int e = 0; e < 8; ++e)
-        dst[e * pitch] = __builtin_amdgcn_perm(bw[e >> 1], aw[e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+        dst[e * pitch] = __builtin_amdgcn_perm(b[e >> 1], a[e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
 }
 
 __global__ __launch_bounds__(kWmT) void k_wgrad_mfma(const uint16_t *__restrict__ X, const uint16_t *__restrict__ dZ,
@@ -373,73 +372,69 @@ __global__ __launch_bounds__(kWmT) void k_wgrad_mfma(const uint16_t *__restrict_
     const int tiles_x = n / txv, ncol = tiles_x * (n / 4);
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int ch = l & 15, g = l >> 4;  // operand channel (o for dZ, c for X); voxel run within 32
-    const uint4 *X4 = reinterpret_cast<const uint4 *>(X), *Z4 = reinterpret_cast<const uint4 *>(dZ);
+    const u32x4 *X4 = reinterpret_cast<const u32x4 *>(X), *Z4 = reinterpret_cast<const u32x4 *>(dZ);
     uint32_t *xd = reinterpret_cast<uint32_t *>(xt);
     f32x4 acc[kTaps + 1];
 #pragma unroll
     for (int u = 0; u <= kTaps; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
     const uint32_t one2 = 0x3f803f80u;  // two BF16 ones
     const uint4 ones = make_uint4(one2, one2, one2, one2);
-    // this thread's staging slots: pairs of voxels x half a voxel's channels
+    // this thread's staging slots: pairs of voxels x half a voxel's channels (those beyond the tile repeat
+    // the last one)
     const int nxs = hp * 6 * 2, nzs = txv * 4;
-    int xs[2], xl[2], zl = 0;  // offset of a slot's pair in a row and its place in LDS
+    int xp[2], xr[2], xl[2];  // a slot's pair in its row, the row, and its place in LDS
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-        const int q = tid + u * kWmT, v = q >> 1;
-        xs[u] = v % hp;
-        xl[u] = 8 * (q & 1) * (kWmCh / 2) + (v / hp) * (kWmRow / 2) + v % hp;
+        const int q = std::min(tid + u * kWmT, nxs - 1), v = q >> 1;
+        xp[u] = v % hp;
+        xr[u] = v / hp;
+        xl[u] = 8 * (q & 1) * (kWmCh / 2) + xr[u] * (kWmRow / 2) + xp[u];
     }
-    const int zp = (tid >> 1) & (txv / 2 - 1), zy = (tid >> 1) >> (lt - 1);
-    zl = 8 * (tid & 1) * (kWmZCh / 2) + zy * (txv / 2) + zp;
-    for (int b = blockIdx.x; b < ncol * nch; b += gridDim.x) {
+    const int zq = std::min(tid, nzs - 1), zp = (zq >> 1) & (txv / 2 - 1), zy = (zq >> 1) >> (lt - 1);
+    const int zl = 8 * (zq & 1) * (kWmZCh / 2) + zy * (txv / 2) + zp;
+    for (int b = int(xcd_block(blockIdx.x, gridDim.x)); b < ncol * nch; b += gridDim.x) {
         const int col = b % ncol, x0 = (col % tiles_x) * txv, y0 = (col / tiles_x) * 4;
         const int z0 = int(int64_t(n) * (b / ncol) / nch), z1 = int(int64_t(n) * (b / ncol + 1) / nch);
-        int64_t xa[2], xb[2], za = 0;
+        int xa[2], xb[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int q = tid + u * kWmT, row = wrapi(y0 + (q >> 1) / hp - 1, n), gx = x0 + 2 * xs[u];
-            xa[u] = ((int64_t(row) << lg) + wrapi(gx - 1, n)) * 2 + (q & 1);
-            xb[u] = ((int64_t(row) << lg) + wrapi(gx, n)) * 2 + (q & 1);
+            const int row = wrapi(y0 + xr[u] - 1, n) << lg, gx = x0 + 2 * xp[u], half = (tid + u * kWmT < nxs ? tid : nxs - 1) & 1;
+            xa[u] = (row + wrapi(gx - 1, n)) * 2 + half;
+            xb[u] = (row + wrapi(gx, n)) * 2 + half;
         }
-        za = ((int64_t(y0 + zy) << lg) + x0 + 2 * zp) * 2 + (tid & 1);
-        uint4 xv[2][2], zv[2];
-        auto fetch_x = [&](int z) {
-            const uint4 *p = X4 + (int64_t(wrapi(z, n)) << (2 * lg + 1));
+        const int za = (((y0 + zy) << lg) + x0 + 2 * zp) * 2 + (zq & 1);
+        u32x4 xv[3][2][2], zv[2];  // planes on their way (three at the start of a column, then one)
+        auto fetch_x = [&](int z, u32x4 (&t)[2][2]) {
+            const u32x4 *p = X4 + (int64_t(wrapi(z, n)) << (2 * lg + 1));
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (tid + u * kWmT < nxs) {
-                    xv[u][0] = p[xa[u]];
-                    xv[u][1] = p[xb[u]];
-                }
-        };
-        auto store_x = [&](int slot) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (tid + u * kWmT < nxs) wm_put(xd + xl[u] + slot * (6 * kWmRow / 2), kWmCh / 2, xv[u][0], xv[u][1]);
-        };
-        auto fetch_z = [&](int z) {
-            if (tid < nzs) {
-                const uint4 *p = Z4 + (int64_t(z) << (2 * lg + 1)) + za;
-                zv[0] = p[0];
-                zv[1] = p[2];
+            for (int u = 0; u < 2; ++u) {
+                t[u][0] = p[xa[u]];
+                t[u][1] = p[xb[u]];
             }
         };
+        auto store_x = [&](int slot, const u32x4 (&t)[2][2]) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) wm_put(xd + xl[u] + slot * (6 * kWmRow / 2), kWmCh / 2, t[u][0], t[u][1]);
+        };
+        auto fetch_z = [&](int z) {
+            const u32x4 *p = Z4 + (int64_t(z) << (2 * lg + 1)) + za;
+            zv[0] = p[0];
+            zv[1] = p[2];
+        };
         auto store_z = [&](int z) {
-            if (tid < nzs) wm_put(reinterpret_cast<uint32_t *>(zt[z & 1]) + zl, kWmZCh / 2, zv[0], zv[1]);
+            wm_put(reinterpret_cast<uint32_t *>(zt[z & 1]) + zl, kWmZCh / 2, zv[0], zv[1]);
         };
         __syncthreads();  // the previous column's operands are read
         fetch_z(z0);
-        fetch_x(z0 - 1);
-        store_x((z0 - 1) & 3);
-        fetch_x(z0);
-        store_x(z0 & 3);
-        fetch_x(z0 + 1);
-        store_x((z0 + 1) & 3);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) fetch_x(z0 - 1 + t, xv[t]);
         store_z(z0);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) store_x((z0 - 1 + t) & 3, xv[t]);
         for (int z = z0; z < z1; ++z) {
             __syncthreads();  // planes z - 1 .. z + 1 and dZ's z are in LDS; z - 2 and dZ's z - 1 are read
             if (z + 1 < z1) {
-                fetch_x(z + 2);
+                fetch_x(z + 2, xv[0]);
                 fetch_z(z + 1);
             }
             for (int kb = w; kb < txv * 4 / 32; kb += 4) {
@@ -467,7 +462,7 @@ __global__ __launch_bounds__(kWmT) void k_wgrad_mfma(const uint16_t *__restrict_
                                                                      0, 0);
             }
             if (z + 1 < z1) {
-                store_x((z + 2) & 3);
+                store_x((z + 2) & 3, xv[0]);
                 store_z(z + 1);
             }
         }
