@@ -338,7 +338,8 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t *__restrict__ X, c
 // is a 16 x 16 product with the voxels as the contraction (v_mfma_f32_16x16x32_bf16, 32 voxels per step);
 // the bias gradient is one more product with X = 1.  A workgroup marches through a chunk of planes of a
 // column of TXV x 4 voxels: a ring of four X planes with their halo and two dZ planes lie in LDS, three and
-// one of them in use while the next of each arrives through registers, so that a plane costs one barrier.  Both are staged channel-major, two voxels of a
+// one of them in use while the next of each arrives through registers, so that a plane costs one barrier.
+// Both are staged channel-major, two voxels of a
 // channel per dword, so that a lane's operand (8 consecutive voxels of one channel) is one 16-byte read for
 // dZ and, for X, one 16-byte and one 4-byte read that serve the three taps of a (dz, dy) row, funnel-shifted
 // by 0, 2 or 4 bytes.  The channel pitches put the 16 channels of a read on different banks.  A wave owns

@@ -133,16 +133,19 @@ __device__ __forceinline__ double wave2_leg(const S *__restrict__ ec, const S *_
     };
     const bool dir = !bc;
     double acc = 0.0;
-    C pa[NC];  // residual sums of an even row's column pairs
+    // residual sums of an even row's column pairs; two scalars, as an array that the lambda keeps goes to
+    // scratch in FP32, and waiting for it waits for every row on its way
+    // (2048^2 FP32 solve 1490 -> 1453 us)
+    C pa0 = C(0), pa1 = C(0);
     auto restrict_row = [&](int r, const C (&rv)[N]) {  // row r of the residual, in order
         if (r < j0 || r >= j1) return;
         if (!(r & 1)) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c) pa[c] = rv[2 * c] + rv[2 * c + 1];
+            pa0 = rv[0] + rv[1];
+            if constexpr (NC == 2) pa1 = rv[2] + rv[3];
         } else {
             C o[NC];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) o[c] = ((pa[c] + rv[2 * c]) + rv[2 * c + 1]) * C(0.25);
+            o[0] = ((pa0 + rv[0]) + rv[1]) * C(0.25);
+            if constexpr (NC == 2) o[1] = ((pa1 + rv[2]) + rv[3]) * C(0.25);
             if (own) Run<S, NC>::st(fc + ((uint32_t(r >> 1) << (lg - 1)) + uint32_t(col >> 1)), o);
         }
     };
