@@ -47,6 +47,15 @@ __device__ __forceinline__ int bmap(int g, int n, int bc, int &sgn) {
     return g;
 }
 
+// The start of a small level's kernel: its operands and the stop flag are asked for together and used
+// once they are all there, as a field or flag written by another XCD's kernel comes from beyond the L2
+// and the kernel is little more than a chain of such round trips.  `landed` keeps the compiler from
+// moving the loads behind the test of the flag.
+template <class C, int N> __device__ __forceinline__ void landed(C (&v)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
+}
+
 // Block of B^3 cells and its one- and two-cell rings; NT_ threads (B^3 or more: the ring
 // stages then take fewer passes per thread).
 template <int B, int NT_ = B * B * B> struct BTile {

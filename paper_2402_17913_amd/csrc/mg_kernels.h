@@ -471,7 +471,9 @@ enum StopReason { kRunning = 0, kConverged = 1, kFixedDone = 2, kMaxCycles = 3, 
 // thread 0 (0 to the others).
 template <int NT>
 __device__ __forceinline__ int check_block(const double *__restrict__ partial, int np, Ctl *__restrict__ c) {
-    if (c->stop) return threadIdx.x == 0 ? c->stop : 0;  // uniform: one value for the workgroup
+    // the controller's fields arrive with the partials
+    const int stopped = c->stop, k = c->k, fixed = c->fixed, maxc = c->maxc;
+    const double nf = c->nf, tol = c->tol;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     if (int(threadIdx.x) < kBlock) {
         int b = threadIdx.x;
@@ -483,17 +485,17 @@ __device__ __forceinline__ int check_block(const double *__restrict__ partial, i
         }
         for (; b < np; b += kBlock) a0 += partial[b];
     }
+    if (stopped) return threadIdx.x == 0 ? stopped : 0;  // uniform: one value for the workgroup
     const double acc = block_sum_n<NT>((a0 + a1) + (a2 + a3));
     if (threadIdx.x != 0) return 0;
-    const int k = c->k;
-    const double rr = sqrt(acc) / c->nf;
+    const double rr = sqrt(acc) / nf;
     if (k < 256) c->hist[k] = rr;
     c->nhist = k + 1 < 256 ? k + 1 : 256;
     int st = kRunning;
     if (!(rr <= 1.0e300)) st = kNonFinite;  // NaN or Inf
-    else if (c->fixed > 0) { if (k >= c->fixed) st = kFixedDone; }
-    else if (rr <= c->tol) st = kConverged;
-    else if (k >= c->maxc) st = kMaxCycles;
+    else if (fixed > 0) { if (k >= fixed) st = kFixedDone; }
+    else if (rr <= tol) st = kConverged;
+    else if (k >= maxc) st = kMaxCycles;
     else if (k >= 3 && k < 256 && c->hist[k - 3] < c->hist[k - 2] && c->hist[k - 2] < c->hist[k - 1] &&
              c->hist[k - 1] < rr)
         st = kDiverged;

@@ -274,6 +274,24 @@ template <int D, class Fn> __device__ __forceinline__ void tail_by_level(int lg,
     else fn(std::integral_constant<int, 2>());
 }
 
+// This thread's share of m values of an array (at most MAX) on their way from memory, and their way
+// into LDS: the kernel's other round trips to memory run meanwhile.
+template <class S, int NT, int MAX> struct TailLoad {
+    static constexpr int per = (MAX + NT - 1) / NT;
+    typename St<S>::C v[per];
+    __device__ __forceinline__ void ask(const S *p, int m) {
+#pragma unroll
+        for (int u = 0; u < per; ++u) v[u] = St<S>::ld(p + min(int(threadIdx.x) + u * NT, m - 1));
+    }
+    template <class Put> __device__ __forceinline__ void put(int m, Put &&dst) const {
+#pragma unroll
+        for (int u = 0; u < per; ++u) {
+            const int c = int(threadIdx.x) + u * NT;
+            if (c < m) dst(c, v[u]);
+        }
+    }
+};
+
 // The coarsest inverse (row-major Minv, scaled by `sc`) into LDS, transposed with padded rows:
 // thread i reading entry (i, q) hits consecutive banks.
 template <int D, int NT> __device__ __forceinline__ void tail_minv(double *Ms, const double *Minv, double sc = 1.0) {
@@ -300,7 +318,9 @@ template <class S, int NT, int MAX> __device__ __forceinline__ void tail_fetch(t
 
 // One-workgroup V-cycle from a zero iterate on levels lg_t .. 2.  ctl: first the
 // cycle's convergence check on the np partials of the finest level's residual
-// norm (the check of k_check), and nothing more if it stops the solve.
+// norm (the check of k_check), and nothing more if it stops the solve; its operands
+// arrive meanwhile (one after the other they took the tail from 8.8 to 11.2 us in 3D BF16
+// and from 11.5 to 12.3 in 2D FP64).
 template <int D, class S, class OPS>
 __global__ __launch_bounds__(Tail<D>::NT) void k_tail(const S *__restrict__ f_t, S *__restrict__ x_t,
                                                       const double *__restrict__ Minv, int lg_t, int bc, OPS ops,
@@ -312,17 +332,24 @@ __global__ __launch_bounds__(Tail<D>::NT) void k_tail(const S *__restrict__ f_t,
     __shared__ C fs[Tail<D>::levels_sum()];
     __shared__ C ts[Tail<D>::cells(Tail<D>::LG)];
     __shared__ double Ms[m * (m + 1)];
-    if (stop && *stop) return;
-    if (ctl) {
+    const int stopped = stop ? *stop : 0;
+    const int o = tail_off<D>(lg_t), mt = 1 << (D * lg_t);
+    TailLoad<S, NT, int(Tail<D>::cells(Tail<D>::LG))> tf;
+    TailLoad<double, NT, m * m> tm;
+    tf.ask(f_t, mt);
+    tm.ask(Minv, m * m);
+    if (ctl) {  // the operands arrive while the check is made
         __shared__ int halt;
         const int st = check_block<NT>(partial, np, ctl);
         if (threadIdx.x == 0) halt = st;
         __syncthreads();
         if (halt) return;
     }
-    const int o = tail_off<D>(lg_t), mt = 1 << (D * lg_t);
-    tail_minv<D, NT>(Ms, Minv);
-    tail_fetch<S, NT, int(Tail<D>::cells(Tail<D>::LG))>(fs + o, f_t, mt);
+    landed(tf.v);
+    landed(tm.v);
+    if (stopped) return;
+    tm.put(m * m, [&](int g, double v) { Ms[(g % m) * (m + 1) + g / m] = v; });
+    tf.put(mt, [&](int c, C v) { fs[o + c] = v; });
     __syncthreads();
     tail_by_level<D>(lg_t, [&](auto lg) {
         tail_zero<D, C, NT, decltype(lg)::value>(xs, fs, ts, Ms, bc, ops, nu1, nu2);
