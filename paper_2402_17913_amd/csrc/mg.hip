@@ -137,6 +137,7 @@ struct Tuning {
     int fbnt = 1024;      // threads per workgroup of those block kernels (512: one per cell, or 1024)
     int z2wg = 1;         // one-pass kernels that fit fewer than four workgroups per CU aim at 512 workgroups
     int blk2 = 1;         // 2D levels of 128^2 .. 1024^2: one block kernel per leg (64 x 16 cells per workgroup)
+    int link = 11;        // smallest 2D FP64 finest level (log2) whose up-leg runs with the next cycle's down-leg
     int w2min = 10;       // smallest 2D level (log2 cells per axis) whose legs run on row-marching wavefronts (14: none)
 };
 static Tuning g_tune;
@@ -151,8 +152,8 @@ constexpr int kPartials = 65536;
 constexpr unsigned kNormBlocks = 2048;  // workgroups of a sweep that also reduces the residual norm  // per-workgroup partial sums (fixed order)
 
 struct GraphKey {
-    int kind;  // 0: FP64 cycle; mixed: 1 first update, 2 inner cycles + update (a->b or b->a); 5 sawtooth;
-               // advection-diffusion: 6 V-cycle, 7 sawtooth; mixed from a zero iterate x does not hold:
+    int kind;  // 0: FP64 cycle (10: linked to the one before it, 11: the first of a linked row); mixed: 1 first update, 2 inner cycles + update (a->b or b->a); 5 sawtooth;
+               // advection-diffusion: 6 V-cycle (12, 13: linked), 7 sawtooth; mixed from a zero iterate x does not hold:
                // 8 first check, 9 first update
     int zero0, check;
     const void *x, *f;
@@ -188,6 +189,8 @@ struct Hier {
     double *f64 = nullptr;    // FP64 copy of the rhs (periodic mean removal)
     double *x64 = nullptr;    // second FP64 solution buffer (mixed path)
     double *saw = nullptr;    // level-0 correction and its partner (sawtooth cycle)
+    double *t0b = nullptr;    // a second partner of the level-0 iterate (linked FP64 cycles)
+    bool t0b_none = false;    // there was no memory for it
     double *ad_minv = nullptr;  // advection-diffusion: inverse of the coarsest operator
     double ad_key[6] = {-1.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // ad_minv built for: coarsest spacing, dt, nu, a[3]
     int ad_key_scheme = -1;
@@ -234,6 +237,7 @@ void free_hier(Hier *H) {
     if (H->f64) (void)hipFree(H->f64);
     if (H->x64) (void)hipFree(H->x64);
     if (H->saw) (void)hipFree(H->saw);
+    if (H->t0b) (void)hipFree(H->t0b);
     if (H->ad_minv) (void)hipFree(H->ad_minv);
     if (H->xold) (void)hipFree(H->xold);
     if (H->ad_l1) (void)hipFree(H->ad_l1);
@@ -277,6 +281,19 @@ static np_status ensure_levels(Hier *H) {
     if (H->prec != NP_FP64) NP_TRY(dmalloc((void **)&H->x64, sizeof(double) * cells(H->d, H->lg)));
     H->levels = true;
     return NP_OK;
+}
+
+// The second partner of the level-0 iterate, allocated on first use; false without memory for it (the
+// cycles then run unlinked).
+static bool ensure_t0b(Hier *H) {
+    if (H->t0b) return true;
+    if (H->t0b_none) return false;
+    if (hipMalloc((void **)&H->t0b, sizeof(double) * size_t(cells(H->d, H->lg))) != hipSuccess) {
+        (void)hipGetLastError();
+        H->t0b = nullptr;
+        H->t0b_none = true;
+    }
+    return H->t0b != nullptr;
 }
 
 static np_status get_hier(int d, int lg, int bc, np_prec prec, Hier **out) {
@@ -418,17 +435,18 @@ static bool aligned16(const void *a, const void *b) { return ((uintptr_t(a) | ui
 static bool w2_on(int lg, bool al) { return lg >= 7 && lg >= g_tune.w2min && al; }
 template <class S, class OP, int MODE, bool NORM>
 static np_status launch_leg2(bool al, const S *ec, const S *f, const S *xin, S *xout, S *fc, double *partial,
-                             unsigned *np, int lg, int bc, const OP &op, hipStream_t s, const int *stop) {
+                             unsigned *np, int lg, int bc, const OP &op, hipStream_t s, const int *stop,
+                             S *xmid = nullptr) {
     const int n = 1 << lg;
-    if (w2_on(lg, al)) {
+    if (MODE == 3 || w2_on(lg, al)) {
         // wavefronts aimed for: FP64 2048 (twelve cycles at 4096^2 4.06 ms, against 4.47 with 1024 and 4.12
         // with 4096), else 4096 (four FP32 refinement steps at 2048^2 1.29 ms, against 1.33 and 1.32)
-        const int strips = w2_strips<S, MODE>(n, bc).count, ry = wave2_rows(n, strips, sizeof(S) == 8 ? 2048 : 4096);
+        const int strips = w2_strips<S, MODE>(n, bc).count, ry = wave2_rows(n, strips, sizeof(S) == 8 || MODE == 3 ? 2048 : 4096);
         const int64_t waves = int64_t(strips) * ((n + ry - 1) / ry);
         *np = unsigned((waves * 64 + kW2T - 1) / kW2T);
         hipLaunchKernelGGL((k_wave2<S, OP, MODE, NORM>), dim3(*np), dim3(kW2T), 0, s, ec, f, xin, xout, fc, partial, lg,
-                           bc, ry, op, stop);
-    } else {
+                           bc, ry, op, stop, xmid);
+    } else if constexpr (MODE != 3) {
         *np = unsigned((n / B2<S>::BX) * (n / B2<S>::BY));
         hipLaunchKernelGGL((k_lvl2_b<S, OP, MODE, NORM>), dim3(*np), dim3(B2<S>::NT), 0, s, ec, f, xin, xout, fc, partial,
                            lg, bc, op, stop);
@@ -759,16 +777,17 @@ template <int D, class S> struct Ops {
     }
     template <int MODE, bool NORM>
     static np_status leg2(bool al, const S *ec, const S *f, const S *xin, S *xout, S *fc, double *partial, int *np,
-                          int lg, int bc, double h, double omega, hipStream_t s, const int *stop) {
+                          int lg, int bc, double h, double omega, hipStream_t s, const int *stop, S *xmid = nullptr) {
         if constexpr (D == 2) {
             const Lap2<C> op{C(1.0 / (h * h)), C(omega * h * h / (2.0 * D))};
             unsigned nb = 0;
-            NP_TRY((launch_leg2<S, Lap2<C>, MODE, NORM>(al, ec, f, xin, xout, fc, partial, &nb, lg, bc, op, s, stop)));
+            NP_TRY((launch_leg2<S, Lap2<C>, MODE, NORM>(al, ec, f, xin, xout, fc, partial, &nb, lg, bc, op, s, stop,
+                                                        xmid)));
             if (np) *np = int(nb);
             return NP_OK;
         } else {
             (void)al; (void)ec; (void)f; (void)xin; (void)xout; (void)fc; (void)partial; (void)np; (void)lg; (void)bc;
-            (void)h; (void)omega; (void)s; (void)stop;
+            (void)h; (void)omega; (void)s; (void)stop; (void)xmid;
             return NP_EINVAL;
         }
     }
@@ -896,12 +915,36 @@ template <int D, class S> struct Ops {
         return NP_OK;
     }
 
+    // A cycle whose finest up-leg runs with the next cycle's down-leg, in one pass (MODE 3).  in: where
+    // the previous cycle left its pre-smoothed iterate (null: the cycle opens with a down-leg of its own);
+    // out: where this cycle leaves its own; open: the up-leg is left to the next cycle.  The iterate between
+    // the two goes to x0 in FP64, where its residual is checked, else nowhere.
+    struct Link {
+        const S *in;
+        S *out;
+        bool open;
+    };
+    // Which cycles are linked: V(2,2) on 2D finest levels on wavefronts (aligned fields) whose next level ends
+    // in t[1] and whose check the tail makes, where memory bounds the legs: the pass moves 36 bytes per
+    // FP64 cell with the check (28 without) against 52 of the two legs, and holds 150 registers, three
+    // wavefronts per SIMD.  Twelve FP64 cycles: 4096^2 3.93 -> 3.36 ms, 2048^2 1.41 -> 1.29, 1024^2 0.82
+    // either way; four FP32 refinement steps of three cycles: 4096^2 2.77 -> 2.54 ms, 2048^2 1.11 either
+    // way; BF16 is bound by the arithmetic and slower linked (4096^2 2.40 against 2.47).
+    static constexpr bool kLinks = D == 2 && sizeof(S) >= 4;
+    static bool link_on(const Hier *H, const CycleOpts &o, bool al) {
+        const int lg = H->lg;
+        return kLinks && lg >= g_tune.link + (sizeof(S) == 8 ? 0 : 1) && !prof_on() && !g_tune.fused && o.nu1 == 2 && o.nu2 == 2 && w2_on(lg, al) &&
+               lg > Tail<2>::LG + 1 && leg2_on(lg - 1, true) && psweep_on(lg - 1, o.nu2) && g_tune.tail &&
+               g_tune.tailck && g_tune.zero2;
+    }
+
     // Enqueues one V(nu1, nu2) cycle on the hierarchy.  Level 0 works on
     // (x0, f0) with t0 as partner; zero0: x0 is zero on entry (it is not
     // read); check: the residual norm of x0 is reduced and the controller's
     // stop rule runs before the rest of the cycle.  The level-0 result is in x0.
     static np_status cycle(Hier *H, S *x0, const S *f0, S *t0, bool zero0, bool check, double h,
-                           const CycleOpts &o, hipStream_t s, const CgcHook *hook = nullptr) {
+                           const CycleOpts &o, hipStream_t s, const CgcHook *hook = nullptr,
+                           const Link *link = nullptr) {
         const int L = H->L, bc = H->bc;
         const int *stop = &H->ctl->stop;
         H_lg_top = H->lg;
@@ -948,6 +991,27 @@ template <int D, class S> struct Ops {
                 if (used) zero = false;
             }
             S *fc = (S *)H->f[l + 1];
+            if (link && l == 0) {
+                int nb = 0;
+                if (link->in) {
+                    if constexpr (kLinks && sizeof(S) == 8)  // FP64 cycles check, the inner cycles of a refinement don't
+                        NP_TRY((leg2<3, true>(true, (const S *)H->t[1], f0, link->in, link->out, fc, H->red, &nb, lg, bc,
+                                              hl, o.omega, s, stop, x0)));
+                    else if constexpr (kLinks)
+                        NP_TRY((leg2<3, false>(true, (const S *)H->t[1], f0, link->in, link->out, fc, nullptr, nullptr, lg,
+                                               bc, hl, o.omega, s, stop)));
+                } else if (zero) {
+                    NP_TRY((leg2<0, false>(true, nullptr, f0, nullptr, link->out, fc, nullptr, nullptr, lg, bc, hl,
+                                           o.omega, s, stop)));
+                } else {
+                    NP_TRY((leg2<1, true>(true, nullptr, f0, x0, link->out, fc, H->red, &nb, lg, bc, hl, o.omega, s,
+                                          stop)));
+                }
+                if (nb) NP_TRY(check_now(nb));
+                cur[0] = link->out;
+                oth[0] = x0;
+                continue;
+            }
             if (fl[l]) {
                 int nb = 0;
                 if (zero) {
@@ -1064,7 +1128,7 @@ template <int D, class S> struct Ops {
             res[L] = cur[L];
         }
         // -------------------------------------------------------------- up
-        for (int l = (tl > 0 ? tl : L) - 1; l >= 0; --l) {
+        for (int l = (tl > 0 ? tl : L) - 1; l >= (link && link->open ? 1 : 0); --l) {
             hl *= 0.5;
             const int lg = H->lg - l;
             if (fl[l]) {
@@ -1105,6 +1169,13 @@ template <int D, class S> struct Ops {
                 std::swap(cur[l], oth[l]);
             }
             res[l] = cur[l];
+        }
+        if (link && link->open) {
+            if (res[1] != (S *)H->t[1]) {
+                set_error("linked cycles: the next level's correction is not in its partner buffer");
+                return NP_EINVAL;
+            }
+            return NP_OK;
         }
         if (res[0] != x0) {
             hipLaunchKernelGGL((k_copy<S>), dim3(blocks_for(cells(D, H->lg))), dim3(kBlock), 0, s, res[0], x0,
@@ -1333,7 +1404,17 @@ static np_status solve_fp64(Hier *H, const double *f, double *x, double h, doubl
             };
         }
     }
-    if (x_zero) {
+    // linked cycles j = 0, 1, ...: the pre-smoothed iterate alternates between the two partners of x
+    const bool linked = cgc == 0 && O::link_on(H, co, aligned16(x, f)) && ensure_t0b(H);
+    auto link_cycle = [&](hipStream_t q, int j) -> np_status {
+        double *tb[2] = {t0, H->t0b};
+        const typename O::Link ln{j > 0 ? tb[(j - 1) & 1] : nullptr, tb[j & 1], true};
+        return O::cycle(H, x, f, t0, j == 0 && x_zero, j > 0 || !x_zero, h, co, q, nullptr, &ln);
+    };
+    if (linked) {
+        GraphKey k0{11, x_zero ? 1 : 0, x_zero ? 0 : 1, x, f, h, co.nu1, co.nu2, 0, co.omega};
+        NP_TRY(run_graph(H, k0, s, [&](hipStream_t q) { return link_cycle(q, 0); }));
+    } else if (x_zero) {
         if (cgc > 0) {
             NP_TRY(O::cycle(H, x, f, t0, true, false, h, co, s, &hook));
             --cgc;
@@ -1347,11 +1428,16 @@ static np_status solve_fp64(Hier *H, const double *f, double *x, double h, doubl
         NP_TRY(read_ctl(H, s));
         if (H->hctl->stop) break;
     }
-    GraphKey key{0, 0, 1, x, f, h, co.nu1, co.nu2, 0, co.omega};
-    int batch = o.fixed_cycles > 0 ? o.fixed_cycles + 1 : g_tune.batch;
+    GraphKey key{linked ? 10 : 0, 0, 1, x, f, h, co.nu1, co.nu2, 0, co.omega};
+    int batch = o.fixed_cycles > 0 ? o.fixed_cycles + 1 : g_tune.batch, next = 1;
     for (;;) {
-        NP_TRY(run_graphs(H, key, s, batch, 0, false,
-                          [&](hipStream_t q, int) { return O::cycle(H, x, f, t0, false, true, h, co, q); }));
+        if (linked) {
+            NP_TRY(run_graphs(H, key, s, batch, next, true, link_cycle));
+            next += batch;
+        } else {
+            NP_TRY(run_graphs(H, key, s, batch, 0, false,
+                              [&](hipStream_t q, int) { return O::cycle(H, x, f, t0, false, true, h, co, q); }));
+        }
         NP_TRY(read_ctl(H, s));
         if (H->hctl->stop) break;
         batch = next_batch(*H->hctl, o, false);
@@ -1555,7 +1641,18 @@ static np_status solve_mixed(Hier *H, const double *f, double *x, double h, doub
     };
     // the inner cycles of one step: e from the rounded residual
     auto cycles = [&](hipStream_t q) -> np_status {
-        for (int c = 0; c < inner; ++c) NP_TRY(O::cycle(H, e, rlo, tt, c == 0, false, h, co, q));
+        if (inner < 2 || !O::link_on(H, co, aligned16(e, rlo))) {
+            for (int c = 0; c < inner; ++c) NP_TRY(O::cycle(H, e, rlo, tt, c == 0, false, h, co, q));
+            return NP_OK;
+        }
+        // linked: the pre-smoothed iterate alternates between e and its partner, so that the last cycle's is
+        // in the partner and its up-leg ends in e
+        SL *tb[2] = {tt, e};
+        for (int c = 0; c < inner; ++c) {
+            const int p = (inner - 1 - c) & 1;
+            const typename O::Link ln{c > 0 ? tb[1 - p] : nullptr, tb[p], c + 1 < inner};
+            NP_TRY(O::cycle(H, e, rlo, tt, c == 0, false, h, co, q, nullptr, &ln));
+        }
         return NP_OK;
     };
     // graphs: the first update (x = x0); outer steps j = 1, 2, ...: the inner cycles, then
@@ -1674,7 +1771,7 @@ extern "C" np_status np_set_tuning(const char *key, int value) {
         {"batch", &g_tune.batch, 1, 64},        {"sweep3", &g_tune.sweep3, 0, 1},
         {"zero2", &g_tune.zero2, 0, 1},         {"psweep", &g_tune.psweep, 0, 1},
         {"ir_cpt", &g_tune.ir_cpt, 1, 2},      {"fuseb", &g_tune.fuseb, 0, 1}, {"fbnt", &g_tune.fbnt, 512, 1024},  {"sweep2z", &g_tune.sweep2z, 0, 1}, {"down2z", &g_tune.down2z, 0, 1}, {"blk2", &g_tune.blk2, 0, 1}, {"z2wg", &g_tune.z2wg, 0, 1}, {"greps", &g_tune.greps, 1, 8}, {"tailck", &g_tune.tailck, 0, 1}, {"one", &g_tune.one, 0, 1}, {"zbar", &g_tune.zbar, 1, 2}, {"d2cpt", &g_tune.d2cpt, 1, 2}, {"d2wg", &g_tune.d2wg, 0, 1024},
-        {"fbmax", &g_tune.fbmax, 5, 10},        {"w2min", &g_tune.w2min, 7, 14},
+        {"fbmax", &g_tune.fbmax, 5, 10},        {"w2min", &g_tune.w2min, 7, 14},        {"link", &g_tune.link, 8, 15},
         {"batched_graphs", &g_batched_graphs, 0, 1}, {"batched_autotune", &g_batched_autotune, 0, 1},
         {"batched_rm", &g_batched_rm, 0, 1},    {"batched_wg", &g_batched_wg, 64, 1 << 20},
         {"zmarch_explicit", &g_zmarch_explicit, 0, 1}, {"mom_rows", &g_mom_rows, 4, 8}, {"mom_ring", &g_mom_ring, 2, 3}, {"zc3", &g_zc3, 0, 64}, {"conv3z", &g_conv3z, 0, 64},
@@ -1737,6 +1834,7 @@ extern "C" int np_get_tuning(const char *key) {
     if (!std::strcmp(key, "d2wg")) return g_tune.d2wg;
     if (!std::strcmp(key, "fbmax")) return g_tune.fbmax;
     if (!std::strcmp(key, "w2min")) return g_tune.w2min;
+    if (!std::strcmp(key, "link")) return g_tune.link;
     if (!std::strcmp(key, "batched_graphs")) return g_batched_graphs;
     if (!std::strcmp(key, "batched_autotune")) return g_batched_autotune;
     if (!std::strcmp(key, "batched_rm")) return g_batched_rm;
@@ -2527,10 +2625,11 @@ static np_status ad_launch_prolong(const double *ec, double *x, int lg, int bc, 
 
 // One V(nu1, nu2) cycle of the operator on x (level 0 uses x, f and t[0]),
 // opened by the convergence check of the input iterate; every launch is
-// gated by the controller.  l1: record the change of x over the cycle.
+// gated by the controller.  l1: record the change of x over the cycle.  link: the finest up-leg runs with
+// the next cycle's down-leg (Ops::Link).
 template <int D>
 static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double *x, double h, const CycleOpts &co,
-                           bool l1, hipStream_t s) {
+                           bool l1, hipStream_t s, const typename Ops<D, double>::Link *link = nullptr) {
     const int L = H->L, bc = H->bc, lg0 = H->lg;
     const int *stop = &H->ctl->stop;
     const int64_t m0 = cells(D, lg0);
@@ -2586,6 +2685,17 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
             hipLaunchKernelGGL((k_zero<double>), dim3(blocks_for(m)), dim3(kBlock), 0, s, cur[l], m, stop);
             NP_LAUNCH_CHECK();
         }
+        if constexpr (D == 2) {
+            if (link && l == 0 && link->in) {
+                const Ad2 ao{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], wd};
+                unsigned nb = 0;
+                NP_TRY((launch_leg2<double, Ad2, 3, true>(true, (const double *)H->t[1], F[0], link->in, link->out,
+                                                          (double *)H->f[1], H->red, &nb, lg, bc, ao, s, stop, x)));
+                pend = int(nb);
+                continue;
+            }
+        }
+        if (link && l == 0) oth[0] = link->out;
         if (co.nu1 == 2 && ad_leg<D>(lg, l > 0 || al0, zero)) {
             // both pre-sweeps, the residual and its restriction in one pass
             int nb = 0;
@@ -2627,7 +2737,7 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
         NP_TRY(ad_launch_restrict<D>(F[l], cur[l], (double *)H->f[l + 1], lg, bc, W, s, stop));
         if (prof) NP_TRY(prof_end(s, tok, double(m) * (2 + 1.0 / (1 << D)) * sizeof(double)));
     }
-    for (int l = (tl > 0 ? tl : L) - 1; l >= 0; --l) {
+    for (int l = (tl > 0 ? tl : L) - 1; l >= (link ? 1 : 0); --l) {
         const int lg = lg0 - l;
         const int64_t m = cells(D, lg);
         const AdW W = ad_weights(op, D, h * double(int64_t(1) << l));
@@ -2650,6 +2760,13 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
             if (pj) NP_TRY(prof_end(s, tk, double(m) * 3 * sizeof(double)));
             std::swap(cur[l], oth[l]);
         }
+    }
+    if (link) {
+        if (cur[1] != (double *)H->t[1]) {
+            set_error("linked cycles: the next level's correction is not in its partner buffer");
+            return NP_EINVAL;
+        }
+        return NP_OK;
     }
     if (cur[0] != x) {
         hipLaunchKernelGGL((k_copy<double>), dim3(blocks_for(m0)), dim3(kBlock), 0, s, cur[0], x, m0, stop);
@@ -2725,11 +2842,32 @@ static np_status solve_ad(Hier *H, const np_ad_op &op, const double *f, double *
     NP_TRY(init_ctl(H, o, nf, tol, 0, 0.0, s));
     GraphKey key{o.cycle == 1 ? 7 : 6, o.prolong, 1, x, f, h, co.nu1, co.nu2, 0, co.omega,
                  {op.dt, op.nu, op.a[0], op.a[1], op.a[2]}, op.scheme, l1 ? 1 : 0};
-    int batch = o.fixed_cycles > 0 ? o.fixed_cycles + 1 : g_tune.batch;
+    int batch = o.fixed_cycles > 0 ? o.fixed_cycles + 1 : g_tune.batch, next = 0;
+    // linked cycles, as solve_fp64's
+    typedef Ops<D, double> O;
+    const bool linked = o.cycle == 0 && !l1 && O::link_on(H, co, aligned16(x, f)) && ensure_t0b(H);
+    auto link_cycle = [&](hipStream_t q, int j) -> np_status {
+        double *tb[2] = {(double *)H->t[0], H->t0b};
+        const typename O::Link ln{j > 0 ? tb[(j - 1) & 1] : nullptr, tb[j & 1], true};
+        return ad_vcycle<D>(H, op, f, x, h, co, l1, q, &ln);
+    };
+    if (linked) {
+        key.kind = 13;
+        NP_TRY(run_graph(H, key, s, [&](hipStream_t q) { return link_cycle(q, 0); }));
+        key.kind = 12;
+        next = 1;
+        batch = std::max(1, batch - 1);
+    }
     for (;;) {
-        NP_TRY(run_graphs(H, key, s, batch, 0, false, [&](hipStream_t q, int) {
-            return o.cycle == 1 ? ad_saw_cycle<D>(H, op, f, x, h, o, l1, q) : ad_vcycle<D>(H, op, f, x, h, co, l1, q);
-        }));
+        if (linked) {
+            NP_TRY(run_graphs(H, key, s, batch, next, true, link_cycle));
+        } else {
+            NP_TRY(run_graphs(H, key, s, batch, 0, false, [&](hipStream_t q, int) {
+                return o.cycle == 1 ? ad_saw_cycle<D>(H, op, f, x, h, o, l1, q)
+                                    : ad_vcycle<D>(H, op, f, x, h, co, l1, q);
+            }));
+        }
+        next += batch;
         NP_TRY(read_ctl(H, s));
         if (H->hctl->stop) break;
         batch = next_batch(*H->hctl, o, false);

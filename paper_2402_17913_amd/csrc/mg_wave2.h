@@ -11,13 +11,16 @@
 //  - MODE 1 (down-leg of an iterate): two sweeps, the residual and its
 //    restriction; NORM also sums |f - A x|^2 of the input iterate;
 //  - MODE 2 (up-leg): prolongation + correction, formed where the first sweep
-//    reads it and rounded to storage, and both post-sweeps.
+//    reads it and rounded to storage, and both post-sweeps;
+//  - MODE 3: MODE 2 of one cycle and MODE 1 of the next in one pass, for the
+//    finest level of consecutive cycles.
 // What bounds it: memory.  A leg reads its operands once (ghost lanes 3 or 6%,
 // four to six rows per chunk again) against three or more passes of the
 // per-stage kernels, and keeps four rows of every operand in flight per wave.
 // Measured, whole solves against the per-stage kernels: 2048^2 Poisson FP64 3.03
 // -> 1.76 ms, 4096^2 twelve FP64 cycles 9.83 -> 4.06 ms, 4096^2 advection-diffusion
 // 11.9 -> 5.83 ms; at 1024^2 against blocks a projection step 1.33 -> 1.26 ms.
+// MODE 3 for MODE 2 and MODE 1: twelve FP64 cycles at 4096^2 3.93 -> 3.36 ms.
 // A value outside the grid is minus the cell's own value of that stage
 // (Dirichlet; selected next to the wall, never computed) or the wrapped cell's
 // (periodic: wrapped lanes and rows are computed like any other).  Terms, their
@@ -78,12 +81,14 @@ template <class S, int N> struct Run {
 };
 
 // Columns: CPL cells per lane (16 bytes in FP64 and FP32); GL ghost lanes per
-// side.  MODE 0 reads two cells beyond its own, MODE 1 three, and MODE 2 two,
-// whose outer one takes the coarse value of the lane beyond when CPL is 2.
+// side.  MODE 0 reads two cells beyond its own, MODE 1 three, MODE 2 two,
+// whose outer one takes the coarse value of the lane beyond when CPL is 2, and
+// MODE 3 five.
 template <class S, int MODE> struct W2 {
     static constexpr int CPL = sizeof(S) == 8 ? 2 : 4;
-    static constexpr int GL = MODE != 0 && CPL == 2 ? 2 : 1;
+    static constexpr int GL = MODE == 3 ? (CPL == 2 ? 3 : 2) : (MODE != 0 && CPL == 2 ? 2 : 1);
 };
+template <int I> using Row = std::integral_constant<int, I>;  // a step of an unrolled row loop
 constexpr int kW2T = 256;  // threads per workgroup: four wavefronts on adjacent strips
 
 // Strips of an n x n level: `gl` ghost lanes per side, none where one wavefront
@@ -104,7 +109,7 @@ template <class S, class OP, int MODE, bool NORM>
 __device__ __forceinline__ double wave2_leg(const S *__restrict__ ec, const S *__restrict__ f,
                                             const S *__restrict__ xin, S *__restrict__ xout, S *__restrict__ fc,
                                             int lg, int bc, int c0, int gl, int j0, int j1,
-                                            const OP &op) {
+                                            const OP &op, S *__restrict__ xmid = nullptr) {
     typedef typename St<S>::C C;
     typedef W2<S, MODE> G;
     constexpr int N = G::CPL, NC = N / 2;
@@ -149,7 +154,45 @@ __device__ __forceinline__ double wave2_leg(const S *__restrict__ ec, const S *_
             if (own) Run<S, NC>::st(fc + ((uint32_t(r >> 1) << (lg - 1)) + uint32_t(col >> 1)), o);
         }
     };
-    C F[6][N];
+    C F[MODE == 3 ? 12 : 6][N];
+    // the correction of modes 2 and 3: coarse values in E, x' = x + P ec of row q into x, where eo and en are
+    // the coarse rows of q and its neighbour
+    [[maybe_unused]] const int lgc = lg - 1, nc = n >> 1, lastc = nc - 1, colc = col >> 1;  // col: a multiple of N
+    [[maybe_unused]] const int lcc = bc ? (colc & lastc) : min(max(colc, 0), nc - NC);
+    auto rowc = [&](int r) -> uint32_t {
+        const int q = bc ? (r & lastc) : min(max(r, 0), lastc);
+        return (uint32_t(q) << lgc) + uint32_t(lcc);
+    };
+    typedef Run<S, NC> VC;
+    auto correct = [&](int q, const C (&eo)[NC], const C (&en)[NC], C (&x)[N]) {
+        const C w00 = C(0.75) * C(0.75) * C(1.0), w01 = C(0.25) * C(0.75) * C(1.0);
+        const C w10 = C(0.75) * C(0.25) * C(1.0), w11 = C(0.25) * C(0.25) * C(1.0);
+        const bool g = dir && (q == 0 || q == last);  // neighbour row outside: minus the own row
+        C e[NC], h[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            e[c] = eo[c];
+            h[c] = g ? -eo[c] : en[c];
+        }
+        const C el = lane_dn(e[NC - 1]), er = lane_up(e[0]), hl = lane_dn(h[NC - 1]), hr = lane_up(h[0]);
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            const int k = c >> 1;
+            C a, b;  // the neighbour coarse column's values
+            if (!(c & 1)) {
+                a = k > 0 ? e[k > 0 ? k - 1 : 0] : (west ? -e[0] : el);
+                b = k > 0 ? h[k > 0 ? k - 1 : 0] : (west ? -h[0] : hl);
+            } else {
+                a = k < NC - 1 ? e[k < NC - 1 ? k + 1 : 0] : (east ? -e[NC - 1] : er);
+                b = k < NC - 1 ? h[k < NC - 1 ? k + 1 : 0] : (east ? -h[NC - 1] : hr);
+            }
+            C p = np_fma(w00, e[k], C(0));
+            p = np_fma(w01, a, p);
+            p = np_fma(w10, h[k], p);
+            p = np_fma(w11, b, p);
+            x[c] = st_round<S>(x[c] + p);
+        }
+    };
     if constexpr (MODE == 0) {
         // step z: second sweep of row z from w f of rows z - 1 .. z + 1, residual of row z - 1
         C B[3][N];
@@ -227,17 +270,10 @@ __device__ __forceinline__ double wave2_leg(const S *__restrict__ ec, const S *_
                 V::ld(f + rowp(min(z + 4, j1 + 1)), F[u]);
             }
         }
-    } else {
+    } else if constexpr (MODE == 2) {
         // step z: x' of row z + 1, first sweep of row z, second of row z - 1 (stored)
         C X[6][N], A[3][N];
         const int z0 = j0 - 3, z1 = j1 + 1;
-        const int lgc = lg - 1, nc = n >> 1, lastc = nc - 1, colc = col >> 1;  // col is a multiple of N: floor
-        const int lcc = bc ? (colc & lastc) : min(max(colc, 0), nc - NC);
-        auto rowc = [&](int r) -> uint32_t {
-            const int q = bc ? (r & lastc) : min(max(r, 0), lastc);
-            return (uint32_t(q) << lgc) + uint32_t(lcc);
-        };
-        typedef Run<S, NC> VC;
         C E[3][NC];
         const int K0 = (j0 - 2) >> 1;
 #pragma unroll
@@ -251,8 +287,6 @@ __device__ __forceinline__ double wave2_leg(const S *__restrict__ ec, const S *_
         for (int q = 0; q < 3; ++q)
 #pragma unroll
             for (int c = 0; c < N; ++c) A[q][c] = C(0);
-        const C w00 = C(0.75) * C(0.75) * C(1.0), w01 = C(0.25) * C(0.75) * C(1.0);
-        const C w10 = C(0.75) * C(0.25) * C(1.0), w11 = C(0.25) * C(0.25) * C(1.0);
         for (int zz = z0; zz < z1; zz += 6) {
 #pragma unroll
             for (int u = 0; u < 6; ++u) {
@@ -262,34 +296,7 @@ __device__ __forceinline__ double wave2_leg(const S *__restrict__ ec, const S *_
                 {
                     constexpr int dn[6] = {0, 2, 1, 0, 2, 1};  // slot of the neighbour row
                     const int q = z + 1;
-                    const C(&eo)[NC] = E[((u >> 1) + 1) % 3];
-                    const C(&en)[NC] = E[dn[u]];
-                    const bool g = dir && (q == 0 || q == last);  // neighbour row outside: minus the own row
-                    C e[NC], h[NC];
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        e[c] = eo[c];
-                        h[c] = g ? -eo[c] : en[c];
-                    }
-                    const C el = lane_dn(e[NC - 1]), er = lane_up(e[0]), hl = lane_dn(h[NC - 1]), hr = lane_up(h[0]);
-                    C(&x)[N] = X[(u + 2) % 6];
-#pragma unroll
-                    for (int c = 0; c < N; ++c) {
-                        const int k = c >> 1;
-                        C a, b;  // the neighbour coarse column's values
-                        if (!(c & 1)) {
-                            a = k > 0 ? e[k > 0 ? k - 1 : 0] : (west ? -e[0] : el);
-                            b = k > 0 ? h[k > 0 ? k - 1 : 0] : (west ? -h[0] : hl);
-                        } else {
-                            a = k < NC - 1 ? e[k < NC - 1 ? k + 1 : 0] : (east ? -e[NC - 1] : er);
-                            b = k < NC - 1 ? h[k < NC - 1 ? k + 1 : 0] : (east ? -h[NC - 1] : hr);
-                        }
-                        C p = np_fma(w00, e[k], C(0));
-                        p = np_fma(w01, a, p);
-                        p = np_fma(w10, h[k], p);
-                        p = np_fma(w11, b, p);
-                        x[c] = st_round<S>(x[c] + p);
-                    }
+                    correct(q, E[((u >> 1) + 1) % 3], E[dn[u]], X[(u + 2) % 6]);
                     if (u & 1) VC::ld(ec + rowc(min((q >> 1) + 2, (j1 >> 1) + 1)), E[(u >> 1) % 3]);
                 }
                 if (z >= j0 - 1) {
@@ -311,6 +318,78 @@ __device__ __forceinline__ double wave2_leg(const S *__restrict__ ec, const S *_
                 V::ld(f + rowp(min(z + 5, j1)), F[u]);
             }
         }
+    } else {
+        // the up-leg of one cycle and the down-leg of the next.  Step z: x' of row z + 1; post-sweeps of rows z and
+        // z - 1 (the cycle's iterate, to xmid where that is asked for); its residual norm and the first pre-sweep of
+        // row z - 2; the second of row z - 3 (stored); the residual of row z - 4
+        C X[6][N], A[3][N], B[3][N], P[3][N], Q[3][N], E[3][NC];
+        const int z0 = j0 - 7, z1 = j1 + 4, K0 = (j0 - 6) >> 1;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) V::ld(xin + rowp(z0 - 1 + q), X[q]);
+#pragma unroll
+        for (int q = 0; q < 7; ++q) V::ld(f + rowp(z0 + q), F[q]);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) VC::ld(ec + rowc(K0 - 1 + q), E[q]);
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int c = 0; c < N; ++c) A[q][c] = B[q][c] = P[q][c] = Q[q][c] = C(0);
+#pragma unroll
+        for (int q = 7; q < 12; ++q)
+#pragma unroll
+            for (int c = 0; c < N; ++c) F[q][c] = C(0);
+        auto step = [&](int z, auto uc) __attribute__((always_inline)) {
+            constexpr int u = decltype(uc)::value;
+            constexpr int dn[6] = {0, 2, 1, 0, 2, 1};  // slot of the neighbour coarse row
+            const int q = z + 1;
+            correct(q, E[((u >> 1) + 1) % 3], E[dn[u % 6]], X[(u + 2) % 6]);
+            if (u & 1) VC::ld(ec + rowc(min((q >> 1) + 2, (j1 >> 1) + 3)), E[(u >> 1) % 3]);
+            if (z >= j0 - 5) {
+                C r[N];
+                // row z - d of a stage is row z - d + 1 of the one before it, at its middle; f of row z - d is
+                // F[(u - d) mod 12]
+                resid(X[(u + 1) % 6], X[u % 6], X[(u + 2) % 6], F[u], dir && z == 0, dir && z == last, r);
+                C(&a)[N] = A[u % 3];
+#pragma unroll
+                for (int c = 0; c < N; ++c) a[c] = st_round<S>(X[(u + 1) % 6][c] + op.wd * r[c]);
+                const C(&am)[N] = A[(u + 2) % 3];
+                resid(am, A[(u + 1) % 3], a, F[(u + 11) % 12], dir && z == 1, dir && z == n, r);
+                C(&b)[N] = B[u % 3];
+#pragma unroll
+                for (int c = 0; c < N; ++c) b[c] = st_round<S>(am[c] + op.wd * r[c]);
+                if (xmid && own && z > j0 && z <= j1) V::st(xmid + ((uint32_t(z - 1) << lg) + uint32_t(col)), b);
+                if (z >= j0) {
+                    const C(&bm)[N] = B[(u + 2) % 3];
+                    resid(bm, B[(u + 1) % 3], b, F[(u + 10) % 12], dir && z == 2, dir && z == n + 1, r);
+                    if (NORM && own && z >= j0 + 2 && z < j1 + 2) {
+#pragma unroll
+                        for (int c = 0; c < N; ++c) acc += double(r[c]) * double(r[c]);
+                    }
+                    C(&p)[N] = P[u % 3];
+#pragma unroll
+                    for (int c = 0; c < N; ++c) p[c] = st_round<S>(bm[c] + op.wd * r[c]);
+                    const C(&pm)[N] = P[(u + 2) % 3];
+                    resid(pm, P[(u + 1) % 3], p, F[(u + 9) % 12], dir && z == 3, dir && z == n + 2, r);
+                    C(&s)[N] = Q[u % 3];
+#pragma unroll
+                    for (int c = 0; c < N; ++c) s[c] = st_round<S>(pm[c] + op.wd * r[c]);
+                    if (own && z >= j0 + 3 && z < j1 + 3) V::st(xout + ((uint32_t(z - 3) << lg) + uint32_t(col)), s);
+                    if (z >= j0 + 4) {
+                        resid(Q[(u + 2) % 3], Q[(u + 1) % 3], s, F[(u + 8) % 12], dir && z == 4, dir && z == n + 3,
+                              r);
+                        restrict_row(z - 4, r);
+                    }
+                }
+            }
+            V::ld(xin + rowp(min(z + 5, j1 + 4)), X[u % 6]);
+            V::ld(f + rowp(min(z + 7, j1 + 3)), F[(u + 7) % 12]);
+        };
+        auto steps = [&](int zz, auto... uc) __attribute__((always_inline)) {
+            ((zz + uc.value < z1 ? step(zz + uc.value, uc) : void()), ...);
+        };
+        for (int zz = z0; zz < z1; zz += 12)
+            steps(zz, Row<0>{}, Row<1>{}, Row<2>{}, Row<3>{}, Row<4>{}, Row<5>{}, Row<6>{}, Row<7>{}, Row<8>{}, Row<9>{},
+                  Row<10>{}, Row<11>{});
     }
     return acc;
 }
@@ -330,7 +409,7 @@ template <class S, class OP, int MODE, bool NORM>
 __global__ __launch_bounds__(kW2T) void k_wave2(const S *__restrict__ ec, const S *__restrict__ f,
                                                 const S *__restrict__ xin, S *__restrict__ xout, S *__restrict__ fc,
                                                 double *__restrict__ partial, int lg, int bc, int ry, OP op,
-                                                const int *stop) {
+                                                const int *stop, S *__restrict__ xmid) {
     if (stop && *stop) return;
     const int n = 1 << lg;
     const W2Strips t = w2_strips<S, MODE>(n, bc);
@@ -338,7 +417,8 @@ __global__ __launch_bounds__(kW2T) void k_wave2(const S *__restrict__ ec, const 
                                                  (int(threadIdx.x) >> 6));
     const int c0 = (w % t.count) * t.cols, j0 = (w / t.count) * ry;
     double acc = 0.0;
-    if (j0 < n) acc = wave2_leg<S, OP, MODE, NORM>(ec, f, xin, xout, fc, lg, bc, c0, t.gl, j0, min(j0 + ry, n), op);
+    if (j0 < n) acc = wave2_leg<S, OP, MODE, NORM>(ec, f, xin, xout, fc, lg, bc, c0, t.gl, j0, min(j0 + ry, n), op,
+                                                 xmid);
     if constexpr (NORM) {
         acc = block_sum_n<kW2T>(acc);
         if (threadIdx.x == 0) partial[blockIdx.x] = acc;
