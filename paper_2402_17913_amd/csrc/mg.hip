@@ -284,10 +284,10 @@ static np_status ensure_levels(Hier *H) {
 }
 
 // The second partner of the level-0 iterate, allocated on first use; false without memory for it (the
-// cycles then run unlinked).
+// cycles then run unlinked), as in a static workspace, which allocates nothing.
 static bool ensure_t0b(Hier *H) {
     if (H->t0b) return true;
-    if (H->t0b_none) return false;
+    if (H->t0b_none || H->direct) return false;
     if (hipMalloc((void **)&H->t0b, sizeof(double) * size_t(cells(H->d, H->lg))) != hipSuccess) {
         (void)hipGetLastError();
         H->t0b = nullptr;
