@@ -1278,11 +1278,32 @@ static np_status dsum(Hier *H, const double *v, int64_t m, int square, int slot,
     return NP_OK;
 }
 
-static np_status remove_mean(Hier *H, double *v, int64_t m, hipStream_t s) {
+// dst = v - mean(v); dst may be v.
+static np_status remove_mean(Hier *H, const double *v, double *dst, int64_t m, hipStream_t s) {
     NP_TRY(dsum(H, v, m, 0, 7, s));
-    hipLaunchKernelGGL(k_sub_scaled, dim3(blocks_for(m)), dim3(kBlock), 0, s, v, m, H->red + kPartials + 7,
+    hipLaunchKernelGGL(k_sub_scaled, dim3(blocks_for(m)), dim3(kBlock), 0, s, v, dst, m, H->red + kPartials + 7,
                        1.0 / double(m));
     NP_LAUNCH_CHECK();
+    return NP_OK;
+}
+
+// |v| (of v - mean(v), written to cen, when that is given) into scalar slot 0, by way of *np partials in
+// H->red; lo: the field (less its mean) rounded to S as well, unless null.
+template <class S>
+static np_status norm_round(Hier *H, const double *v, int64_t m, S *lo, double *cen, unsigned *np, hipStream_t s) {
+    const unsigned nb = std::min<unsigned>(kRedBlocks, blocks_for(m));
+    if (cen) {
+        NP_TRY(dsum(H, v, m, 0, 7, s));
+        hipLaunchKernelGGL((k_sum_round<S, true>), dim3(nb), dim3(kBlock), 0, s, v, m, lo, cen,
+                           H->red + kPartials + 7, 1.0 / double(m), H->red);
+    } else {
+        hipLaunchKernelGGL((k_sum_round<S, false>), dim3(nb), dim3(kBlock), 0, s, v, m, lo, nullptr, nullptr, 0.0,
+                           H->red);
+    }
+    NP_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kBlock), 0, s, H->red, int(nb), H->red + kPartials, 1);
+    NP_LAUNCH_CHECK();
+    *np = nb;
     return NP_OK;
 }
 
@@ -1367,6 +1388,9 @@ static np_status solve_fp64(Hier *H, const double *f, double *x, double h, doubl
     double *t0 = (double *)H->t[0];
     np_status st0;
     if (x_zero && stop_before_first(o, tol, &st0)) {
+        hipLaunchKernelGGL((k_zero<double>), dim3(blocks_for(cells(D, H->lg))), dim3(kBlock), 0, s, x,
+                           cells(D, H->lg), nullptr);
+        NP_LAUNCH_CHECK();
         Ctl c{};
         c.nhist = 1;
         c.hist[0] = 1.0;
@@ -1573,9 +1597,10 @@ template <int D, class SL>
 // part0 (np0 partials of |f|^2, with f already rounded into the low-precision
 // right-hand side): the solve starts from a zero iterate that x does not hold --
 // the first check reads those partials, and the first update reads no iterate.
+// *last: the buffer of the last iterate, x or H->x64.
 static np_status solve_mixed(Hier *H, const double *f, double *x, double h, double tol, const np_mg_opts &o,
                              const CycleOpts &co, hipStream_t s, double nf, bool warm, np_mg_stats *stats,
-                             const double *part0 = nullptr, int np0 = 0) {
+                             const double **last, const double *part0 = nullptr, int np0 = 0) {
     typedef Ops<D, SL> O;
     NP_TRY(ensure_levels(H));
     const int64_t m = cells(D, H->lg);
@@ -1698,7 +1723,7 @@ static np_status solve_mixed(Hier *H, const double *f, double *x, double h, doub
         NP_LAUNCH_CHECK();
     }
     // the iterate whose residual was checked last: x_a after an even number of updates
-    if (c.k & 1) NP_HIP_TRY(hipMemcpyAsync(x, xb, sizeof(double) * m, hipMemcpyDeviceToDevice, s));
+    *last = (c.k & 1) ? xb : xa;
     fill_stats(stats, c, c.k * inner, c.k);
     return status_of(c, tol);
 }
@@ -1923,9 +1948,7 @@ np_status poisson_solve(np_dims dims, double h, np_bc bc, const double *rhs, dou
     const double *f = rhs;
     if (bc == NP_BC_PERIODIC) {
         if (!H->f64) NP_TRY(dmalloc((void **)&H->f64, sizeof(double) * m));
-        NP_HIP_TRY(hipMemcpyAsync(H->f64, rhs, sizeof(double) * m, hipMemcpyDeviceToDevice, s));
-        NP_TRY(remove_mean(H, H->f64, m, s));
-        f = H->f64;
+        f = H->f64;  // rhs less its mean, written with its norm below
     }
     // The 3D mixed solve from a zero iterate on z-marching levels (n >= 128): its first
     // residual is f itself, so the norm's pass also rounds f into the low-precision
@@ -1934,18 +1957,13 @@ np_status poisson_solve(np_dims dims, double h, np_bc bc, const double *rhs, dou
     const bool cold = HL && o.warm_start == 0 && o.cycle == 0 && d == 3 && lg >= 7 && g_tune.sweep3 &&
                       g_tune.ir_cpt == 2;
     unsigned np0 = 0;
+    double *cen = bc == NP_BC_PERIODIC ? H->f64 : nullptr;
     if (cold) {
         NP_TRY(ensure_levels(HL));
-        np0 = std::min<unsigned>(kRedBlocks, blocks_for(m));
-        if (o.smooth_prec == NP_FP32)
-            hipLaunchKernelGGL((k_sum_round<float>), dim3(np0), dim3(kBlock), 0, s, f, m, (float *)HL->f[0], H->red);
-        else
-            hipLaunchKernelGGL((k_sum_round<bf16>), dim3(np0), dim3(kBlock), 0, s, f, m, (bf16 *)HL->f[0], H->red);
-        NP_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kBlock), 0, s, H->red, int(np0), H->red + kPartials, 1);
-        NP_LAUNCH_CHECK();
+        if (o.smooth_prec == NP_FP32) NP_TRY(norm_round(H, rhs, m, (float *)HL->f[0], cen, &np0, s));
+        else NP_TRY(norm_round(H, rhs, m, (bf16 *)HL->f[0], cen, &np0, s));
     } else {
-        NP_TRY(dsum(H, f, m, 1, 0, s));
+        NP_TRY(norm_round(H, rhs, m, (float *)nullptr, cen, &np0, s));
     }
     NP_TRY(read_scalars(H, 1, s));
     const double nf = H->hred[0];
@@ -1954,7 +1972,8 @@ np_status poisson_solve(np_dims dims, double h, np_bc bc, const double *rhs, dou
         return NP_ENAN;
     }
     bool warm = o.warm_start == 2;
-    if (nf == 0.0 || (!warm && !cold)) {
+    // (the FP64 V-cycles' first cycle reads no zero iterate and writes x)
+    if (nf == 0.0 || (!warm && !cold && (HL || o.cycle != 0 || o.warm_start == 1))) {
         hipLaunchKernelGGL((k_zero<double>), dim3(blocks_for(m)), dim3(kBlock), 0, s, x, m, nullptr);
         NP_LAUNCH_CHECK();
     }
@@ -1973,7 +1992,7 @@ np_status poisson_solve(np_dims dims, double h, np_bc bc, const double *rhs, dou
         bool used = false;
         NP_TRY(cnn_warm_start(d, lg, bc, f, x, H->f, H->x, nullptr, s, &used));
         if (used) {
-            if (bc == NP_BC_PERIODIC) NP_TRY(remove_mean(H, x, m, s));
+            if (bc == NP_BC_PERIODIC) NP_TRY(remove_mean(H, x, x, m, s));
             int nb = 0;
             if (d == 2) NP_TRY((Ops<2, double>::energy(f, x, lg, bc, h, H->red, s, &nb)));
             else NP_TRY((Ops<3, double>::energy(f, x, lg, bc, h, H->red, s, &nb)));
@@ -1991,6 +2010,7 @@ np_status poisson_solve(np_dims dims, double h, np_bc bc, const double *rhs, dou
         fallback = used ? 0 : 1;
     }
     np_status st;
+    const double *last = x;
     if (o.cycle == 1) {
         st = d == 2 ? solve_saw<2>(H, f, x, h, tol, o, s, nf, stats)
                     : solve_saw<3>(H, f, x, h, tol, o, s, nf, stats);
@@ -1998,17 +2018,19 @@ np_status poisson_solve(np_dims dims, double h, np_bc bc, const double *rhs, dou
         st = d == 2 ? solve_fp64<2>(H, f, x, h, tol, o, co, s, !warm, nf, stats)
                     : solve_fp64<3>(H, f, x, h, tol, o, co, s, !warm, nf, stats);
     } else if (o.smooth_prec == NP_FP32) {
-        st = d == 2 ? solve_mixed<2, float>(HL, f, x, h, tol, o, co, s, nf, warm, stats)
-                    : solve_mixed<3, float>(HL, f, x, h, tol, o, co, s, nf, warm, stats, cold ? H->red : nullptr,
-                                            int(np0));
+        st = d == 2 ? solve_mixed<2, float>(HL, f, x, h, tol, o, co, s, nf, warm, stats, &last)
+                    : solve_mixed<3, float>(HL, f, x, h, tol, o, co, s, nf, warm, stats, &last,
+                                            cold ? H->red : nullptr, int(np0));
     } else {
-        st = d == 2 ? solve_mixed<2, bf16>(HL, f, x, h, tol, o, co, s, nf, warm, stats)
-                    : solve_mixed<3, bf16>(HL, f, x, h, tol, o, co, s, nf, warm, stats, cold ? H->red : nullptr,
-                                           int(np0));
+        st = d == 2 ? solve_mixed<2, bf16>(HL, f, x, h, tol, o, co, s, nf, warm, stats, &last)
+                    : solve_mixed<3, bf16>(HL, f, x, h, tol, o, co, s, nf, warm, stats, &last,
+                                           cold ? H->red : nullptr, int(np0));
     }
     if (st == NP_EHIP || st == NP_ENOMEM || st == NP_EINVAL) return st;
     if (stats) stats->used_fallback = fallback;
-    if (bc == NP_BC_PERIODIC) NP_TRY(remove_mean(H, x, m, s));
+    // the refinement's last iterate may be in its second buffer
+    if (bc == NP_BC_PERIODIC) NP_TRY(remove_mean(H, last, x, m, s));
+    else if (last != x) NP_HIP_TRY(hipMemcpyAsync(x, last, sizeof(double) * m, hipMemcpyDeviceToDevice, s));
     NP_HIP_TRY(hipStreamSynchronize(s));
     return st;
 }
@@ -2129,32 +2151,26 @@ extern "C" np_status mg_poisson_solve_noalloc(np_dims dims, double h, np_bc bc, 
     if (one_on(d, lg, tol, o))
         return d == 2 ? solve_one<2>(&H, lg, bc, rhs, x, h, tol, o, s, stats)
                       : solve_one<3>(&H, lg, bc, rhs, x, h, tol, o, s, stats);
-    const double *f = rhs;
-    if (bc == NP_BC_PERIODIC) {
-        NP_HIP_TRY(hipMemcpyAsync(H.f64, rhs, sizeof(double) * m, hipMemcpyDeviceToDevice, s));
-        NP_TRY(remove_mean(&H, H.f64, m, s));
-        f = H.f64;
-    }
-    NP_TRY(dsum(&H, f, m, 1, 0, s));
+    const double *f = bc == NP_BC_PERIODIC ? H.f64 : rhs;
+    unsigned np0 = 0;
+    NP_TRY(norm_round(&H, rhs, m, (float *)nullptr, bc == NP_BC_PERIODIC ? H.f64 : nullptr, &np0, s));
     NP_TRY(read_scalars(&H, 1, s));
     const double nf = hred[0];
     if (!std::isfinite(nf)) {
         set_error("non-finite right-hand side");
         return NP_ENAN;
     }
-    const bool warm = o.warm_start == 2 && nf != 0.0;
-    if (!warm) {
+    const bool warm = o.warm_start == 2;
+    if (nf == 0.0) {
         hipLaunchKernelGGL((k_zero<double>), dim3(blocks_for(m)), dim3(kBlock), 0, s, x, m, nullptr);
         NP_LAUNCH_CHECK();
-    }
-    if (nf == 0.0) {
         NP_HIP_TRY(hipStreamSynchronize(s));
         return NP_OK;
     }
     np_status st = d == 2 ? solve_fp64<2>(&H, f, x, h, tol, o, co, s, !warm, nf, stats)
                           : solve_fp64<3>(&H, f, x, h, tol, o, co, s, !warm, nf, stats);
     if (st == NP_EHIP || st == NP_ENOMEM || st == NP_EINVAL) return st;
-    if (bc == NP_BC_PERIODIC) NP_TRY(remove_mean(&H, x, m, s));
+    if (bc == NP_BC_PERIODIC) NP_TRY(remove_mean(&H, x, x, m, s));
     NP_HIP_TRY(hipStreamSynchronize(s));
     return st;
 }

@@ -266,34 +266,54 @@ __global__ __launch_bounds__(kBlock) void k_energy(const S *__restrict__ f, cons
     if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
 
+// use(c, ld(c)) for this thread's cells c of a grid-strided pass over m, in order, four loads in flight.
+template <class Ld, class Use> __device__ __forceinline__ void strided4(int64_t m, Ld &&ld, Use &&use) {
+    const int64_t st = int64_t(gridDim.x) * blockDim.x;
+    int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    for (; c + 3 * st < m; c += 4 * st) {
+        const double a0 = ld(c), a1 = ld(c + st), a2 = ld(c + 2 * st), a3 = ld(c + 3 * st);
+        use(c, a0);
+        use(c + st, a1);
+        use(c + 2 * st, a2);
+        use(c + 3 * st, a3);
+    }
+    for (; c < m; c += st) use(c, ld(c));
+}
+
 // Partial sums of v (square = 0) or v^2 (square = 1) in FP64.
 template <class S>
 __global__ __launch_bounds__(kBlock) void k_sum(const S *__restrict__ v, int64_t m, int square,
                                                 double *__restrict__ partial) {
     double acc = 0.0;
-    for (int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; c < m;
-         c += int64_t(gridDim.x) * blockDim.x) {
-        const double a = double(St<S>::ld(v + c));
-        acc += square ? a * a : a;
-    }
+    strided4(m, [&](int64_t c) { return double(St<S>::ld(v + c)); },
+             [&](int64_t, double a) { acc += square ? a * a : a; });
     acc = block_sum(acc);
     if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
 
-// k_sum's squared-norm partials of an FP64 field (the same order) and the field
-// rounded to the storage S: the mixed solve's first residual r = f, and its
-// check, when the iterate starts at zero.
-template <class S>
+// k_sum's squared-norm partials of an FP64 field (the same order), in the same
+// pass minus its mean into `cen` (MEAN: sum[0] * scale is the mean), or rounded
+// to the storage S into `lo` (null: not): the mixed solve's first residual r = f,
+// and its check, when the iterate starts at zero.  A periodic 256^3 right-hand
+// side went through a copy, a subtraction and this kernel on the copy, and the solution
+// through a copy: a 256^3 BF16-mixed projection step 5.33 -> 5.23 ms.
+template <class S, bool MEAN>
 __global__ __launch_bounds__(kBlock) void k_sum_round(const double *__restrict__ v, int64_t m,
-                                                      S *__restrict__ lo, double *__restrict__ partial) {
+                                                      S *__restrict__ lo, double *__restrict__ cen,
+                                                      const double *__restrict__ sum, double scale,
+                                                      double *__restrict__ partial) {
     typedef typename St<S>::C C;
-    double acc = 0.0;
-    for (int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; c < m;
-         c += int64_t(gridDim.x) * blockDim.x) {
-        const double a = v[c];
-        acc += a * a;
-        St<S>::st(lo + c, C(a));
-    }
+    double acc = 0.0, mean = 0.0;
+    if constexpr (MEAN) mean = sum[0];
+    strided4(m, [&](int64_t c) { return v[c]; },
+             [&](int64_t c, double a) {
+                 if constexpr (MEAN) {
+                     a -= mean * scale;
+                     cen[c] = a;
+                 }
+                 acc += a * a;
+                 if (lo) St<S>::st(lo + c, C(a));
+             });
     acc = block_sum(acc);
     if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
@@ -307,11 +327,11 @@ static __global__ __launch_bounds__(kBlock) void k_finalize(const double *__rest
     if (threadIdx.x == 0) out[0] = root ? sqrt(acc) : acc;
 }
 
-// v[c] -= sum[0] * scale (mean removal with the sum left on the device).
-static __global__ __launch_bounds__(kBlock) void k_sub_scaled(double *__restrict__ v, int64_t m,
+// dst = v - sum[0] * scale (mean removal with the sum left on the device); dst may be v.
+static __global__ __launch_bounds__(kBlock) void k_sub_scaled(const double *v, double *dst, int64_t m,
                                                        const double *__restrict__ sum, double scale) {
     const int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (c < m) v[c] -= sum[0] * scale;
+    if (c < m) dst[c] = v[c] - sum[0] * scale;
 }
 
 // FP64 refinement step of the mixed-precision solve: x_out = x + e (e in the
