@@ -201,8 +201,8 @@ __global__ __launch_bounds__(kS3Threads) void k_sweep2z(const S *__restrict__ ec
         else return st_round<S>(v + prolong_mix(a1, a0));
     };
     // a sweep at an LDS position of plane z (in-plane neighbours from Ax), z-neighbours given
-    auto sweep1 = [&](const C *A, int q, C xc, C xm, C xp, C fv, C &r) -> C {
-        r = op.resid(fv, xc, A[q - 1], A[q + 1], A[q - W2], A[q + W2], xm, xp);
+    auto sweep1 = [&](const C *A, int q, C xc, C xw, C xe, C xm, C xp, C fv, C &r) -> C {
+        r = op.resid(fv, xc, xw, xe, A[q - W2], A[q + W2], xm, xp);
         return xc + op.wd * r;
     };
 
@@ -307,13 +307,16 @@ __global__ __launch_bounds__(kS3Threads) void k_sweep2z(const S *__restrict__ ec
         C sn[CPT];
         for (int c = 0; c < CPT; ++c) {
             C r;
-            sn[c] = st_round<S>(sweep1(A, own_a + c, xo[1][c], xo[0][c], xo[2][c], fo[0][c], r));
+            const int q = own_a + c;
+            const C xw = c > 0 ? xo[1][c > 0 ? c - 1 : 0] : A[q - 1];  // the pair's other cell is in a register
+            const C xe = c + 1 < CPT ? xo[1][c + 1 < CPT ? c + 1 : 0] : A[q + 1];
+            sn[c] = st_round<S>(sweep1(A, q, xo[1][c], xw, xe, xo[0][c], xo[2][c], fo[0][c], r));
             if (NORM && z >= k0 && z < k0 + zc) acc += double(r) * double(r);
             B[own_b + c] = sn[c];
         }
         if (r1) {
             C r;
-            B[ring_b] = st_round<S>(sweep1(A, ring_a, rx1, rx0, rx2, rf, r));
+            B[ring_b] = st_round<S>(sweep1(A, ring_a, rx1, A[ring_a - 1], A[ring_a + 1], rx0, rx2, rf, r));
         }
         if constexpr (!ONE) __syncthreads();
         // second sweep of plane z - 1, own cells (its first sweep was written by the previous step)
@@ -325,7 +328,9 @@ __global__ __launch_bounds__(kS3Threads) void k_sweep2z(const S *__restrict__ ec
             for (int c = 0; c < CPT; ++c) {
                 const int q = own_b + c;
                 const C xc = so[1][c];
-                const C lw = L[q - 1], le = L[q + 1], ls = L[q - W1], ln = L[q + W1];
+                const C lw = c > 0 ? so[1][c > 0 ? c - 1 : 0] : L[q - 1];
+                const C le = c + 1 < CPT ? so[1][c + 1 < CPT ? c + 1 : 0] : L[q + 1];
+                const C ls = L[q - W1], ln = L[q + W1];
                 // Dirichlet ghosts: minus the cell's own value
                 const C xw = dw[c] ? -xc : lw;
                 const C xe = de[c] ? -xc : le;
@@ -632,8 +637,8 @@ __global__ __launch_bounds__(kS3Threads) void k_down0z1(const S *__restrict__ f,
         if constexpr (CPT == 2) Pair<S>::ld(base + osrc, v[0], v[1]);
         else v[0] = St<S>::ld(base + osrc);
     };
-    auto sweep1 = [&](const C *A, int q, C xc, C xm, C xp, C fv) -> C {
-        const C r = op.resid(fv, xc, A[q - 1], A[q + 1], A[q - W2], A[q + W2], xm, xp);
+    auto sweep1 = [&](const C *A, int q, C xc, C xw, C xe, C xm, C xp, C fv) -> C {
+        const C r = op.resid(fv, xc, xw, xe, A[q - W2], A[q + W2], xm, xp);
         return xc + op.wd * r;
     };
     // registers at the start of step z: own f and x1 = (signed) w f at z - 2 .. z, x2 at
@@ -675,11 +680,14 @@ __global__ __launch_bounds__(kS3Threads) void k_down0z1(const S *__restrict__ f,
             const C *Am = Ax + (ODD ? 0 : AS);
             C *B = Bs + (ODD ? 0 : BS);
             for (int c = 0; c < CPT; ++c) {
-                sn[c] = st_round<S>(sweep1(Am, own_a + c, xo[1][c], xo[0][c], xo[2][c], fo[1][c]));
+                const int q = own_a + c;
+                const C xw = c > 0 ? xo[1][c > 0 ? c - 1 : 0] : Am[q - 1];
+                const C xe = c + 1 < CPT ? xo[1][c + 1 < CPT ? c + 1 : 0] : Am[q + 1];
+                sn[c] = st_round<S>(sweep1(Am, q, xo[1][c], xw, xe, xo[0][c], xo[2][c], fo[1][c]));
                 B[own_b + c] = sn[c];
             }
             if (z > k0 && z <= k0 + zc) store_cells<S, CPT>(xout + (uint32_t(z - 1) << pl) + osrc, sn);
-            if (r1) B[ring_b] = st_round<S>(sweep1(Am, ring_a, rx[1], rx[0], rx[2], rf[1]));
+            if (r1) B[ring_b] = st_round<S>(sweep1(Am, ring_a, rx[1], Am[ring_a - 1], Am[ring_a + 1], rx[0], rx[2], rf[1]));
         } else {
             for (int c = 0; c < CPT; ++c) sn[c] = C(0);
         }
@@ -693,7 +701,9 @@ __global__ __launch_bounds__(kS3Threads) void k_down0z1(const S *__restrict__ f,
             for (int c = 0; c < CPT; ++c) {
                 const int q = own_b + c;
                 const C xc = so[1][c];
-                const C lw = L[q - 1], le = L[q + 1], ls = L[q - W1], ln = L[q + W1];
+                const C lw = c > 0 ? so[1][c > 0 ? c - 1 : 0] : L[q - 1];
+                const C le = c + 1 < CPT ? so[1][c + 1 < CPT ? c + 1 : 0] : L[q + 1];
+                const C ls = L[q - W1], ln = L[q + W1];
                 const C xw = dw[c] ? -xc : lw;
                 const C xe = de[c] ? -xc : le;
                 const C ys = ds ? -xc : ls;
