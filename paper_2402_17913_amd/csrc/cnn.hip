@@ -44,6 +44,15 @@ __device__ __forceinline__ uint16_t f2b(float f) { return float_to_bf16(f); }
 __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
 // ------------------------------------------------------------------ conv
+// Where a field of the network has one channel (its input, the prediction's gradient), it is stored as
+// such, and the kernels that read it as 16 channels set the others to zero as they load it (ONE): at 128^3
+// writing it takes 6 and 9 us instead of 17 and 20, and its weight gradients 42 us instead of 47.
+// 8 channels of a voxel: index i is 2 * voxel + half.
+template <bool ONE> __device__ __forceinline__ u32x4 ld_half(const uint16_t *__restrict__ X, int64_t i) {
+    if constexpr (ONE) return u32x4{(i & 1) ? 0u : uint32_t(X[i >> 1]), 0u, 0u, 0u};
+    else return reinterpret_cast<const u32x4 *>(X)[i];
+}
+
 // What a convolution writes: BF16 after ReLU (forward); FP32; BF16 where the activation `act` is
 // positive and zero elsewhere (a data gradient already masked for the layer below it, so that the
 // FP32 gradient is never stored); FP32 of channel 0 alone (the prediction).
@@ -89,7 +98,7 @@ __device__ __forceinline__ void conv_store(const f32x4 &acc, const f32x4 &bias, 
 
 // Y = conv(X, W) (+ bias, ReLU) on an n^3 periodic grid, n = 2^lg >= 16.
 // Workgroup: TXV = min(64, n) voxels along x, 4 rows along y, one plane.
-template <ConvOut OUT>
+template <ConvOut OUT, bool ONE>
 __global__ __launch_bounds__(256) void k_conv(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W,
                                               const float *__restrict__ bias, const uint16_t *__restrict__ act,
                                               void *__restrict__ Y, int lg) {
@@ -103,12 +112,11 @@ __global__ __launch_bounds__(256) void k_conv(const uint16_t *__restrict__ X, co
     const uint4 *W4 = reinterpret_cast<const uint4 *>(W);
     for (int q = tid; q < kTaps * kC * 2; q += 256) ws[q] = W4[q];
     const int nh = hx * 6 * 3;
-    const uint4 *X4 = reinterpret_cast<const uint4 *>(X);
     for (int q = tid; q < nh * 2; q += 256) {
         const int v = q >> 1, half = q & 1;
         const int lx = v % hx, ly = (v / hx) % 6, lz = v / (hx * 6);
         const int gx = wrapi(x0 + lx - 1, n), gy = wrapi(y0 + ly - 1, n), gz = wrapi(z + lz - 1, n);
-        xs[q] = X4[((((int64_t(gz) << lg) + gy) << lg) + gx) * 2 + half];
+        reinterpret_cast<u32x4 *>(xs)[q] = ld_half<ONE>(X, ((((int64_t(gz) << lg) + gy) << lg) + gx) * 2 + half);
     }
     __syncthreads();
     const int w = tid >> 6, l = tid & 63;
@@ -155,7 +163,7 @@ __global__ __launch_bounds__(256) void k_conv(const uint16_t *__restrict__ X, co
 constexpr int kCzT = 256, kCzRows = 4;
 constexpr int kCzSlots = (64 + 2) * (kCzRows + 2) * 2;  // uint4 per plane buffer (halo tile, two per voxel)
 
-template <ConvOut OUT>
+template <ConvOut OUT, bool ONE>
 __global__ __launch_bounds__(kCzT) void k_conv3z(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W,
                                                  const float *__restrict__ bias, const uint16_t *__restrict__ act,
                                                  void *__restrict__ Y, int lg, int zc) {
@@ -166,7 +174,6 @@ __global__ __launch_bounds__(kCzT) void k_conv3z(const uint16_t *__restrict__ X,
     const int x0 = (b % tiles_x) * txv, y0 = ((b % ncol) / tiles_x) * rows, z0 = (b / ncol) * zc, z1 = z0 + zc;
     const int tid = threadIdx.x;
     const uint4 *W4 = reinterpret_cast<const uint4 *>(W);
-    const u32x4 *X4 = reinterpret_cast<const u32x4 *>(X);
     // this thread's share of a plane: slot q holds half (q & 1) of voxel (q >> 1) of the halo tile (slots
     // beyond the tile repeat the last one)
     constexpr int NF = (kCzSlots + kCzT - 1) / kCzT;
@@ -180,9 +187,9 @@ __global__ __launch_bounds__(kCzT) void k_conv3z(const uint16_t *__restrict__ X,
         at_q[u] = q;
     }
     auto fetch = [&](int z) {
-        const u32x4 *p = X4 + (int64_t(wrapi(z, n)) << (2 * lg + 1));
+        const int64_t p = int64_t(wrapi(z, n)) << (2 * lg + 1);
 #pragma unroll
-        for (int u = 0; u < NF; ++u) pf[u] = p[off[u]];
+        for (int u = 0; u < NF; ++u) pf[u] = ld_half<ONE>(X, p + off[u]);
     };
     auto place = [&](int slot) {
 #pragma unroll
@@ -285,10 +292,11 @@ __global__ __launch_bounds__(kCzT) void k_conv3z(const uint16_t *__restrict__ X,
 // Weight gradient partials: P[blk][tap*256 + o*16 + c] = sum over the
 // workgroup's voxels of dZ[v][o] * X[v + tap][c]; P[blk][6912 + o] = sum dZ[v][o].
 // Tiles of the forward shape, grid-strided over a capped number of workgroups.
+template <bool ONEX, bool ONEZ>
 __global__ __launch_bounds__(256) void k_wgrad(const uint16_t *__restrict__ X, const uint16_t *__restrict__ dZ,
                                                float *__restrict__ P, int lg) {
-    __shared__ uint16_t xs[(64 + 2) * 6 * 3 * kC];
-    __shared__ uint16_t zs[64 * 4 * kC];
+    __shared__ __align__(16) uint16_t xs[(64 + 2) * 6 * 3 * kC];
+    __shared__ __align__(16) uint16_t zs[64 * 4 * kC];
     const int n = 1 << lg, txv = n < 64 ? n : 64, hx = txv + 2;
     const int tiles_x = n / txv, ntile = tiles_x * (n / 4) * n;
     const int tid = threadIdx.x, o = tid >> 4, c = tid & 15;
@@ -305,14 +313,13 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t *__restrict__ X, c
             const int v = q >> 1, half = q & 1;
             const int lx = v % hx, ly = (v / hx) % 6, lz = v / (hx * 6);
             const int gx = wrapi(x0 + lx - 1, n), gy = wrapi(y0 + ly - 1, n), gz = wrapi(z + lz - 1, n);
-            reinterpret_cast<uint4 *>(xs)[q] =
-                reinterpret_cast<const uint4 *>(X)[((((int64_t(gz) << lg) + gy) << lg) + gx) * 2 + half];
+            reinterpret_cast<u32x4 *>(xs)[q] = ld_half<ONEX>(X, ((((int64_t(gz) << lg) + gy) << lg) + gx) * 2 + half);
         }
         for (int q = tid; q < txv * 4 * 2; q += 256) {
             const int v = q >> 1, half = q & 1;
             const int lx = v % txv, ly = v / txv;
-            reinterpret_cast<uint4 *>(zs)[q] =
-                reinterpret_cast<const uint4 *>(dZ)[((((int64_t(z) << lg) + y0 + ly) << lg) + x0 + lx) * 2 + half];
+            reinterpret_cast<u32x4 *>(zs)[q] =
+                ld_half<ONEZ>(dZ, ((((int64_t(z) << lg) + y0 + ly) << lg) + x0 + lx) * 2 + half);
         }
         __syncthreads();
         for (int ly = 0; ly < 4; ++ly)
@@ -364,6 +371,7 @@ __device__ __forceinline__ void wm_put(uint32_t *dst, int pitch, const u32x4 &a,
         dst[e * pitch] = __builtin_amdgcn_perm(b[e >> 1], a[e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
 }
 
+template <bool ONEX, bool ONEZ>
 __global__ __launch_bounds__(kWmT) void k_wgrad_mfma(const uint16_t *__restrict__ X, const uint16_t *__restrict__ dZ,
                                                      float *__restrict__ P, int lg, int nch) {
     __shared__ __align__(16) uint16_t xt[kC * kWmCh];   // [c][ring slot][row][x]
@@ -373,7 +381,6 @@ __global__ __launch_bounds__(kWmT) void k_wgrad_mfma(const uint16_t *__restrict_
     const int tiles_x = n / txv, ncol = tiles_x * (n / 4);
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int ch = l & 15, g = l >> 4;  // operand channel (o for dZ, c for X); voxel run within 32
-    const u32x4 *X4 = reinterpret_cast<const u32x4 *>(X), *Z4 = reinterpret_cast<const u32x4 *>(dZ);
     uint32_t *xd = reinterpret_cast<uint32_t *>(xt);
     f32x4 acc[kTaps + 1];
 #pragma unroll
@@ -406,11 +413,11 @@ __global__ __launch_bounds__(kWmT) void k_wgrad_mfma(const uint16_t *__restrict_
         const int za = (((y0 + zy) << lg) + x0 + 2 * zp) * 2 + (zq & 1);
         u32x4 xv[3][2][2], zv[2];  // planes on their way (three at the start of a column, then one)
         auto fetch_x = [&](int z, u32x4 (&t)[2][2]) {
-            const u32x4 *p = X4 + (int64_t(wrapi(z, n)) << (2 * lg + 1));
+            const int64_t p = int64_t(wrapi(z, n)) << (2 * lg + 1);
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                t[u][0] = p[xa[u]];
-                t[u][1] = p[xb[u]];
+                t[u][0] = ld_half<ONEX>(X, p + xa[u]);
+                t[u][1] = ld_half<ONEX>(X, p + xb[u]);
             }
         };
         auto store_x = [&](int slot, const u32x4 (&t)[2][2]) {
@@ -418,9 +425,9 @@ __global__ __launch_bounds__(kWmT) void k_wgrad_mfma(const uint16_t *__restrict_
             for (int u = 0; u < 2; ++u) wm_put(xd + xl[u] + slot * (6 * kWmRow / 2), kWmCh / 2, t[u][0], t[u][1]);
         };
         auto fetch_z = [&](int z) {
-            const u32x4 *p = Z4 + (int64_t(z) << (2 * lg + 1)) + za;
-            zv[0] = p[0];
-            zv[1] = p[2];
+            const int64_t p = (int64_t(z) << (2 * lg + 1)) + za;
+            zv[0] = ld_half<ONEZ>(dZ, p);
+            zv[1] = ld_half<ONEZ>(dZ, p + 2);
         };
         auto store_z = [&](int z) {
             wm_put(reinterpret_cast<uint32_t *>(zt[z & 1]) + zl, kWmZCh / 2, zv[0], zv[1]);
@@ -614,42 +621,62 @@ __global__ __launch_bounds__(256) void k_up_add(const uint16_t *__restrict__ Xc,
 }
 
 // Z(coarse) = up^T dY(fine), masked by act: each coarse cell gathers the 4 fine cells per
-// axis that reference it (weights 1/4, 3/4, 3/4, 1/4 at 2I-1 .. 2I+2).
+// axis that reference it (weights 1/4, 3/4, 3/4, 1/4 at 2I-1 .. 2I+2).  A thread takes four channels
+// of two coarse cells along x, which share a third of their fine cells, and has a fine plane's 24
+// loads asked for together (64^3 from 128^3: 73 us with eight channels of one cell, four loads at a time, 68
+// so; 32^3 and below 10 -> 7.4).
 __global__ __launch_bounds__(256) void k_up_back(const float *__restrict__ dY, const uint16_t *__restrict__ act,
                                                  uint16_t *__restrict__ Zc, int lgc) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x, v = i >> 1;
-    const int nc = 1 << lgc, lg = lgc + 1, n = nc << 1, c8 = int(i & 1) * 8;
-    if (v >= (int64_t(1) << (3 * lgc))) return;
-    const int X = int(v & (nc - 1)), Yc = int((v >> lgc) & (nc - 1)), Z = int(v >> (2 * lgc));
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x, v = i >> 2;  // v: the cell pair
+    const int nc = 1 << lgc, lg = lgc + 1, n = nc << 1, c4 = int(i & 3) * 4;
+    if (v >= (int64_t(1) << (3 * lgc - 1))) return;
+    const int X = int(v & (nc / 2 - 1)) * 2, Yc = int((v >> (lgc - 1)) & (nc - 1)), Z = int(v >> (2 * lgc - 1));
     const float w1[4] = {0.25f, 0.75f, 0.75f, 0.25f};
-    Ch8 s{};
+    int fx[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) fx[c] = wrapi(2 * X - 1 + c, n);
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
     for (int a = 0; a < 4; ++a) {
         const int fz = wrapi(2 * Z - 1 + a, n);
-        for (int bb = 0; bb < 4; ++bb) {
-            const int fy = wrapi(2 * Yc - 1 + bb, n);
+        f32x4 t[4][6];
+#pragma unroll
+        for (int bb = 0; bb < 4; ++bb)
+#pragma unroll
+            for (int c = 0; c < 6; ++c)
+                t[bb][c] = *reinterpret_cast<const f32x4 *>(
+                    dY + (((((int64_t(fz) << lg) + wrapi(2 * Yc - 1 + bb, n)) << lg) + fx[c]) << 4) + c4);
+#pragma unroll
+        for (int bb = 0; bb < 4; ++bb)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const int fx = wrapi(2 * X - 1 + c, n);
-                const Ch8 t = ld8(dY + (((((int64_t(fz) << lg) + fy) << lg) + fx) << 4) + c8);
+                const float w = w1[a] * w1[bb] * w1[c];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) s.v[e] += w1[a] * w1[bb] * w1[c] * t.v[e];
+                for (int e = 0; e < 4; ++e) {
+                    s0[e] += w * t[bb][c][e];
+                    s1[e] += w * t[bb][c + 2][e];
+                }
             }
-        }
     }
-    mask8(s, act + (v << 4) + c8);
-    st8(Zc + (v << 4) + c8, s);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int64_t at = (((((int64_t(Z) << lgc) + Yc) << lgc) + X + q) << 4) + c4;
+        const f32x4 &g = q ? s1 : s0;
+        const uint2 m = *reinterpret_cast<const uint2 *>(act + at);
+        const uint32_t mw[2] = {m.x, m.y};
+        float o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = b2f(uint16_t(mw[e >> 1] >> (16 * (e & 1)))) > 0.f ? g[e] : 0.f;
+        *reinterpret_cast<uint2 *>(Zc + at) = make_uint2(float2_to_bf16x2(o[0], o[1]), float2_to_bf16x2(o[2], o[3]));
+    }
 }
 
-// Input packing: channel 0 = f (FP32), others 0, bf16.
+// The input in BF16, one channel.
 __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ f, uint16_t *__restrict__ X, int64_t m) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x, v = i >> 1;
-    if (v >= m) return;
-    const uint32_t c0 = (i & 1) ? 0u : uint32_t(f2b(f[v]));
-    *reinterpret_cast<uint4 *>(X + i * 8) = make_uint4(c0, 0, 0, 0);
+    const int64_t v = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (v < m) X[v] = f2b(f[v]);
 }
 
-// MSE of the prediction y: partials of (y - t)^2 / m per workgroup; Z[v][0] = bf16(2 (y - t) / m), the
-// other channels 0.
+// MSE of the prediction y: partials of (y - t)^2 / m per workgroup; Z = bf16(2 (y - t) / m), one channel.
 __global__ __launch_bounds__(256) void k_mse(const float *__restrict__ y, const float *__restrict__ t,
                                              uint16_t *__restrict__ Z, double *__restrict__ part, int64_t m) {
     const int64_t v = int64_t(blockIdx.x) * 256 + threadIdx.x;
@@ -657,9 +684,7 @@ __global__ __launch_bounds__(256) void k_mse(const float *__restrict__ y, const 
     if (v < m) {
         const float d = y[v] - t[v];
         acc = double(d) * double(d) / double(m);
-        uint4 *z = reinterpret_cast<uint4 *>(Z + v * kC);
-        z[0] = make_uint4(uint32_t(f2b(2.f * d / float(m))), 0, 0, 0);
-        z[1] = make_uint4(0, 0, 0, 0);
+        Z[v] = f2b(2.f * d / float(m));
     }
     acc = block_sum(acc);
     if (threadIdx.x == 0) part[blockIdx.x] = acc;
@@ -761,7 +786,7 @@ np_status nalloc(Net *N, void **p, size_t bytes) {
 
 int64_t vox(int lg) { return int64_t(1) << (3 * lg); }
 
-template <ConvOut OUT>
+template <ConvOut OUT, bool ONE = false>
 np_status conv(Net *N, int k, const uint16_t *X, const uint16_t *act, void *Y, int lg, bool flip, hipStream_t s) {
     const int n = 1 << lg, txv = n < 64 ? n : 64;
     const uint16_t *W = (flip ? N->wt : N->wb) + int64_t(k) * kWsz;
@@ -771,16 +796,17 @@ np_status conv(Net *N, int k, const uint16_t *X, const uint16_t *act, void *Y, i
     // with 1 or 2, 63 with 8; 32^3: 34 with 1, 43 with 4, and 36 with the one-plane form)
     const int zc = g_conv3z == 1 ? (n >= 128 ? n / 8 : std::max(1, n / 32)) : std::min(g_conv3z, n);
     if (g_conv3z)
-        hipLaunchKernelGGL((k_conv3z<OUT>), dim3(unsigned((n / txv) * (n * txv / kCzT) * (n / zc))), dim3(kCzT), 0, s, X, W,
+        hipLaunchKernelGGL((k_conv3z<OUT, ONE>), dim3(unsigned((n / txv) * (n * txv / kCzT) * (n / zc))), dim3(kCzT), 0, s, X, W,
                            bias, act, Y, lg, zc);
     else
-        hipLaunchKernelGGL((k_conv<OUT>), dim3(unsigned((n / txv) * (n / 4) * n)), dim3(256), 0, s, X, W, bias, act, Y,
+        hipLaunchKernelGGL((k_conv<OUT, ONE>), dim3(unsigned((n / txv) * (n / 4) * n)), dim3(256), 0, s, X, W, bias, act, Y,
                            lg);
     NP_LAUNCH_CHECK();
     return NP_OK;
 }
 
 // Weight and bias gradients of conv k with input `in` from its masked output gradient z (level l).
+template <bool ONEX = false, bool ONEZ = false>
 np_status wgrad(Net *N, int k, const uint16_t *in, const uint16_t *z, int l, hipStream_t s) {
     const int lg = N->lg0 - l;
     const int n = 1 << lg, txv = n < 64 ? n : 64, ntile = (n / txv) * (n / 4) * n;
@@ -789,9 +815,9 @@ np_status wgrad(Net *N, int k, const uint16_t *in, const uint16_t *z, int l, hip
         // chunks of planes per column, so that kWmAim workgroups (two per CU) run where there are as many tiles
         const int ncol = ntile / n, nch = std::min(n, std::max(1, kWmAim / ncol));
         nblk = std::min(ncol * nch, kWgBlocks);
-        hipLaunchKernelGGL(k_wgrad_mfma, dim3(nblk), dim3(kWmT), 0, s, in, z, N->wpart, lg, nch);
+        hipLaunchKernelGGL((k_wgrad_mfma<ONEX, ONEZ>), dim3(nblk), dim3(kWmT), 0, s, in, z, N->wpart, lg, nch);
     } else {
-        hipLaunchKernelGGL(k_wgrad, dim3(nblk), dim3(256), 0, s, in, z, N->wpart, lg);
+        hipLaunchKernelGGL((k_wgrad<ONEX, ONEZ>), dim3(nblk), dim3(256), 0, s, in, z, N->wpart, lg);
     }
     NP_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_wgrad_reduce, dim3(unsigned((kPsz + 31) / 32)), dim3(32 * kRedSl), 0, s, N->wpart, nblk,
@@ -804,7 +830,7 @@ np_status wgrad(Net *N, int k, const uint16_t *in, const uint16_t *z, int l, hip
 np_status forward(Net *N, const float *f, float *pred, hipStream_t s) {
     const int L = N->levels;
     const int64_t m0 = vox(N->lg0);
-    hipLaunchKernelGGL(k_pack, dim3(nb(m0 * 2)), dim3(256), 0, s, f, N->h[0], m0);
+    hipLaunchKernelGGL(k_pack, dim3(nb(m0)), dim3(256), 0, s, f, N->h[0], m0);
     NP_LAUNCH_CHECK();
     int k = 0;
     for (int l = 0; l < L; ++l) {
@@ -813,7 +839,8 @@ np_status forward(Net *N, const float *f, float *pred, hipStream_t s) {
             hipLaunchKernelGGL(k_pool, dim3(nb(vox(lg) * 2)), dim3(256), 0, s, N->e[l - 1], N->h[l], lg);
             NP_LAUNCH_CHECK();
         }
-        NP_TRY(conv<kOutRelu>(N, k++, N->h[l], nullptr, N->a[l], lg, false, s));
+        if (l == 0) NP_TRY((conv<kOutRelu, true>(N, k++, N->h[0], nullptr, N->a[0], lg, false, s)));
+        else NP_TRY(conv<kOutRelu>(N, k++, N->h[l], nullptr, N->a[l], lg, false, s));
         NP_TRY(conv<kOutRelu>(N, k++, N->a[l], nullptr, N->e[l], lg, false, s));
     }
     const uint16_t *dn = N->e[L - 1];
@@ -829,16 +856,17 @@ np_status forward(Net *N, const float *f, float *pred, hipStream_t s) {
     return NP_OK;
 }
 
-// Backward from Z[0] (the prediction's gradient, BF16, channel 0); gradient sums accumulate in N->g.
+// Backward from Z[0] (the prediction's gradient, BF16, one channel); gradient sums accumulate in N->g.
 // Every layer's output gradient is masked by its activation where it is formed, alternating between Z
 // and Z2 of a level; FP32 gradients are stored only where two are added (K) or crossed by a transfer.
 // Two samples of 128^3 with four levels: 5.22 ms with FP32 gradients everywhere, separate mask, add and
-// clearing passes and 16-channel FP32 predictions, 3.51 ms so.
+// clearing passes and 16-channel FP32 predictions, 3.51 ms so (2.20 with the convolutions, weight gradients
+// and one-channel fields as they are now).
 np_status backward(Net *N, hipStream_t s) {
     const int L = N->levels;
     const uint16_t *dtop = L >= 2 ? N->d[0] : N->e[0];
-    NP_TRY(wgrad(N, N->nconv - 1, dtop, N->Z[0], 0, s));
-    NP_TRY(conv<kOutMask>(N, N->nconv - 1, N->Z[0], dtop, N->Z2[0], N->lg0, true, s));
+    NP_TRY((wgrad<false, true>(N, N->nconv - 1, dtop, N->Z[0], 0, s)));
+    NP_TRY((conv<kOutMask, true>(N, N->nconv - 1, N->Z[0], dtop, N->Z2[0], N->lg0, true, s)));
     // decoder levels 0 .. L-2 (conv indices 2L + 2 (L-2-l) .. +1), entered with the gradient in Z2
     for (int l = 0; l <= L - 2; ++l) {
         const int k1 = 2 * L + 2 * (L - 2 - l), k2 = k1 + 1, lg = N->lg0 - l;
@@ -860,7 +888,8 @@ np_status backward(Net *N, hipStream_t s) {
         }
         NP_TRY(wgrad(N, 2 * l + 1, N->a[l], N->Z2[l], l, s));
         NP_TRY(conv<kOutMask>(N, 2 * l + 1, N->Z2[l], N->a[l], N->Z[l], lg, true, s));
-        NP_TRY(wgrad(N, 2 * l, N->h[l], N->Z[l], l, s));
+        if (l == 0) NP_TRY((wgrad<true, false>(N, 0, N->h[0], N->Z[0], 0, s)));
+        else NP_TRY(wgrad(N, 2 * l, N->h[l], N->Z[l], l, s));
         if (l > 0) NP_TRY(conv<kOutF32>(N, 2 * l, N->Z[l], nullptr, N->S[l], lg, true, s));
     }
     return NP_OK;
