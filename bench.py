@@ -486,8 +486,8 @@ def leg_explicit(B, inputs, steps, warmup):
     """Explicit advection-diffusion step with the paper's filter families (Section 2.1,
     Appendix A): central, upwind and finite element, on 4096^2 (rotation) and 256^3
     (divergence-free field), Dirichlet-0.  Throughput in cell-steps/s and the step's
-    algorithmic bytes (predictor: T and a read, T~ and a copy of T written; corrector:
-    the copy, T~ and a read, T written) against HBM peak."""
+    algorithmic bytes (both stages in one pass: T and a read, the result written; the
+    result copied back into T) against HBM peak."""
     import torch
     out = {}
     for name, d, n in (("2d_4096", 2, 4096), ("3d_256", 3, 256)):
@@ -495,7 +495,7 @@ def leg_explicit(B, inputs, steps, warmup):
         Tg = torch.from_numpy(T).cuda()
         ag = [torch.from_numpy(c).cuda() for c in a]
         m = Tg.numel()
-        nbytes = m * (8 * (1 + d + 2) + 8 * (2 + d + 1))  # predictor writes T~ and a copy of T
+        nbytes = m * 8 * (1 + d + 1 + 2)
         res = {}
         for sname, scheme in (("central", 0), ("upwind", 1), ("finite_element", 2)):
             dt_s, _ = timed(lambda: B.np_ad_explicit_step(Tg, h, dt, nu, B.BC_DIRICHLET0, a=ag, scheme=scheme),
