@@ -497,24 +497,34 @@ __global__ __launch_bounds__(kWmT) void k_wgrad_mfma(const uint16_t *__restrict_
 }
 
 // G[i] += sum over workgroups of P[blk][i] (fixed order): a workgroup owns 32
-// consecutive entries; its kRedSl slices of 32 threads sum every kRedSl-th partial,
-// then the slices are added in order through LDS.  Bound by the chain of dependent
-// loads of a slice: with 8 slices (96 loads) it took 21 us, with 32 (24 loads) 8 us.
+// consecutive entries; its kRedSl slices of 8 threads (four entries each) sum every
+// kRedSl-th partial, then the slices are added in order through LDS.  Bound by the
+// latency of a slice's loads: 8 slices of 32 threads (96 loads in a row) took 21 us, 32
+// slices 6.1, with 16-byte loads, eight of them in flight, 5.2 (average over the levels).
 constexpr int kRedSl = 32;
-__global__ __launch_bounds__(32 * kRedSl) void k_wgrad_reduce(const float *__restrict__ P, int nblk,
-                                                              float *__restrict__ G) {
-    __shared__ float part[kRedSl][32];
-    const int li = threadIdx.x & 31, sl = threadIdx.x >> 5, i = blockIdx.x * 32 + li;
-    float s = 0.f;
-    if (i < kPsz)
-        for (int b = sl; b < nblk; b += kRedSl) s += P[int64_t(b) * kPsz + i];
+__global__ __launch_bounds__(8 * kRedSl) void k_wgrad_reduce(const float *__restrict__ P, int nblk,
+                                                             float *__restrict__ G) {
+    static_assert(kPsz % 4 == 0, "rows of whole float4");
+    __shared__ f32x4 part[kRedSl][8];
+    const int li = threadIdx.x & 7, sl = threadIdx.x >> 3, i = blockIdx.x * 8 + li;  // i: four entries
+    const f32x4 *P4 = reinterpret_cast<const f32x4 *>(P) + (i < kPsz / 4 ? i : 0);
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    int b = sl;
+    for (; b + 7 * kRedSl < nblk; b += 8 * kRedSl) {
+        f32x4 t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = P4[int64_t(b + u * kRedSl) * (kPsz / 4)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += t[u];
+    }
+    for (; b < nblk; b += kRedSl) s += P4[int64_t(b) * (kPsz / 4)];
     part[sl][li] = s;
     __syncthreads();
-    if (sl == 0 && i < kPsz) {
-        float t = part[0][li];
+    if (sl == 0 && i < kPsz / 4) {
+        f32x4 t = part[0][li];
 #pragma unroll
         for (int q = 1; q < kRedSl; ++q) t += part[q][li];
-        G[i] += t;
+        reinterpret_cast<f32x4 *>(G)[i] += t;
     }
 }
 
@@ -699,7 +709,15 @@ __global__ __launch_bounds__(256) void k_clear(float *__restrict__ g, int64_t np
 
 __global__ __launch_bounds__(256) void k_dsum(const double *__restrict__ part, int np, double *__restrict__ out) {
     double a = 0.0;
-    for (int b = threadIdx.x; b < np; b += 256) a += part[b];
+    int b = threadIdx.x;
+    for (; b + 7 * 256 < np; b += 8 * 256) {  // eight loads in flight, summed in order
+        double t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = part[b + u * 256];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a += t[u];
+    }
+    for (; b < np; b += 256) a += part[b];
     a = block_sum(a);
     if (threadIdx.x == 0) out[0] += a;
 }
@@ -820,7 +838,7 @@ np_status wgrad(Net *N, int k, const uint16_t *in, const uint16_t *z, int l, hip
         hipLaunchKernelGGL((k_wgrad<ONEX, ONEZ>), dim3(nblk), dim3(256), 0, s, in, z, N->wpart, lg);
     }
     NP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(unsigned((kPsz + 31) / 32)), dim3(32 * kRedSl), 0, s, N->wpart, nblk,
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(unsigned((kPsz + 31) / 32)), dim3(8 * kRedSl), 0, s, N->wpart, nblk,
                        N->g + int64_t(k) * kPsz);
     NP_LAUNCH_CHECK();
     return NP_OK;
