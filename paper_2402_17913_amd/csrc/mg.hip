@@ -441,7 +441,8 @@ static np_status launch_leg2(bool al, const S *ec, const S *f, const S *xin, S *
     if (MODE == 3 || w2_on(lg, al)) {
         // wavefronts aimed for: FP64 2048 (twelve cycles at 4096^2 4.06 ms, against 4.47 with 1024 and 4.12
         // with 4096), else 4096 (four FP32 refinement steps at 2048^2 1.29 ms, against 1.33 and 1.32)
-        const int strips = w2_strips<S, MODE>(n, bc).count, ry = wave2_rows(n, strips, sizeof(S) == 8 || MODE == 3 ? 2048 : 4096);
+        const int strips = w2_strips<S, MODE>(n, bc).count;
+        const int ry = wave2_rows(n, strips, sizeof(S) == 8 || MODE == 3 ? 2048 : 4096, sizeof(S) == 2 ? 4 : 8);
         const int64_t waves = int64_t(strips) * ((n + ry - 1) / ry);
         *np = unsigned((waves * 64 + kW2T - 1) / kW2T);
         hipLaunchKernelGGL((k_wave2<S, OP, MODE, NORM>), dim3(*np), dim3(kW2T), 0, s, ec, f, xin, xout, fc, partial, lg,

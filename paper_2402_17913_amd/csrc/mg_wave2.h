@@ -394,12 +394,13 @@ __device__ __forceinline__ double wave2_leg(const S *__restrict__ ec, const S *_
     return acc;
 }
 
-// Rows per chunk: even, for about `waves` wavefronts over the level, at least 8
-// (a chunk computes two to four rows beyond its own).
-inline int wave2_rows(int n, int64_t strips, int waves) {
+// Rows per chunk: even, for about `waves` wavefronts over the level, at least `least` (a chunk computes
+// two to four rows beyond its own): 8, or 4 in BF16, whose rows carry half the bytes (four BF16
+// refinement steps at 1024^2 750 -> 724 us; FP32 and FP64 the same or slower).
+inline int wave2_rows(int n, int64_t strips, int waves, int least = 8) {
     int64_t ry = (int64_t(n) * strips + waves - 1) / waves;
     ry = (ry + 1) & ~int64_t(1);
-    return int(ry < 8 ? (n < 8 ? n : 8) : (ry > n ? n : ry));
+    return int(ry < least ? (n < least ? n : least) : (ry > n ? n : ry));
 }
 
 // A leg of one n x n level; ry rows per wavefront.  Wavefront w takes strip
