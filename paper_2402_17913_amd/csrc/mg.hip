@@ -137,6 +137,7 @@ struct Tuning {
     int fbnt = 1024;      // threads per workgroup of those block kernels (512: one per cell, or 1024)
     int z2wg = 1;         // one-pass kernels that fit fewer than four workgroups per CU aim at 512 workgroups
     int blk2 = 1;         // 2D levels of 128^2 .. 1024^2: one block kernel per leg (64 x 16 cells per workgroup)
+    int pair = 1;         // the legs of 256^2 and 128^2 under a finer 2D level: one kernel for both
     int link = 11;        // smallest 2D FP64 finest level (log2) whose up-leg runs with the next cycle's down-leg
     int w2min = 10;       // smallest 2D level (log2 cells per axis) whose legs run on row-marching wavefronts (14: none)
 };
@@ -916,6 +917,33 @@ template <int D, class S> struct Ops {
         return NP_OK;
     }
 
+    // The two levels above the tail (256^2, 128^2) under a finer one run one kernel per leg between them
+    // (k_pair_down, k_pair_up), where each is on blocks.
+    static bool pair_on(int lg, int l, int tl, const CycleOpts &o) {
+        return D == 2 && g_tune.pair && l >= 1 && tl == l + 2 && lg == Tail<2>::LG + 2 && o.nu1 == 2 && o.nu2 == 2 &&
+               !w2_on(lg, true) && !w2_on(lg - 1, true) && leg2_on(lg, true) && leg2_on(lg - 1, true) &&
+               psweep_on(lg, 2) && g_tune.zero2 && !g_tune.fused;
+    }
+    static Lap2<C> lap2(double h, double omega) { return Lap2<C>{C(1.0 / (h * h)), C(omega * h * h / (2.0 * D))}; }
+    template <class OP>
+    static np_status pair_down(const S *fa, S *xa, S *fb, S *xb, S *fc, int lg, int bc, const OP &oa, const OP &ob,
+                               hipStream_t s, const int *stop) {
+        const int n = 1 << lg;
+        hipLaunchKernelGGL((k_pair_down<S, OP>), dim3(unsigned((n / P2<S>::BX) * (n / P2<S>::BY))), dim3(P2<S>::ND), 0, s,
+                           fa, xa, fb, xb, fc, lg, bc, oa, ob, stop);
+        NP_LAUNCH_CHECK();
+        return NP_OK;
+    }
+    template <class OP>
+    static np_status pair_up(const S *ec, const S *fb, const S *xb, const S *fa, const S *xa, S *xo, int lg, int bc,
+                             const OP &oa, const OP &ob, hipStream_t s, const int *stop) {
+        const int n = 1 << lg;
+        hipLaunchKernelGGL((k_pair_up<S, OP>), dim3(unsigned((n / P2<S>::BX) * (n / P2<S>::BY))), dim3(P2<S>::NU), 0, s,
+                           ec, fb, xb, fa, xa, xo, lg, bc, oa, ob, stop);
+        NP_LAUNCH_CHECK();
+        return NP_OK;
+    }
+
     // A cycle whose finest up-leg runs with the next cycle's down-leg, in one pass (MODE 3).  in: where
     // the previous cycle left its pre-smoothed iterate (null: the cycle opens with a down-leg of its own);
     // out: where this cycle leaves its own; open: the up-leg is left to the next cycle.  The iterate between
@@ -972,6 +1000,7 @@ template <int D, class S> struct Ops {
         // launch of its own
         const bool defer = tl > 0 && !hook && g_tune.tailck;
         int pend = -1;
+        bool paired = false;  // the two levels above the tail share their legs' kernels
         auto check_now = [&](int nb, bool safe = true) -> np_status {
             if (defer && safe) {
                 pend = nb;
@@ -992,6 +1021,14 @@ template <int D, class S> struct Ops {
                 if (used) zero = false;
             }
             S *fc = (S *)H->f[l + 1];
+            if constexpr (D == 2) {
+                if (zero && !hook && !fl[l] && !fl[l + 1 <= L ? l + 1 : L] && pair_on(lg, l, tl, o)) {
+                    NP_TRY(pair_down(F[l], cur[l], fc, cur[l + 1], (S *)H->f[l + 2], lg, bc, lap2(hl, o.omega),
+                                     lap2(2.0 * hl, o.omega), s, stop));
+                    paired = true;
+                    break;
+                }
+            }
             if (link && l == 0) {
                 int nb = 0;
                 if (link->in) {
@@ -1132,6 +1169,17 @@ template <int D, class S> struct Ops {
         for (int l = (tl > 0 ? tl : L) - 1; l >= (link && link->open ? 1 : 0); --l) {
             hl *= 0.5;
             const int lg = H->lg - l;
+            if constexpr (D == 2) {
+                if (paired && l == tl - 1) {
+                    NP_TRY(pair_up(res[tl], F[l], cur[l], F[l - 1], cur[l - 1], oth[l - 1], lg + 1, bc,
+                                   lap2(0.5 * hl, o.omega), lap2(hl, o.omega), s, stop));
+                    --l;
+                    hl *= 0.5;
+                    std::swap(cur[l], oth[l]);
+                    res[l] = cur[l];
+                    continue;
+                }
+            }
             if (fl[l]) {
                 // pre-smoothed iterate in cur[l]; result into the other buffer
                 NP_TRY((fused<2, PRE_PROLONG, false, false>(cur[l], F[l], oth[l], res[l + 1], nullptr, nullptr, lg,
@@ -1797,7 +1845,7 @@ extern "C" np_status np_set_tuning(const char *key, int value) {
         {"batch", &g_tune.batch, 1, 64},        {"sweep3", &g_tune.sweep3, 0, 1},
         {"zero2", &g_tune.zero2, 0, 1},         {"psweep", &g_tune.psweep, 0, 1},
         {"ir_cpt", &g_tune.ir_cpt, 1, 2},      {"fuseb", &g_tune.fuseb, 0, 1}, {"fbnt", &g_tune.fbnt, 512, 1024},  {"sweep2z", &g_tune.sweep2z, 0, 1}, {"down2z", &g_tune.down2z, 0, 1}, {"blk2", &g_tune.blk2, 0, 1}, {"z2wg", &g_tune.z2wg, 0, 1}, {"greps", &g_tune.greps, 1, 8}, {"tailck", &g_tune.tailck, 0, 1}, {"one", &g_tune.one, 0, 1}, {"zbar", &g_tune.zbar, 1, 2}, {"d2cpt", &g_tune.d2cpt, 1, 2}, {"d2wg", &g_tune.d2wg, 0, 1024},
-        {"fbmax", &g_tune.fbmax, 5, 10},        {"w2min", &g_tune.w2min, 7, 14},        {"link", &g_tune.link, 8, 15},
+        {"fbmax", &g_tune.fbmax, 5, 10},        {"w2min", &g_tune.w2min, 7, 14},        {"link", &g_tune.link, 8, 15}, {"pair", &g_tune.pair, 0, 1},
         {"batched_graphs", &g_batched_graphs, 0, 1}, {"batched_autotune", &g_batched_autotune, 0, 1},
         {"batched_rm", &g_batched_rm, 0, 1},    {"batched_wg", &g_batched_wg, 64, 1 << 20},
         {"zmarch_explicit", &g_zmarch_explicit, 0, 1}, {"mom_rows", &g_mom_rows, 4, 8}, {"mom_ring", &g_mom_ring, 2, 3}, {"zc3", &g_zc3, 0, 64}, {"conv3z", &g_conv3z, 0, 64},
@@ -1861,6 +1909,7 @@ extern "C" int np_get_tuning(const char *key) {
     if (!std::strcmp(key, "fbmax")) return g_tune.fbmax;
     if (!std::strcmp(key, "w2min")) return g_tune.w2min;
     if (!std::strcmp(key, "link")) return g_tune.link;
+    if (!std::strcmp(key, "pair")) return g_tune.pair;
     if (!std::strcmp(key, "batched_graphs")) return g_batched_graphs;
     if (!std::strcmp(key, "batched_autotune")) return g_batched_autotune;
     if (!std::strcmp(key, "batched_rm")) return g_batched_rm;
@@ -2669,6 +2718,8 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
         for (int l = 1; l <= L; ++l)
             if (lg0 - l <= Tail<D>::LG && lg0 - l > 2) { tl = l; break; }
     int pend = 0;  // partials of the check that the tail runs
+    bool paired = false;
+    [[maybe_unused]] auto ad2 = [](const AdW &w, double q) { return Ad2{w.c0, w.cm[0], w.cp[0], w.cm[1], w.cp[1], q}; };
     double hl = h;
     for (int l = 0; l <= L; ++l, hl *= 2.0) {
         const int lg = lg0 - l;
@@ -2703,6 +2754,15 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
             NP_LAUNCH_CHECK();
         }
         if constexpr (D == 2) {
+            if (zero && Ops<2, double>::pair_on(lg, l, tl, co)) {
+                const AdW Wb = ad_weights(op, D, 2.0 * hl);
+                NP_TRY((Ops<2, double>::pair_down(F[l], cur[l], (double *)H->f[l + 1], cur[l + 1], (double *)H->f[l + 2], lg,
+                                                  bc, ad2(W, wd), ad2(Wb, co.omega / Wb.c0), s, stop)));
+                paired = true;
+                ++l;
+                hl *= 2.0;
+                continue;
+            }
             if (link && l == 0 && link->in) {
                 const Ad2 ao{W.c0, W.cm[0], W.cp[0], W.cm[1], W.cp[1], wd};
                 unsigned nb = 0;
@@ -2759,6 +2819,16 @@ static np_status ad_vcycle(Hier *H, const np_ad_op &op, const double *f, double 
         const int64_t m = cells(D, lg);
         const AdW W = ad_weights(op, D, h * double(int64_t(1) << l));
         const double wd = co.omega / W.c0;
+        if constexpr (D == 2) {
+            if (paired && l == tl - 1) {
+                const AdW Wa = ad_weights(op, D, h * double(int64_t(1) << (l - 1)));
+                NP_TRY((Ops<2, double>::pair_up(cur[tl], F[l], cur[l], F[l - 1], cur[l - 1], oth[l - 1], lg + 1, bc,
+                                                ad2(Wa, co.omega / Wa.c0), ad2(W, wd), s, stop)));
+                --l;
+                std::swap(cur[l], oth[l]);
+                continue;
+            }
+        }
         if (co.nu2 == 2 && ad_leg<D>(lg, l > 0 || al0, true)) {  // prolongation + correction and both post-sweeps
             NP_TRY((ad_up<D>(l > 0 || al0, cur[l + 1], F[l], cur[l], oth[l], lg, bc, W, wd, s, stop)));
             std::swap(cur[l], oth[l]);

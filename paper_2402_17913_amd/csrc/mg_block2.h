@@ -255,4 +255,240 @@ __global__ __launch_bounds__(B2<S>::NT) void k_lvl2_b(const S *__restrict__ ec, 
     }
 }
 
+// Both levels above the tail in one kernel per leg (256^2 and 128^2 under a finer grid), where a leg of
+// one level is little more than a launch: 2.5 of its 4.1 (down) and 4.5 us (up).  A workgroup owns
+// 32 x 16 cells of the finer level and computes the rings that the coarser one's stages need itself:
+// 2.4 times its own cells at the first stage, still one or two LDS passes of 1024 threads a stage.
+// Arithmetic, term order and rounding of k_lvl2_b: the same bits.  4.4 us down and 5.1 up for both levels
+// (4.1 to 4.4 and 4.5 to 4.8 for each before); a 512^2 FP64 solve 673 -> 577 us, a 1024^2 projection step
+// 1.10 -> 0.99 ms.
+template <class S> struct P2 {
+    static constexpr int BX = 32, BY = 16, ND = 1024, NU = 768;  // cells; threads of the down- and the up-leg
+    static constexpr int CX = BX / 2, CY = BY / 2;               // the block on the coarser level
+    // a region of `ring` cells around a W x H block
+    static constexpr int w(int W, int ring) { return W + 2 * ring; }
+};
+
+// The cell a stage is evaluated at for position (a, b), by the boundary rule, and the sign of its value
+// there (a corner outside along both axes: the cell itself, as a field read from memory has it).
+__device__ __forceinline__ int mirror_pos2(int &a, int &b, int x0, int y0, int n, int bc) {
+    if (bc) return 1;
+    int s = 1;
+    a = bmap(x0 + a, n, 0, s) - x0;
+    b = bmap(y0 + b, n, 0, s) - y0;
+    return s;
+}
+
+// Two sweeps from zero at (a, b) from f (LDS, width W, `ring` cells around the block).
+template <class S, class OP, class C>
+__device__ __forceinline__ C pair_zero2(const C *F, int W, int ring, int a, int b, const OP &op) {
+    const int q = (b + ring) * W + a + ring;
+    const C fv = F[q];
+    const C xc = op.wd * fv;
+    const C xm = op.wd * F[q - 1];
+    const C xp = op.wd * F[q + 1];
+    const C ym = op.wd * F[q - W];
+    const C yp = op.wd * F[q + W];
+    const C r = op.resid(fv, xc, xm, xp, ym, yp);
+    return st_round<S>(xc + op.wd * r);
+}
+
+// Down-legs from zero of a level (n = 2^lg, operator oa) and the next (ob): xa, fb, xb and fc.
+template <class S, class OP>
+__global__ __launch_bounds__(P2<S>::ND) void k_pair_down(const S *__restrict__ fa, S *__restrict__ xa,
+                                                         S *__restrict__ fb, S *__restrict__ xb, S *__restrict__ fc,
+                                                         int lg, int bc, OP oa, OP ob, const int *stop) {
+    typedef typename St<S>::C C;
+    typedef P2<S> G;
+    constexpr int BX = G::BX, BY = G::BY, CX = G::CX, CY = G::CY, NT = G::ND;
+    constexpr int WF = G::w(BX, 6), WX = G::w(BX, 5), WR = G::w(BX, 4), WG = G::w(CX, 2), WY = G::w(CX, 1);
+    constexpr int RF = WF * G::w(BY, 6), RX = WX * G::w(BY, 5), RR = WR * G::w(BY, 4), RG = WG * G::w(CY, 2),
+                  RY = WY * G::w(CY, 1);
+    __shared__ C F[RF], X[RX], Rr[RR], Gf[RG], Y[RY], Rb[CX * CY];
+    const int halt = stop ? *stop : 0;
+    const int n = 1 << lg, nb = n >> 1, t = int(threadIdx.x);
+    const int nbx = n / BX, blk = int(xcd_block(blockIdx.x, gridDim.x));
+    const int x0 = (blk % nbx) * BX, y0 = (blk / nbx) * BY, X0 = x0 >> 1, Y0 = y0 >> 1;
+    constexpr int PF = (RF + NT - 1) / NT;
+    C fv[PF];
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+        int a, b, s = 1;
+        region_pos2(min(t + u * NT, RF - 1), WF, 6, a, b);
+        const int gi = bmap(x0 + a, n, bc, s), gj = bmap(y0 + b, n, bc, s);
+        fv[u] = C(s) * St<S>::ld(fa + (int64_t(gj) << lg) + gi);
+    }
+    landed(fv);
+    if (halt) return;
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+        if (t + u * NT < RF) F[t + u * NT] = fv[u];
+    __syncthreads();
+    for (int e = t; e < RX; e += NT) {
+        int a, b;
+        region_pos2(e, WX, 5, a, b);
+        const bool own = a >= 0 && a < BX && b >= 0 && b < BY;
+        const int sgn = mirror_pos2(a, b, x0, y0, n, bc);
+        const C v = C(sgn) * pair_zero2<S>(F, WF, 6, a, b, oa);
+        X[e] = v;
+        if (own) St<S>::st(xa + (int64_t(y0 + b) << lg) + x0 + a, v);
+    }
+    __syncthreads();
+    for (int e = t; e < RR; e += NT) {
+        int a, b;
+        region_pos2(e, WR, 4, a, b);
+        const int q = (b + 5) * WX + a + 5;
+        Rr[e] = oa.resid(F[(b + 6) * WF + a + 6], X[q], X[q - 1], X[q + 1], X[q - WX], X[q + WX]);
+    }
+    __syncthreads();
+    if (t < RG) {
+        int a, b;
+        region_pos2(t, WG, 2, a, b);
+        const bool own = a >= 0 && a < CX && b >= 0 && b < CY;
+        const int sgn = mirror_pos2(a, b, X0, Y0, nb, bc);
+        C r = C(0);
+#pragma unroll
+        for (int cy = 0; cy < 2; ++cy)
+#pragma unroll
+            for (int cx = 0; cx < 2; ++cx) r += Rr[(2 * b + cy + 4) * WR + 2 * a + cx + 4];
+        const C v = st_round<S>(r * C(0.25));
+        Gf[t] = C(sgn) * v;
+        if (own) St<S>::st(fb + (int64_t(Y0 + b) << (lg - 1)) + X0 + a, v);
+    }
+    __syncthreads();
+    if (t < RY) {
+        int a, b;
+        region_pos2(t, WY, 1, a, b);
+        const bool own = a >= 0 && a < CX && b >= 0 && b < CY;
+        const int sgn = mirror_pos2(a, b, X0, Y0, nb, bc);
+        const C v = C(sgn) * pair_zero2<S>(Gf, WG, 2, a, b, ob);
+        Y[t] = v;
+        if (own) St<S>::st(xb + (int64_t(Y0 + b) << (lg - 1)) + X0 + a, v);
+    }
+    __syncthreads();
+    if (t < CX * CY) {
+        const int a = t % CX, b = t / CX, q = (b + 1) * WY + a + 1;
+        Rb[t] = ob.resid(Gf[(b + 2) * WG + a + 2], Y[q], Y[q - 1], Y[q + 1], Y[q - WY], Y[q + WY]);
+    }
+    __syncthreads();
+    if (t < CX * CY / 4) {
+        const int I = t % (CX / 2), J = t / (CX / 2);
+        C r = C(0);
+#pragma unroll
+        for (int cy = 0; cy < 2; ++cy)
+#pragma unroll
+            for (int cx = 0; cx < 2; ++cx) r += Rb[(2 * J + cy) * CX + 2 * I + cx];
+        St<S>::st(fc + (int64_t((Y0 >> 1) + J) << (lg - 2)) + (X0 >> 1) + I, r * C(0.25));
+    }
+}
+
+// x + P e at (a, b) of a block at (x0, y0): terms and order of pro_cell; E has its block's origin at (ring, ring).
+template <class S, class C>
+__device__ __forceinline__ C pair_corr(C x, const C *E, int W, int ring, int a, int b, int x0, int y0) {
+    const int fx = x0 + a, fy = y0 + b;
+    const int oi = (fx >> 1) - (x0 >> 1) + ring, ni = oi + ((fx & 1) ? 1 : -1);
+    const int oj = (fy >> 1) - (y0 >> 1) + ring, nj = oj + ((fy & 1) ? 1 : -1);
+    C p = C(0);
+#pragma unroll
+    for (int bb = 0; bb < 2; ++bb)
+#pragma unroll
+        for (int aa = 0; aa < 2; ++aa) {
+            const C w = C(aa ? 0.25 : 0.75) * C(bb ? 0.25 : 0.75) * C(1.0);
+            p = np_fma(w, E[(bb ? nj : oj) * W + (aa ? ni : oi)], p);
+        }
+    return st_round<S>(x + p);
+}
+
+// Up-legs of both levels from the correction ec of the level below them; xo: the finer level's result.
+template <class S, class OP>
+__global__ __launch_bounds__(P2<S>::NU) void k_pair_up(const S *__restrict__ ec, const S *__restrict__ fb,
+                                                       const S *__restrict__ xb, const S *__restrict__ fa,
+                                                       const S *__restrict__ xa, S *__restrict__ xo, int lg, int bc,
+                                                       OP oa, OP ob, const int *stop) {
+    typedef typename St<S>::C C;
+    typedef P2<S> G;
+    constexpr int BX = G::BX, BY = G::BY, CX = G::CX, CY = G::CY, NT = G::NU;
+    constexpr int WE = G::w(CX / 2, 3), W4 = G::w(CX, 4), W3 = G::w(CX, 3), W2c = G::w(CX, 2), V2 = G::w(BX, 2),
+                  V1 = G::w(BX, 1);
+    constexpr int RE = WE * G::w(CY / 2, 3), R4 = W4 * G::w(CY, 4), R3 = W3 * G::w(CY, 3), R2 = W2c * G::w(CY, 2),
+                  Q2 = V2 * G::w(BY, 2), Q1 = V1 * G::w(BY, 1);
+    static_assert(Q2 <= NT && R4 <= NT, "a cell of a region per thread");
+    __shared__ C E[RE], Xb[R4], Gf[R3], S1[R3], S2[R2], Xa[Q2], F[Q1], A1[Q1];
+    const int halt = stop ? *stop : 0;
+    const int n = 1 << lg, nb = n >> 1, nc = n >> 2, t = int(threadIdx.x);
+    const int nbx = n / BX, blk = int(xcd_block(blockIdx.x, gridDim.x));
+    const int x0 = (blk % nbx) * BX, y0 = (blk / nbx) * BY, X0 = x0 >> 1, Y0 = y0 >> 1;
+    // this thread's cell of a field on a region (clamped past its end)
+    auto load = [&](const S *p, int l, int m, int rw, int W, int ring, int bx, int by) -> C {
+        int a, b, s = 1;
+        region_pos2(min(t, rw - 1), W, ring, a, b);
+        const int gi = bmap(bx + a, m, bc, s), gj = bmap(by + b, m, bc, s);
+        return C(s) * St<S>::ld(p + (int64_t(gj) << l) + gi);
+    };
+    C v[5] = {load(ec, lg - 2, nc, RE, WE, 3, X0 >> 1, Y0 >> 1), load(xb, lg - 1, nb, R4, W4, 4, X0, Y0),
+              load(fb, lg - 1, nb, R3, W3, 3, X0, Y0), load(xa, lg, n, Q2, V2, 2, x0, y0),
+              load(fa, lg, n, Q1, V1, 1, x0, y0)};
+    landed(v);
+    if (halt) return;
+    if (t < RE) E[t] = v[0];
+    if (t < R4) Xb[t] = v[1];
+    if (t < R3) Gf[t] = v[2];
+    if (t < Q2) Xa[t] = v[3];
+    if (t < Q1) F[t] = v[4];
+    __syncthreads();
+    // the coarser level: x' on four rings (each thread's own cell, through a register as mirrors read others)
+    C c = C(0);
+    int a = 0, b = 0, sgn = 1;
+    if (t < R4) {
+        region_pos2(t, W4, 4, a, b);
+        sgn = mirror_pos2(a, b, X0, Y0, nb, bc);
+        c = C(sgn) * pair_corr<S>(Xb[(b + 4) * W4 + a + 4], E, WE, 3, a, b, X0, Y0);
+    }
+    __syncthreads();
+    if (t < R4) Xb[t] = c;
+    __syncthreads();
+    if (t < R3) {
+        region_pos2(t, W3, 3, a, b);
+        sgn = mirror_pos2(a, b, X0, Y0, nb, bc);
+        const int q = (b + 4) * W4 + a + 4;
+        const C xc = Xb[q];
+        const C r = ob.resid(Gf[(b + 3) * W3 + a + 3], xc, Xb[q - 1], Xb[q + 1], Xb[q - W4], Xb[q + W4]);
+        S1[t] = C(sgn) * st_round<S>(xc + ob.wd * r);
+    }
+    __syncthreads();
+    if (t < R2) {
+        region_pos2(t, W2c, 2, a, b);
+        sgn = mirror_pos2(a, b, X0, Y0, nb, bc);
+        const int q = (b + 3) * W3 + a + 3;
+        const C xc = S1[q];
+        const C r = ob.resid(Gf[q], xc, S1[q - 1], S1[q + 1], S1[q - W3], S1[q + W3]);
+        S2[t] = C(sgn) * st_round<S>(xc + ob.wd * r);
+    }
+    __syncthreads();
+    // the finer level
+    if (t < Q2) {
+        region_pos2(t, V2, 2, a, b);
+        sgn = mirror_pos2(a, b, x0, y0, n, bc);
+        c = C(sgn) * pair_corr<S>(Xa[(b + 2) * V2 + a + 2], S2, W2c, 2, a, b, x0, y0);
+    }
+    __syncthreads();
+    if (t < Q2) Xa[t] = c;
+    __syncthreads();
+    if (t < Q1) {
+        region_pos2(t, V1, 1, a, b);
+        sgn = mirror_pos2(a, b, x0, y0, n, bc);
+        const int q = (b + 2) * V2 + a + 2;
+        const C xc = Xa[q];
+        const C r = oa.resid(F[(b + 1) * V1 + a + 1], xc, Xa[q - 1], Xa[q + 1], Xa[q - V2], Xa[q + V2]);
+        A1[t] = C(sgn) * st_round<S>(xc + oa.wd * r);
+    }
+    __syncthreads();
+    if (t < BX * BY) {
+        const int ax = t % BX, by = t / BX, q = (by + 1) * V1 + ax + 1;
+        const C xc = A1[q];
+        const C r = oa.resid(F[q], xc, A1[q - 1], A1[q + 1], A1[q - V1], A1[q + V1]);
+        St<S>::st(xo + (int64_t(y0 + by) << lg) + x0 + ax, xc + oa.wd * r);
+    }
+}
+
 }  // namespace np
