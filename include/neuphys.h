@@ -203,7 +203,8 @@ np_status np_last_batched_settings(int *inner_cycles, int *nu1, int *nu2, int *r
  * (T~ + T^n)/2): T~ = T - dt R(T), T <- T - dt R((T~ + T)/2) with
  * R(T) = sum_e a_e (T[+e] - T[-e]) / (2h) - nu Lap T.  Unlike the solver,
  * any n >= 3 is accepted (all axes equal).  T: device FP64 in/out.
- * a: host array of ndim device pointers to collocated velocity fields, or
+ * a: host array of ndim device pointers to collocated velocity fields (T
+ * itself may be one of them: its values before the step are taken), or
  * NULL for pure diffusion.  opts: only opts->stream is used.
  */
 np_status np_ad_scalar_step(np_dims dims, double h, double *T, const double *const *a, double dt,

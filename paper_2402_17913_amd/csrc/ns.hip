@@ -1068,26 +1068,40 @@ extern "C" np_status np_ad_explicit_step(np_dims dims, double h, double *T, cons
         hipLaunchKernelGGL((k_adx_stage<D, S, 0>), grd, blk, 0, s, T, nullptr, scr, ap, ni, int(bc), dt, K);      \
         hipLaunchKernelGGL((k_adx_stage<D, S, 1>), grd, blk, 0, s, T, scr, T, ap, ni, int(bc), dt, K);            \
     } while (0)
-    const bool vec = ni % 2 == 0 && ((uintptr_t(T) | uintptr_t(ap.a[0]) | uintptr_t(ap.a[1])) & 15) == 0;
+    // T may be one of its own velocity components.  The two launches read a velocity at the cell they are about
+    // to write only; the one-pass kernels also read it around the cells they own, where other wavefronts or
+    // workgroups write T meanwhile, so they take such a component from the copy, which then holds the whole field.
+    APtrs av = ap;
+    bool self = false;
+    for (int e = 0; e < dims.ndim; ++e)
+        if (ap.has && ap.a[e] == T) {
+            av.a[e] = scr;
+            self = true;
+        }
+    const bool vec = ni % 2 == 0 && ((uintptr_t(T) | uintptr_t(av.a[0]) | uintptr_t(av.a[1])) & 15) == 0;
+    const unsigned ncopy = blocks_for((m + 3) / 4);
     const int ry = step2_rows(ni), strips = (ni + kStep2Cols - 1) / kStep2Cols, chunks = (ni + ry - 1) / ry;
     const unsigned nw2 = unsigned((int64_t(strips) * chunks * 64 + kBlock - 1) / kBlock);
 #define NP_STEP2(S)                                                                                               \
     do {                                                                                                          \
-        hipLaunchKernelGGL(k_adx_shell2, dim3(blocks_for(int64_t(chunks) * 4 * n + n * strips * 4)), dim3(kBlock), \
-                           0, s, T, scr, ni, ry, strips, chunks);                                                 \
+        if (self)                                                                                                 \
+            hipLaunchKernelGGL(k_adx_copy, dim3(ncopy), dim3(kBlock), 0, s, T, scr, m);                           \
+        else                                                                                                      \
+            hipLaunchKernelGGL(k_adx_shell2, dim3(blocks_for(int64_t(chunks) * 4 * n + n * strips * 4)),          \
+                               dim3(kBlock), 0, s, T, scr, ni, ry, strips, chunks);                               \
         if (vec)                                                                                                  \
-            hipLaunchKernelGGL((k_adx_step2<S, true>), dim3(nw2), dim3(kBlock), 0, s, T, scr, ap, ni, int(bc), ry, \
+            hipLaunchKernelGGL((k_adx_step2<S, true>), dim3(nw2), dim3(kBlock), 0, s, T, scr, av, ni, int(bc), ry, \
                                strips, dt, K);                                                                    \
         else                                                                                                      \
-            hipLaunchKernelGGL((k_adx_step2<S, false>), dim3(nw2), dim3(kBlock), 0, s, T, scr, ap, ni, int(bc), ry, \
+            hipLaunchKernelGGL((k_adx_step2<S, false>), dim3(nw2), dim3(kBlock), 0, s, T, scr, av, ni, int(bc), ry, \
                                strips, dt, K);                                                                    \
     } while (0)
     const int zc = step3_planes(ni);
     const unsigned nt3 = unsigned(int64_t((ni + kSx - 1) / kSx) * ((ni + kSy - 1) / kSy) * ((ni + zc - 1) / zc));
 #define NP_STEP3(S)                                                                                               \
     do {                                                                                                          \
-        hipLaunchKernelGGL(k_adx_copy, dim3(blocks_for((m + 3) / 4)), dim3(kBlock), 0, s, T, scr, m);             \
-        hipLaunchKernelGGL((k_adx_step3<S>), dim3(nt3), dim3(kSt), 0, s, scr, T, ap, ni, int(bc), zc, dt, K);     \
+        hipLaunchKernelGGL(k_adx_copy, dim3(ncopy), dim3(kBlock), 0, s, T, scr, m);                               \
+        hipLaunchKernelGGL((k_adx_step3<S>), dim3(nt3), dim3(kSt), 0, s, scr, T, av, ni, int(bc), zc, dt, K);     \
     } while (0)
     if (dims.ndim == 2 && ni >= kStep2Min && g_zmarch_explicit) {
         if (scheme == 0) NP_STEP2(0);
