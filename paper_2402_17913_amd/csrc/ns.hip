@@ -716,7 +716,13 @@ struct NsWork {
 };
 std::mutex g_ns_mu;
 std::map<std::tuple<int, int, int>, NsWork *> g_ns;
-std::map<std::tuple<int, int64_t>, double *> g_ad;  // (dev, cells) -> 2 scratch fields
+// Two scratch fields of the explicit steps; a step holds `mu` until its work on them is complete, as calls on
+// other streams share them.
+struct AdScratch {
+    double *buf = nullptr;
+    std::mutex mu;
+};
+std::map<std::tuple<int, int64_t>, AdScratch *> g_ad;  // (dev, cells)
 std::map<std::tuple<int, int, int>, NsWork *> g_nsc;  // collocated step: 2*d fields + rhs + dp
 
 np_status ns_work(int d, int lg, NsWork **out, bool collocated = false) {
@@ -756,7 +762,10 @@ void release_ns_cache() {
         delete kv.second;
     }
     g_nsc.clear();
-    for (auto &kv : g_ad) (void)hipFree(kv.second);
+    for (auto &kv : g_ad) {
+        (void)hipFree(kv.second->buf);
+        delete kv.second;
+    }
     g_ad.clear();
 }
 
@@ -969,25 +978,23 @@ extern "C" np_status ns_projection_step(np_dims dims, double h, double *u, doubl
     return ns_projection_step_io(dims, h, u, v, w, p, dt, nu, bc, tol, opts, stats, nullptr, nullptr);
 }
 
-// Two scratch fields of m cells for the explicit steps (np_ad_explicit_step uses the first) (cached per device and size).
-static np_status ad_scratch(int64_t m, double **out) {
+// The explicit steps' scratch for m cells (np_ad_explicit_step uses the first field), cached per device and size.
+static np_status ad_scratch(int64_t m, AdScratch **out) {
     int dev = 0;
     NP_HIP_TRY(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lk(g_ns_mu);
     auto key = std::make_tuple(dev, m);
     auto it = g_ad.find(key);
-    if (it != g_ad.end()) {
-        *out = it->second;
-        return NP_OK;
-    }
-    double *scr = nullptr;
-    if (hipMalloc((void **)&scr, sizeof(double) * 2 * m) != hipSuccess) {
+    if (it != g_ad.end()) { *out = it->second; return NP_OK; }
+    AdScratch *W = new AdScratch;
+    if (hipMalloc((void **)&W->buf, sizeof(double) * 2 * m) != hipSuccess) {
         (void)hipGetLastError();
+        delete W;
         set_error("hipMalloc failed");
         return NP_ENOMEM;
     }
-    g_ad[key] = scr;
-    *out = scr;
+    g_ad[key] = W;
+    *out = W;
     return NP_OK;
 }
 
@@ -1011,8 +1018,10 @@ extern "C" np_status np_ad_scalar_step(np_dims dims, double h, double *T, const 
     }
     hipStream_t s = opts ? (hipStream_t)opts->stream : nullptr;
     const int64_t m = dims.ndim == 3 ? n * n * n : n * n;
-    double *scr = nullptr;
-    NP_TRY(ad_scratch(m, &scr));
+    AdScratch *W = nullptr;
+    NP_TRY(ad_scratch(m, &W));
+    std::lock_guard<std::mutex> lk(W->mu);
+    double *scr = W->buf;
     Gen g{n, (int)bc};
     const unsigned nb = blocks_for(m);
     const double inv_2h = 0.5 / h, nu_inv_h2 = nu / (h * h);
@@ -1056,8 +1065,10 @@ extern "C" np_status np_ad_explicit_step(np_dims dims, double h, double *T, cons
     }
     hipStream_t s = opts ? (hipStream_t)opts->stream : nullptr;
     const int64_t m = dims.ndim == 3 ? n * n * n : n * n;
-    double *scr = nullptr;
-    NP_TRY(ad_scratch(m, &scr));
+    AdScratch *W = nullptr;
+    NP_TRY(ad_scratch(m, &W));
+    std::lock_guard<std::mutex> lk(W->mu);
+    double *scr = W->buf;
     const dim3 blk(kAdxX, kAdxY), grd(unsigned((n + kAdxX - 1) / kAdxX), unsigned((n + kAdxY - 1) / kAdxY),
                                       dims.ndim == 3 ? unsigned(n) : 1u);
     const int ni = int(n);
