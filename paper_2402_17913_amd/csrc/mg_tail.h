@@ -371,13 +371,30 @@ struct Solve1 {
     int warm, known0;           // x is the starting iterate; the zero iterate's check is known (rr = 1)
 };
 
-// v -= its mean.
+// v -= its mean; m a power of two.  Never more than four terms are added in a row: four times a value, or sums of
+// two equal values, are exact, so that a constant field becomes zero as it does on larger grids (up to 2^20 cells),
+// where eight in a row can leave every cell one rounding off.
 template <int NT> __device__ __forceinline__ void tail_demean(double *v, int m) {
-    __shared__ double mean;
-    double a = 0.0;
-    for (int c = int(threadIdx.x); c < m; c += NT) a += v[c];
-    a = block_sum_n<NT>(a);
-    if (threadIdx.x == 0) mean = a * (1.0 / double(m));
+    constexpr int NW = NT / 64;
+    static_assert(NW <= 8, "two runs of four wavefronts");
+    __shared__ double mean, wsum[NW];
+    const int tid = int(threadIdx.x);
+    double a = 0.0, b = 0.0;  // at most 8 cells per thread
+    for (int c = tid; c < m; c += 2 * NT) {
+        a += v[c];
+        if (c + NT < m) b += v[c + NT];
+    }
+    a += b;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+    if ((tid & 63) == 0) wsum[tid >> 6] = a;
+    __syncthreads();
+    if (tid == 0) {
+        double s[2] = {0.0, 0.0};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) s[w / 4] += wsum[w];
+        mean = (s[0] + s[1]) * (1.0 / double(m));
+    }
     __syncthreads();
     for (int c = int(threadIdx.x); c < m; c += NT) v[c] -= mean;
     __syncthreads();
