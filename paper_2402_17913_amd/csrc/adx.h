@@ -408,18 +408,19 @@ __global__ __launch_bounds__(kBlock) void k_adx_step2(double *T, const double *_
 // tiles (66 x 15 with the ring: 990 of 1024 threads) keep 16 waves on a CU; two
 // cells on the first waves of a 64 x 8 tile took 176 registers, 8 waves and 316 us a call at
 // 256^3.  Measured, a call (central / finite element), the copy included: 256^3 350 / 389 ->
-// 234 / 254 us, 192^3 161 / 192 -> 117 / 127; from 128^3 on, 96^3 for the 27-point family (two
-// launches of one cell per thread take 52 / 80 us at 128^3, this 50 / 55; at 64^3 26 / 31
-// against 42 / 46).  A ring cell outside the grid is formed at the cell it mirrors, which the
-// tile and its ring hold.
+// 234 / 254 us, 192^3 161 / 192 -> 117 / 127; from 128^3 on, 65^3 for the 27-point family (two
+// launches of one cell per thread take 52 / 80 us at 128^3, this 50 / 55; at 95^3 36 / 55 against 40 / 44, at 72^3
+// 31 / 47 against 36 / 39, at 64^3, which fills the launches' rows of 64 cells, 26 / 31 against 35 / 38).  A ring
+// cell outside the grid is formed at the cell it mirrors, which the tile and its ring hold.
 constexpr int kSx = 64, kSy = 13, kSt = 1024;
-constexpr int step3_min(int scheme) { return scheme == 2 ? 96 : 128; }
+constexpr int step3_min(int scheme) { return scheme == 2 ? 65 : 128; }
 
-// Planes per workgroup: as many as fill the CUs with one workgroup each, at least 8.
+// Planes per workgroup: as many as fill the CUs with one workgroup each, at least 4 (five more are computed per
+// workgroup; finite elements at 72^3 46 us with at least 8, 41 with 5, 39 with 4).
 inline int step3_planes(int n) {
     const int tiles = ((n + kSx - 1) / kSx) * ((n + kSy - 1) / kSy);
     const int chunks = tiles >= 256 ? 1 : 256 / tiles, zc = (n + chunks - 1) / chunks;
-    return zc < 8 ? 8 : zc;
+    return zc < 4 ? 4 : zc;
 }
 
 // b = a.
