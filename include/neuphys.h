@@ -173,7 +173,8 @@ np_status ns_projection_step(np_dims dims, double h, double *u, double *v, doubl
  * kernels' tiles (row-marching or one cell pair per thread; the workgroups a
  * row-marching launch aims for, which set its rows per group) by timing full
  * solves of this batch.  Its choice is cached for the process and in a JSON
- * file keyed by (GPU architecture, precision, omega, the multiset of sizes):
+ * file keyed by (GPU architecture, precision, generation of the library's
+ * batched kernels, omega, the multiset of sizes):
  * $NEUPHYS_TUNE_CACHE if set (empty: no file), else
  * $XDG_CACHE_HOME/neuphys/batched_autotune.json, else
  * $HOME/.cache/neuphys/batched_autotune.json; a cached entry skips the tuning.

@@ -1138,11 +1138,14 @@ np_status batched_run(Plan *B, int inner, const BOpts &o, const np_mg_opts &mo, 
 
 // ---------------------------------------------------- autotuning cache
 // The tuned settings persist in a small JSON file keyed by (GPU architecture,
-// precision, omega, the multiset of problem sizes): $NEUPHYS_TUNE_CACHE if set
+// precision, kernel generation, omega, the multiset of problem sizes): $NEUPHYS_TUNE_CACHE if set
 // (empty: no file), else $XDG_CACHE_HOME/neuphys/batched_autotune.json, else
 // $HOME/.cache/neuphys/batched_autotune.json.  One entry per line:
 //   "<key>": {"inner": 4, "nu": 2, "rm": 1, "wg": 4096, "ms": 52.3},
-// A missing or unreadable file is a cache miss; a failed write is ignored.
+// A missing or unreadable file is a cache miss; a failed write is ignored.  The key also holds the generation of the
+// batched level kernels: settings timed on other kernels, or with another meaning of "wg", are not this one's
+// (an entry with rm 0 would keep a batch off the one-pass legs for good).
+constexpr int kTuneGen = 2;  // raise it when a change of the batched kernels can change which settings win
 std::string tune_cache_path() {
     if (const char *e = std::getenv("NEUPHYS_TUNE_CACHE")) return std::string(e);
     if (const char *x = std::getenv("XDG_CACHE_HOME"); x && *x) return std::string(x) + "/neuphys/batched_autotune.json";
@@ -1190,7 +1193,7 @@ void write_tune_file(const std::string &path, const std::string &key, const BTun
     if (!ok || std::rename(tmp.c_str(), path.c_str()) != 0) (void)std::remove(tmp.c_str());
 }
 
-// Cache key: architecture, precision, omega and the sorted multiset of sizes.
+// Cache key: architecture, precision, kernel generation, omega and the sorted multiset of sizes.
 std::string tune_key(int dev, int prec, double omega, std::vector<int> lgs) {
     hipDeviceProp_t prop;
     std::string arch = "unknown";
@@ -1200,7 +1203,8 @@ std::string tune_key(int dev, int prec, double omega, std::vector<int> lgs) {
     char buf[96];
     uint64_t ob;
     std::memcpy(&ob, &omega, sizeof ob);
-    std::snprintf(buf, sizeof buf, "|%s|omega=%016llx|", prec == NP_FP32 ? "fp32" : "fp64", (unsigned long long)ob);
+    std::snprintf(buf, sizeof buf, "|%s|gen%d|omega=%016llx|", prec == NP_FP32 ? "fp32" : "fp64", kTuneGen,
+                  (unsigned long long)ob);
     std::string key = arch + buf;
     for (size_t i = 0; i < lgs.size();) {
         size_t j = i;
