@@ -486,8 +486,8 @@ def leg_explicit(B, inputs, steps, warmup):
     """Explicit advection-diffusion step with the paper's filter families (Section 2.1,
     Appendix A): central, upwind and finite element, on 4096^2 (rotation) and 256^3
     (divergence-free field), Dirichlet-0.  Throughput in cell-steps/s and the step's
-    algorithmic bytes (both stages in one pass: T and a read, the result written; the
-    result copied back into T) against HBM peak."""
+    algorithmic bytes (T and a read once, the result written once; not the copies that a
+    result in T's place needs) against HBM peak."""
     import torch
     out = {}
     for name, d, n in (("2d_4096", 2, 4096), ("3d_256", 3, 256)):
@@ -495,7 +495,7 @@ def leg_explicit(B, inputs, steps, warmup):
         Tg = torch.from_numpy(T).cuda()
         ag = [torch.from_numpy(c).cuda() for c in a]
         m = Tg.numel()
-        nbytes = m * 8 * (1 + d + 1 + 2)
+        nbytes = m * 8 * (1 + d + 1)
         res = {}
         for sname, scheme in (("central", 0), ("upwind", 1), ("finite_element", 2)):
             dt_s, _ = timed(lambda: B.np_ad_explicit_step(Tg, h, dt, nu, B.BC_DIRICHLET0, a=ag, scheme=scheme),

@@ -170,8 +170,9 @@ np_status ns_projection_step(np_dims dims, double h, double *u, double *v, doubl
  * refinement steps).  opts->inner_cycles = 0 hands the settings to the
  * autotuner, which picks the cycles per refinement step (1..4), the sweeps
  * per level (nu1 = nu2 in 1..3, in place of the caller's) and the level
- * kernels' tiles (row-marching or one cell pair per thread; the workgroups a
- * row-marching launch aims for, which set its rows per group) by timing full
+ * kernels' tiles (row-marching or one cell pair per thread; the workgroups, or
+ * with two sweeps per leg the wavefronts, a row-marching launch aims for, which
+ * set its rows per group) by timing full
  * solves of this batch.  Its choice is cached for the process and in a JSON
  * file keyed by (GPU architecture, precision, generation of the library's
  * batched kernels, omega, the multiset of sizes):
@@ -191,8 +192,8 @@ np_status np_last_autotune(int *inner_cycles, double *ms);
 
 /* Settings the last batched solve on this thread ran with (host outputs,
  * each nullable): inner cycles per refinement step, sweeps nu1 and nu2, the
- * row-marching tiles (1) or one cell pair per thread (0), the workgroups a
- * row-marching launch aims for, and where they came from: 0 the caller
+ * row-marching tiles (1) or one cell pair per thread (0), the workgroups (with
+ * nu1 = nu2 = 2 the wavefronts) a row-marching launch aims for, and where they came from: 0 the caller
  * (inner_cycles > 0), 1 tuned by this call, 2 this process's cache, 3 the
  * cache file. */
 np_status np_last_batched_settings(int *inner_cycles, int *nu1, int *nu2, int *row_marching, int *workgroups,
@@ -472,19 +473,23 @@ np_status np_prof_level(np_dims dims, double h, np_bc bc, np_prec prec, int kind
  * up-leg with prolongation + correction; default 1), "down2z" (0/1: in FP64 and FP32, from 256^3, the
  * residual and the restriction in the down-leg's two-sweep pass too; default 1), "d2cpt" (1 or 2: that pass on
  * one cell per thread or two, default 2; FP32 takes it only with 2), "d2wg" (256, 512 or 1024: workgroups the
- * two-cell form aims for; default 0, which takes 256 in FP64 and 512 in FP32), "blk2" (0/1: 2D levels of
- * 128^2 .. 1024^2 take one block kernel per leg, both sweeps with the residual and restriction, or prolongation +
- * correction with both post-sweeps; default 1), "z2wg" (0/1: the 3D one-pass kernels that fit fewer than four
+ * two-cell form aims for; default 0, which takes 256 in FP64 and 512 in FP32), "blk2" (0/1: 2D levels from
+ * 128^2 up to 1024^2 that "w2min" leaves take one block kernel per leg, both sweeps with the residual and
+ * restriction, or prolongation + correction with both post-sweeps; default 1), "w2min" (7 .. 14: log2 of the
+ * smallest 2D level whose V(2,2) legs run on row-marching wavefronts, given 16-byte aligned fields; default 10,
+ * 14 none), "pair" (0/1: the legs of the 256^2 and 128^2 blocks under a finer level in one kernel; default 1),
+ * "link" (8 .. 15: log2 of the smallest 2D FP64 finest level, one more in FP32, whose up-leg runs with the next
+ * cycle's down-leg; default 11), "one" (0/1: FP64 and FP32-refined V-cycle solves with nu1 >= 1, and implicit
+ * advection-diffusion ones, of at most 64^2 / 16^3 cells in one launch of one workgroup; default 1), "z2wg" (0/1: the 3D one-pass kernels that fit fewer than four
  * workgroups per CU -- the up-leg, FP64's zero-start down-leg -- take planes for 512 workgroups, not 1024
  * (the FP64 up-leg for 256); default 1), "greps" (1, 2, 4 or 8: the most cycles, or refinement steps, one replayed graph holds;
  * default 8), "tailck" (0/1: a cycle's convergence check run by the one-workgroup kernel of its coarse levels
  * rather than by a launch of its own; default 1), "zbar" (1 or 2: barriers per plane step of the 3D zero-start
  * down-leg pass, default 1), "batched_graphs", "batched_autotune" and "batched_rm" (0/1 for the
  * batched solver; batched_rm: row-marching level kernels above the one-workgroup depths),
- * "batched_wg" (workgroups a row-marching batched launch aims for, 64 .. 2^20, default 4096; the
- * caller's setting when the autotuner does not run), "zmarch_explicit" (0/1: z-marching tiles for the 3D explicit, collocated and staggered
- * momentum steps, n >= 32,
- * and row-marching tiles for the 2D explicit step, n >= 1024 a multiple of 256), "mom_rows" (4 or 8: tile rows
+ * "batched_wg" (workgroups, with nu1 = nu2 = 2 wavefronts, a row-marching batched launch aims for,
+ * 64 .. 2^20, default 4096; the caller's setting when the autotuner does not run), "zmarch_explicit" (0/1: z-marching tiles for the 3D collocated and staggered
+ * momentum steps, n >= 32, and the explicit step in one pass: 2D from n = 1280, 3D from 128, finite elements 65), "mom_rows" (4 or 8: tile rows
  * of the staggered corrector stage on those tiles, default 4), "mom_ring" (2 or 3: planes per field in the staggered
  * stages' LDS rings; 2 keeps the own column's out-of-ring z-neighbours in registers; default 2),
  * "zc3" (planes per workgroup of the 3D z-marching solver kernels: 0 automatic, else a power of two

@@ -243,9 +243,10 @@ __global__ __launch_bounds__(kAdxX * kAdxY) void k_adx_stage(const double *T, co
 // per side) and marches a chunk of rows, predictor and corrector one row apart in
 // registers, column neighbours from adjacent lanes.  Only the cells that another
 // wavefront reads are copied: two rows and two columns along each edge of a chunk
-// (k_adx_shell2), a tenth of the field at 4096^2.  Bound by memory: 32 bytes
+// (k_adx_shell2), 15 % of the field at 4096^2.  Bound by memory: 32 bytes
 // per cell against 80 for two stages that also copied T.  Measured, a call (central /
-// finite element): 4096^2 299 / 299 -> 152 / 150 us, 2048^2 74 / 74 -> 56 / 59; from 1280^2 on
+// finite element): 4096^2 299 / 299 -> 152 / 150 us (the two kernels 127 / 127 and 17 us; 4.8 TB/s of
+// traffic, of which 0.88 is those 32 bytes), 2048^2 74 / 74 -> 56 / 59; from 1280^2 on
 // (at 1024^2 34.2 / 35.6 against 31.5 / 35.4 for two launches of one cell per thread).  VEC: n even and 16-byte aligned fields,
 // pairs loaded at once.
 constexpr int kStep2Min = 1280, kStep2Cols = 124;

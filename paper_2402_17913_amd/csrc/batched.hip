@@ -820,7 +820,7 @@ std::map<std::vector<int64_t>, Plan *> g_plans;
 
 // Settings of a batched solve chosen by the autotuner: inner cycles per
 // refinement step, sweeps per level (nu1 = nu2 = nu) and the level-kernel
-// tiles (row-marching on/off, workgroups a row-marching launch aims for), with
+// tiles (row-marching on/off, BOpts::wg), with
 // the tuned batch's time.
 struct BTuned {
     int inner = 0, nu = 2, rm = 1, wg = 4096;
@@ -958,7 +958,7 @@ struct BOpts {
     int nu1, nu2;
     double omega;
     int rm;  // row-marching level kernels above the tail depths (else one cell pair per thread)
-    int wg;  // row-marching: workgroups a level launch aims for (sets the rows per group)
+    int wg;  // row-marching: workgroups, in V(2,2) legs wavefronts, a level launch aims for (sets the rows per group)
 };
 
 // One refinement step: kind 0 (x_a = caller x, no correction yet), 1 (x -> y),
@@ -1217,8 +1217,8 @@ std::string tune_key(int dev, int prec, double omega, std::vector<int> lgs) {
 
 // Picks the batch's settings by timing full solves of it: first the inner
 // cycles and sweeps per level jointly (inner 1..4 x nu 1..3 on row-marching
-// tiles aiming at 4096 workgroups), then the tiles for the winner (one cell
-// pair per thread; row-marching aiming at 1024 or 16384 workgroups).  A
+// tiles, wg 4096), then the tiles for the winner (one cell
+// pair per thread; row-marching with wg 1024 or 16384).  A
 // candidate counts only if every problem converged; each runs once untimed
 // (capturing its graphs) and is timed as the faster of two runs.
 template <class Run>

@@ -46,7 +46,7 @@ __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >
 // ------------------------------------------------------------------ conv
 // Where a field of the network has one channel (its input, the prediction's gradient), it is stored as
 // such, and the kernels that read it as 16 channels set the others to zero as they load it (ONE): at 128^3
-// writing it takes 6 and 9 us instead of 17 and 20, and its weight gradients 42 us instead of 47.
+// writing it takes 6 and 9 us instead of 17 and 20, and its weight gradients 42 us instead of 44.
 // 8 channels of a voxel: index i is 2 * voxel + half.
 template <bool ONE> __device__ __forceinline__ u32x4 ld_half(const uint16_t *__restrict__ X, int64_t i) {
     if constexpr (ONE) return u32x4{(i & 1) ? 0u : uint32_t(X[i >> 1]), 0u, 0u, 0u};
@@ -158,8 +158,9 @@ __global__ __launch_bounds__(256) void k_conv(const uint16_t *__restrict__ X, co
 // own, 5 .. 8 its own, 9 .. 13 the plane above.  Neighbouring outputs share most operands of a plane: with
 // row operands A (dx -1, 0), B (dx 0, 1), C (dx 1, then -1 of the next row), D (dx 1 of the row above in the
 // plane below, then -1 of the row below) and E (dx 1, then nothing), four rows and three planes take 26 LDS
-// reads where one output row at a time takes 56.  At 128^3 a forward convolution takes 33 us against 67 us
-// of a kernel that read all operands per output row (its floor, 64 MB read and 64 MB written: 28 us).
+// reads where one output row at a time takes 56.  At 128^3 a forward convolution takes 39 us against 67 us
+// of a kernel that read all operands per output row, both in a training gradient (its floor, 64 MB read and 64 MB
+// written: 28 us).
 constexpr int kCzT = 256, kCzRows = 4;
 constexpr int kCzSlots = (64 + 2) * (kCzRows + 2) * 2;  // uint4 per plane buffer (halo tile, two per voxel)
 
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t *__restrict__ X, c
 // dZ and, for X, one 16-byte and one 4-byte read that serve the three taps of a (dz, dy) row, funnel-shifted
 // by 0, 2 or 4 bytes.  The channel pitches put the 16 channels of a read on different banks.  A wave owns
 // every fourth step of 32 voxels and all 28 products, and the waves' sums are added in order at the end.
-// At 128^3 it takes 47 us, against 125 us when every plane of a tile staged
+// At 128^3 it takes 44 us, against 125 us when every plane of a tile staged
 // a three-plane halo of its own with 2-byte LDS writes and each wave read all of dZ for its share of the taps.
 // The two operands read once would take 28 us; what is left is one barrier and a full load latency per plane
 // at two workgroups per CU, which the 28 accumulators of a lane allow.

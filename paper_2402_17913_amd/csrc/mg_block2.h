@@ -1,5 +1,6 @@
 // 2D level kernels on 64 x 16 blocks for the levels above the one-workgroup
-// tail (128^2 .. 1024^2), where each per-cell kernel costs about a launch:
+// tail (128^2 .. 512^2, and 1024^2 where its fields are not aligned for the wavefront legs),
+// where each per-cell kernel costs about a launch:
 //  - MODE 0 (down-leg from a zero iterate): the two sweeps from zero (the
 //    first, w f, formed per value as k_sweep's zero-start pair forms it), the
 //    residual and its restriction;
