@@ -489,7 +489,9 @@ np_status np_prof_level(np_dims dims, double h, np_bc bc, np_prec prec, int kind
  * batched solver; batched_rm: row-marching level kernels above the one-workgroup depths),
  * "batched_wg" (workgroups, with nu1 = nu2 = 2 wavefronts, a row-marching batched launch aims for,
  * 64 .. 2^20, default 4096; the caller's setting when the autotuner does not run), "zmarch_explicit" (0/1: z-marching tiles for the 3D collocated and staggered
- * momentum steps, n >= 32, and the explicit step in one pass: 2D from n = 1280, 3D from 128, finite elements 65), "mom_rows" (4 or 8: tile rows
+ * momentum steps, n >= 32, and for the 3D explicit step from n = 128, finite elements 65; one pass for the whole
+ * explicit step in 2D from n = 1280 and in 3D from 192, finite elements without a velocity 288, never central or
+ * upwind ones without), "mom_rows" (4 or 8: tile rows
  * of the staggered corrector stage on those tiles, default 4), "mom_ring" (2 or 3: planes per field in the staggered
  * stages' LDS rings; 2 keeps the own column's out-of-ring z-neighbours in registers; default 2),
  * "zc3" (planes per workgroup of the 3D z-marching solver kernels: 0 automatic, else a power of two

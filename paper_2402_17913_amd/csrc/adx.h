@@ -409,19 +409,46 @@ __global__ __launch_bounds__(kBlock) void k_adx_step2(double *T, const double *_
 // tiles (66 x 15 with the ring: 990 of 1024 threads) keep 16 waves on a CU; two
 // cells on the first waves of a 64 x 8 tile took 176 registers, 8 waves and 316 us a call at
 // 256^3.  Measured, a call (central / finite element), the copy included: 256^3 350 / 389 ->
-// 234 / 254 us, 192^3 161 / 192 -> 117 / 127; from 128^3 on, 65^3 for the 27-point family (two
-// launches of one cell per thread take 52 / 80 us at 128^3, this 50 / 55; at 95^3 36 / 55 against 40 / 44, at 72^3
-// 31 / 47 against 36 / 39, at 64^3, which fills the launches' rows of 64 cells, 26 / 31 against 35 / 38).  A ring
-// cell outside the grid is formed at the cell it mirrors, which the tile and its ring hold.
+// 234 / 254 us, 192^3 161 / 192 -> 117 / 127.  A ring cell outside the grid is formed at the cell it mirrors,
+// which the tile and its ring hold.
 constexpr int kSx = 64, kSy = 13, kSt = 1024;
-constexpr int step3_min(int scheme) { return scheme == 2 ? 65 : 128; }
 
-// Planes per workgroup: as many as fill the CUs with one workgroup each, at least 4 (five more are computed per
-// workgroup; finite elements at 72^3 46 us with at least 8, 41 with 5, 39 with 4).
+// How a 3D step runs: two launches of one cell per thread (k_adx_stage), two launches on z-marching tiles
+// (k_adx_stage3z), or one pass.  Cells are best while a stage is little more than a launch, for the 27-point family
+// only up to 64^3, which fills its rows of 64 cells.  One pass moves 32 bytes per cell and 8 per velocity component
+// where two launches move 40 and 16, but computes rings and waits at a barrier per plane; it pays where the fields
+// leave the caches.  Measured, us a call (cells / tiles / one pass; periodic, central or finite element):
+//   with a velocity, central: 96^3 36 / 40 / 44, 128^3 54 / 50 / 53, 160^3 77 / 76 / 85, 192^3 130 / 120 / 122,
+//     256^3 315 / 307 / 241, 512^3 2353 / 2317 / 1727
+//   with a velocity, finite element: 64^3 30 / 30 / 41, 72^3 47 / 35 / 42, 128^3 80 / 56 / 59, 160^3 154 / 94 / 100,
+//     192^3 248 / 150 / 134, 256^3 621 / 331 / 264, 512^3 4854 / 2458 / 1873
+//   without, central: 96^3 33 / 34 / 41, 128^3 41 / 40 / 50, 192^3 84 / 78 / 96, 256^3 164 / 126 / 185,
+//     512^3 1586 / 1110 / 1429
+//   without, finite element: 72^3 42 / 32 / 37, 128^3 73 / 48 / 54, 256^3 420 / 186 / 209, 288^3 774 / 391 / 351,
+//     512^3 3886 / 1736 / 1597
+enum Step3 { kStepCells, kStepTiles, kStepOnePass };
+inline Step3 step3_route(int n, int scheme, bool has_a) {
+    if (n < (scheme == 2 ? 65 : 128)) return kStepCells;
+    if (has_a) return n < 192 ? kStepTiles : kStepOnePass;
+    return scheme == 2 && n >= 288 ? kStepOnePass : kStepTiles;
+}
+
+// Planes per workgroup: a workgroup fills a CU and computes five planes more than it writes, so the chunks (of
+// at least four planes) for which the rounds of 256 workgroups take the fewest plane steps.  512^3, with a velocity:
+// 1727 us on four chunks of its 320 tiles, 2358 on one (a second round of 64 workgroups).
 inline int step3_planes(int n) {
-    const int tiles = ((n + kSx - 1) / kSx) * ((n + kSy - 1) / kSy);
-    const int chunks = tiles >= 256 ? 1 : 256 / tiles, zc = (n + chunks - 1) / chunks;
-    return zc < 4 ? 4 : zc;
+    const int64_t tiles = int64_t((n + kSx - 1) / kSx) * ((n + kSy - 1) / kSy);
+    int64_t least = INT64_MAX;
+    int best = n;
+    for (int chunks = 1; chunks <= n / 4; ++chunks) {
+        const int zc = (n + chunks - 1) / chunks;
+        const int64_t steps = (tiles * ((n + zc - 1) / zc) + 255) / 256 * (zc + 5);
+        if (steps < least) {
+            least = steps;
+            best = zc;
+        }
+    }
+    return best;
 }
 
 // b = a.

@@ -299,6 +299,33 @@ struct ZRing {
     }
 };
 
+// A stage of the explicit step (as k_adx_stage, bit for bit) on z-marching tiles.  Bound by the barriers and LDS
+// reads of a plane step: 256^3 without a velocity 63 us a stage (126 us a call), finite elements 93.
+template <int SCHEME, int STAGE>
+__global__ __launch_bounds__(kZx * zrows(SCHEME)) void k_adx_stage3z(const double *T, const double *__restrict__ H,
+                                                                     double *out, APtrs ap, int n, int bc, int zc,
+                                                                     double dt, AdxK K) {
+    typedef ZRing<1, zrows(SCHEME)> Ring;
+    __shared__ typename Ring::Plane pl[1];
+    Ring R(n, bc, zc);
+    auto ld = [&](int, int64_t q) { return STAGE == 0 ? T[q] : H[q]; };
+    const int i = R.x0 + R.tx, j = R.y0 + R.ty;
+    R.march(ld, pl, [&](int z) {
+        if (i < n && j < n) {
+            double v[3][3][3] = {};
+            R.template gather<SCHEME>(pl[0], z, v);
+            const int64_t c = int64_t(z) * R.P + int64_t(j) * n + i;
+            double a[3] = {0.0, 0.0, 0.0};
+            if (ap.has)
+#pragma unroll
+                for (int e = 0; e < 3; ++e) a[e] = ap.a[e][c];
+            const double t = STAGE == 1 ? T[c] : v[1][1][1];
+            const double o = t - dt * adx_rate_at<3, SCHEME>(v, a, ap.has != 0, K);
+            out[c] = STAGE == 0 ? 0.5 * (o + t) : o;
+        }
+    });
+}
+
 // Collocated momentum stage (as k_nsc_stage) on z-marching tiles: the three
 // components' stage input and the pressure in LDS rings.
 template <int SCHEME, int STAGE>
@@ -1079,7 +1106,7 @@ extern "C" np_status np_ad_explicit_step(np_dims dims, double h, double *T, cons
         hipLaunchKernelGGL((k_adx_stage<D, S, 0>), grd, blk, 0, s, T, nullptr, scr, ap, ni, int(bc), dt, K);      \
         hipLaunchKernelGGL((k_adx_stage<D, S, 1>), grd, blk, 0, s, T, scr, T, ap, ni, int(bc), dt, K);            \
     } while (0)
-    // T may be one of its own velocity components.  The two launches read a velocity at the cell they are about
+    // T may be one of its own velocity components.  Two launches read a velocity at the cell they are about
     // to write only; the one-pass kernels also read it around the cells they own, where other wavefronts or
     // workgroups write T meanwhile, so they take such a component from the copy, which then holds the whole field.
     APtrs av = ap;
@@ -1107,7 +1134,18 @@ extern "C" np_status np_ad_explicit_step(np_dims dims, double h, double *T, cons
             hipLaunchKernelGGL((k_adx_step2<S, false>), dim3(nw2), dim3(kBlock), 0, s, T, scr, av, ni, int(bc), ry, \
                                strips, dt, K);                                                                    \
     } while (0)
-    const int zc = step3_planes(ni);
+#define NP_TILES3(S)                                                                                              \
+    do {                                                                                                          \
+        constexpr int ty = zrows(S);                                                                              \
+        const int zt = adx_planes(ni, ty);                                                                        \
+        const unsigned nz3 = zgrid(ni, ty, zt);                                                                   \
+        hipLaunchKernelGGL((k_adx_stage3z<S, 0>), dim3(nz3), dim3(kZx * ty), 0, s, T, nullptr, scr, ap, ni,       \
+                           int(bc), zt, dt, K);                                                                   \
+        hipLaunchKernelGGL((k_adx_stage3z<S, 1>), dim3(nz3), dim3(kZx * ty), 0, s, T, scr, T, ap, ni, int(bc), zt, \
+                           dt, K);                                                                                \
+    } while (0)
+    const Step3 route = dims.ndim == 3 && g_zmarch_explicit ? step3_route(ni, scheme, ap.has != 0) : kStepCells;
+    const int zc = route == kStepOnePass ? step3_planes(ni) : 1;
     const unsigned nt3 = unsigned(int64_t((ni + kSx - 1) / kSx) * ((ni + kSy - 1) / kSy) * ((ni + zc - 1) / zc));
 #define NP_STEP3(S)                                                                                               \
     do {                                                                                                          \
@@ -1122,10 +1160,14 @@ extern "C" np_status np_ad_explicit_step(np_dims dims, double h, double *T, cons
         if (scheme == 0) NP_ADX(2, 0);
         else if (scheme == 1) NP_ADX(2, 1);
         else NP_ADX(2, 2);
-    } else if (ni >= step3_min(scheme) && g_zmarch_explicit) {
+    } else if (route == kStepOnePass) {
         if (scheme == 0) NP_STEP3(0);
         else if (scheme == 1) NP_STEP3(1);
         else NP_STEP3(2);
+    } else if (route == kStepTiles) {
+        if (scheme == 0) NP_TILES3(0);
+        else if (scheme == 1) NP_TILES3(1);
+        else NP_TILES3(2);
     } else {
         if (scheme == 0) NP_ADX(3, 0);
         else if (scheme == 1) NP_ADX(3, 1);
@@ -1133,6 +1175,7 @@ extern "C" np_status np_ad_explicit_step(np_dims dims, double h, double *T, cons
     }
 #undef NP_ADX
 #undef NP_STEP2
+#undef NP_TILES3
 #undef NP_STEP3
     NP_LAUNCH_CHECK();
     NP_HIP_TRY(hipStreamSynchronize(s));

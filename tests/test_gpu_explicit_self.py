@@ -5,8 +5,8 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-# two launches (301, 64), and the one-pass kernels at their smallest sizes, with rows that are loaded cell
-# by cell (1281), partial tiles and a last chunk of few planes (131)
+# 2D: two launches (301) and one pass at its smallest sizes, with rows that are loaded cell by cell (1281); 3D: two
+# launches of one cell per thread (64) and on z-marching tiles, with partial tiles and a last chunk of few planes (131)
 @pytest.mark.parametrize("d,n", [(2, 301), (2, 1280), (2, 1281), (2, 1488), (3, 64), (3, 96), (3, 128), (3, 131)])
 def test_own_velocity(d, n):
     import torch
