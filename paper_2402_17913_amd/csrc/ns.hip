@@ -299,8 +299,9 @@ struct ZRing {
     }
 };
 
-// A stage of the explicit step (as k_adx_stage, bit for bit) on z-marching tiles.  Bound by the barriers and LDS
-// reads of a plane step: 256^3 without a velocity 63 us a stage (126 us a call), finite elements 93.
+// A stage of the explicit step (as k_adx_stage, bit for bit) on z-marching tiles.  256^3 without a velocity: predictor and
+// corrector 53 and 64 us (5.3 and 6.5 TB/s, bound by memory), finite elements 89 and 99 us (bound by the 27 LDS
+// reads of a cell); one cell per thread takes 164 and 420 us a call, these 126 and 186.
 template <int SCHEME, int STAGE>
 __global__ __launch_bounds__(kZx * zrows(SCHEME)) void k_adx_stage3z(const double *T, const double *__restrict__ H,
                                                                      double *out, APtrs ap, int n, int bc, int zc,
